@@ -2,7 +2,7 @@
 #include "common.h"
 
 namespace nsa {
-int64_t index_scan_tmp_ints(int64_t n_lists);
+int index_chunks(int t_cap);
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -23,11 +23,11 @@ static int check_shape(const nsa_sel_shape* s) {
   if (s->nseq > (1 << 20)) return NSA_SEL_EUNSUPPORTED;
   if ((int64_t)s->total_tokens * s->hq >= ((int64_t)1 << 31)) return NSA_SEL_EUNSUPPORTED;  // 32-bit row indices
   const int64_t b_cap = (int64_t)s->total_tokens / s->block + s->nseq;
-  // LDS tables of the inversion (12 bytes per block) must fit in one CU's 160 KB
+  // block count: the inversion keeps a counter per block of a sequence in LDS
   if (b_cap * 12 + 2 * 64 * (int64_t)(s->topk + 1) * 4 > 160 * 1024) return NSA_SEL_EUNSUPPORTED;
   const int64_t p_max = (int64_t)s->total_tokens * s->hkv * s->topk;
   if (p_max >= ((int64_t)1 << 31) - 4096) return NSA_SEL_EUNSUPPORTED;
-  const int64_t n_chunks = ((int64_t)s->total_tokens + kChunkTokens - 1) / kChunkTokens;
+  const int64_t n_chunks = ((int64_t)s->total_tokens + 511) / 512;
   if (b_cap * s->hkv * (n_chunks > 0 ? n_chunks : 1) >= ((int64_t)1 << 31) - 4096) return NSA_SEL_EUNSUPPORTED;
   return NSA_SEL_OK;
 }
@@ -43,9 +43,9 @@ static IndexLayout make_layout(const nsa_sel_shape* s) {
   L.window = s->window;
   L.b_cap = s->total_tokens / s->block + s->nseq;
   L.n_lists = s->hkv * L.b_cap;
-  L.n_chunks = (s->total_tokens + kChunkTokens - 1) / kChunkTokens;
-  if (L.n_chunks < 1) L.n_chunks = 1;
-  L.n_counters = (int64_t)L.n_lists * L.n_chunks;
+  L.t_cap = s->total_tokens / kTileTokens + s->nseq;
+  L.n_chunks = index_chunks(L.t_cap);
+  L.n_groups = (L.b_cap + 63) / 64;
   L.p_max = (int64_t)s->total_tokens * s->hkv * L.topk;
   L.unit = s->unit != 0 ? s->unit : work_unit_entries(L.p_max);
   L.units_max = (int32_t)units_bound(L.hkv, L.b_cap, L.T, L.topk, L.unit);
@@ -54,14 +54,12 @@ static IndexLayout make_layout(const nsa_sel_shape* s) {
   // g = 4 .. 8), unless the call is the sliding-window branch, where every pair is dense
   // (and not for inputs so small that the step is a few launch latencies: below 2^18 (token, kv head, column) triples)
   L.dense = s->dense == 1 || (s->dense == 0 && L.p_max >= (1 << 18) && (s->hq / s->hkv >= 2 || s->window > 0)) ? 1 : 0;
-  L.t_cap = s->total_tokens / kTileTokens + s->nseq;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
-  L.hdr = take(64);
   L.blk_base = take(4 * (size_t)(L.nseq + 1));
   L.blk_tok0 = take(4 * (size_t)L.b_cap);
   L.blk_len = take(4 * (size_t)L.b_cap);
-  L.chunk_off = take(4 * (size_t)(L.n_counters + 1));
+  L.chunk_off = take(4 * (size_t)L.n_lists * L.n_chunks);
   L.cnt = take(4 * (size_t)L.n_lists);
   L.off = take(4 * (size_t)(L.n_lists + 1));
   L.qent = take(8 * (size_t)(L.p_max + 1));
@@ -70,10 +68,11 @@ static IndexLayout make_layout(const nsa_sel_shape* s) {
   L.u_nu = take(4 * (size_t)(L.n_lists + 1));
   L.u_list = take(4 * (size_t)(L.units_max + 1));
   L.u_start = take(4 * (size_t)(L.units_max + 1));
-  L.scan_tmp = take(4 * (size_t)index_scan_tmp_ints(L.n_lists));
+  L.group_sum = take(8 * (size_t)L.hkv * L.n_groups);
   L.tile_base = take(4 * (size_t)(L.nseq + 1));
   L.tile_tok0 = take(4 * (size_t)L.t_cap);
   L.tile_len = take(4 * (size_t)L.t_cap);
+  L.tile_seq = take(4 * (size_t)L.t_cap);
   L.dmask = take(4 * ((size_t)L.T * L.hkv + 1));
   L.d_cnt = take(4 * (size_t)L.t_cap * L.hkv);
   L.d_piece = take(8 * (size_t)L.t_cap * L.hkv * kDenseMax);

@@ -13,7 +13,6 @@ namespace nsa {
 
 constexpr int kBlock = 64;         // tokens of the smaller of the two block sizes (B_K = 64 or 2 * 64)
 constexpr int kD = 128;            // head dimension
-constexpr int kChunkTokens = 512;  // token chunk of the inversion histogram / scatter
 constexpr int kMaxUnit = 2048;     // most list entries of one work unit (the size used for long inputs)
 constexpr int kMinUnit = 256;
 constexpr int kMaxTopk = 32;
@@ -29,24 +28,20 @@ struct IndexLayout {
   int32_t bk;           // B_K: tokens per KV block, 64 or 128
   int32_t b_cap;        // list stride: T / bk + nseq  (>= real number of blocks)
   int32_t n_lists;      // hkv * b_cap
-  int32_t n_chunks;     // ceil(T / kChunkTokens)
-  int64_t n_counters;   // n_lists * n_chunks
+  int32_t n_chunks;     // chunks of query tiles the inversion works by (index_chunks)
+  int32_t n_groups;     // groups of 64 lists of a kv head: ceil(b_cap / 64)
   int64_t p_max;        // T * hkv * topk
   int32_t unit;         // list entries per work unit of the attention kernels (see work_unit_entries)
   int32_t units_max;    // upper bound of the number of work units
   int32_t dense;        // 1: (query tile, KV block) pairs most of the tile's tokens keep go through the dense path
   int32_t t_cap;        // query tiles of kTileTokens tokens: T / kTileTokens + nseq (>= real number of tiles)
-  size_t hdr, blk_base, blk_tok0, blk_len, chunk_off, cnt, off, qent, vmask, slotpos;
-  size_t u_nu, u_list, u_start, scan_tmp;
-  size_t tile_base, tile_tok0, tile_len, dmask, d_cnt, d_piece, d_mask;
+  size_t blk_base, blk_tok0, blk_len, chunk_off, cnt, off, qent, vmask, slotpos;
+  size_t u_nu, u_list, u_start, group_sum;
+  size_t tile_base, tile_tok0, tile_len, tile_seq, dmask, d_cnt, d_piece, d_mask;
   size_t total;
 };
 
-// hdr words
-enum { HDR_BTOT = 0, HDR_NPAIRS = 1, HDR_UNITS = 2, HDR_NTILES = 3 };
-
 struct IndexPtrs {
-  int32_t* hdr;
   int32_t* blk_base;
   int32_t* blk_tok0;
   int32_t* blk_len;
@@ -58,11 +53,11 @@ struct IndexPtrs {
   int32_t* slotpos;  // [T, hkv, topk]: position in qent of the entry a kept column produced
   // work units (shared by forward and backward): scanned units per list, and per unit its list and first entry
   int32_t *u_nu, *u_list, *u_start;
-  int32_t* scan_tmp;
+  int2* group_sum;     // [hkv, n_groups] (entries, work units) of 64 lists
   // dense forward path: query tiles (kTileTokens consecutive tokens of one sequence) and, per (tile, kv head), the
   // 64-key pieces of the KV blocks at least half of the tile's tokens keep, each with the 64-bit mask of the tokens
   // that keep its block
-  int32_t *tile_base, *tile_tok0, *tile_len;
+  int32_t *tile_base, *tile_tok0, *tile_len, *tile_seq;
   uint32_t* dmask;     // [T, hkv]: columns of idx the dense path takes over (a subset of vmask)
   int32_t* d_cnt;      // [t_cap, hkv]
   int2* d_piece;       // [t_cap, hkv, kDenseMax] (first key token, number of keys <= 64)
@@ -72,7 +67,6 @@ struct IndexPtrs {
 inline IndexPtrs index_ptrs(const IndexLayout& L, void* base) {
   char* p = static_cast<char*>(base);
   IndexPtrs r;
-  r.hdr = (int32_t*)(p + L.hdr);
   r.blk_base = (int32_t*)(p + L.blk_base);
   r.blk_tok0 = (int32_t*)(p + L.blk_tok0);
   r.blk_len = (int32_t*)(p + L.blk_len);
@@ -85,10 +79,11 @@ inline IndexPtrs index_ptrs(const IndexLayout& L, void* base) {
   r.u_nu = (int32_t*)(p + L.u_nu);
   r.u_list = (int32_t*)(p + L.u_list);
   r.u_start = (int32_t*)(p + L.u_start);
-  r.scan_tmp = (int32_t*)(p + L.scan_tmp);
+  r.group_sum = (int2*)(p + L.group_sum);
   r.tile_base = (int32_t*)(p + L.tile_base);
   r.tile_tok0 = (int32_t*)(p + L.tile_tok0);
   r.tile_len = (int32_t*)(p + L.tile_len);
+  r.tile_seq = (int32_t*)(p + L.tile_seq);
   r.dmask = (uint32_t*)(p + L.dmask);
   r.d_cnt = (int32_t*)(p + L.d_cnt);
   r.d_piece = (int2*)(p + L.d_piece);

@@ -3,150 +3,369 @@
 // Sec. 3.2, the paragraph on the token-selection kernel) together with the column each entry came from, and, per kept
 // (token, kv head, column), the entry's position in its list, which is where its partial result lives in the
 // compact partial buffers (the role of the paper's O_i), plus the work-unit tables of the attention kernels.
-// Pipeline: per-(kv head, token chunk, block) histogram -> prefix over the chunks of every list -> exclusive scan
-// of the list lengths -> ordered scatter.  The counters are stored chunk-major, [kv head][chunk][block], so that
+//
+// Three launches (a fourth, k_prep, for packed batches):
+//   k_hist     per (kv head, chunk, block) counts, kept columns per token, dense (query tile, KV block) pairs
+//   k_prefix   per list: prefix over the chunks, length; per 64 lists: sums
+//   k_scatter  exclusive scan of the list lengths (redone by every workgroup from the 64-list sums), list entries and
+//              their positions, work units
+// Everything is organised by query tile: 64 consecutive tokens of one sequence, one wavefront, lane = token.  A chunk
+// is kTilesPerChunk tiles = one workgroup.  The counters are stored chunk-major, [kv head][chunk][block], so that
 // the histogram and the scatter of one (chunk, kv head) touch one contiguous row.
-// The scatter is deterministic: a chunk is walked by one wavefront in rounds of 64 tokens, and a token's rank
-// inside a round is a popcount over a 64-bit membership mask, so no ordering depends on atomics.
+// Lists come out ascending without a sort and without order-dependent atomics: a token's rank inside its tile is a
+// popcount over a 64-bit membership mask, the tiles of a chunk are ordered by a byte count per (block, tile).
+//
+// The inversion reads a few MB and is bound by latency and launches, not by bandwidth.  An earlier cut (12 launches; one
+// wavefront walked a chunk's 512 tokens in eight dependent rounds; separate scan, dense-detection and unit kernels) took
+// 105 us at 2000 tokens x 2 kv heads and 233 us at 65536 tokens x 8 kv heads.
 #include "common.h"
 
 namespace nsa {
 
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
-constexpr int kScanTile = kScanThreads * kScanItems;  // 4096
+constexpr int kTilesPerChunk = 8;                    // wavefronts of a k_hist / k_scatter workgroup
+constexpr int kChunkThreads = 64 * kTilesPerChunk;
+constexpr int kPrefixWaves = 16;                     // wavefronts of a k_prefix workgroup (64 lists each)
+constexpr int kScatterWindow = 1024;                 // most blocks k_scatter handles at a time (its LDS tables)
+
+struct IndexGeom {
+  int32_t nseq, T, hkv, k, bk, causal, window, b_cap, t_cap, n_chunks, n_groups, unit, dense;
+};
+
+// A query tile: its first token and length (0: none), its sequence's bounds and first global block.
+struct Tile {
+  int tok0, len, c0, c1, bb;
+};
+
+__device__ __forceinline__ Tile load_tile(const IndexGeom& G, int qt, const int32_t* cu, const IndexPtrs& p) {
+  Tile t = {0, 0, 0, 0, 0};
+  if (qt >= G.t_cap) return t;
+  if (G.nseq == 1) {
+    t.tok0 = qt * kTileTokens;
+    t.len = max(min(G.T - t.tok0, kTileTokens), 0);
+    t.c1 = G.T;
+    return t;
+  }
+  t.len = p.tile_len[qt];
+  if (t.len == 0) return t;
+  const int s = p.tile_seq[qt];
+  t.tok0 = p.tile_tok0[qt];
+  t.c0 = cu[s];
+  t.c1 = cu[s + 1];
+  t.bb = p.blk_base[s];
+  return t;
+}
+
+// One past the last global block the tile's tokens can keep.
+__device__ __forceinline__ int tile_blocks_end(const IndexGeom& G, const Tile& t) {
+  return t.bb + (G.causal ? (t.tok0 + t.len - 1 - t.c0) / G.bk + 1 : (t.c1 - t.c0 + G.bk - 1) / G.bk);
+}
+
+// The window [lo, hi) of global blocks the tokens of a chunk can keep; block-wide (every wavefront passes its own tile).
+__device__ __forceinline__ void chunk_window(const IndexGeom& G, const Tile& t, int wave, int* s_win, int& lo, int& hi) {
+  if ((threadIdx.x & 63) == 0) {
+    s_win[2 * wave] = t.len > 0 ? t.bb : 0x7fffffff;
+    s_win[2 * wave + 1] = t.len > 0 ? tile_blocks_end(G, t) : 0;
+  }
+  __syncthreads();
+  lo = 0x7fffffff;
+  hi = 0;
+#pragma unroll
+  for (int w = 0; w < kTilesPerChunk; ++w) {
+    lo = min(lo, s_win[2 * w]);
+    hi = max(hi, s_win[2 * w + 1]);
+  }
+  if (lo > hi) lo = hi;
+}
+
+// One row of idx in registers; columns past k hold -1.
+template <int KMAX>
+__device__ __forceinline__ void load_row(const int32_t* __restrict__ src, int k, bool vec4, int32_t (&row)[KMAX]) {
+  if (vec4) {
+#pragma unroll
+    for (int m = 0; m < KMAX; m += 4) {
+      int4 x = make_int4(-1, -1, -1, -1);
+      if (m < k) x = *reinterpret_cast<const int4*>(src + m);
+      row[m] = x.x; row[m + 1] = x.y; row[m + 2] = x.z; row[m + 3] = x.w;
+    }
+  } else {
+#pragma unroll
+    for (int m = 0; m < KMAX; ++m) row[m] = m < k ? src[m] : -1;
+  }
+}
+
+__device__ __forceinline__ bool rows_are_vec4(const void* a, int k) {
+  return (k & 3) == 0 && (reinterpret_cast<uintptr_t>(a) & 15) == 0;
+}
+
+__device__ __forceinline__ void wave_lds_sync() {  // orders a wavefront's own LDS traffic
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// table[x] += 1 for every lane with `on`.  The forced columns (sink, own block) hold the same id in every lane, which
+// would serialise 64 atomics on one address: a column all of whose lanes agree is counted by one of them.
+__device__ __forceinline__ void count_column(int32_t* table, int x, bool on, int lane) {
+  const unsigned long long act = __builtin_amdgcn_ballot_w64(on);
+  if (act == 0ull) return;
+  const int lead = __builtin_ctzll(act);
+  const int x0 = __builtin_amdgcn_readlane(x, lead);
+  if (__builtin_amdgcn_ballot_w64(on && x == x0) == act) {
+    if (lane == lead) atomicAdd(&table[x0], __popcll(act));
+  } else if (on) {
+    atomicAdd(&table[x], 1);
+  }
+}
 
 // ------------------------------------------------------------------------------------------------ prep
-// blk_base[s] = number of blocks (of bk = B_K tokens) of sequences < s; per global block its first token and its
-// key count.
-__global__ void k_prep(const int32_t* __restrict__ cu, int nseq, int T, int bk, int b_cap,
-                       int32_t* __restrict__ blk_base,
-                       int32_t* __restrict__ blk_tok0, int32_t* __restrict__ blk_len, int32_t* __restrict__ hdr_slot) {
-  __shared__ int s_btot;
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int s = 0; s < nseq; ++s) {
-      int c0 = cu ? cu[s] : 0, c1 = cu ? cu[s + 1] : T;
-      blk_base[s] = acc;
-      acc += (c1 - c0 + bk - 1) / bk;
+// Packed batches: blk_base[s] / tile_base[s] = number of KV blocks / query tiles of sequences < s; per global block its
+// first token and its key count, per tile its first token, length and sequence.  One workgroup.  (For a single sequence
+// the tables are closed forms that k_hist writes.)
+__global__ void __launch_bounds__(1024) k_prep(IndexGeom G, const int32_t* __restrict__ cu, IndexPtrs p) {
+  __shared__ int s_sum[2][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int carry_b = 0, carry_t = 0;
+  for (int s0 = 0; s0 < G.nseq; s0 += 1024) {
+    const int s = s0 + tid;
+    const int len = s < G.nseq ? cu[s + 1] - cu[s] : 0;
+    const int nb = (len + G.bk - 1) / G.bk, nt = (len + kTileTokens - 1) / kTileTokens;
+    int ib = nb, it = nt;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int xb = __shfl_up(ib, d), xt = __shfl_up(it, d);
+      if (lane >= d) { ib += xb; it += xt; }
     }
-    blk_base[nseq] = acc;
-    s_btot = acc;
-    *hdr_slot = acc;
+    __syncthreads();  // the previous round's sums are no longer read
+    if (lane == 63) { s_sum[0][wave] = ib; s_sum[1][wave] = it; }
+    __syncthreads();
+    int before_b = carry_b, before_t = carry_t;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) { before_b += s_sum[0][w]; before_t += s_sum[1][w]; }
+      carry_b += s_sum[0][w];
+      carry_t += s_sum[1][w];
+    }
+    if (s < G.nseq) {
+      p.blk_base[s] = before_b + ib - nb;
+      p.tile_base[s] = before_t + it - nt;
+    }
+  }
+  if (tid == 0) {
+    p.blk_base[G.nseq] = carry_b;
+    p.tile_base[G.nseq] = carry_t;
   }
   __threadfence_block();
   __syncthreads();
-  const int b_tot = s_btot;
-  for (int gb = threadIdx.x; gb < b_cap; gb += blockDim.x) {
-    int tok0 = 0, len = 0;
-    if (gb < b_tot) {
-      int lo = 0, hi = nseq;  // blk_base[lo] <= gb < blk_base[hi]
-      while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (blk_base[mid] <= gb) lo = mid; else hi = mid;
-      }
-      int c0 = cu ? cu[lo] : 0, c1 = cu ? cu[lo + 1] : T;
-      tok0 = c0 + (gb - blk_base[lo]) * bk;
-      len = min(bk, c1 - tok0);
+  auto owner = [&](const int32_t* base, int i) {  // base[s] <= i < base[s + 1]
+    int lo = 0, hi = G.nseq;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (base[mid] <= i) lo = mid; else hi = mid;
     }
-    blk_tok0[gb] = tok0;
-    blk_len[gb] = len;
+    return lo;
+  };
+  for (int gb = tid; gb < G.b_cap; gb += 1024) {
+    int tok0 = 0, len = 0;
+    if (gb < carry_b) {
+      const int s = owner(p.blk_base, gb);
+      tok0 = cu[s] + (gb - p.blk_base[s]) * G.bk;
+      len = min(G.bk, cu[s + 1] - tok0);
+    }
+    p.blk_tok0[gb] = tok0;
+    p.blk_len[gb] = len;
+  }
+  for (int qt = tid; qt < G.t_cap; qt += 1024) {
+    int tok0 = 0, len = 0, s = 0;
+    if (qt < carry_t) {
+      s = owner(p.tile_base, qt);
+      tok0 = cu[s] + (qt - p.tile_base[s]) * kTileTokens;
+      len = min(kTileTokens, cu[s + 1] - tok0);
+    }
+    p.tile_tok0[qt] = tok0;
+    p.tile_len[qt] = len;
+    p.tile_seq[qt] = s;
   }
 }
 
-// Bit m of the result is set when column m of the row is a kept selection: in range for the sequence, not in
-// the token's future when causal, not wholly before the token's window (first_blk = the block of the oldest
-// visible key, 0 without a window), and not a repeat of an earlier column.
-__device__ __forceinline__ uint32_t kept_columns(const int32_t* row, int k, int b_s, int cur, int causal,
-                                                 int first_blk) {
-  uint32_t vm = 0;
-  for (int m = 0; m < k; ++m) {
-    int x = row[m];
-    const bool ok = x >= first_blk && x < b_s && (!causal || x <= cur);
-    bool dup = false;  // no early exit: the reads of the earlier columns are independent and overlap
-    for (int mp = 0; mp < m; ++mp) dup |= row[mp] == x;
-    if (ok && !dup) vm |= 1u << m;
+// ------------------------------------------------------------------------------------------------ dense detection
+// Dense forward path: which (query tile, KV block) pairs skip the gather route.  One wavefront per (tile, kv head), lane =
+// token: a KV block that at least `need` = half of the tile's tokens keep (the attention-sink block, the tokens' own
+// block and the blocks next to it are kept by all of them) becomes a dense pair: the forward computes it for the whole
+// tile with the query tile read once and the output accumulated on chip, a 64-bit mask saying which tokens really keep
+// it.  The tokens' columns that hold such a block are recorded in dmask; the scatter flags their list entries, and the
+// gather route of the forward skips them.  Nothing here is assumed about the selection: pairs come from counting, and
+// any pair may take either route.  Candidates are the kept blocks of three tokens of the tile (first, middle, last); a
+// block that qualifies but is kept by none of the three simply stays on the gather route.  A per-wavefront table of
+// counters (block id modulo kDenseHash, LDS atomics: counts are order-free) tells which candidates can reach `need`:
+// only the few that pass get the exact count (a ballot).
+// The dense table lists 64-key pieces (a 128-token block gives two) by first key and key count, in the order found;
+// pieces no token of the tile can see (wholly in the future, or wholly before every token's window) are left out.
+// Returns the lane's dense columns.
+template <int KMAX>
+__device__ __forceinline__ uint32_t dense_detect(const IndexGeom& G, const Tile& t, const int32_t (&row)[KMAX], uint32_t vm,
+                                                 int lane, size_t slot, int32_t* hash, const IndexPtrs& p) {
+  for (int i = lane; i < kDenseHash / 4; i += 64) reinterpret_cast<int4*>(hash)[i] = make_int4(0, 0, 0, 0);
+  wave_lds_sync();
+  int kept[KMAX];  // -1 where the column is not kept: no candidate matches it
+#pragma unroll
+  for (int m = 0; m < KMAX; ++m) {
+    const bool on = (vm >> m) & 1u;
+    kept[m] = on ? row[m] : -1;
+    if (m < G.k) count_column(hash, row[m] & (kDenseHash - 1), on, lane);
   }
-  return vm;
-}
-
-// Window of global blocks a token chunk can touch: the blocks of the sequences it overlaps, and under the
-// causal rule none past the block of the chunk's last token.
-__device__ __forceinline__ void chunk_window(const int32_t* cu, const int32_t* blk_base, int nseq, int T, int t0,
-                                             int t1, int bk, int causal, int& gb_lo, int& gb_hi) {
-  int s0, s1, a, b, c0;
-  seq_bounds(cu, nseq, T, t0, s0, a, b);
-  seq_bounds(cu, nseq, T, t1 - 1, s1, c0, b);
-  gb_lo = blk_base[s0];
-  gb_hi = blk_base[s1 + 1];
-  if (causal) gb_hi = min(gb_hi, blk_base[s1] + (t1 - 1 - c0) / bk + 1);
+  wave_lds_sync();
+  const int need = (t.len + 1) >> 1;
+  const int prop[3] = {0, t.len >> 1, t.len - 1};
+  int nd = 0;
+  uint32_t dm = 0;
+  for (int pi = 0; pi < 3; ++pi) {
+    const int pr = prop[pi];
+    if ((pi == 1 && pr == prop[0]) || (pi == 2 && (pr == prop[0] || pr == prop[1]))) continue;
+    const uint32_t pvm = (uint32_t)__builtin_amdgcn_readlane((int)vm, pr);
+    // lane m: column m of token pr's row
+    int cand_blk = 0;
+#pragma unroll
+    for (int m = 0; m < KMAX; ++m) {
+      const int x = __builtin_amdgcn_readlane(row[m], pr);
+      cand_blk = lane == m ? x : cand_blk;
+    }
+    const bool mine = lane < G.k && ((pvm >> (lane & 31)) & 1u);
+    const int cand_cnt = mine ? hash[cand_blk & (kDenseHash - 1)] : 0;
+    unsigned long long cand = __builtin_amdgcn_ballot_w64(cand_cnt >= need);
+    while (cand != 0ull) {
+      const int m = __builtin_ctzll(cand);
+      cand &= cand - 1ull;
+      const int c = __builtin_amdgcn_readlane(cand_blk, m);
+      int mycol = -1;
+#pragma unroll
+      for (int mm = KMAX - 1; mm >= 0; --mm) mycol = kept[mm] == c ? mm : mycol;
+      const unsigned long long members = __builtin_amdgcn_ballot_w64(mycol >= 0);
+      // an earlier proposer that keeps c has already dealt with it
+      bool seen = false;
+      for (int pj = 0; pj < pi; ++pj) seen |= ((members >> prop[pj]) & 1ull) != 0ull;
+      if (seen || __popcll(members) < need) continue;
+      // the block's 64-key pieces some token of the tile can see
+      const int btok0 = t.c0 + c * G.bk, blen = min(G.bk, t.c1 - btok0);
+      int np = 0, ptok[2], plen[2];
+      for (int sub = 0; sub < (G.bk >> 6); ++sub) {
+        const int pt = btok0 + 64 * sub, pl = min(64, blen - 64 * sub);
+        if (pl <= 0) continue;
+        if (G.causal && pt > t.tok0 + t.len - 1) continue;
+        if (G.window > 0 && pt + pl - 1 < t.tok0 - G.window + 1) continue;
+        ptok[np] = pt;
+        plen[np] = pl;
+        ++np;
+      }
+      if (nd + np > kDenseMax) continue;
+      if (lane == 0)
+        for (int q = 0; q < np; ++q) {
+          p.d_piece[slot * kDenseMax + nd + q] = make_int2(ptok[q], plen[q]);
+          p.d_mask[slot * kDenseMax + nd + q] = members;
+        }
+      if (mycol >= 0) dm |= 1u << mycol;  // also when no piece is visible: the pair then contributes nothing
+      nd += np;
+    }
+  }
+  if (lane == 0) p.d_cnt[slot] = nd;
+  return dm;
 }
 
 // ------------------------------------------------------------------------------------------------ histogram
-// grid (n_chunks, hkv), 256 threads.  counters[(j*n_chunks + chunk)*b_cap + gb] = number of tokens of the
-// chunk that keep block gb for kv head j; the whole row is written (zeros outside the chunk's window), so the
-// array needs no clearing.  Dynamic LDS: b_cap ints + 256*(k+1) ints.
-__global__ void __launch_bounds__(256) k_hist(const int32_t* __restrict__ idx, const int32_t* __restrict__ cu,
-                                              const int32_t* __restrict__ blk_base, int nseq, int T, int hkv, int k,
-                                              int bk, int causal, int window, int b_cap, int n_chunks,
-                                              int32_t* __restrict__ counters, uint32_t* __restrict__ vmask) {
-  extern __shared__ int32_t lds[];
-  int32_t* hist = lds;
-  int32_t* rows = lds + b_cap;
+// grid (n_chunks, hkv).  chunk_off[(j*n_chunks + chunk)*b_cap + gb] = number of tokens of the chunk that keep block gb
+// for kv head j; the whole row is written (zeros outside the chunk's window), so the array needs no clearing.  The rows
+// of idx stay in registers (one 16-byte load per four columns); the duplicate test is k^2/2 register compares.
+// Dynamic LDS: b_cap ints, with the dense route + kTilesPerChunk * kDenseHash ints.
+template <int KMAX>
+__global__ void __launch_bounds__(kChunkThreads) k_hist(IndexGeom G, const int32_t* __restrict__ idx,
+                                                        const int32_t* __restrict__ cu, IndexPtrs p) {
+  extern __shared__ __attribute__((aligned(16))) int32_t lds[];
+  __shared__ int s_win[2 * kTilesPerChunk];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int chunk = blockIdx.x, j = blockIdx.y;
-  const int t0 = chunk * kChunkTokens, t1 = min(t0 + kChunkTokens, T);
+  const int qt = chunk * kTilesPerChunk + wave;
+  const Tile t = load_tile(G, qt, cu, p);
+  const int tok = t.tok0 + lane;
+  const bool live = lane < t.len;
+  int32_t row[KMAX];
+#pragma unroll
+  for (int m = 0; m < KMAX; ++m) row[m] = -1;
+  if (live) load_row<KMAX>(idx + ((size_t)tok * G.hkv + j) * G.k, G.k, rows_are_vec4(idx, G.k), row);
   int gb_lo, gb_hi;
-  chunk_window(cu, blk_base, nseq, T, t0, t1, bk, causal, gb_lo, gb_hi);
-  const int win = gb_hi - gb_lo;
-  for (int i = threadIdx.x; i < win; i += blockDim.x) hist[i] = 0;
-  __syncthreads();
-  int32_t* row = rows + threadIdx.x * (k + 1);
-  for (int t = t0 + threadIdx.x; t < t1; t += blockDim.x) {
-    int s, c0, c1;
-    seq_bounds(cu, nseq, T, t, s, c0, c1);
-    const int32_t* src = idx + ((size_t)t * hkv + j) * k;
-    for (int m = 0; m < k; ++m) row[m] = src[m];
-    const int b_s = (c1 - c0 + bk - 1) / bk;
-    const int cur = (t - c0) / bk;
-    // oldest key a window of `window` tokens shows to this token: position p - window + 1 of its sequence
-    const int first_blk = window > 0 ? max(t - c0 - window + 1, 0) / bk : 0;
-    const uint32_t vm = kept_columns(row, k, b_s, cur, causal, first_blk);
-    vmask[(size_t)t * hkv + j] = vm;
-    const int base = blk_base[s] - gb_lo;
-    for (int m = 0; m < k; ++m)
-      if ((vm >> m) & 1u) atomicAdd(&hist[base + row[m]], 1);
+  chunk_window(G, t, wave, s_win, gb_lo, gb_hi);
+  int32_t* hash = lds + wave * kDenseHash;
+  int32_t* hist = lds + (G.dense ? kTilesPerChunk * kDenseHash : 0);
+  for (int i = tid; i < gb_hi - gb_lo; i += kChunkThreads) hist[i] = 0;
+  if (G.nseq == 1 && j == 0) {  // block and tile tables of a single sequence
+    if (lane == 0 && qt < G.t_cap) {
+      p.tile_tok0[qt] = t.tok0;
+      p.tile_len[qt] = t.len;
+    }
+    const int per = kTilesPerChunk * kTileTokens / G.bk;
+    for (int gb = chunk * per + tid; gb < min((chunk + 1) * per, G.b_cap); gb += kChunkThreads) {
+      const int len = max(min(G.bk, G.T - gb * G.bk), 0);
+      p.blk_tok0[gb] = len > 0 ? gb * G.bk : 0;
+      p.blk_len[gb] = len;
+    }
+  }
+  // Bit m of vm: column m is a kept selection - in range for the sequence, not in the token's future when causal, not
+  // wholly before the token's window, and not a repeat of an earlier column.
+  uint32_t vm = 0;
+  if (live) {
+    const int last = G.causal ? (tok - t.c0) / G.bk : (t.c1 - t.c0 + G.bk - 1) / G.bk - 1;
+    // oldest key a window of G.window tokens shows to this token: position tok - c0 - window + 1 of its sequence
+    const int first = G.window > 0 ? max(tok - t.c0 - G.window + 1, 0) / G.bk : 0;
+#pragma unroll
+    for (int m = 0; m < KMAX; ++m) {
+      bool dup = false;
+#pragma unroll
+      for (int mp = 0; mp < m; ++mp) dup |= row[mp] == row[m];
+      if (m < G.k && row[m] >= first && row[m] <= last && !dup) vm |= 1u << m;
+    }
+    p.vmask[(size_t)tok * G.hkv + j] = vm;
   }
   __syncthreads();
-  int32_t* out = counters + ((size_t)j * n_chunks + chunk) * b_cap;
-  for (int i = threadIdx.x; i < b_cap; i += blockDim.x) out[i] = (i >= gb_lo && i < gb_hi) ? hist[i - gb_lo] : 0;
+  const int base = t.bb - gb_lo;
+#pragma unroll
+  for (int m = 0; m < KMAX; ++m)
+    if (m < G.k) count_column(hist, base + row[m], (vm >> m) & 1u, lane);
+  if (G.dense && qt < G.t_cap) {
+    const size_t slot = (size_t)qt * G.hkv + j;
+    if (t.len > 0) {
+      const uint32_t dm = dense_detect<KMAX>(G, t, row, vm, lane, slot, hash, p);
+      if (live) p.dmask[(size_t)tok * G.hkv + j] = dm;
+    } else if (lane == 0) {
+      p.d_cnt[slot] = 0;
+    }
+  }
+  __syncthreads();
+  int32_t* out = p.chunk_off + ((size_t)j * G.n_chunks + chunk) * G.b_cap;
+  for (int i = tid; i < G.b_cap; i += kChunkThreads) out[i] = (i >= gb_lo && i < gb_hi) ? hist[i - gb_lo] : 0;
 }
 
-// ------------------------------------------------------------------------------------------------ chunk prefix
-// For every list (kv head j, block gb): counters[j][chunk][gb] becomes the number of entries the list gets from
-// earlier chunks, and cnt / len_scan receive the list's length.  A workgroup owns 64 consecutive blocks of one kv
-// head; its four wavefronts take a quarter of the chunks each (sum, exchange through LDS, then prefix), so the
-// column walk is a handful of coalesced row accesses per thread.  grid (ceil(b_cap / 64), hkv), 256 threads.
-__global__ void __launch_bounds__(256) k_chunk_prefix(int32_t* __restrict__ counters, int b_cap, int n_chunks,
-                                                      int n_lists, int32_t* __restrict__ cnt,
-                                                      int32_t* __restrict__ len_scan) {
-  __shared__ int32_t part[4][64];
+// ------------------------------------------------------------------------------------------------ prefix
+// For every list (kv head j, block gb): chunk_off[j][chunk][gb] becomes the number of entries the list gets from
+// earlier chunks, cnt receives the list's length, group_sum the (entries, work units) of 64 lists.  A workgroup owns 64
+// consecutive blocks of one kv head; its wavefronts take a share of the chunks each (sum, exchange through LDS, then
+// prefix), so the column walk is a handful of coalesced row accesses per thread.  grid (n_groups, hkv).
+__global__ void __launch_bounds__(64 * kPrefixWaves) k_prefix(IndexGeom G, int32_t* __restrict__ counters,
+                                                              int32_t* __restrict__ cnt, int2* __restrict__ group_sum) {
+  __shared__ int32_t part[kPrefixWaves][64];
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6, j = blockIdx.y;
   const int gb = blockIdx.x * 64 + lane;
-  const bool live = gb < b_cap;
-  const int per = (n_chunks + 3) / 4;
-  const int c0 = min(q * per, n_chunks), c1 = min(c0 + per, n_chunks);
-  int32_t* col = counters + (size_t)j * n_chunks * b_cap + (live ? gb : 0);
+  const bool live = gb < G.b_cap;
+  const int per = (G.n_chunks + kPrefixWaves - 1) / kPrefixWaves;
+  const int c0 = min(q * per, G.n_chunks), c1 = min(c0 + per, G.n_chunks);
+  int32_t* col = counters + (size_t)j * G.n_chunks * G.b_cap + (live ? gb : 0);
   int32_t sum = 0;
   if (live) {
     int c = c0;
     for (; c + 8 <= c1; c += 8) {
       int32_t v[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = col[(size_t)(c + i) * b_cap];
+      for (int i = 0; i < 8; ++i) v[i] = col[(size_t)(c + i) * G.b_cap];
 #pragma unroll
       for (int i = 0; i < 8; ++i) sum += v[i];
     }
-    for (; c < c1; ++c) sum += col[(size_t)c * b_cap];
+    for (; c < c1; ++c) sum += col[(size_t)c * G.b_cap];
   }
   part[q][lane] = sum;
   __syncthreads();
@@ -157,399 +376,274 @@ __global__ void __launch_bounds__(256) k_chunk_prefix(int32_t* __restrict__ coun
     for (; c + 8 <= c1; c += 8) {
       int32_t v[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = col[(size_t)(c + i) * b_cap];
+      for (int i = 0; i < 8; ++i) v[i] = col[(size_t)(c + i) * G.b_cap];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        col[(size_t)(c + i) * b_cap] = run;
+        col[(size_t)(c + i) * G.b_cap] = run;
         run += v[i];
       }
     }
     for (; c < c1; ++c) {
-      const int32_t v = col[(size_t)c * b_cap];
-      col[(size_t)c * b_cap] = run;
+      const int32_t v = col[(size_t)c * G.b_cap];
+      col[(size_t)c * G.b_cap] = run;
       run += v;
     }
-    if (q == 3) {
-      const int L = j * b_cap + gb;
-      cnt[L] = run;
-      len_scan[L] = run;
-    }
   }
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) len_scan[n_lists] = 0;
-}
-
-// ------------------------------------------------------------------------------------------------ dense detection
-// Dense forward path: which (query tile, KV block) pairs skip the gather route.  A query tile is kTileTokens
-// consecutive tokens of one sequence.  One wavefront per (tile, kv head), lane = token: a KV block that at least
-// `need` = half of the tile's tokens keep (the attention-sink block, the tokens' own block and the blocks next to it
-// are kept by all of them) becomes a dense pair: the forward computes it for the whole tile with the query tile read
-// once and the output accumulated on chip, a 64-bit mask saying which tokens really keep it.  The tokens' columns
-// that hold such a block are recorded in dmask; the scatter flags their list entries, and the gather route of the
-// forward skips them.  Nothing here is assumed about the selection: pairs come from counting, and any pair may take
-// either route.  Candidates are the kept blocks of three tokens of the tile (first, middle, last); a block that
-// qualifies but is kept by none of the three simply stays on the gather route.  A per-wavefront table of counters
-// (block id modulo kDenseHash, LDS atomics: counts are order-free) tells which candidates can reach `need`: lane m
-// looks up column m of the proposing token, so only the few that pass get the exact count (a ballot).
-// The dense table lists 64-key pieces (a 128-token block gives two) by first key and key count, in the order found;
-// pieces no token of the tile can see (wholly in the future, or wholly before every token's window) are left out.
-// grid (ceil(t_cap / 4), hkv), 256 threads.  Dynamic LDS: 4 * (kDenseHash + 64 * (k + 1)) ints.
-__global__ void __launch_bounds__(256) k_dense_detect(const int32_t* __restrict__ idx, const int32_t* __restrict__ cu,
-                                                      const int32_t* __restrict__ tile_tok0,
-                                                      const int32_t* __restrict__ tile_len, int nseq, int T, int hkv,
-                                                      int k, int bk, int causal, int window, int t_cap, int on,
-                                                      const uint32_t* __restrict__ vmask,
-                                                      uint32_t* __restrict__ dmask, int32_t* __restrict__ d_cnt,
-                                                      int2* __restrict__ d_piece,
-                                                      unsigned long long* __restrict__ d_mask) {
-  extern __shared__ int32_t lds[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = blockIdx.y;
-  const int qt = blockIdx.x * 4 + wave;
-  if (qt >= t_cap) return;  // no block-wide barrier below
-  int32_t* hash = lds + wave * (kDenseHash + 64 * (k + 1));
-  int32_t* rows = hash + kDenseHash;
-  const int tlen = tile_len[qt], ttok0 = tile_tok0[qt];
-  const size_t slot = (size_t)qt * hkv + j;
-  if (tlen == 0 || !on) {
-    if (lane == 0) d_cnt[slot] = 0;
-    if (lane < tlen) dmask[(size_t)(ttok0 + lane) * hkv + j] = 0u;
-    return;
-  }
-  const int t = ttok0 + lane;
-  const bool live = lane < tlen;
-  int s, c0, c1;
-  seq_bounds(cu, nseq, T, ttok0, s, c0, c1);  // a tile lies in one sequence
-  for (int i = lane; i < kDenseHash; i += 64) hash[i] = 0;
-  int32_t* row = rows + lane * (k + 1);
-  const uint32_t vm = live ? vmask[(size_t)t * hkv + j] : 0u;
-  if ((k & 3) == 0 && (reinterpret_cast<uintptr_t>(idx) & 15) == 0) {
-    // the tile's rows of idx, 16 bytes per lane: k / 4 lanes cover a row, 256 / k rows per access
-    const int lpr = k >> 2, rpa = 64 / lpr;
-    const int sub = lane % lpr, r0 = lane / lpr;
-    for (int rr = r0; rr < tlen; rr += rpa) {
-      const int4 x = *reinterpret_cast<const int4*>(idx + ((size_t)(ttok0 + rr) * hkv + j) * k + 4 * sub);
-      int32_t* dst = rows + rr * (k + 1) + 4 * sub;
-      dst[0] = x.x; dst[1] = x.y; dst[2] = x.z; dst[3] = x.w;
-    }
-  } else if (live) {
-    const int32_t* src = idx + ((size_t)t * hkv + j) * k;
-    for (int m = 0; m < k; ++m) row[m] = src[m];
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  for (int m = 0; m < k; ++m)
-    if ((vm >> m) & 1u) atomicAdd(&hash[row[m] & (kDenseHash - 1)], 1);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  // this token's kept block ids in registers (-1 where the column is not kept: no candidate matches it)
-  int kept[kMaxTopk];
+  if (q == kPrefixWaves - 1) {
+    if (live) cnt[j * G.b_cap + gb] = run;
+    int e = live ? run : 0, nu = (e + G.unit - 1) / G.unit;
 #pragma unroll
-  for (int m = 0; m < kMaxTopk; ++m) kept[m] = (m < k && ((vm >> m) & 1u)) ? row[m] : -1;
-  const int need = (tlen + 1) >> 1;
-  const int prop[3] = {0, tlen >> 1, tlen - 1};
-  int nd = 0;
-  uint32_t dm = 0;
-  for (int pi = 0; pi < 3; ++pi) {
-    const int p = prop[pi];
-    if ((pi == 1 && p == prop[0]) || (pi == 2 && (p == prop[0] || p == prop[1]))) continue;
-    const uint32_t pvm = (uint32_t)__builtin_amdgcn_readlane((int)vm, p);
-    // lane m: could column m of token p's row reach `need`?
-    const bool mine = lane < k && ((pvm >> lane) & 1u);
-    const int cand_blk = mine ? rows[p * (k + 1) + lane] : 0;
-    const int cand_cnt = mine ? hash[cand_blk & (kDenseHash - 1)] : 0;
-    unsigned long long cand = __builtin_amdgcn_ballot_w64(cand_cnt >= need);
-    while (cand != 0ull) {
-      const int m = __builtin_ctzll(cand);
-      cand &= cand - 1ull;
-      const int c = __builtin_amdgcn_readlane(cand_blk, m);
-      int mycol = -1;
-#pragma unroll
-      for (int mm = kMaxTopk - 1; mm >= 0; --mm) mycol = kept[mm] == c ? mm : mycol;
-      const unsigned long long members = __builtin_amdgcn_ballot_w64(mycol >= 0);
-      // an earlier proposer that keeps c has already dealt with it
-      bool seen = false;
-      for (int pj = 0; pj < pi; ++pj) seen |= ((members >> prop[pj]) & 1ull) != 0ull;
-      if (seen || __popcll(members) < need) continue;
-      // the block's 64-key pieces some token of the tile can see
-      const int btok0 = c0 + c * bk, blen = min(bk, c1 - btok0);
-      int np = 0, ptok[2], plen[2];
-      for (int sub = 0; sub < (bk >> 6); ++sub) {
-        const int pt = btok0 + 64 * sub, pl = min(64, blen - 64 * sub);
-        if (pl <= 0) continue;
-        if (causal && pt > ttok0 + tlen - 1) continue;
-        if (window > 0 && pt + pl - 1 < ttok0 - window + 1) continue;
-        ptok[np] = pt;
-        plen[np] = pl;
-        ++np;
-      }
-      if (nd + np > kDenseMax) continue;
-      if (lane == 0)
-        for (int q = 0; q < np; ++q) {
-          d_piece[slot * kDenseMax + nd + q] = make_int2(ptok[q], plen[q]);
-          d_mask[slot * kDenseMax + nd + q] = members;
-        }
-      if (mycol >= 0) dm |= 1u << mycol;  // also when no piece is visible: the pair then contributes nothing
-      nd += np;
+    for (int d = 32; d > 0; d >>= 1) {
+      e += __shfl_xor(e, d);
+      nu += __shfl_xor(nu, d);
     }
+    if (lane == 0) group_sum[j * G.n_groups + blockIdx.x] = make_int2(e, nu);
   }
-  if (lane == 0) d_cnt[slot] = nd;
-  if (live) dmask[(size_t)t * hkv + j] = dm;
 }
 
-// ------------------------------------------------------------------------------------------------ scan
-__global__ void __launch_bounds__(kScanThreads) k_scan_reduce(const int32_t* __restrict__ a, int64_t n,
-                                                              int32_t* __restrict__ sums) {
-  __shared__ int32_t part[kScanThreads];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  int32_t acc = 0;
-  for (int i = 0; i < kScanItems; ++i)
-    if (base + i < n) acc += a[base + i];
-  part[threadIdx.x] = acc;
+// Block-wide (kChunkThreads threads) sums of two values; ends with a barrier.
+__device__ __forceinline__ int2 block_sum(int2 v, int2* s_red) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    v.x += __shfl_xor(v.x, d);
+    v.y += __shfl_xor(v.y, d);
+  }
+  if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int s = kScanThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-    __syncthreads();
+  int2 r = make_int2(0, 0);
+#pragma unroll
+  for (int w = 0; w < kTilesPerChunk; ++w) {
+    r.x += s_red[w].x;
+    r.y += s_red[w].y;
   }
-  if (threadIdx.x == 0) sums[blockIdx.x] = part[0];
-}
-
-// In-place exclusive scan of one 4096-item tile, plus offsets[blockIdx.x] when given.
-__global__ void __launch_bounds__(kScanThreads) k_scan_tile(int32_t* __restrict__ a, int64_t n,
-                                                            const int32_t* __restrict__ offsets) {
-  __shared__ int32_t part[2][kScanThreads];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  int32_t v[kScanItems];
-  int32_t acc = 0;
-  for (int i = 0; i < kScanItems; ++i) {
-    v[i] = (base + i < n) ? a[base + i] : 0;
-    acc += v[i];
-  }
-  int cur = 0;
-  part[0][threadIdx.x] = acc;
   __syncthreads();
-  for (int s = 1; s < kScanThreads; s <<= 1) {  // Hillis-Steele inclusive scan of the thread totals
-    int32_t x = part[cur][threadIdx.x];
-    if ((int)threadIdx.x >= s) x += part[cur][threadIdx.x - s];
-    part[cur ^ 1][threadIdx.x] = x;
-    cur ^= 1;
-    __syncthreads();
-  }
-  int32_t run = part[cur][threadIdx.x] - acc + (offsets ? offsets[blockIdx.x] : 0);
-  for (int i = 0; i < kScanItems; ++i) {
-    if (base + i < n) a[base + i] = run;
-    run += v[i];
-  }
+  return r;
 }
 
-static int64_t scan_tmp_ints(int64_t n) {
-  int64_t total = 0;
-  while (n > kScanTile) {
-    n = (n + kScanTile - 1) / kScanTile;
-    total += (n + 63) / 64 * 64;
+// Block-wide exclusive scan of two values per thread; `total` receives the sums.  Ends with a barrier.
+__device__ __forceinline__ int2 block_scan(int2 v, int2* s_red, int2& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int2 inc = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int x = __shfl_up(inc.x, d), y = __shfl_up(inc.y, d);
+    if (lane >= d) { inc.x += x; inc.y += y; }
   }
-  return total + 64;
-}
-
-static void scan_exclusive(int32_t* a, int64_t n, int32_t* tmp, hipStream_t st) {
-  const int64_t nb = (n + kScanTile - 1) / kScanTile;
-  if (nb <= 1) {
-    hipLaunchKernelGGL(k_scan_tile, dim3(1), dim3(kScanThreads), 0, st, a, n, (const int32_t*)nullptr);
-    return;
+  if (lane == 63) s_red[wave] = inc;
+  __syncthreads();
+  int2 before = make_int2(0, 0);
+  total = make_int2(0, 0);
+#pragma unroll
+  for (int w = 0; w < kTilesPerChunk; ++w) {
+    const int2 x = s_red[w];
+    if (w < wave) { before.x += x.x; before.y += x.y; }
+    total.x += x.x;
+    total.y += x.y;
   }
-  hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, st, a, n, tmp);
-  scan_exclusive(tmp, nb, tmp + (nb + 63) / 64 * 64, st);
-  hipLaunchKernelGGL(k_scan_tile, dim3((unsigned)nb), dim3(kScanThreads), 0, st, a, n, (const int32_t*)tmp);
+  __syncthreads();
+  return make_int2(before.x + inc.x - v.x, before.y + inc.y - v.y);
 }
 
 // ------------------------------------------------------------------------------------------------ scatter
-// grid (n_chunks, hkv), ONE wavefront per group.  off[list] + chunk_off[kv head][chunk][block] is the position in
-// qent where the chunk's tokens of that list start.  Every kept column costs one
-// scattered 8-byte store (the list entry); the positions of a token's columns are collected in LDS and leave
-// as one contiguous row of slotpos.  Dynamic LDS: b_cap u64 masks + b_cap int cursors + 2 * 64*(k+1) ints.
-__global__ void __launch_bounds__(64) k_scatter(const int32_t* __restrict__ idx, const int32_t* __restrict__ cu,
-                                                const int32_t* __restrict__ blk_base, int nseq, int T, int hkv, int k,
-                                                int bk, int causal, int b_cap, int n_chunks,
-                                                const int32_t* __restrict__ chunk_off,
-                                                const int32_t* __restrict__ off, int2* __restrict__ qent,
-                                                const uint32_t* __restrict__ vmask,
-                                                const uint32_t* __restrict__ dmask, int32_t* __restrict__ slotpos) {
-  extern __shared__ int32_t lds[];
-  unsigned long long* mask = reinterpret_cast<unsigned long long*>(lds);
-  int32_t* cursor = lds + 2 * b_cap;
-  int32_t* rows = cursor + b_cap;
-  int32_t* prows = rows + 64 * (k + 1);
-  const int chunk = blockIdx.x, j = blockIdx.y, lane = threadIdx.x;
-  const int t0 = chunk * kChunkTokens, t1 = min(t0 + kChunkTokens, T);
-  int gb_lo, gb_hi;
-  chunk_window(cu, blk_base, nseq, T, t0, t1, bk, causal, gb_lo, gb_hi);
-  const int win = gb_hi - gb_lo;
-  for (int i = lane; i < win; i += 64) {
-    mask[i] = 0ull;
-    cursor[i] = off[j * b_cap + gb_lo + i] + chunk_off[((size_t)j * n_chunks + chunk) * b_cap + gb_lo + i];
-  }
-  __syncthreads();
-  int32_t* row = rows + lane * (k + 1);
-  int32_t* prow = prows + lane * (k + 1);
-  const unsigned long long below = (1ull << lane) - 1ull;
-  const bool vec4 = (k & 3) == 0 && ((reinterpret_cast<uintptr_t>(idx) | reinterpret_cast<uintptr_t>(slotpos)) & 15) == 0;
-  for (int r0 = t0; r0 < t1; r0 += 64) {
-    const int t = r0 + lane;
-    uint32_t vm = 0, dm = 0;
-    int base = 0;
-    if (t < t1) {
-      int s, c0, c1;
-      seq_bounds(cu, nseq, T, t, s, c0, c1);
-      const int32_t* src = idx + ((size_t)t * hkv + j) * k;
-      if (vec4) {
-        for (int m = 0; m < k; m += 4) {
-          const int4 x = *reinterpret_cast<const int4*>(src + m);
-          row[m] = x.x; row[m + 1] = x.y; row[m + 2] = x.z; row[m + 3] = x.w;
+// grid (n_chunks + 1, hkv).  Workgroup x = 0 of a kv head writes its scanned list offsets and work units; workgroup
+// x = 1 + chunk writes the chunk's list entries and, per token, the row of their positions.  The exclusive scan over the
+// lists is not a pass of its own: every workgroup sums the 64-list sums in front of its first list and scans the lengths
+// of the lists it needs (a few KB from L2).
+// A chunk's blocks are taken `win` at a time (one pass unless a sequence has more than kScatterWindow blocks).  Per
+// pass: every wavefront marks its tokens in its own 64-bit mask per block; the lowest member of a mask leaves the count
+// as the wavefront's byte of the block's word; a token's position is list offset + entries of earlier chunks +
+// the bytes of the wavefronts before its own + popcount(mask below its lane).
+// Dynamic LDS: win * (8 masks + 1 word of bytes + 1 offset) = 76 win bytes.
+template <int KMAX>
+__global__ void __launch_bounds__(kChunkThreads) k_scatter(IndexGeom G, int win, const int32_t* __restrict__ idx,
+                                                           const int32_t* __restrict__ cu, IndexPtrs p) {
+  extern __shared__ __attribute__((aligned(16))) int32_t lds[];
+  __shared__ int s_win[2 * kTilesPerChunk];
+  __shared__ int2 s_red[kTilesPerChunk];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = blockIdx.y;
+  const int2* gsum = p.group_sum + j * G.n_groups;  // the 64-list sums of this kv head, those of the others before it
+  if (blockIdx.x == 0) {
+    int2 run = make_int2(0, 0);
+    for (int i = tid - j * G.n_groups; i < 0; i += kChunkThreads) {
+      const int2 x = gsum[i];
+      run.x += x.x;
+      run.y += x.y;
+    }
+    run = block_sum(run, s_red);
+    for (int b0 = 0; b0 < G.b_cap; b0 += kChunkThreads) {
+      const int gb = b0 + tid, L = j * G.b_cap + gb;
+      const int len = gb < G.b_cap ? p.cnt[L] : 0, nu = (len + G.unit - 1) / G.unit;
+      int2 total;
+      const int2 ex = block_scan(make_int2(len, nu), s_red, total);
+      const int e0 = run.x + ex.x, u0 = run.y + ex.y;
+      if (gb < G.b_cap) {
+        p.off[L] = e0;
+        p.u_nu[L] = u0;
+        for (int u = 0; u < nu; ++u) {
+          p.u_list[u0 + u] = L;
+          p.u_start[u0 + u] = e0 + u * G.unit;
         }
-      } else {
-        for (int m = 0; m < k; ++m) row[m] = src[m];
       }
-      vm = vmask[(size_t)t * hkv + j];  // kept columns, decided by the histogram pass
-      dm = dmask[(size_t)t * hkv + j];  // those of them the dense forward path takes over
-      base = blk_base[s] - gb_lo;
+      run.x += total.x;
+      run.y += total.y;
     }
-    // A: mark membership of this round's tokens in every block they keep
-    for (int m = 0; m < k; ++m)
-      if ((vm >> m) & 1u) atomicOr(&mask[base + row[m]], 1ull << lane);
-    __syncthreads();
-    // B: rank among the lower tokens of the round gives the position; lists come out ascending.  Four columns
-    // per step so that their LDS reads are in flight together.
-    for (int m0 = 0; m0 < k; m0 += 4) {
-      int w[4], c[4];
-      unsigned long long mk[4];
-      bool on[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        on[u] = m0 + u < k && ((vm >> (m0 + u)) & 1u);
-        w[u] = on[u] ? base + row[m0 + u] : 0;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        c[u] = cursor[w[u]];
-        mk[u] = mask[w[u]];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int pos = on[u] ? c[u] + __popcll(mk[u] & below) : -1;
-        // the sign bit of the column flags an entry of a dense (tile, block) pair: the forward's gather route skips
-        // it, the backward (which walks whole lists) ignores the flag
-        if (on[u]) qent[pos] = make_int2(t, (m0 + u) | (int)(((dm >> (m0 + u)) & 1u) << 31));
-        if (m0 + u < k) prow[m0 + u] = pos;
-      }
+    if (j == G.hkv - 1 && tid == 0) {
+      p.off[G.hkv * G.b_cap] = run.x;
+      p.u_nu[G.hkv * G.b_cap] = run.y;
     }
-    if (t < t1) {
-      int32_t* dst = slotpos + ((size_t)t * hkv + j) * k;
-      if (vec4) {
-        for (int m = 0; m < k; m += 4)
-          *reinterpret_cast<int4*>(dst + m) = make_int4(prow[m], prow[m + 1], prow[m + 2], prow[m + 3]);
-      } else {
-        for (int m = 0; m < k; ++m) dst[m] = prow[m];
-      }
-    }
-    __syncthreads();
-    // C: the lowest member of each touched block advances its cursor and clears the mask
-    for (int m0 = 0; m0 < k; m0 += 4) {
-      int w[4];
-      unsigned long long mk[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bool on = m0 + u < k && ((vm >> (m0 + u)) & 1u);
-        w[u] = on ? base + row[m0 + u] : -1;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) mk[u] = w[u] >= 0 ? mask[w[u]] : 0ull;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (mk[u] != 0ull && (mk[u] & below) == 0ull) {
-          cursor[w[u]] += __popcll(mk[u]);
-          mask[w[u]] = 0ull;
-        }
-    }
-    __syncthreads();
-  }
-}
-
-// ------------------------------------------------------------------------------------------------ finalize
-// number of work units per list (off is the scanned list lengths, n_lists + 1 entries)
-__global__ void k_finalize(const int32_t* __restrict__ cnt, const int32_t* __restrict__ off, int n_lists, int unit,
-                           int32_t* __restrict__ u_nu, int32_t* __restrict__ hdr) {
-  const int L = blockIdx.x * blockDim.x + threadIdx.x;
-  if (L > n_lists) return;
-  if (L == n_lists) {
-    hdr[HDR_NPAIRS] = off[n_lists];
-    u_nu[L] = 0;
     return;
   }
-  const int32_t c = cnt[L];
-  u_nu[L] = (c + unit - 1) / unit;
+  const int chunk = blockIdx.x - 1;
+  const Tile t = load_tile(G, chunk * kTilesPerChunk + wave, cu, p);
+  const int tok = t.tok0 + lane;
+  const bool live = lane < t.len;
+  int32_t row[KMAX];
+#pragma unroll
+  for (int m = 0; m < KMAX; ++m) row[m] = -1;
+  uint32_t vm = 0, dm = 0;
+  if (live) {
+    load_row<KMAX>(idx + ((size_t)tok * G.hkv + j) * G.k, G.k, rows_are_vec4(idx, G.k), row);
+    vm = p.vmask[(size_t)tok * G.hkv + j];               // kept columns, decided by the histogram pass
+    if (G.dense) dm = p.dmask[(size_t)tok * G.hkv + j];  // those of them the dense forward path takes over
+  }
+  int gb_lo, gb_hi;
+  chunk_window(G, t, wave, s_win, gb_lo, gb_hi);
+  unsigned long long* masks = reinterpret_cast<unsigned long long*>(lds);
+  unsigned long long* bytes = masks + kTilesPerChunk * win;
+  int32_t* cursor = reinterpret_cast<int32_t*>(bytes + win);
+  unsigned long long* mask = masks + wave * win;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  int32_t pos[KMAX];
+#pragma unroll
+  for (int m = 0; m < KMAX; ++m) pos[m] = -1;
+
+  const int w_first = gb_lo & ~63;  // passes start at a 64-list boundary
+  int2 part = make_int2(0, 0);
+  for (int i = tid - j * G.n_groups; i < (w_first >> 6); i += kChunkThreads) part.x += gsum[i].x;
+  int run = block_sum(part, s_red).x;  // first position of list (j, w_first)
+  const int32_t* chunk_off = p.chunk_off + ((size_t)j * G.n_chunks + chunk) * G.b_cap;
+  for (int w0 = w_first; w0 < gb_hi; w0 += win) {
+    // list offsets of the window's blocks: two consecutive blocks per thread
+    const int i0 = 2 * tid, gb = w0 + i0;
+    const bool on0 = i0 < win && gb < G.b_cap, on1 = i0 + 1 < win && gb + 1 < G.b_cap;
+    const int len0 = on0 ? p.cnt[j * G.b_cap + gb] : 0, len1 = on1 ? p.cnt[j * G.b_cap + gb + 1] : 0;
+    const int co0 = on0 ? chunk_off[gb] : 0, co1 = on1 ? chunk_off[gb + 1] : 0;
+    for (int i = tid; i < 9 * win / 2; i += kChunkThreads)  // masks and bytes, 16 bytes at a time
+      reinterpret_cast<uint4*>(lds)[i] = make_uint4(0, 0, 0, 0);
+    int2 total;
+    const int2 ex = block_scan(make_int2(len0 + len1, 0), s_red, total);
+    if (i0 < win) cursor[i0] = run + ex.x + co0;
+    if (i0 + 1 < win) cursor[i0 + 1] = run + ex.x + len0 + co1;
+    run += total.x;
+    __syncthreads();
+    const int base = t.bb - w0;
+    int at[KMAX];  // the column's block inside the window, -1 where it is not kept or belongs to another pass
+#pragma unroll
+    for (int m = 0; m < KMAX; ++m) {
+      const int b = base + row[m];
+      at[m] = (((vm >> m) & 1u) && b >= 0 && b < win) ? b : -1;
+      if (m >= G.k) continue;
+      const unsigned long long act = __builtin_amdgcn_ballot_w64(at[m] >= 0);
+      if (act == 0ull) continue;
+      const int lead = __builtin_ctzll(act);
+      const int x0 = __builtin_amdgcn_readlane(at[m], lead);
+      if (__builtin_amdgcn_ballot_w64(at[m] == x0) == act) {  // a column all lanes agree on: one atomic (see count_column)
+        if (lane == lead) atomicOr(&mask[x0], act);
+      } else if (at[m] >= 0) {
+        atomicOr(&mask[at[m]], 1ull << lane);
+      }
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int m = 0; m < KMAX; ++m) {
+      if (at[m] < 0) continue;
+      const unsigned long long mk = mask[at[m]];
+      if ((mk & below) == 0ull) reinterpret_cast<uint8_t*>(bytes + at[m])[wave] = (uint8_t)__popcll(mk);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < KMAX; ++m) {
+      if (at[m] < 0) continue;
+      // tokens of this tile before the lane, then of the chunk's earlier tiles (v_sad_u8 adds four bytes)
+      int q = cursor[at[m]] + __popcll(mask[at[m]] & below);
+      const unsigned long long earlier = bytes[at[m]] & ((1ull << (8 * wave)) - 1ull);
+      q = (int)__builtin_amdgcn_sad_u8((uint32_t)earlier, 0u, (uint32_t)q);
+      q = (int)__builtin_amdgcn_sad_u8((uint32_t)(earlier >> 32), 0u, (uint32_t)q);
+      // the sign bit of the column flags an entry of a dense (tile, block) pair: the forward's gather route skips
+      // it, the backward (which walks whole lists) ignores the flag
+      p.qent[q] = make_int2(tok, m | (int)(((dm >> m) & 1u) << 31));
+      pos[m] = q;
+    }
+    if (w0 + win < gb_hi) __syncthreads();  // the tables are rewritten by the next pass
+  }
+  if (live) {
+    int32_t* dst = p.slotpos + ((size_t)tok * G.hkv + j) * G.k;
+    if (rows_are_vec4(p.slotpos, G.k)) {
+#pragma unroll
+      for (int m = 0; m < KMAX; m += 4)
+        if (m < G.k) *reinterpret_cast<int4*>(dst + m) = make_int4(pos[m], pos[m + 1], pos[m + 2], pos[m + 3]);
+    } else {
+#pragma unroll
+      for (int m = 0; m < KMAX; ++m)
+        if (m < G.k) dst[m] = pos[m];
+    }
+  }
 }
 
-// nu_scan is the exclusive scan of units per list (n_lists + 1 entries).
-__global__ void k_units(const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off, int n_lists, int unit,
-                        int32_t* __restrict__ u_list, int32_t* __restrict__ u_start, int32_t* __restrict__ hdr_slot) {
-  const int L = blockIdx.x * blockDim.x + threadIdx.x;
-  if (L >= n_lists) return;
-  const int u0 = nu_scan[L], u1 = nu_scan[L + 1];
-  for (int u = u0; u < u1; ++u) {
-    u_list[u] = L;
-    u_start[u] = off[L] + (u - u0) * unit;
+template <int KMAX>
+static hipError_t launch_inversion(const IndexGeom& G, const int32_t* idx, const int32_t* cu, const IndexPtrs& p,
+                                   hipStream_t st) {
+  const int lds_hist = 4 * (G.b_cap + (G.dense ? kTilesPerChunk * kDenseHash : 0));
+  const int win = min((G.b_cap + 63) & ~63, kScatterWindow);
+  const int lds_scat = 76 * win;
+  if (lds_hist > 60 * 1024 || lds_scat > 60 * 1024) {  // beyond the default 64 KB
+    static std::atomic<uint64_t> ready_hist, ready_scat;
+    hipError_t e = allow_dynamic_lds((const void*)k_hist<KMAX>, 150 * 1024, ready_hist);
+    if (e == hipSuccess) e = allow_dynamic_lds((const void*)k_scatter<KMAX>, 150 * 1024, ready_scat);
+    if (e != hipSuccess) return e;
   }
-  if (L == n_lists - 1) *hdr_slot = u1;
+  {
+    ProfScope ps(KID_INDEX_HIST, st);
+    hipLaunchKernelGGL(k_hist<KMAX>, dim3(G.n_chunks, G.hkv), dim3(kChunkThreads), lds_hist, st, G, idx, cu, p);
+  }
+  if (G.dense) ProfScope in_hist(KID_INDEX_DENSE, st);  // part of the launch above: recorded, with no time of its own
+  {
+    ProfScope ps(KID_INDEX_SCAN, st);
+    hipLaunchKernelGGL(k_prefix, dim3(G.n_groups, G.hkv), dim3(64 * kPrefixWaves), 0, st, G, p.chunk_off, p.cnt,
+                       p.group_sum);
+  }
+  ProfScope ps(KID_INDEX_SCATTER, st);
+  hipLaunchKernelGGL(k_scatter<KMAX>, dim3(G.n_chunks + 1, G.hkv), dim3(kChunkThreads), lds_scat, st, G, win, idx, cu, p);
+  return hipGetLastError();
 }
 
 hipError_t launch_build_index(const IndexLayout& L, const int32_t* idx, const int32_t* cu, void* index_ws,
                               hipStream_t st) {
-  IndexPtrs p = index_ptrs(L, index_ws);
-  const size_t lds_hist = (size_t)L.b_cap * 4 + 256 * (size_t)(L.topk + 1) * 4;
-  const size_t lds_scat = (size_t)L.b_cap * 12 + 2 * 64 * (size_t)(L.topk + 1) * 4;
-  if (lds_hist > 64 * 1024 || lds_scat > 64 * 1024) {  // long sequences: block tables beyond the default 64 KB
-    static std::atomic<uint64_t> ready_hist, ready_scat;
-    hipError_t e = allow_dynamic_lds((const void*)k_hist, 160 * 1024, ready_hist);
-    if (e == hipSuccess) e = allow_dynamic_lds((const void*)k_scatter, 160 * 1024, ready_scat);
-    if (e != hipSuccess) return e;
+  const IndexPtrs p = index_ptrs(L, index_ws);
+  IndexGeom G;
+  G.nseq = L.nseq;
+  G.T = L.T;
+  G.hkv = L.hkv;
+  G.k = L.topk;
+  G.bk = L.bk;
+  G.causal = L.causal;
+  G.window = L.window;
+  G.b_cap = L.b_cap;
+  G.t_cap = L.t_cap;
+  G.n_chunks = L.n_chunks;
+  G.n_groups = L.n_groups;
+  G.unit = L.unit;
+  G.dense = L.dense;
+  if (G.nseq > 1) {
+    ProfScope ps(KID_INDEX_PREP, st);
+    hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, G, cu, p);
   }
-  { ProfScope ps(KID_INDEX_PREP, st);
-  hipLaunchKernelGGL(k_prep, dim3(1), dim3(256), 0, st, cu, L.nseq, L.T, L.bk, L.b_cap, p.blk_base, p.blk_tok0, p.blk_len,
-                     p.hdr + HDR_BTOT);
-  // the query tiles of the dense forward path: the same table for blocks of kTileTokens tokens
-  hipLaunchKernelGGL(k_prep, dim3(1), dim3(256), 0, st, cu, L.nseq, L.T, kTileTokens, L.t_cap, p.tile_base, p.tile_tok0,
-                     p.tile_len, p.hdr + HDR_NTILES); }
-  { ProfScope ps(KID_INDEX_HIST, st);
-  hipLaunchKernelGGL(k_hist, dim3(L.n_chunks, L.hkv), dim3(256), lds_hist, st, idx, cu, p.blk_base, L.nseq, L.T, L.hkv,
-                     L.topk, L.bk, L.causal, L.window, L.b_cap, L.n_chunks, p.chunk_off, p.vmask); }
-  const int nl1 = L.n_lists + 1;
-  { ProfScope ps(KID_INDEX_CHUNK_PREFIX, st);
-  hipLaunchKernelGGL(k_chunk_prefix, dim3((L.b_cap + 63) / 64, L.hkv), dim3(256), 0, st, p.chunk_off, L.b_cap, L.n_chunks,
-                     L.n_lists, p.cnt, p.off); }
-  { ProfScope ps(KID_INDEX_SCAN, st);
-  scan_exclusive(p.off, nl1, p.scan_tmp, st); }
-  { ProfScope ps(KID_INDEX_DENSE, st);
-  const size_t lds_dense = 4 * (size_t)(kDenseHash + 64 * (L.topk + 1)) * 4;
-  hipLaunchKernelGGL(k_dense_detect, dim3((L.t_cap + 3) / 4, L.hkv), dim3(256), lds_dense, st, idx, cu, p.tile_tok0,
-                     p.tile_len, L.nseq, L.T, L.hkv, L.topk, L.bk, L.causal, L.window, L.t_cap,
-                     L.dense, p.vmask,
-                     p.dmask, p.d_cnt, p.d_piece, p.d_mask); }
-  { ProfScope ps(KID_INDEX_SCATTER, st);
-  hipLaunchKernelGGL(k_scatter, dim3(L.n_chunks, L.hkv), dim3(64), lds_scat, st, idx, cu, p.blk_base, L.nseq, L.T,
-                     L.hkv, L.topk, L.bk, L.causal, L.b_cap, L.n_chunks, p.chunk_off, p.off, p.qent, p.vmask, p.dmask,
-                     p.slotpos); }
-  { ProfScope ps(KID_INDEX_FINALIZE, st);
-  hipLaunchKernelGGL(k_finalize, dim3((nl1 + 255) / 256), dim3(256), 0, st, p.cnt, p.off, L.n_lists, L.unit, p.u_nu,
-                     p.hdr); }
-  { ProfScope ps(KID_INDEX_SCAN, st);
-  scan_exclusive(p.u_nu, nl1, p.scan_tmp, st); }
-  { ProfScope ps(KID_INDEX_UNITS, st);
-  hipLaunchKernelGGL(k_units, dim3((L.n_lists + 255) / 256), dim3(256), 0, st, p.u_nu, p.off, L.n_lists, L.unit,
-                     p.u_list, p.u_start, p.hdr + HDR_UNITS); }
-  return hipGetLastError();
+  // rows of idx live in registers: a variant per width
+  if (G.k <= 8) return launch_inversion<8>(G, idx, cu, p, st);
+  if (G.k <= 16) return launch_inversion<16>(G, idx, cu, p, st);
+  return launch_inversion<32>(G, idx, cu, p, st);
 }
 
-// scratch of the scans: the longest scanned array has one entry per list plus one
-int64_t index_scan_tmp_ints(int64_t n_lists) { return scan_tmp_ints(n_lists + 1); }
+int index_chunks(int t_cap) { return (t_cap + kTilesPerChunk - 1) / kTilesPerChunk; }
 
 }  // namespace nsa
