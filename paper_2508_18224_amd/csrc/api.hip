@@ -66,8 +66,7 @@ static IndexLayout make_layout(const nsa_sel_shape* s) {
   L.vmask = take(4 * ((size_t)L.T * L.hkv + 1));
   L.slotpos = take(4 * (size_t)(L.p_max + 1));
   L.u_nu = take(4 * (size_t)(L.n_lists + 1));
-  L.u_list = take(4 * (size_t)(L.units_max + 1));
-  L.u_start = take(4 * (size_t)(L.units_max + 1));
+  L.u_rec = take(sizeof(UnitRec) * (size_t)(L.units_max + 1));
   L.group_sum = take(8 * (size_t)L.hkv * L.n_groups);
   L.tile_base = take(4 * (size_t)(L.nseq + 1));
   L.tile_tok0 = take(4 * (size_t)L.t_cap);

@@ -5,7 +5,7 @@
 //
 //   k_bwd_delta       delta[t,h] = <dO[t,h], O[t,h]>, stored next to LSE[t,h] log2(e) as one 8-byte pair so that the
 //                     main kernel fetches both row statistics with one gather
-//   k_bwd_tiled<NKB>  the main kernel for B_K = 64 (NKB = B_K / 32 = 2).  One work unit = (kv head j, KV block i, up to
+//   k_bwd_tiled       the main kernel for B_K = 64.  One work unit = (kv head j, KV block i, up to
 //                     P.unit list entries): four wavefronts and half of a CU's LDS, so two workgroups share a CU and
 //                     cover each other's barriers and waits.  The waves share tiles of 64 gathered rows and take three
 //                     roles per tile (see the comment above the kernel): S = Q K_i^T, dP = dO V_i^T,
@@ -49,129 +49,147 @@ __device__ __forceinline__ void wave_sync_bwd() {  // orders a wavefront's own L
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// delta[t, h] = <dO[t, h], O[t, h]> next to LSE[t, h] log2(e).  The pair is gathered by the main kernels once per (pair,
+// head), so it is laid out head-major, [kv head][token][head of the group]: one kv head's pairs (8 g bytes a token, 2 MB
+// at 65536 tokens and g = 4) stay in an XCD's L2 while the main kernels work on that head.  In token-major order every
+// gather of 8 g bytes fetched a line of its own (2 GB per pass at 65536 tokens, 32 kv heads, g = 1).
+// A workgroup takes kDeltaTokens tokens x kDeltaHeads query heads: rows are read in memory order (16 lanes x 16 bytes a
+// row, four rows per lane in flight), the pairs are turned around in LDS and leave as runs of 8 g kDeltaTokens bytes.
+constexpr int kDeltaTokens = 8;
+constexpr int kDeltaKv = 8;   // kv heads per workgroup: at most 64 query heads
+
 __global__ void __launch_bounds__(256)
-k_bwd_delta(int64_t rows, const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO, const float* __restrict__ LSE,
+k_bwd_delta(Problem P, const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO, const float* __restrict__ LSE,
             float2* __restrict__ stats, const float* __restrict__ gate, float* __restrict__ dgate) {
-  const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-  const int sub = threadIdx.x & 15;
-  float acc = 0.f;
-  if (row < rows) {
-    const uint4 a = *reinterpret_cast<const uint4*>(O + row * kD + 8 * sub);
-    const uint4 b = *reinterpret_cast<const uint4*>(dO + row * kD + 8 * sub);
-    acc = bf16_lo(a.x) * bf16_lo(b.x) + bf16_hi(a.x) * bf16_hi(b.x) + bf16_lo(a.y) * bf16_lo(b.y) +
-          bf16_hi(a.y) * bf16_hi(b.y) + bf16_lo(a.z) * bf16_lo(b.z) + bf16_hi(a.z) * bf16_hi(b.z) +
-          bf16_lo(a.w) * bf16_lo(b.w) + bf16_hi(a.w) * bf16_hi(b.w);
+  __shared__ float deltas[kDeltaTokens * kDeltaKv * 8];
+  const int t0 = blockIdx.x * kDeltaTokens, j0 = blockIdx.y * kDeltaKv;
+  const int nt = min(kDeltaTokens, P.T - t0), nj = min(kDeltaKv, P.hkv - j0), nh = nj * P.g;
+  const int sub = threadIdx.x & 15, rows = nt * nh;
+  constexpr int kB = 4, kOut = kDeltaTokens * kDeltaKv * 8 / 256;
+  // the pairs this thread writes, in (kv head, token, head of the group) order; their LSE is requested before the rows
+  int from[kOut];
+  int64_t row_out[kOut];
+  size_t to[kOut];
+  float lse2[kOut];
+#pragma unroll
+  for (int q = 0; q < kOut; ++q) {
+    const int i = min((int)threadIdx.x + 256 * q, rows - 1);
+    const int jl = i / (nt * P.g), rem = i - jl * nt * P.g, tt = rem / P.g, hh = rem - tt * P.g;
+    from[q] = tt * nh + jl * P.g + hh;
+    row_out[q] = (int64_t)(t0 + tt) * P.hq + (j0 + jl) * P.g + hh;
+    to[q] = ((size_t)(j0 + jl) * P.T + t0 + tt) * P.g + hh;
+    lse2[q] = LSE[row_out[q]] * 1.4426950408889634f;
   }
-  acc += __shfl_xor(acc, 8);
-  acc += __shfl_xor(acc, 4);
-  acc += __shfl_xor(acc, 2);
-  acc += __shfl_xor(acc, 1);
-  if (row < rows && sub == 0) {
-    float lse2 = LSE[row] * 1.4426950408889634f;
+  for (int r0 = threadIdx.x >> 4; r0 < rows; r0 += 16 * kB) {
+    uint4 a[kB], b[kB];
+    int64_t row[kB];
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+      const int r = min(r0 + 16 * i, rows - 1), tt = r / nh;
+      row[i] = (int64_t)(t0 + tt) * P.hq + j0 * P.g + (r - tt * nh);
+      a[i] = *reinterpret_cast<const uint4*>(O + row[i] * kD + 8 * sub);
+      b[i] = *reinterpret_cast<const uint4*>(dO + row[i] * kD + 8 * sub);
+    }
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+      float acc = bf16_lo(a[i].x) * bf16_lo(b[i].x) + bf16_hi(a[i].x) * bf16_hi(b[i].x) +
+                  bf16_lo(a[i].y) * bf16_lo(b[i].y) + bf16_hi(a[i].y) * bf16_hi(b[i].y) +
+                  bf16_lo(a[i].z) * bf16_lo(b[i].z) + bf16_hi(a[i].z) * bf16_hi(b[i].z) +
+                  bf16_lo(a[i].w) * bf16_lo(b[i].w) + bf16_hi(a[i].w) * bf16_hi(b[i].w);
+      acc += __shfl_xor(acc, 8);
+      acc += __shfl_xor(acc, 4);
+      acc += __shfl_xor(acc, 2);
+      acc += __shfl_xor(acc, 1);
+      if (sub == 0 && r0 + 16 * i < rows) deltas[r0 + 16 * i] = acc;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kOut; ++q) {
+    if ((int)threadIdx.x + 256 * q >= rows) break;
+    const float delta = deltas[from[q]];
     if (gate != nullptr) {
       // Gated output (Eq. (2)): the gradient that reaches this branch is gate * dO.  Every place the main kernel
       // uses it carries a factor P = exp2(s - lse2) (dV += P^T dO, dS = P (dP - delta)), so the gate is folded into
       // the row's log-sum-exp, lse2 - log2(gate), and dO and delta stay as they are; a zero gate gives +inf, P = 0.
       // d(loss)/d(gate) is the same <dO, O> as delta.
-      if (lse2 > -INFINITY) lse2 -= log2f(gate[row]);
-      dgate[row] = acc;
+      if (lse2[q] > -INFINITY) lse2[q] -= log2f(gate[row_out[q]]);
+      dgate[row_out[q]] = delta;
     }
-    stats[row] = make_float2(lse2, acc);
+    stats[to[q]] = make_float2(lse2[q], delta);
   }
 }
 
 // ---- the tiled backward main kernel ----------------------------------------------------------------------------
-// NKB = B_K / 32 key blocks, 2 NKB wavefronts per workgroup, tiles of 64 gathered rows.
-// With B_K = 64 (NKB = 2) a workgroup is four wavefronts (256 registers each) and half of a CU's LDS, so TWO
-// workgroups share a CU and run out of phase: one's barriers, gather waits, unit prologue and LDS-bound phases are
-// covered by the other's MFMA work (with one eight-wave workgroup per CU all waves sat in the same phase, and LDS,
-// MFMA and VALU time simply added up).  The kernel is written for any NKB, but only NKB = 2 is built: with B_K = 128 the
-// fp32 dK/dV accumulators leave room for one workgroup per CU only, and k_bwd_pipe128 below serves that case.
-// Per tile, wave w takes three roles in turn:
-//   rows/keys   (rb = w / NKB, kb = w % NKB): S = Q K_i^T, dP = dO V_i^T, P, dS for rows 32 rb.. and keys 32 kb..; K_i
-//               fragments from LDS, V_i fragments of the wave's 32 keys held in registers for the whole unit (only this
-//               role uses V_i).  The products are taken with lane = key, so that a lane holds four consecutive rows of
-//               P^T / dS^T per register quad (one 8-byte LDS store); the rows' statistics come from a record per row
-//               that the staging waves leave in LDS
-//   keys/chans  (kb2 = w / 2, hf = w % 2): dV_i, dK_i accumulators for keys 32 kb2.. and channels 64 hf.. (two
-//               32-channel blocks share every P^T / dS^T operand read)
-//   rows/chans  (rb = w / NKB, part = w % NKB): dQ^T for rows 32 rb.. and the 128 / NKB channels of `part`; the same
-//               wave stages / prefetches that part of the Q and dO tiles and stores that part of dQ
+// B_K = 64: four wavefronts (256 registers each) and half of a CU's LDS, so TWO workgroups share a CU and run out of
+// phase: one's barriers, gather waits, unit prologue and LDS-bound phases are covered by the other's MFMA work (with one
+// eight-wave workgroup per CU all waves sat in the same phase, and LDS, MFMA and VALU time simply added up).
+// Tiles of 64 gathered rows; per tile, wave (rb = w / 2, kb = w % 2) takes three roles in turn:
+//   rows/keys   S = Q K_i^T, dP = dO V_i^T, P, dS for rows 32 rb.. and keys 32 kb..; K_i fragments from LDS, V_i fragments
+//               of the wave's 32 keys held in registers for the whole unit (only this role uses V_i).  The products are
+//               taken with lane = key, so that a lane holds four consecutive rows of P^T / dS^T per register quad (one
+//               8-byte LDS store); the rows' statistics come from a record per row that the staging waves leave in LDS
+//   keys/chans  dV_i, dK_i accumulators for keys 32 rb.. and channels 64 kb.. (two 32-channel blocks share every
+//               P^T / dS^T operand read)
+//   rows/chans  dQ^T for rows 32 rb.. and channels 64 kb..; the same wave stages / prefetches that part of the Q and dO
+//               tiles and stores that part of dQ
 // K_i, Q, dO (304-byte pitch) and P^T, dS^T (144-byte pitch) are row-major tiles in LDS; "lane = column" operands
 // are LDS transpose reads.  The list's token ids are kept in LDS 1024 entries at a time.
+// A row's place in memory is worked out once, by the lane that owns it, one tile before its loads are issued, and handed
+// to the lanes that move it; rows move through buffer instructions without branches (see RowTensor), so the wait for a
+// tile's rows does not wait for the stores of the tile before.  That took 40 % of the vector instructions out of the loop
+// and a full drain of the memory queue out of every tile: 4.59 -> 4.25 ms at 65536 tokens, g = 4 (26.5 GB: 6.2 TB/s of the
+// 7.2 TB/s that plain gather + store kernels reach between the XCDs and the memory side).
 constexpr int kTile = 64;      // rows per tile
 constexpr int kPStride = 72;   // bf16 per row of the P^T / dS^T tiles: 64 rows + 8 pad
 constexpr int kEntSeg = 1024;  // list entries whose token ids are resident in LDS
 
-template <int NKB>
 struct BwdLds {
-  static constexpr int kKeys = 32 * NKB;
   static constexpr int K = 0;
-  static constexpr int Q = K + kKeys * kRowStride * 2;
+  static constexpr int Q = K + 64 * kRowStride * 2;
   static constexpr int DO = Q + kTile * kRowStride * 2;
   static constexpr int Pt = DO + kTile * kRowStride * 2;
-  static constexpr int DSt = Pt + kKeys * kPStride * 2;
-  static constexpr int Ent = DSt + kKeys * kPStride * 2;
-  static constexpr int Rec = Ent + kEntSeg * 4;    // per row of the tile: LSE (log2 domain), delta * scale, visible keys
-  static constexpr int Bytes = Rec + 3 * kTile * 4;  // 81664 (NKB = 2)
+  static constexpr int DSt = Pt + 64 * kPStride * 2;
+  static constexpr int Ent = DSt + 64 * kPStride * 2;
+  static constexpr int Rec = Ent + kEntSeg * 4;      // per row of the tile: LSE (log2 domain), delta * scale, visible keys
+  static constexpr int Bytes = Rec + 3 * kTile * 4;  // 81664
 };
-static_assert(2 * BwdLds<2>::Bytes <= 160 * 1024, "two workgroups of the 64-key backward must fit one CU's LDS");
+static_assert(2 * BwdLds::Bytes <= 160 * 1024, "two workgroups of the 64-key backward must fit one CU's LDS");
 
-template <int NKB, bool kWin>
-__global__ void __launch_bounds__(128 * NKB, NKB == 2 ? 2 : 1)
+template <bool kWin, bool kWide>
+__global__ void __launch_bounds__(256, 2)
 k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-            const bf16_t* __restrict__ dO, const float2* __restrict__ stats, const int32_t* __restrict__ u_list,
-            const int32_t* __restrict__ u_start, const int32_t* __restrict__ off,
-            const int32_t* __restrict__ blk_tok0, const int32_t* __restrict__ blk_len,
-            const int2* __restrict__ qent, const int32_t* __restrict__ nu_scan, bf16_t* __restrict__ dqpart,
-            float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
-  using Lds = BwdLds<NKB>;
-  constexpr int kKeys = 32 * NKB;      // B_K
-  constexpr int kThreads = 128 * NKB;
-  constexpr int kCW = 128 / NKB;       // channels of the rows/chans part of a wave: 64 or 32
-  constexpr int kNDB = kCW / 32;       // its 32-channel accumulator blocks: 2 or 1
-  constexpr int kLPR = kCW / 8;        // lanes (16 bytes each) that cover the part's channels of one row: 8 or 4
-  constexpr int kRPP = 64 / kLPR;      // rows staged per access: 8 or 16
-  constexpr int kNP = 32 / kRPP;       // accesses per tile and tensor: 4 or 2
+            const bf16_t* __restrict__ dO, const float2* __restrict__ stats, const UnitRec* __restrict__ u_rec,
+            const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off, const int2* __restrict__ qent,
+            bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16_t* Ks = reinterpret_cast<bf16_t*>(smem + Lds::K);
-  bf16_t* Qs = reinterpret_cast<bf16_t*>(smem + Lds::Q);
-  bf16_t* dOs = reinterpret_cast<bf16_t*>(smem + Lds::DO);
-  bf16_t* Pt = reinterpret_cast<bf16_t*>(smem + Lds::Pt);
-  bf16_t* dSt = reinterpret_cast<bf16_t*>(smem + Lds::DSt);
-  int32_t* ent = reinterpret_cast<int32_t*>(smem + Lds::Ent);
+  int32_t* ent = reinterpret_cast<int32_t*>(smem + BwdLds::Ent);
+  UnitRec U;
+  int ubase, pos0;
+  if (!load_unit(P, u_rec, nu_scan, off, U, ubase, pos0)) return;
+  const int j = U.j, ne = U.ne, tok0 = U.tok0, blen = U.blen;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 31, qh = lane >> 5, rb = wave >> 1, kb = wave & 1;
+  const uint32_t hbase = (uint32_t)(j * P.g), row_bytes = (uint32_t)P.hkv * (kD * 2);
 
-  const int ubase = nu_scan[P.j0 * P.b_cap];
-  const int u = ubase + blockIdx.x;
-  if (u >= nu_scan[(P.j0 + P.nj) * P.b_cap]) return;
-  const int L = u_list[u];
-  const int j = L / P.b_cap;
-  const int gb = L - j * P.b_cap;
-  const int e0 = u_start[u];
-  const int pos0 = off[P.j0 * P.b_cap];
-  const int ne = min(P.unit, off[L + 1] - e0);
-  const int tok0 = blk_tok0[gb], blen = blk_len[gb];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int col = lane & 31, qh = lane >> 5;  // not const: made opaque at the top of the tile loop
-  const int rb = wave / NKB, kb = wave % NKB;   // rows/keys role; rows/chans role uses (rb, part = kb)
-  const int kb2 = wave >> 1, hf = wave & 1;     // keys/chans role
-  const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-
-  {  // K_i -> LDS, row-major; rows past the end of a ragged block are zero
-    const int key = tid >> 2, d0 = (tid & 3) * 32;
-    const bf16_t* src = K + ((size_t)(tok0 + key) * P.hkv + j) * kD + d0;
+  // first segment's token ids, K_i (thread = key, 32 channels) and V_i fragments: all requested before any is waited for
+  int ids[kEntSeg / 256];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<bf16x8*>(&Ks[key * kRowStride + d0 + 8 * i]) =
-          key < blen ? *reinterpret_cast<const bf16x8*>(src + 8 * i) : zero8;
-  }
-  bf16x8 vf[8];  // V_i fragments of keys 32 kb.. (A operand of dP^T = V_i dO^T)
+  for (int i = 0; i < kEntSeg / 256; ++i) ids[i] = tid + 256 * i < ne ? qent[U.e0 + tid + 256 * i].x : 0;
+  bf16x8 kreg[4], vf[8];
   {
-    const int key = 32 * kb + col;
-    const bf16_t* src = V + ((size_t)(tok0 + key) * P.hkv + j) * kD + 8 * qh;
+    const __amdgpu_buffer_rsrc_t k_buf = block_buffer(K, P, U), v_buf = block_buffer(V, P, U);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) vf[s] = key < blen ? *reinterpret_cast<const bf16x8*>(src + 16 * s) : zero8;
+    for (int i = 0; i < 4; ++i) kreg[i] = load_frag(k_buf, (tid >> 2) * row_bytes + (tid & 3) * 64 + 16 * i);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) vf[s] = load_frag(v_buf, (32 * kb + col) * row_bytes + 16 * qh + 32 * s);
   }
+#pragma unroll
+  for (int i = 0; i < kEntSeg / 256; ++i) ent[tid + 256 * i] = ids[i];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    *reinterpret_cast<bf16x8*>(smem + BwdLds::K + (tid >> 2) * (kRowStride * 2) + (tid & 3) * 64 + 16 * i) = kreg[i];
+
   f32x16 dkacc[2], dvacc[2];
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb)
@@ -180,74 +198,102 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
       dkacc[cb][v] = 0.f;
       dvacc[cb][v] = 0.f;
     }
-
   const float c2 = P.scale * 1.4426950408889634f;
-  const int hbase = j * P.g;
-  const int grp = lane >> 4, sl = lane & 15;
-  // this lane's share of a transposing read of four rows x 16 columns (see lds_read_tr), for the two row pitches
-  int tr_lane = ((sl >> 2) + 8 * (grp >> 1)) * kRowStride + 16 * (grp & 1) + 4 * (sl & 3);
-  int tr_lane_p = ((sl >> 2) + 8 * (grp >> 1)) * kPStride + 16 * (grp & 1) + 4 * (sl & 3);
-  // staging layout of this wave's part: kLPR lanes x 16 B cover its channels of a row, kRPP rows per access
-  int srow = lane / kLPR, schunk = kCW * kb + (lane % kLPR) * 8;
-  bf16_t* Qmine = Qs + (32 * rb) * kRowStride;
-  bf16_t* dOmine = dOs + (32 * rb) * kRowStride;
 
-  u32x4 qc[kNP], dc[kNP];
-  float lse2_n, dl_n;
-  int seg0 = 0;  // first list entry whose token id is in `ent`
-  int rows_end = 0;
-  auto issue_rows = [&](int tile0) {
-    // rows past the end of the list re-read its last row: their P and dS are forced to zero (lim = 0) and their
-    // dQ is never stored, so no branch and no zero fill is needed
-#pragma unroll
-    for (int i = 0; i < kNP; ++i) {
-      const int r = min(tile0 + 32 * rb + kRPP * i + srow, rows_end - 1);
-      const int e = div_g(r, P.g, P.g_magic);
-      // (token, head) row index in 32 bits (total_tokens * hq < 2^31 is checked on the host), widened once
-      const uint32_t grow = (uint32_t)ent[e - seg0] * (uint32_t)P.hq + (uint32_t)(hbase + (r - e * P.g));
-      const size_t o = (size_t)grow * kD + schunk;
-      qc[i] = *reinterpret_cast<const u32x4*>(Q + o);
-      dc[i] = *reinterpret_cast<const u32x4*>(dO + o);
+  // this lane's places in the LDS tiles (everything else is an immediate offset)
+  const int grp = lane >> 4, sl = lane & 15, srow = lane >> 3;
+  unsigned char* const stage = smem + BwdLds::Q + (32 * rb + srow) * (kRowStride * 2) + 128 * kb + 16 * (lane & 7);
+  const unsigned char* const qfrag = smem + BwdLds::Q + (32 * rb + col) * (kRowStride * 2) + 16 * qh;
+  const unsigned char* const kfrag = smem + BwdLds::K + (32 * kb + col) * (kRowStride * 2) + 16 * qh;
+  const float* const rec_rd = reinterpret_cast<const float*>(smem + BwdLds::Rec) + 32 * rb + 4 * qh;
+  float* const rec_wr = reinterpret_cast<float*>(smem + BwdLds::Rec) + 32 * rb + col;
+  unsigned char* const pt_wr = smem + BwdLds::Pt + (32 * kb + col) * (kPStride * 2) + (32 * rb + 4 * qh) * 2;
+  const unsigned char* const pt_rd = smem + BwdLds::Pt + (32 * rb + col) * (kPStride * 2) + 16 * qh;
+  // transposing reads of four rows x 16 columns (see lds_read_tr), for the two row pitches
+  const bf16_t* const tr_row = reinterpret_cast<const bf16_t*>(smem + BwdLds::Q) +
+                               ((sl >> 2) + 8 * (grp >> 1)) * kRowStride + 16 * (grp & 1) + 4 * (sl & 3) + 64 * kb;
+  const bf16_t* const tr_ds = reinterpret_cast<const bf16_t*>(smem + BwdLds::DSt) +
+                              ((sl >> 2) + 8 * (grp >> 1)) * kPStride + 16 * (grp & 1) + 4 * (sl & 3) + 32 * rb;
+  unsigned char* const dq_wr = smem + BwdLds::Q + (32 * rb + col) * (kRowStride * 2) + 128 * kb + 8 * qh;
+  constexpr int kDoOff = BwdLds::DO - BwdLds::Q, kDsOff = BwdLds::DSt - BwdLds::Pt;
+
+  const RowTensor<kWide> Qrows(Q, (int64_t)P.T * P.hq), dOrows(dO, (int64_t)P.T * P.hq);
+  const uint32_t lane_off = 128 * kb + 16 * (lane & 7);  // 8 lanes cover the wave's 64 channels of a row
+  u32x4 qc[4], dc[4];
+  const float2* const head_stats = stats + (size_t)j * P.T * P.g;
+  float2 st;                // (LSE in the log2 domain, delta) of row col
+  int seg0 = 0, rows_end = 0;
+
+  // Row 32 rb + col of the tile at row tile0 of the unit: its (token, head) row in Q / dO (in 32 bits: total_tokens * hq <
+  // 2^31 is checked on the host), its place in the kv head's statistics and the keys of the block it sees.  Rows past the end of the list re-read its
+  // last row: they see no key, so their P and dS are zero, and their dQ is dropped by the store.
+  auto find_row = [&](int tile0, uint32_t& row, uint32_t& sidx, uint32_t& vis) __attribute__((always_inline)) {
+    const int r = tile0 + 32 * rb + col, rc = min(r, rows_end - 1);
+    const int e = div_g(rc, P.g, P.g_magic);
+    const int t = ent[e - seg0];
+    const uint32_t hh = (uint32_t)(rc - e * P.g);
+    row = (uint32_t)t * (uint32_t)P.hq + hbase + hh;
+    sidx = (uint32_t)t * (uint32_t)P.g + hh;
+    int lim = P.causal ? min(blen, t - tok0 + 1) : blen;  // keys [lo, lim)
+    if (r >= rows_end) lim = 0;
+    if constexpr (kWin) {
+      const int lo = min(max(t - P.window + 1 - tok0, 0), 64);
+      vis = (uint32_t)(lo | (max(lim - lo, 0) << 16));
+    } else {
+      vis = (uint32_t)lim;
     }
-    const int rc = min(tile0 + 32 * rb + col, rows_end - 1);
-    const int ec = div_g(rc, P.g, P.g_magic);
-    const float2 st = stats[(uint32_t)ent[ec - seg0] * (uint32_t)P.hq + (uint32_t)(hbase + (rc - ec * P.g))];  // (LSE in log2 domain, delta)
-    lse2_n = st.x;
-    dl_n = st.y;
   };
+  auto issue_rows = [&](uint32_t row, uint32_t sidx) __attribute__((always_inline)) {
+    uint32_t r4[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r4[i] = lane_value(row, 8 * i + srow);
+    st = head_stats[sidx];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      qc[i] = Qrows.load(r4[i], lane_off);
+      dc[i] = dOrows.load(r4[i], lane_off);
+    }
+  };
+  // the unit's partial dQ rows, one tile at a time: stores past the tile's last row are dropped
+  bf16_t* const dq_unit = dqpart + (size_t)(U.e0 - pos0) * P.g * kD;
+  const uint32_t dq_lane = (32 * rb + srow) * (kD * 2) + lane_off;
 
   for (seg0 = 0; seg0 < ne; seg0 += kEntSeg) {
     const int seg_n = min(kEntSeg, ne - seg0);
-    __syncthreads();  // the previous segment's ids are no longer read
-    for (int i = tid; i < seg_n; i += kThreads) ent[i] = qent[e0 + seg0 + i].x;
+    if (seg0 > 0) {
+      __syncthreads();  // the previous segment's ids are no longer read
+      for (int i = tid; i < seg_n; i += 256) ent[i] = qent[U.e0 + seg0 + i].x;
+    }
     __syncthreads();  // ids (and K_i on the first pass) visible
     rows_end = (seg0 + seg_n) * P.g;
-    issue_rows(seg0 * P.g);
-
-    for (int tile0 = seg0 * P.g; tile0 < rows_end; tile0 += kTile) {
-      // keep the lane-derived LDS addresses from being precomputed and held across the loop (register budget)
-      asm volatile("" : "+v"(col), "+v"(qh), "+v"(tr_lane), "+v"(tr_lane_p), "+v"(srow), "+v"(schunk));
+    uint32_t row_n, sidx_n, vis_c, vis_n;
+    find_row(seg0 * P.g, row_n, sidx_n, vis_c);
+    issue_rows(row_n, sidx_n);
+    find_row(seg0 * P.g + kTile, row_n, sidx_n, vis_n);
+    // as many (dropped) stores as an iteration issues after its loads, so that both ways into the loop agree on what is
+    // outstanding and the wait at its top leaves the previous tile's stores in flight
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      const __amdgpu_buffer_rsrc_t none = buffer_of(dq_unit, 0);
 #pragma unroll
-      for (int i = 0; i < kNP; ++i) {
-        *reinterpret_cast<u32x4*>(&Qmine[(kRPP * i + srow) * kRowStride + schunk]) = qc[i];
-        *reinterpret_cast<u32x4*>(&dOmine[(kRPP * i + srow) * kRowStride + schunk]) = dc[i];
+      for (int i = 0; i < 4; ++i) __builtin_amdgcn_raw_buffer_store_b32(0u, none, kNoRow + 16 * i, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    int tile0 = seg0 * P.g;
+    do {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        *reinterpret_cast<u32x4*>(stage + 8 * i * (kRowStride * 2)) = qc[i];
+        *reinterpret_cast<u32x4*>(stage + kDoOff + 8 * i * (kRowStride * 2)) = dc[i];
       }
-      const float lse2 = lse2_n, dl = dl_n;
-      const bool more = tile0 + kTile < rows_end;
-      if (more) issue_rows(tile0 + kTile);  // the next tile's rows fly while this one computes
-      const int r = tile0 + 32 * rb + col;
-      const bool valid = r < rows_end;
-      const int t = valid ? ent[div_g(r, P.g, P.g_magic) - seg0] : -1;
-      int lim = P.causal ? min(blen, t - tok0 + 1) : blen;  // keys [0, lim) of the block are visible to this row
-      if (!valid) lim = 0;
-      // kWin: the kernel variant for a sliding window, whose rows also hide the keys before lo
-      const int lo = kWin ? min(max(t - P.window + 1 - tok0, 0), kKeys) : 0;
       if (kb == 0 && qh == 0) {  // this row's record, for the lanes of the rows/keys role (which hold keys, not rows)
-        float* rec = reinterpret_cast<float*>(smem + Lds::Rec) + 32 * rb + col;
-        rec[0] = lse2;
-        rec[kTile] = dl * P.scale;
-        reinterpret_cast<uint32_t*>(rec)[2 * kTile] = (uint32_t)(lo | (max(lim - lo, 0) << 16));  // keys [lo, lo + span)
+        rec_wr[0] = st.x;
+        rec_wr[kTile] = st.y * P.scale;
+        reinterpret_cast<uint32_t*>(rec_wr)[2 * kTile] = vis_c;
       }
+      issue_rows(row_n, sidx_n);  // the next tile's rows fly while this one computes (past the last: its last row, unused)
+      vis_c = vis_n;
       __syncthreads();  // Q / dO tile and the row records staged by all waves
 
       {  // role rows/keys: S = Q K_i^T, dP = dO V_i^T for rows 32 rb.. x keys 32 kb..: lane = key, register v = row
@@ -258,29 +304,24 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
           sacc[v] = 0.f;
           dpacc[v] = 0.f;
         }
-        const bf16_t* qrow = Qmine + col * kRowStride + 8 * qh;
-        const bf16_t* drow = dOmine + col * kRowStride + 8 * qh;
-        const bf16_t* krow = Ks + (32 * kb + col) * kRowStride + 8 * qh;
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-          const bf16x8 qf = *reinterpret_cast<const bf16x8*>(qrow + 16 * s);
-          const bf16x8 dof = *reinterpret_cast<const bf16x8*>(drow + 16 * s);
-          const bf16x8 kfa = *reinterpret_cast<const bf16x8*>(krow + 16 * s);
+          const bf16x8 qf = *reinterpret_cast<const bf16x8*>(qfrag + 32 * s);
+          const bf16x8 dof = *reinterpret_cast<const bf16x8*>(qfrag + kDoOff + 32 * s);
+          const bf16x8 kfa = *reinterpret_cast<const bf16x8*>(kfrag + 32 * s);
           sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kfa, sacc, 0, 0, 0);
           dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dof, vf[s], dpacc, 0, 0, 0);
         }
-        const float* rec = reinterpret_cast<const float*>(smem + Lds::Rec);
-        const int key = 32 * kb + col;
+        const uint32_t key = 32 * kb + col;
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-          const int r4 = 32 * rb + 8 * a + 4 * qh;
-          const f32x4 lse4 = *reinterpret_cast<const f32x4*>(rec + r4);
-          const f32x4 dls4 = *reinterpret_cast<const f32x4*>(rec + kTile + r4);
-          const u32x4 vis4 = *reinterpret_cast<const u32x4*>(rec + 2 * kTile + r4);
+          const f32x4 lse4 = *reinterpret_cast<const f32x4*>(rec_rd + 8 * a);
+          const f32x4 dls4 = *reinterpret_cast<const f32x4*>(rec_rd + kTile + 8 * a);
+          const u32x4 vis4 = *reinterpret_cast<const u32x4*>(rec_rd + 2 * kTile + 8 * a);
           float p[4], ds[4];
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            const bool seen = (uint32_t)key - (vis4[c] & 0xffffu) < (vis4[c] >> 16);
+            const bool seen = kWin ? key - (vis4[c] & 0xffffu) < (vis4[c] >> 16) : (int)key < (int)vis4[c];
             p[c] = seen ? __builtin_amdgcn_exp2f(fmaf(sacc[4 * a + c], c2, -lse4[c])) : 0.f;
             ds[c] = p[c] * fmaf(dpacc[4 * a + c], P.scale, -dls4[c]);  // P (dP - delta) scale
           }
@@ -289,28 +330,23 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
           pw.y = pack_bf16x2(p[2], p[3]);
           sw2.x = pack_bf16x2(ds[0], ds[1]);
           sw2.y = pack_bf16x2(ds[2], ds[3]);
-          *reinterpret_cast<uint2*>(&Pt[key * kPStride + r4]) = pw;
-          *reinterpret_cast<uint2*>(&dSt[key * kPStride + r4]) = sw2;
+          *reinterpret_cast<uint2*>(pt_wr + 16 * a) = pw;
+          *reinterpret_cast<uint2*>(pt_wr + kDsOff + 16 * a) = sw2;
         }
       }
       __syncthreads();  // P^T, dS^T complete
-      {  // role keys/chans: dV_i += P^T dO, dK_i += dS^T Q for keys 32 kb2.., channels 64 hf + 32 cb..
-        int tr_row = tr_lane + 64 * hf;
-        asm volatile("" : "+v"(tr_row));
-        const bf16_t* do_tr = dOs + tr_row;  // one base per tile: the reads below differ by immediate offsets only
-        const bf16_t* q_tr = Qs + tr_row;
-        const bf16_t* parow = Pt + (32 * kb2 + col) * kPStride + 8 * qh;
-        const bf16_t* sarow = dSt + (32 * kb2 + col) * kPStride + 8 * qh;
+      find_row(tile0 + 2 * kTile, row_n, sidx_n, vis_n);
+      {  // role keys/chans: dV_i += P^T dO, dK_i += dS^T Q for keys 32 rb.., channels 64 kb + 32 cb..
 #pragma unroll
         for (int qs = 0; qs < 4; ++qs) {
-          const bf16x8 pa = *reinterpret_cast<const bf16x8*>(parow + 16 * qs);
-          const bf16x8 sa = *reinterpret_cast<const bf16x8*>(sarow + 16 * qs);
+          const bf16x8 pa = *reinterpret_cast<const bf16x8*>(pt_rd + 32 * qs);
+          const bf16x8 sa = *reinterpret_cast<const bf16x8*>(pt_rd + kDsOff + 32 * qs);
 #pragma unroll
           for (int cb = 0; cb < 2; ++cb) {
-            const bf16x4 d0 = lds_read_tr(do_tr + (16 * qs * kRowStride + 32 * cb));
-            const bf16x4 d1 = lds_read_tr(do_tr + ((16 * qs + 4) * kRowStride + 32 * cb));
-            const bf16x4 q0 = lds_read_tr(q_tr + (16 * qs * kRowStride + 32 * cb));
-            const bf16x4 q1 = lds_read_tr(q_tr + ((16 * qs + 4) * kRowStride + 32 * cb));
+            const bf16_t* q_tr = tr_row + (16 * qs * kRowStride + 32 * cb);
+            const bf16_t* do_tr = q_tr + kDoOff / 2;
+            const bf16x4 d0 = lds_read_tr(do_tr), d1 = lds_read_tr(do_tr + 4 * kRowStride);
+            const bf16x4 q0 = lds_read_tr(q_tr), q1 = lds_read_tr(q_tr + 4 * kRowStride);
             const bf16x8 dob = __builtin_shufflevector(d0, d1, 0, 1, 2, 3, 4, 5, 6, 7);
             const bf16x8 qb = __builtin_shufflevector(q0, q1, 0, 1, 2, 3, 4, 5, 6, 7);
             dvacc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa, dob, dvacc[cb], 0, 0, 0);
@@ -318,64 +354,57 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
           }
         }
       }
-      f32x16 dqacc[kNDB];
-      {  // role rows/chans: dQ^T[kCW kb.., 32 rb..] = K_i^T dS^T over the block's keys
+      f32x16 dqacc[2];
+      {  // role rows/chans: dQ^T[64 kb.., 32 rb..] = K_i^T dS^T over the block's keys
 #pragma unroll
-        for (int db = 0; db < kNDB; ++db)
+        for (int db = 0; db < 2; ++db)
 #pragma unroll
           for (int v = 0; v < 16; ++v) dqacc[db][v] = 0.f;
-        int tr_key = tr_lane + kCW * kb;
-        int tr_ds = tr_lane_p + 32 * rb;
-        asm volatile("" : "+v"(tr_key), "+v"(tr_ds));
-        const bf16_t* k_tr = Ks + tr_key;
-        const bf16_t* ds_tr = dSt + tr_ds;
 #pragma unroll
-        for (int sp = 0; sp < kKeys / 16; ++sp) {
-          const bf16x4 b0 = lds_read_tr(ds_tr + 16 * sp * kPStride);
-          const bf16x4 b1 = lds_read_tr(ds_tr + (16 * sp + 4) * kPStride);
+        for (int sp = 0; sp < 4; ++sp) {
+          const bf16x4 b0 = lds_read_tr(tr_ds + 16 * sp * kPStride), b1 = lds_read_tr(tr_ds + (16 * sp + 4) * kPStride);
           const bf16x8 dsb = __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
-          for (int db = 0; db < kNDB; ++db) {
-            const bf16x4 a0 = lds_read_tr(k_tr + (16 * sp * kRowStride + 32 * db));
-            const bf16x4 a1 = lds_read_tr(k_tr + ((16 * sp + 4) * kRowStride + 32 * db));
+          for (int db = 0; db < 2; ++db) {
+            const bf16_t* k_tr = tr_row - (BwdLds::Q - BwdLds::K) / 2 + (16 * sp * kRowStride + 32 * db);
+            const bf16x4 a0 = lds_read_tr(k_tr), a1 = lds_read_tr(k_tr + 4 * kRowStride);
             const bf16x8 ktf = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
             dqacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf, dsb, dqacc[db], 0, 0, 0);
           }
         }
       }
       __syncthreads();  // every wave is done reading the Q / dO / P^T / dS^T tiles
-      // dQ rows (32 rows x kCW channels) -> the part of the Q tile this wave staged -> contiguous row segments
+      // dQ rows (32 rows x 64 channels) -> the part of the Q tile this wave staged -> contiguous row segments
 #pragma unroll
-      for (int db = 0; db < kNDB; ++db)
+      for (int db = 0; db < 2; ++db)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
           uint2 w;
           w.x = pack_bf16x2(dqacc[db][4 * a + 0], dqacc[db][4 * a + 1]);
           w.y = pack_bf16x2(dqacc[db][4 * a + 2], dqacc[db][4 * a + 3]);
-          *reinterpret_cast<uint2*>(&Qmine[col * kRowStride + kCW * kb + 32 * db + 8 * a + 4 * qh]) = w;
+          *reinterpret_cast<uint2*>(dq_wr + 64 * db + 16 * a) = w;
         }
       wave_sync_bwd();
-      const size_t prow0 = (size_t)(e0 - pos0) * P.g + (size_t)(tile0 + 32 * rb);
+      const __amdgpu_buffer_rsrc_t dq_buf =
+          buffer_of(dq_unit + (size_t)tile0 * kD, (uint32_t)min(rows_end - tile0, kTile) * (kD * 2));
 #pragma unroll
-      for (int i = 0; i < kNP; ++i) {
-        const int row = kRPP * i + srow;
-        if (tile0 + 32 * rb + row < rows_end)
-          store_streaming(dqpart + (prow0 + row) * kD + schunk,
-                          *reinterpret_cast<const uint4*>(&Qmine[row * kRowStride + schunk]));
-      }
+      for (int i = 0; i < 4; ++i)
+        __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(stage + 8 * i * (kRowStride * 2)), dq_buf,
+                                               dq_lane + 8 * i * (kD * 2), 0, kNonTemporal);
       wave_sync_bwd();
-    }
+      tile0 += kTile;
+    } while (tile0 < rows_end);
   }
 
-  if (nu_scan[L + 1] - nu_scan[L] == 1) {
+  if (U.n_units == 1) {
     // the whole list fitted this unit: dK_i, dV_i are final, write them as bf16 (keys of a ragged tail excluded)
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
-      bf16_t* outk = dK + ((size_t)tok0 * P.hkv + j) * kD + 64 * hf + 32 * cb + col;
-      bf16_t* outv = dV + ((size_t)tok0 * P.hkv + j) * kD + 64 * hf + 32 * cb + col;
+      bf16_t* outk = dK + ((size_t)tok0 * P.hkv + j) * kD + 64 * kb + 32 * cb + col;
+      bf16_t* outv = dV + ((size_t)tok0 * P.hkv + j) * kD + 64 * kb + 32 * cb + col;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int key = 32 * kb2 + 8 * (v >> 2) + 4 * qh + (v & 3);
+        const int key = 32 * rb + 8 * (v >> 2) + 4 * qh + (v & 3);
         if (key < blen) {
           outk[(size_t)key * P.hkv * kD] = (bf16_t)dkacc[cb][v];
           outv[(size_t)key * P.hkv * kD] = (bf16_t)dvacc[cb][v];
@@ -387,11 +416,11 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
   // unit partial: [u][0 = dK, 1 = dV][key][d] fp32, summed by k_bwd_dkv_reduce in unit order
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) {
-    float* outk = dkv_part + (size_t)(u - ubase) * 2 * kKeys * kD + 64 * hf + 32 * cb + col;
-    float* outv = outk + kKeys * kD;
+    float* outk = dkv_part + (size_t)blockIdx.x * 2 * 64 * kD + 64 * kb + 32 * cb + col;
+    float* outv = outk + 64 * kD;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int key = 32 * kb2 + 8 * (v >> 2) + 4 * qh + (v & 3);
+      const int key = 32 * rb + 8 * (v >> 2) + 4 * qh + (v & 3);
       outk[key * kD] = dkacc[cb][v];
       outv[key * kD] = dvacc[cb][v];
     }
@@ -413,7 +442,8 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 // Q / dO tiles and P^T / dS^T tiles are double-buffered in LDS (154 KB in all), so the S-waves' MFMA and exponential work
 // on tile n runs beside the A-waves' LDS-bound products on tile n - 1 on the same SIMD; two block-wide barriers per
 // tile order the hand-over.  Rows are requested three tiles ahead into two register sets and staged after the second
-// barrier.  Measured at 65536 tokens, g = 4, (128, 8): 3.5 ms against 4.1 ms for the eight-waves-in-step kernel.
+// barrier.  Measured at 65536 tokens, g = 4, (128, 8): 3.5 ms against 4.1 ms for the eight-waves-in-step kernel, 3.25 ms
+// since rows move by buffer instructions (no 64-bit address per access on the P/dS waves' staging path).
 struct PipeLds {
   static constexpr int QB = kTile * kRowStride * 2;   // one Q or dO tile: 19456 bytes
   static constexpr int PB = 128 * kPStride * 2;       // one P^T or dS^T tile: 18432 bytes
@@ -424,8 +454,8 @@ struct PipeLds {
   static constexpr int Ent = DSt0 + 2 * PB;
   static constexpr int St0 = Ent + kEntSeg * 4;       // per-row records of a staged tile, two buffers: three arrays
   static constexpr int SB = 3 * kTile * 4;            // of 64: LSE (log2 domain), delta * scale, visible key range
-  static constexpr int Tb0 = St0 + 2 * SB;            // per row of the tile to request next: (row index into Q / dO /
-  static constexpr int Bytes = Tb0 + kTile * 8;       // stats, visible key range); 157696 in all
+  static constexpr int Tb0 = St0 + 2 * SB;            // per row of the tile to request next: row of Q / dO, place in
+  static constexpr int Bytes = Tb0 + kTile * 12;      // the kv head's statistics, visible keys; 157952 in all
 };
 static_assert(PipeLds::Bytes <= 160 * 1024, "the pipelined 128-key backward must fit one CU's LDS");
 constexpr int kDqPitch = 36;  // bf16 per row of an A-wave's dQ staging (64 rows x 32 channels + pad = 4608 bytes)
@@ -449,18 +479,17 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // What one workgroup of k_bwd_pipe128 works on.
-struct PipeUnit {
-  int u, ubase, L, j, e0, pos0, ne, tok0, blen;
+struct PipeUnit : UnitRec {
+  int pos0;
 };
 
 // One role of the pipeline (kS: an S-wave, else an A-wave).  Both roles run this same skeleton, so they execute the same
 // sequence of block-wide barriers: every loop bound below depends only on the unit, never on the role or the lane.
-template <bool kWin, bool kS>
+template <bool kWin, bool kWide, bool kS>
 __device__ __forceinline__ void
 pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw, const bf16_t* __restrict__ Q,
           const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO,
-          const float2* __restrict__ stats, const int2* __restrict__ qent, const int32_t* __restrict__ nu_scan,
-          bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
+          const float2* __restrict__ stats, const int2* __restrict__ qent, bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
   int32_t* ent = reinterpret_cast<int32_t*>(smem + PipeLds::Ent);
   const int tid = threadIdx.x, lane = tid & 63;
   int col = lane & 31, qh = lane >> 5;
@@ -521,7 +550,9 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
   // keys the row sees.  It is worked out one phase before the loads are issued, by whichever waves have the time
   // (all of them before the pipeline starts, the A-waves inside it) and handed over in LDS, so that the S-waves carry
   // no addresses through their products and issue the loads right after the barrier that frees the registers.
-  uint2* row_table = reinterpret_cast<uint2*>(smem + PipeLds::Tb0);
+  uint32_t* row_table = reinterpret_cast<uint32_t*>(smem + PipeLds::Tb0);  // [3][kTile]
+  const RowTensor<kWide> Qrows(Q, (int64_t)P.T * P.hq), dOrows(dO, (int64_t)P.T * P.hq);
+  const float2* const head_stats = stats + (size_t)j * P.T * P.g;
   auto prepare_rows = [&](int tile0) __attribute__((always_inline)) {
     // rows past the end of the list re-read its last row: their P and dS are forced to zero and their dQ is never stored
     const int rr = tile0 + ((tid & 255) >> 2);
@@ -531,24 +562,26 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
     int lim = P.causal ? min(blen, t - tok0 + 1) : blen;  // keys [lo, lim) of the block are visible to this row
     if (rr >= rows_end) lim = 0;
     const int lo = kWin ? min(max(t - P.window + 1 - tok0, 0), 128) : 0;
-    if ((tid & 3) == 0)
-      row_table[(tid & 255) >> 2] = make_uint2((uint32_t)t * (uint32_t)P.hq + (uint32_t)(hbase + (rc - ec * P.g)),
-                                               (uint32_t)(lo | (max(lim - lo, 0) << 16)));
+    if ((tid & 3) == 0) {
+      uint32_t* e = row_table + ((tid & 255) >> 2);
+      e[0] = (uint32_t)t * (uint32_t)P.hq + (uint32_t)(hbase + (rc - ec * P.g));
+      e[kTile] = (uint32_t)t * (uint32_t)P.g + (uint32_t)(rc - ec * P.g);
+      e[2 * kTile] = (uint32_t)(lo | (max(lim - lo, 0) << 16));
+    }
   };
   auto issue_rows = [&](auto setc) __attribute__((always_inline)) {
     constexpr int set = kS ? decltype(setc)::value : 0;
     uint32_t grow[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) grow[i] = row_table[16 * i + srow].x;
-    const uint2 mine = row_table[(tid & 255) >> 2];
+    for (int i = 0; i < 4; ++i) grow[i] = row_table[16 * i + srow];
+    const uint32_t* mine = row_table + ((tid & 255) >> 2);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const size_t o = (size_t)grow[i] * kD + schunk;
-      qc[set][i] = *reinterpret_cast<const u32x4*>(Q + o);
-      dc[set][i] = *reinterpret_cast<const u32x4*>(dO + o);
+      qc[set][i] = Qrows.load(grow[i], schunk * 2);
+      dc[set][i] = dOrows.load(grow[i], schunk * 2);
     }
-    st_set[set] = stats[mine.x];
-    vis_set[set] = (int)mine.y;
+    st_set[set] = head_stats[mine[kTile]];
+    vis_set[set] = (int)mine[2 * kTile];
   };
   auto stage_rows = [&](int buf, auto setc) __attribute__((always_inline)) {
     constexpr int set = kS ? decltype(setc)::value : 0;
@@ -607,7 +640,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
       PT_STAMP(0)
       if constexpr (kS) {
         if (it < ntiles) {  // ---- S, dP, P, dS of tile `it`: keys 32 sw.., all 64 rows
-          const int buf = it & 1, tile0 = row_first + it * kTile;
+          const int buf = it & 1;
           const bf16_t* Qs = reinterpret_cast<const bf16_t*>(smem + PipeLds::Q0 + buf * PipeLds::QB);
           const bf16_t* dOs = reinterpret_cast<const bf16_t*>(smem + PipeLds::DO0 + buf * PipeLds::QB);
           bf16_t* Pt = reinterpret_cast<bf16_t*>(smem + PipeLds::Pt0 + buf * PipeLds::PB);
@@ -775,18 +808,18 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
                 }
               wave_sync_bwd();
               const int tile0 = row_first + (it - 1) * kTile;
-              const size_t prow0 = (size_t)(U.e0 - U.pos0) * P.g + (size_t)tile0;
+              const __amdgpu_buffer_rsrc_t dq_buf =
+                  buffer_of(dqpart + ((size_t)(U.e0 - U.pos0) * P.g + (size_t)tile0) * kD,
+                            (uint32_t)min(rows_end - tile0, kTile) * (kD * 2));  // rows past the list's end are dropped
               int ln = lane;
               asm volatile("" : "+v"(ln));  // keeps the row addresses from being precomputed and held (register budget)
 #pragma unroll
               for (int i = 0; i < 4; ++i) {
                 const int row = 16 * i + (ln >> 2), piece = (ln & 3) * 8;
-                if (tile0 + row < rows_end) {
-                  const uint2 lo2 = *reinterpret_cast<const uint2*>(&stg[row * kDqPitch + piece]);
-                  const uint2 hi2 = *reinterpret_cast<const uint2*>(&stg[row * kDqPitch + piece + 4]);
-                  store_streaming(dqpart + (prow0 + row) * kD + 32 * sw + piece,
-                                  make_uint4(lo2.x, lo2.y, hi2.x, hi2.y));
-                }
+                const uint2 lo2 = *reinterpret_cast<const uint2*>(&stg[row * kDqPitch + piece]);
+                const uint2 hi2 = *reinterpret_cast<const uint2*>(&stg[row * kDqPitch + piece + 4]);
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{lo2.x, lo2.y, hi2.x, hi2.y}, dq_buf,
+                                                       row * (kD * 2) + 64 * sw + piece * 2, 0, kNonTemporal);
               }
               __builtin_amdgcn_sched_barrier(0);
             }
@@ -812,7 +845,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
   if (lane == 0) atomicAdd(&g_pipe_t[kS ? 0 : 1][4], 1ull);
 #endif
   if constexpr (!kS) {
-    if (nu_scan[U.L + 1] - nu_scan[U.L] == 1) {
+    if (U.n_units == 1) {
       // the whole list fitted this unit: dK_i, dV_i are final, write them as bf16 (keys of a ragged tail excluded)
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb) {
@@ -832,7 +865,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
     // unit partial: [u][0 = dK, 1 = dV][key][d] fp32, summed by k_bwd_dkv_reduce in unit order
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
-      float* outk = dkv_part + (size_t)(U.u - U.ubase) * 2 * 128 * kD + 32 * cb + col;
+      float* outk = dkv_part + (size_t)blockIdx.x * 2 * 128 * kD + 32 * cb + col;
       float* outv = outk + 128 * kD;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -844,32 +877,21 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
   }
 }
 
-template <bool kWin>
+template <bool kWin, bool kWide>
 __global__ void __launch_bounds__(512, 1)
 k_bwd_pipe128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-              const bf16_t* __restrict__ dO, const float2* __restrict__ stats, const int32_t* __restrict__ u_list,
-              const int32_t* __restrict__ u_start, const int32_t* __restrict__ off,
-              const int32_t* __restrict__ blk_tok0, const int32_t* __restrict__ blk_len,
-              const int2* __restrict__ qent, const int32_t* __restrict__ nu_scan, bf16_t* __restrict__ dqpart,
-              float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
+              const bf16_t* __restrict__ dO, const float2* __restrict__ stats, const UnitRec* __restrict__ u_rec,
+              const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off, const int2* __restrict__ qent,
+              bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   PipeUnit U;
-  U.ubase = nu_scan[P.j0 * P.b_cap];
-  U.u = U.ubase + blockIdx.x;
-  if (U.u >= nu_scan[(P.j0 + P.nj) * P.b_cap]) return;
-  U.L = u_list[U.u];
-  U.j = U.L / P.b_cap;
-  const int gb = U.L - U.j * P.b_cap;
-  U.e0 = u_start[U.u];
-  U.pos0 = off[P.j0 * P.b_cap];
-  U.ne = min(P.unit, off[U.L + 1] - U.e0);
-  U.tok0 = blk_tok0[gb];
-  U.blen = blk_len[gb];
+  int ubase;
+  if (!load_unit(P, u_rec, nu_scan, off, U, ubase, U.pos0)) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (wave < 4)
-    pipe_role<kWin, true>(P, U, smem, wave, Q, K, V, dO, stats, qent, nu_scan, dqpart, dkv_part, dK, dV);
+    pipe_role<kWin, kWide, true>(P, U, smem, wave, Q, K, V, dO, stats, qent, dqpart, dkv_part, dK, dV);
   else
-    pipe_role<kWin, false>(P, U, smem, wave - 4, Q, K, V, dO, stats, qent, nu_scan, dqpart, dkv_part, dK, dV);
+    pipe_role<kWin, kWide, false>(P, U, smem, wave - 4, Q, K, V, dO, stats, qent, dqpart, dkv_part, dK, dV);
 }
 
 __global__ void __launch_bounds__(256)
@@ -965,19 +987,23 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
   // 64-token blocks: four waves, two workgroups per CU; 128-token blocks: eight waves, one workgroup per CU
   const bool b128 = P0.bk == 128;
   const bool win = P0.window > 0;
-  auto* main_kernel = b128 ? (win ? k_bwd_pipe128<true> : k_bwd_pipe128<false>)
-                           : (win ? k_bwd_tiled<2, true> : k_bwd_tiled<2, false>);
+  const bool wide = rows_are_wide((int64_t)P0.T * P0.hq);
+  auto pick = [&](auto* w1d1, auto* w1d0, auto* w0d1, auto* w0d0) { return win ? (wide ? w1d1 : w1d0) : (wide ? w0d1 : w0d0); };
+  auto* main_kernel = b128 ? pick(k_bwd_pipe128<true, true>, k_bwd_pipe128<true, false>, k_bwd_pipe128<false, true>,
+                                  k_bwd_pipe128<false, false>)
+                           : pick(k_bwd_tiled<true, true>, k_bwd_tiled<true, false>, k_bwd_tiled<false, true>,
+                                  k_bwd_tiled<false, false>);
   const int main_threads = b128 ? 512 : 256;
-  const int main_lds = b128 ? PipeLds::Bytes : BwdLds<2>::Bytes;
+  const int main_lds = b128 ? PipeLds::Bytes : BwdLds::Bytes;
   {
-    static std::atomic<uint64_t> ready[4];
-    hipError_t e = allow_dynamic_lds((const void*)main_kernel, main_lds, ready[2 * win + b128]);
+    static std::atomic<uint64_t> ready[8];
+    hipError_t e = allow_dynamic_lds((const void*)main_kernel, main_lds, ready[win + 2 * wide + 4 * b128]);
     if (e != hipSuccess) return e;
   }
   {
-    const int64_t rows = (int64_t)P0.T * P0.hq;
     ProfScope ps(KID_BWD_DELTA, st);
-    hipLaunchKernelGGL(k_bwd_delta, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, rows, (const bf16_t*)O,
+    hipLaunchKernelGGL(k_bwd_delta, dim3((P0.T + kDeltaTokens - 1) / kDeltaTokens, (P0.hkv + kDeltaKv - 1) / kDeltaKv),
+                       dim3(256), 0, st, P0, (const bf16_t*)O,
                        (const bf16_t*)dO, LSE, (float2*)delta, G.gate, G.dgate);
   }
   // KV heads are processed heads_per_pass at a time, every pass reusing the partial-dQ and unit-partial buffers
@@ -989,9 +1015,8 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
     const int64_t rows = (int64_t)P.T * P.nj * P.g;
     { ProfScope ps(KID_BWD_MAIN, st);
     hipLaunchKernelGGL(main_kernel, dim3(units_max), dim3(main_threads), main_lds, st, P, (const bf16_t*)Q,
-                       (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, (const float2*)delta, p.u_list,
-                       p.u_start, p.off, p.blk_tok0, p.blk_len, p.qent, p.u_nu, (bf16_t*)dqpart, dkv_part,
-                       (bf16_t*)dK, (bf16_t*)dV); }
+                       (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, (const float2*)delta, p.u_rec, p.u_nu,
+                       p.off, p.qent, (bf16_t*)dqpart, dkv_part, (bf16_t*)dK, (bf16_t*)dV); }
     { ProfScope ps(KID_BWD_DQ_REDUCE, st);
     hipLaunchKernelGGL(k_bwd_dq_reduce, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, P,
                        (const bf16_t*)dqpart, p.vmask, p.slotpos, p.off, (bf16_t*)dQ); }

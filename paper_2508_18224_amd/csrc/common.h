@@ -36,9 +36,19 @@ struct IndexLayout {
   int32_t dense;        // 1: (query tile, KV block) pairs most of the tile's tokens keep go through the dense path
   int32_t t_cap;        // query tiles of kTileTokens tokens: T / kTileTokens + nseq (>= real number of tiles)
   size_t blk_base, blk_tok0, blk_len, chunk_off, cnt, off, qent, vmask, slotpos;
-  size_t u_nu, u_list, u_start, group_sum;
+  size_t u_nu, u_rec, group_sum;
   size_t tile_base, tile_tok0, tile_len, tile_seq, dmask, d_cnt, d_piece, d_mask;
   size_t total;
+};
+
+// One work unit of the attention kernels: up to `unit` consecutive entries of one list.  A workgroup finds everything it
+// needs to request its keys, values and entries in this one record.
+struct UnitRec {
+  int32_t e0, ne;      // first entry (position in qent) and number of entries
+  int32_t tok0, blen;  // the list's KV block: first token and number of keys
+  int32_t j;           // kv head
+  int32_t n_units;     // units of the list
+  int32_t pad[2];
 };
 
 struct IndexPtrs {
@@ -51,8 +61,9 @@ struct IndexPtrs {
   int2* qent;        // list entries: (token, column of idx it came from)
   uint32_t* vmask;
   int32_t* slotpos;  // [T, hkv, topk]: position in qent of the entry a kept column produced
-  // work units (shared by forward and backward): scanned units per list, and per unit its list and first entry
-  int32_t *u_nu, *u_list, *u_start;
+  // work units (shared by forward and backward): scanned units per list, and a record per unit in list order
+  int32_t* u_nu;
+  UnitRec* u_rec;
   int2* group_sum;     // [hkv, n_groups] (entries, work units) of 64 lists
   // dense forward path: query tiles (kTileTokens consecutive tokens of one sequence) and, per (tile, kv head), the
   // 64-key pieces of the KV blocks at least half of the tile's tokens keep, each with the 64-bit mask of the tokens
@@ -77,8 +88,7 @@ inline IndexPtrs index_ptrs(const IndexLayout& L, void* base) {
   r.vmask = (uint32_t*)(p + L.vmask);
   r.slotpos = (int32_t*)(p + L.slotpos);
   r.u_nu = (int32_t*)(p + L.u_nu);
-  r.u_list = (int32_t*)(p + L.u_list);
-  r.u_start = (int32_t*)(p + L.u_start);
+  r.u_rec = (UnitRec*)(p + L.u_rec);
   r.group_sum = (int2*)(p + L.group_sum);
   r.tile_base = (int32_t*)(p + L.tile_base);
   r.tile_tok0 = (int32_t*)(p + L.tile_tok0);
@@ -201,6 +211,64 @@ __device__ __forceinline__ void store_streaming(bf16_t* dst, uint4 v) {
   u32x4 x = {v.x, v.y, v.z, v.w};
   __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(dst));
 }
+
+// ---- rows of 256 bytes through buffer instructions ------------------------------------------------------
+// A tile's rows are moved with raw buffer loads and stores: base in scalar registers, 32-bit offset per lane, and an access
+// past the end of the buffer is dropped by the hardware.  That last point matters most: the accesses need no branch
+// (rows past the end of a list are given kNoRow), so the compiler knows exactly how many are outstanding and a wait
+// for the loads of the next tile does not also wait for the stores of this one.
+constexpr uint32_t kNoRow = 1u << 30;  // byte offset past the end of every buffer it is used with
+constexpr int kNonTemporal = 2;           // cache policy bit of the buffer instructions
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+
+// Value of `v` in lane `src` (any lane of the wavefront).
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int src) {
+  return (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)v);
+}
+
+// The rows of one kv head's block of K or V: rows past the end of a ragged block read as zero.  Row r at r * row_bytes.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t block_buffer(const bf16_t* x, const Problem& P, const UnitRec& U) {
+  return buffer_of(x + ((size_t)U.tok0 * P.hkv + U.j) * kD, (uint32_t)((U.blen - 1) * P.hkv + 1) * (kD * 2));
+}
+__device__ __forceinline__ bf16x8 load_frag(__amdgpu_buffer_rsrc_t b, uint32_t off) {
+  return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0));
+}
+
+// The unit of this workgroup, or false when the launch (sized by an upper bound) has no unit left for it.  The record is
+// requested before the unit count is known: the two loads are independent and every index up to the bound is allocated.
+// base = the pass's first unit, pos0 = its first list position (partial rows are relative to it).
+__device__ __forceinline__ bool load_unit(const Problem& P, const UnitRec* __restrict__ u_rec,
+                                          const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off,
+                                          UnitRec& U, int& base, int& pos0) {
+  base = P.j0 > 0 ? nu_scan[P.j0 * P.b_cap] : 0;
+  pos0 = P.j0 > 0 ? off[P.j0 * P.b_cap] : 0;
+  const int u = base + (int)blockIdx.x;
+  const int4 a = *reinterpret_cast<const int4*>(u_rec + u);
+  const int2 b = *reinterpret_cast<const int2*>(&u_rec[u].j);
+  const int end = nu_scan[(P.j0 + P.nj) * P.b_cap];
+  U.e0 = a.x; U.ne = a.y; U.tok0 = a.z; U.blen = a.w; U.j = b.x; U.n_units = b.y;
+  asm volatile("" : "+s"(U.e0), "+s"(U.ne), "+s"(U.tok0), "+s"(U.blen), "+s"(U.j), "+s"(U.n_units));  // requested here
+  return u < end;
+}
+
+// A gathered bf16 [rows, 128] tensor.  kWide: 4 GB or more, which a 32-bit offset does not reach.
+template <bool kWide>
+struct RowTensor {
+  const char* base;
+  uint32_t bytes;
+  __device__ __forceinline__ RowTensor(const void* p, int64_t rows)
+      : base(static_cast<const char*>(p)), bytes(kWide ? 0u : (uint32_t)(rows * (kD * 2))) {}
+  __device__ __forceinline__ u32x4 load(uint32_t row, uint32_t lane_off) const {
+    if constexpr (kWide)
+      return *reinterpret_cast<const u32x4*>(base + ((size_t)row * (kD * 2) + lane_off));
+    else
+      return __builtin_amdgcn_raw_buffer_load_b128(buffer_of(base, bytes), row * (kD * 2) + lane_off, 0, 0);
+  }
+};
+inline bool rows_are_wide(int64_t rows) { return rows * (kD * 2) >= ((int64_t)1 << 32) - 65536; }
 
 // Sequence bounds of token t in a packed batch (cu may be null for a single sequence).
 __device__ __forceinline__ void seq_bounds(const int32_t* cu, int nseq, int T, int t, int& s, int& c0, int& c1) {

@@ -91,55 +91,55 @@ constexpr int kF64Tiles = kF64Vt + kD * kVtStride * 2;
 constexpr int kF64Ent = kF64Tiles + 4 * 32 * kTileStride * 2;
 constexpr int kF64Epos = kF64Ent + kMaxUnit * 4;
 constexpr int kF64Cnts = kF64Epos + kMaxUnit * 2;
-constexpr int kF64Rowpos = kF64Cnts + (kMaxUnit / 64) * 4;
-constexpr int kF64Bytes = kF64Rowpos + 4 * 32 * 8;
+constexpr int kF64Bytes = kF64Cnts + (kMaxUnit / 64) * 4;
 static_assert(2 * kF64Bytes <= 160 * 1024, "two workgroups of the 64-key forward must fit one CU's LDS");
 
+// Bound by the traffic between the XCDs and the memory side: 14.3 GB per launch at 65536 tokens, g = 4, which this kernel
+// moves at 6.9 TB/s (plain gather + store kernels reach 7.2).  Rows move by branch-free buffer instructions with the
+// row's place worked out once per tile and lane: with branches around the stores and 64-bit addresses per access every
+// wait for the next rows also drained the stores and the tile cost twice the address arithmetic (2.14 -> 2.06 ms; at
+// 8192 tokens, g = 1: 367 -> 330 us).
+template <bool kWide>
 __global__ void __launch_bounds__(256, 2)  // two workgroups per CU: 256 registers per wavefront
 k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-           const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ u_list, const int32_t* __restrict__ u_start,
-           const int32_t* __restrict__ off, const int32_t* __restrict__ blk_tok0, const int32_t* __restrict__ blk_len,
-           const int2* __restrict__ qent, bf16_t* __restrict__ opart,
-           float* __restrict__ lse_part) {
+           const UnitRec* __restrict__ u_rec, const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off,
+           const int2* __restrict__ qent, bf16_t* __restrict__ opart, float* __restrict__ lse_part) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   bf16_t* Vt = reinterpret_cast<bf16_t*>(smem + kF64Vt);
   int32_t* ent = reinterpret_cast<int32_t*>(smem + kF64Ent);     // tokens of the unit's list entries that take this route
   uint16_t* epos = reinterpret_cast<uint16_t*>(smem + kF64Epos);  // and their index inside the unit
   int32_t* cnts = reinterpret_cast<int32_t*>(smem + kF64Cnts);
-  // units of this pass's KV heads [j0, j0 + nj); nu_scan is the exclusive scan of units per list
-  const int u = nu_scan[P.j0 * P.b_cap] + blockIdx.x;
-  if (u >= nu_scan[(P.j0 + P.nj) * P.b_cap]) return;
-  const int L = u_list[u];
-  const int j = L / P.b_cap;
-  const int gb = L - j * P.b_cap;
-  const int e0 = u_start[u];
-  const int pos0 = off[P.j0 * P.b_cap];  // first list position of the pass: partial rows are relative to it
-  const int ne_all = min(P.unit, off[L + 1] - e0);
-  const int tok0 = blk_tok0[gb], blen = blk_len[gb];
+  UnitRec U;
+  int ubase, pos0;
+  if (!load_unit(P, u_rec, nu_scan, off, U, ubase, pos0)) return;
+  const int j = U.j, e0 = U.e0, ne_all = U.ne, tok0 = U.tok0, blen = U.blen;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, qh = lane >> 5;
   const int crow = lane >> 4, cchunk = (lane & 15) * 8;  // coalesced layout: 16 lanes per row, 4 rows per access
-  const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+  const uint32_t row_bytes = (uint32_t)P.hkv * (kD * 2);
+  // The block's V (thread = key, 32 channels) and K fragments.  They are requested before the entries are looked at, except
+  // with a window and the dense route, where nearly every unit turns out to have no entry left.
+  bf16x8 vreg[4], kf[2][8];
+  auto load_block = [&]() __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t k_buf = block_buffer(K, P, U), v_buf = block_buffer(V, P, U);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) vreg[i] = load_frag(v_buf, (tid >> 2) * row_bytes + (tid & 3) * 64 + 16 * i);
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+      for (int s = 0; s < 8; ++s) kf[mb][s] = load_frag(k_buf, (32 * mb + col) * row_bytes + 16 * qh + 32 * s);
+  };
+  const bool late = P.window > 0 && P.dense;
+  if (!late) load_block();
   // entries of dense (tile, block) pairs are the dense kernel's: a unit made of them only (the sink block's) ends here
   const int ne = load_sparse_entries<256>(qent, e0, ne_all, ent, epos, cnts);
   if (ne == 0) return;
-
+  if (late) load_block();
   {  // V_i -> LDS, transposed and key-permuted
-    const int key = tid >> 2, d0 = (tid & 3) * 32, pos = key_pos(key);
-    const bf16_t* src = V + ((size_t)(tok0 + key) * P.hkv + j) * kD + d0;
+    const int d0 = (tid & 3) * 32, pos = key_pos(tid >> 2);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      bf16x8 v = key < blen ? *reinterpret_cast<const bf16x8*>(src + 8 * i) : zero8;
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) Vt[(d0 + 8 * i + e) * kVtStride + pos] = v[e];
-    }
-  }
-  bf16x8 kf[2][8];
-#pragma unroll
-  for (int mb = 0; mb < 2; ++mb) {
-    const int key = 32 * mb + col;
-    const bf16_t* src = K + ((size_t)(tok0 + key) * P.hkv + j) * kD + 8 * qh;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) kf[mb][s] = key < blen ? *reinterpret_cast<const bf16x8*>(src + 16 * s) : zero8;
+      for (int e = 0; e < 8; ++e) Vt[(d0 + 8 * i + e) * kVtStride + pos] = vreg[i][e];
   }
   __syncthreads();
   const bf16_t* vbase = &Vt[col * kVtStride + 8 * qh];  // this lane's V^T fragments: + 32 db rows, + 16 sp keys
@@ -149,29 +149,56 @@ k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   if (wave >= n_tiles) return;  // no block-wide barrier below this point
   const float c2 = P.scale * 1.4426950408889634f;  // scores in the log2 domain
   bf16_t* tile_lds = reinterpret_cast<bf16_t*>(smem + kF64Tiles) + wave * 32 * kTileStride;
-  // per wavefront: the partial-buffer row of each of the tile's 32 rows
-  int64_t* rowpos = reinterpret_cast<int64_t*>(smem + kF64Rowpos) + 32 * wave;
   const int hbase = j * P.g;
+  const RowTensor<kWide> Qrows(Q, (int64_t)P.T * P.hq);
+  // the unit's partial rows and log-sum-exps: list positions e0 .. of the pass, row = position * g + head
+  const size_t part0 = (size_t)(e0 - pos0) * P.g;
+  const __amdgpu_buffer_rsrc_t o_buf = buffer_of(opart + part0 * kD, (uint32_t)(ne_all * P.g) * (kD * 2));
+  const __amdgpu_buffer_rsrc_t l_buf = buffer_of(lse_part + part0, (uint32_t)(ne_all * P.g) * 4);
 
+  // Row (tile * 32 + col) of the unit, worked out once per tile by the lane that owns the row (both halves of the
+  // wavefront alike) and handed to the lanes that move it by lane_value.  Rows past the end of the list re-read its last
+  // row: they are masked out and never stored.
+  struct Row {
+    uint32_t src;   // (token, head) row of Q; total_tokens * hq < 2^31 is checked on the host
+    uint32_t part;  // row inside the unit's partial rows
+    int t;          // token, -1 past the end
+  };
+  auto find_row = [&](int tile) __attribute__((always_inline)) {
+    const int r = tile * 32 + col, rc = min(r, rows_total - 1);
+    const int e = div_g(rc, P.g, P.g_magic), hh = rc - e * P.g;
+    const int tok = ent[e];
+    Row x;
+    x.src = (uint32_t)tok * (uint32_t)P.hq + (uint32_t)(hbase + hh);
+    x.part = (uint32_t)(epos[e] * P.g + hh);
+    x.t = r < rows_total ? tok : -1;
+    return x;
+  };
   // gather the 32 rows of Q of a tile in coalesced form (a row = 16 lanes x 16 bytes, 4 rows per access)
-  auto issue_q = [&](int tile, u32x4 (&qc)[8]) {
+  u32x4 qc[8];
+  auto issue_q = [&](const Row& x) __attribute__((always_inline)) {
+    uint32_t row[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      // rows past the end of the list re-read the last row: they are masked out below and never stored
-      const int r = min(tile * 32 + 4 * i + crow, rows_total - 1);
-      const int e = div_g(r, P.g, P.g_magic);
-      // (token, head) row index in 32 bits (total_tokens * hq < 2^31 is checked on the host), widened once
-      const uint32_t grow = (uint32_t)ent[e] * (uint32_t)P.hq + (uint32_t)(hbase + (r - e * P.g));
-      qc[i] = *reinterpret_cast<const u32x4*>(Q + ((size_t)grow * kD + cchunk));
-    }
+    for (int i = 0; i < 8; ++i) row[i] = lane_value(x.src, 4 * i + crow);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) qc[i] = Qrows.load(row[i], cchunk * 2);
   };
 
-  auto do_tile = [&](int tile, u32x4 (&qc)[8]) {
+  Row cur = find_row(wave), next = find_row(wave + 4);
+  issue_q(cur);
+  // as many (dropped) stores as an iteration issues after its loads, so that both ways into the loop agree on what is
+  // outstanding and the wait for the rows at its top leaves the previous tile's stores in flight
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 9; ++i) __builtin_amdgcn_raw_buffer_store_b32(0u, l_buf, kNoRow + 16 * i, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  int tile = wave;
+  do {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       *reinterpret_cast<u32x4*>(&tile_lds[(4 * i + crow) * kTileStride + cchunk]) = qc[i];
-    // this wave's next tile: its rows fly during the compute (issued before anything waits on the LDS)
-    if (tile + 4 < n_tiles) issue_q(tile + 4, qc);
+    // this wave's next tile: its rows fly during the compute (past the last tile: the list's last row again, unused)
+    issue_q(next);
     wave_sync();
     bf16x8 qf[8];
 #pragma unroll
@@ -190,10 +217,8 @@ k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
         sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[mb][s], qf[s], sacc[mb], 0, 0, 0);
 
     // keys [0, lim) of the block are visible to this row
-    const int r = tile * 32 + col;
-    const bool valid = r < rows_total;
-    const int ecol = div_g(min(r, rows_total - 1), P.g, P.g_magic);
-    const int t = valid ? ent[ecol] : -1;
+    const int t = cur.t;
+    const bool valid = t >= 0;
     int lim = P.causal ? min(blen, t - tok0 + 1) : blen;
     if (!valid) lim = 0;
     const int lo = P.window > 0 ? t - P.window + 1 - tok0 : 0;  // with a window, keys before lo are hidden (<= 0: none)
@@ -260,26 +285,25 @@ k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
         w.y = pack_bf16x2(oacc[db][4 * a + 2] * inv, oacc[db][4 * a + 3] * inv);
         *reinterpret_cast<uint2*>(&tile_lds[col * kTileStride + 32 * db + 8 * a + 4 * qh]) = w;
       }
-    // this row's place in the partial buffers, published for the lanes that store it
-    const int64_t prow = (int64_t)(e0 - pos0 + epos[ecol]) * P.g + (r - ecol * P.g);
-    if (qh == 0) rowpos[col] = prow;
     wave_sync();
     // partial rows live at the list position of their entry (row = position * g + head): consecutive entries of the
     // unit give one contiguous run, broken only where a dense pair's entries were left out
+    const uint32_t dst = valid ? cur.part : kNoRow / (kD * 2);
+    uint32_t to[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = 4 * i + crow;
-      if (tile * 32 + row < rows_total)
-        store_streaming(opart + (size_t)rowpos[row] * kD + cchunk,
-                        *reinterpret_cast<const uint4*>(&tile_lds[row * kTileStride + cchunk]));
-    }
-    if (valid && qh == 0) lse_part[prow] = (mc + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+    for (int i = 0; i < 8; ++i) to[i] = lane_value(dst, 4 * i + crow);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      __builtin_amdgcn_raw_buffer_store_b128(
+          *reinterpret_cast<const u32x4*>(&tile_lds[(4 * i + crow) * kTileStride + cchunk]), o_buf,
+          to[i] * (kD * 2) + cchunk * 2, 0, kNonTemporal);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, (mc + __builtin_amdgcn_logf(l)) * 0.6931471805599453f),
+                                          l_buf, qh == 0 && valid ? cur.part * 4 : kNoRow, 0, 0);
     wave_sync();
-  };
-
-  u32x4 qa[8];
-  issue_q(wave, qa);
-  for (int tile = wave; tile < n_tiles; tile += 4) do_tile(tile, qa);
+    cur = next;
+    next = find_row(tile + 8);
+    tile += 4;
+  } while (tile < n_tiles);
 }
 
 // ---- B_K = 128 -----------------------------------------------------------------------------------------------
@@ -310,11 +334,8 @@ __device__ __forceinline__ bf16x4 lds_read_tr_f(const bf16_t* p) {
 
 __global__ void __launch_bounds__(64 * kWaves128)
 k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-              const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ u_list,
-              const int32_t* __restrict__ u_start, const int32_t* __restrict__ off,
-              const int32_t* __restrict__ blk_tok0, const int32_t* __restrict__ blk_len,
-              const int2* __restrict__ qent, bf16_t* __restrict__ opart,
-              float* __restrict__ lse_part) {
+              const UnitRec* __restrict__ u_rec, const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off,
+              const int2* __restrict__ qent, bf16_t* __restrict__ opart, float* __restrict__ lse_part) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   bf16_t* Ks = reinterpret_cast<bf16_t*>(smem + kF128K);
   bf16_t* Vs = reinterpret_cast<bf16_t*>(smem + kF128V);
@@ -322,16 +343,10 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
   uint16_t* epos = reinterpret_cast<uint16_t*>(smem + kF128Epos);
   int32_t* cnts = reinterpret_cast<int32_t*>(smem + kF128Cnts);
   int64_t* rowpos = reinterpret_cast<int64_t*>(smem + kF128Rowpos) + 32 * (threadIdx.x >> 6);
-  // units of this pass's KV heads [j0, j0 + nj); nu_scan is the exclusive scan of units per list
-  const int u = nu_scan[P.j0 * P.b_cap] + blockIdx.x;
-  if (u >= nu_scan[(P.j0 + P.nj) * P.b_cap]) return;
-  const int L = u_list[u];
-  const int j = L / P.b_cap;
-  const int gb = L - j * P.b_cap;
-  const int e0 = u_start[u];
-  const int pos0 = off[P.j0 * P.b_cap];  // first list position of the pass: partial rows are relative to it
-  const int ne_all = min(P.unit, off[L + 1] - e0);
-  const int tok0 = blk_tok0[gb], blen = blk_len[gb];
+  UnitRec U;
+  int ubase, pos0;
+  if (!load_unit(P, u_rec, nu_scan, off, U, ubase, pos0)) return;
+  const int j = U.j, e0 = U.e0, ne_all = U.ne, tok0 = U.tok0, blen = U.blen;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int col = lane & 31, qh = lane >> 5;                 // not const: see the top of the tile loop
   int crow = lane >> 4, cchunk = (lane & 15) * 8;
@@ -957,15 +972,17 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
                       const void* V, const void* index_ws, void* opart, float* lse_part, void* O, float* LSE,
                       const GateArgs& G, hipStream_t st) {
   IndexPtrs p = index_ptrs(L, const_cast<void*>(index_ws));
+  const bool wide = rows_are_wide((int64_t)P0.T * P0.hq);
+  auto* main64 = wide ? k_fwd_main<true> : k_fwd_main<false>;
   if (P0.dense) {
     static std::atomic<uint64_t> ready_dense;
     hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge, kDnBytes, ready_dense);
     if (e != hipSuccess) return e;
   }
   {
-    static std::atomic<uint64_t> ready[2];
-    hipError_t e = P0.bk == 128 ? allow_dynamic_lds((const void*)k_fwd_main128, kF128Bytes, ready[1])
-                                : allow_dynamic_lds((const void*)k_fwd_main, kF64Bytes, ready[0]);
+    static std::atomic<uint64_t> ready[3];
+    hipError_t e = P0.bk == 128 ? allow_dynamic_lds((const void*)k_fwd_main128, kF128Bytes, ready[2])
+                                : allow_dynamic_lds((const void*)main64, kF64Bytes, ready[wide]);
     if (e != hipSuccess) return e;
   }
   // KV heads are processed heads_per_pass at a time; every pass reuses the same partial buffers (the lists of
@@ -979,13 +996,11 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
     if (P.bk == 128) {
       ProfScope ps(KID_FWD_MAIN, st);
       hipLaunchKernelGGL(k_fwd_main128, dim3(units_max), dim3(64 * kWaves128), kF128Bytes, st, P, (const bf16_t*)Q,
-                         (const bf16_t*)K, (const bf16_t*)V, p.u_nu, p.u_list, p.u_start, p.off, p.blk_tok0,
-                         p.blk_len, p.qent, (bf16_t*)opart, lse_part);
+                         (const bf16_t*)K, (const bf16_t*)V, p.u_rec, p.u_nu, p.off, p.qent, (bf16_t*)opart, lse_part);
     } else {
       ProfScope ps(KID_FWD_MAIN, st);
-      hipLaunchKernelGGL(k_fwd_main, dim3(units_max), dim3(256), kF64Bytes, st, P, (const bf16_t*)Q, (const bf16_t*)K,
-                         (const bf16_t*)V, p.u_nu, p.u_list, p.u_start, p.off, p.blk_tok0, p.blk_len, p.qent,
-                         (bf16_t*)opart, lse_part);
+      hipLaunchKernelGGL(main64, dim3(units_max), dim3(256), kF64Bytes, st, P, (const bf16_t*)Q, (const bf16_t*)K,
+                         (const bf16_t*)V, p.u_rec, p.u_nu, p.off, p.qent, (bf16_t*)opart, lse_part);
     }
     if (P.dense) {
       // dense pairs and the reduction step in one kernel (every row of the pass's heads)

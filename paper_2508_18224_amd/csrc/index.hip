@@ -479,9 +479,11 @@ __global__ void __launch_bounds__(kChunkThreads) k_scatter(IndexGeom G, int win,
       if (gb < G.b_cap) {
         p.off[L] = e0;
         p.u_nu[L] = u0;
+        const int tok0 = p.blk_tok0[gb], blen = p.blk_len[gb];
         for (int u = 0; u < nu; ++u) {
-          p.u_list[u0 + u] = L;
-          p.u_start[u0 + u] = e0 + u * G.unit;
+          int4* rec = reinterpret_cast<int4*>(p.u_rec + u0 + u);
+          rec[0] = make_int4(e0 + u * G.unit, min(G.unit, len - u * G.unit), tok0, blen);
+          rec[1] = make_int4(j, nu, 0, 0);
         }
       }
       run.x += total.x;
