@@ -270,16 +270,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
     find_row(seg0 * P.g, row_n, sidx_n, vis_c);
     issue_rows(row_n, sidx_n);
     find_row(seg0 * P.g + kTile, row_n, sidx_n, vis_n);
-    // as many (dropped) stores as an iteration issues after its loads, so that both ways into the loop agree on what is
-    // outstanding and the wait at its top leaves the previous tile's stores in flight
-    __builtin_amdgcn_sched_barrier(0);
-    {
-      const __amdgpu_buffer_rsrc_t none = buffer_of(dq_unit, 0);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) __builtin_amdgcn_raw_buffer_store_b32(0u, none, kNoRow + 16 * i, 0, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-
+    pad_stores<4>(buffer_of(dq_unit, 0));
     int tile0 = seg0 * P.g;
     do {
 #pragma unroll

@@ -224,6 +224,16 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint3
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
 
+// N dropped stores.  In front of a loop whose iterations issue loads first and N stores later they make both ways into the
+// loop agree on what is outstanding, so that the wait for the loads at its top leaves the last iteration's stores in flight.
+template <int N>
+__device__ __forceinline__ void pad_stores(__amdgpu_buffer_rsrc_t b) {
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < N; ++i) __builtin_amdgcn_raw_buffer_store_b32(0u, b, kNoRow + 16 * i, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // Value of `v` in lane `src` (any lane of the wavefront).
 __device__ __forceinline__ uint32_t lane_value(uint32_t v, int src) {
   return (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)v);

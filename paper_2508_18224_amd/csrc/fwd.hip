@@ -85,6 +85,44 @@ __device__ __forceinline__ int load_sparse_entries(const int2* __restrict__ qent
   return run;
 }
 
+// One row (list entry, head of the group) of a unit.  It is found once per tile by the lane that owns it (both halves of
+// the wavefront alike) and handed to the lanes that move it by lane_value.
+struct GatherRow {
+  uint32_t src;   // (token, head) row of Q; total_tokens * hq < 2^31 is checked on the host
+  uint32_t part;  // row inside the unit's partial rows: list position in the unit * g + head
+  int t;          // token, -1 past the end of the list (those re-read the last row, are masked out and never stored)
+};
+
+__device__ __forceinline__ GatherRow find_row(const Problem& P, int r, int rows_total, int hbase, const int32_t* ent,
+                                              const uint16_t* epos) {
+  const int rc = min(r, rows_total - 1);
+  const int e = div_g(rc, P.g, P.g_magic), hh = rc - e * P.g;
+  const int tok = ent[e];
+  GatherRow x;
+  x.src = (uint32_t)tok * (uint32_t)P.hq + (uint32_t)(hbase + hh);
+  x.part = (uint32_t)(epos[e] * P.g + hh);
+  x.t = r < rows_total ? tok : -1;
+  return x;
+}
+
+// A tile's 32 partial rows (wave-private LDS tile) to their list positions: consecutive entries of the unit give one
+// contiguous run, broken only where a dense pair's entries were left out.
+__device__ __forceinline__ void store_partial_rows(const bf16_t* tile_lds, const GatherRow& x, bool valid, int crow,
+                                                   int cchunk, __amdgpu_buffer_rsrc_t o_buf) {
+  const uint32_t dst = valid ? x.part : kNoRow / (kD * 2);
+  uint32_t to[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) to[i] = lane_value(dst, 4 * i + crow);
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(&tile_lds[(4 * i + crow) * kTileStride + cchunk]),
+                                           o_buf, to[i] * (kD * 2) + cchunk * 2, 0, kNonTemporal);
+}
+
+__device__ __forceinline__ void store_partial_lse(float lse, const GatherRow& x, bool on, __amdgpu_buffer_rsrc_t l_buf) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, lse), l_buf, on ? x.part * 4 : kNoRow, 0, 0);
+}
+
 // LDS of k_fwd_main (dynamic: 66 KB, two workgroups per CU)
 constexpr int kF64Vt = 0;
 constexpr int kF64Tiles = kF64Vt + kD * kVtStride * 2;
@@ -156,27 +194,12 @@ k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   const __amdgpu_buffer_rsrc_t o_buf = buffer_of(opart + part0 * kD, (uint32_t)(ne_all * P.g) * (kD * 2));
   const __amdgpu_buffer_rsrc_t l_buf = buffer_of(lse_part + part0, (uint32_t)(ne_all * P.g) * 4);
 
-  // Row (tile * 32 + col) of the unit, worked out once per tile by the lane that owns the row (both halves of the
-  // wavefront alike) and handed to the lanes that move it by lane_value.  Rows past the end of the list re-read its last
-  // row: they are masked out and never stored.
-  struct Row {
-    uint32_t src;   // (token, head) row of Q; total_tokens * hq < 2^31 is checked on the host
-    uint32_t part;  // row inside the unit's partial rows
-    int t;          // token, -1 past the end
-  };
-  auto find_row = [&](int tile) __attribute__((always_inline)) {
-    const int r = tile * 32 + col, rc = min(r, rows_total - 1);
-    const int e = div_g(rc, P.g, P.g_magic), hh = rc - e * P.g;
-    const int tok = ent[e];
-    Row x;
-    x.src = (uint32_t)tok * (uint32_t)P.hq + (uint32_t)(hbase + hh);
-    x.part = (uint32_t)(epos[e] * P.g + hh);
-    x.t = r < rows_total ? tok : -1;
-    return x;
+  auto row_of = [&](int tile) __attribute__((always_inline)) {
+    return find_row(P, tile * 32 + col, rows_total, hbase, ent, epos);
   };
   // gather the 32 rows of Q of a tile in coalesced form (a row = 16 lanes x 16 bytes, 4 rows per access)
   u32x4 qc[8];
-  auto issue_q = [&](const Row& x) __attribute__((always_inline)) {
+  auto issue_q = [&](const GatherRow& x) __attribute__((always_inline)) {
     uint32_t row[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) row[i] = lane_value(x.src, 4 * i + crow);
@@ -184,14 +207,9 @@ k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
     for (int i = 0; i < 8; ++i) qc[i] = Qrows.load(row[i], cchunk * 2);
   };
 
-  Row cur = find_row(wave), next = find_row(wave + 4);
+  GatherRow cur = row_of(wave), next = row_of(wave + 4);
   issue_q(cur);
-  // as many (dropped) stores as an iteration issues after its loads, so that both ways into the loop agree on what is
-  // outstanding and the wait for the rows at its top leaves the previous tile's stores in flight
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int i = 0; i < 9; ++i) __builtin_amdgcn_raw_buffer_store_b32(0u, l_buf, kNoRow + 16 * i, 0, 0);
-  __builtin_amdgcn_sched_barrier(0);
+  pad_stores<9>(l_buf);
   int tile = wave;
   do {
 #pragma unroll
@@ -286,22 +304,11 @@ k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
         *reinterpret_cast<uint2*>(&tile_lds[col * kTileStride + 32 * db + 8 * a + 4 * qh]) = w;
       }
     wave_sync();
-    // partial rows live at the list position of their entry (row = position * g + head): consecutive entries of the
-    // unit give one contiguous run, broken only where a dense pair's entries were left out
-    const uint32_t dst = valid ? cur.part : kNoRow / (kD * 2);
-    uint32_t to[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) to[i] = lane_value(dst, 4 * i + crow);
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      __builtin_amdgcn_raw_buffer_store_b128(
-          *reinterpret_cast<const u32x4*>(&tile_lds[(4 * i + crow) * kTileStride + cchunk]), o_buf,
-          to[i] * (kD * 2) + cchunk * 2, 0, kNonTemporal);
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, (mc + __builtin_amdgcn_logf(l)) * 0.6931471805599453f),
-                                          l_buf, qh == 0 && valid ? cur.part * 4 : kNoRow, 0, 0);
+    store_partial_rows(tile_lds, cur, valid, crow, cchunk, o_buf);
+    store_partial_lse((mc + __builtin_amdgcn_logf(l)) * 0.6931471805599453f, cur, valid && qh == 0, l_buf);
     wave_sync();
     cur = next;
-    next = find_row(tile + 8);
+    next = row_of(tile + 8);
     tile += 4;
   } while (tile < n_tiles);
 }
@@ -319,8 +326,7 @@ constexpr int kF128Tiles = kF128V + 128 * kPitch128 * 2;
 constexpr int kF128Ent = kF128Tiles + kWaves128 * 32 * kTileStride * 2;
 constexpr int kF128Epos = kF128Ent + kMaxUnit * 4;
 constexpr int kF128Cnts = kF128Epos + kMaxUnit * 2;
-constexpr int kF128Rowpos = kF128Cnts + (kMaxUnit / 64) * 4;
-constexpr int kF128Bytes = kF128Rowpos + kWaves128 * 32 * 8;
+constexpr int kF128Bytes = kF128Cnts + (kMaxUnit / 64) * 4;
 static_assert(kF128Bytes <= 160 * 1024, "forward 128-key tile set must fit the CU's LDS");
 
 // ds_read_b64_tr_b16: every lane passes the address of 8 bytes (four 16-bit elements); within each group of 16
@@ -332,6 +338,7 @@ __device__ __forceinline__ bf16x4 lds_read_tr_f(const bf16_t* p) {
   return __builtin_bit_cast(bf16x4, v);
 }
 
+template <bool kWide>
 __global__ void __launch_bounds__(64 * kWaves128)
 k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
               const UnitRec* __restrict__ u_rec, const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off,
@@ -342,7 +349,6 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
   int32_t* ent = reinterpret_cast<int32_t*>(smem + kF128Ent);
   uint16_t* epos = reinterpret_cast<uint16_t*>(smem + kF128Epos);
   int32_t* cnts = reinterpret_cast<int32_t*>(smem + kF128Cnts);
-  int64_t* rowpos = reinterpret_cast<int64_t*>(smem + kF128Rowpos) + 32 * (threadIdx.x >> 6);
   UnitRec U;
   int ubase, pos0;
   if (!load_unit(P, u_rec, nu_scan, off, U, ubase, pos0)) return;
@@ -350,21 +356,30 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int col = lane & 31, qh = lane >> 5;                 // not const: see the top of the tile loop
   int crow = lane >> 4, cchunk = (lane & 15) * 8;
-  const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
   bf16_t* tile_lds = reinterpret_cast<bf16_t*>(smem + kF128Tiles) + wave * 32 * kTileStride;
+  // K_i, V_i (thread = key, 32 channels), requested before the entries are looked at (see k_fwd_main)
+  bf16x8 kreg[4], vreg[4];
+  auto load_block = [&]() __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t k_buf = block_buffer(K, P, U), v_buf = block_buffer(V, P, U);
+    const uint32_t o = (uint32_t)(tid >> 2) * (uint32_t)P.hkv * (kD * 2) + (tid & 3) * 64;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      kreg[i] = load_frag(k_buf, o + 16 * i);
+      vreg[i] = load_frag(v_buf, o + 16 * i);
+    }
+  };
+  const bool late = P.window > 0 && P.dense;
+  if (!late) load_block();
   // entries of dense (tile, block) pairs belong to the dense kernel (see load_sparse_entries)
   const int ne = load_sparse_entries<64 * kWaves128>(qent, e0, ne_all, ent, epos, cnts);
   if (ne == 0) return;
-
-  {  // K_i, V_i -> LDS, row-major (rows past the end of a ragged block are zero)
-    const int key = tid >> 2, d0 = (tid & 3) * 32;
-    const size_t o = ((size_t)(tok0 + key) * P.hkv + j) * kD + d0;
+  if (late) load_block();
+  {
+    const int o = (tid >> 2) * kPitch128 + (tid & 3) * 32;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      *reinterpret_cast<bf16x8*>(&Ks[key * kPitch128 + d0 + 8 * i]) =
-          key < blen ? *reinterpret_cast<const bf16x8*>(K + o + 8 * i) : zero8;
-      *reinterpret_cast<bf16x8*>(&Vs[key * kPitch128 + d0 + 8 * i]) =
-          key < blen ? *reinterpret_cast<const bf16x8*>(V + o + 8 * i) : zero8;
+      *reinterpret_cast<bf16x8*>(&Ks[o + 8 * i]) = kreg[i];
+      *reinterpret_cast<bf16x8*>(&Vs[o + 8 * i]) = vreg[i];
     }
   }
   __syncthreads();
@@ -379,27 +394,32 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
   const int grp = lane >> 4, sl = lane & 15;
   int tr_v = ((sl >> 2) + 4 * (grp >> 1)) * kPitch128 + 16 * (grp & 1) + 4 * (sl & 3);
 
-  u32x4 qc[8];
-  auto issue_q = [&](int tile) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      // rows past the end of the list re-read the last row: they are masked out below and never stored
-      const int r = min(tile * 32 + 4 * i + crow, rows_total - 1);
-      const int e = div_g(r, P.g, P.g_magic);
-      // (token, head) row index in 32 bits (total_tokens * hq < 2^31 is checked on the host), widened once
-      const uint32_t grow = (uint32_t)ent[e] * (uint32_t)P.hq + (uint32_t)(hbase + (r - e * P.g));
-      qc[i] = *reinterpret_cast<const u32x4*>(Q + ((size_t)grow * kD + cchunk));
-    }
+  const RowTensor<kWide> Qrows(Q, (int64_t)P.T * P.hq);
+  const size_t part0 = (size_t)(e0 - pos0) * P.g;  // the unit's first partial row
+  const __amdgpu_buffer_rsrc_t o_buf = buffer_of(opart + part0 * kD, (uint32_t)(ne_all * P.g) * (kD * 2));
+  const __amdgpu_buffer_rsrc_t l_buf = buffer_of(lse_part + part0, (uint32_t)(ne_all * P.g) * 4);
+  auto row_of = [&](int tile) __attribute__((always_inline)) {
+    return find_row(P, tile * 32 + col, rows_total, hbase, ent, epos);
   };
-  issue_q(wave);
-
-  for (int tile = wave; tile < n_tiles; tile += kWaves128) {
+  u32x4 qc[8];
+  auto issue_q = [&](const GatherRow& x) __attribute__((always_inline)) {
+    uint32_t row[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) row[i] = lane_value(x.src, 4 * i + crow);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) qc[i] = Qrows.load(row[i], cchunk * 2);
+  };
+  GatherRow cur = row_of(wave), next = row_of(wave + kWaves128);
+  issue_q(cur);
+  pad_stores<9>(l_buf);
+  int tile = wave;
+  do {
     // register budget (256 per wave): keep the lane-derived LDS addresses from being precomputed across the loop
     asm volatile("" : "+v"(col), "+v"(qh), "+v"(crow), "+v"(cchunk), "+v"(tr_v));
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       *reinterpret_cast<u32x4*>(&tile_lds[(4 * i + crow) * kTileStride + cchunk]) = qc[i];
-    if (tile + kWaves128 < n_tiles) issue_q(tile + kWaves128);  // next rows fly during this tile's compute
+    issue_q(next);  // next rows fly during this tile's compute
     wave_sync();
     bf16x8 qf[8];
 #pragma unroll
@@ -419,10 +439,8 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
         sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sacc[mb], 0, 0, 0);
       }
 
-    const int r = tile * 32 + col;
-    const bool valid = r < rows_total;
-    const int ecol = div_g(min(r, rows_total - 1), P.g, P.g_magic);
-    const int t = valid ? ent[ecol] : -1;
+    const int t = cur.t;
+    const bool valid = t >= 0;
     int lim = P.causal ? min(blen, t - tok0 + 1) : blen;
     if (!valid) lim = 0;
     const int lo = P.window > 0 ? t - P.window + 1 - tok0 : 0;  // with a window, keys before lo are hidden
@@ -486,23 +504,15 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
         w.y = pack_bf16x2(oacc[db][4 * a + 2] * inv, oacc[db][4 * a + 3] * inv);
         *reinterpret_cast<uint2*>(&tile_lds[col * kTileStride + 32 * db + 8 * a + 4 * qh]) = w;
       }
-    // this row's place in the partial buffers, published for the lanes that store it
-    const int64_t prow = (int64_t)(e0 - pos0 + epos[ecol]) * P.g + (r - ecol * P.g);
-    if (qh == 0) rowpos[col] = prow;
     wave_sync();
-    // partial rows live at the list position of their entry (see k_fwd_main)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = 4 * i + crow;
-      if (tile * 32 + row < rows_total)
-        store_streaming(opart + (size_t)rowpos[row] * kD + cchunk,
-                        *reinterpret_cast<const uint4*>(&tile_lds[row * kTileStride + cchunk]));
-    }
-    if (valid && qh == 0) lse_part[prow] = (mc + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+    store_partial_rows(tile_lds, cur, valid, crow, cchunk, o_buf);
+    store_partial_lse((mc + __builtin_amdgcn_logf(l)) * 0.6931471805599453f, cur, valid && qh == 0, l_buf);
     wave_sync();
-  }
+    cur = next;
+    next = row_of(tile + 2 * kWaves128);
+    tile += kWaves128;
+  } while (tile < n_tiles);
 }
-
 
 // ---- dense (query-tile-outer) forward, fused with the merge ---------------------------------------------------------
 // The (query tile, KV block) pairs the index marked dense - blocks that at least half of the tile's 64 tokens keep:
@@ -974,14 +984,15 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
   IndexPtrs p = index_ptrs(L, const_cast<void*>(index_ws));
   const bool wide = rows_are_wide((int64_t)P0.T * P0.hq);
   auto* main64 = wide ? k_fwd_main<true> : k_fwd_main<false>;
+  auto* main128 = wide ? k_fwd_main128<true> : k_fwd_main128<false>;
   if (P0.dense) {
     static std::atomic<uint64_t> ready_dense;
     hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge, kDnBytes, ready_dense);
     if (e != hipSuccess) return e;
   }
   {
-    static std::atomic<uint64_t> ready[3];
-    hipError_t e = P0.bk == 128 ? allow_dynamic_lds((const void*)k_fwd_main128, kF128Bytes, ready[2])
+    static std::atomic<uint64_t> ready[4];
+    hipError_t e = P0.bk == 128 ? allow_dynamic_lds((const void*)main128, kF128Bytes, ready[2 + wide])
                                 : allow_dynamic_lds((const void*)main64, kF64Bytes, ready[wide]);
     if (e != hipSuccess) return e;
   }
@@ -995,7 +1006,7 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
     const unsigned units_max = (unsigned)units_bound(P.nj, P.b_cap, P.T, P.topk, P.unit);
     if (P.bk == 128) {
       ProfScope ps(KID_FWD_MAIN, st);
-      hipLaunchKernelGGL(k_fwd_main128, dim3(units_max), dim3(64 * kWaves128), kF128Bytes, st, P, (const bf16_t*)Q,
+      hipLaunchKernelGGL(main128, dim3(units_max), dim3(64 * kWaves128), kF128Bytes, st, P, (const bf16_t*)Q,
                          (const bf16_t*)K, (const bf16_t*)V, p.u_rec, p.u_nu, p.off, p.qent, (bf16_t*)opart, lse_part);
     } else {
       ProfScope ps(KID_FWD_MAIN, st);
