@@ -264,6 +264,31 @@ __device__ __forceinline__ bool load_unit(const Problem& P, const UnitRec* __res
   return u < end;
 }
 
+// LDS by 32-bit address.
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)(uint32_t)(uintptr_t)p;
+}
+__device__ __forceinline__ bf16x8 lds_read_frag(uint32_t a) {
+  return *(__attribute__((address_space(3))) const bf16x8*)a;
+}
+// ds_read_b64_tr_b16: every lane passes the address of 8 bytes (four 16-bit elements); within each group of 16 lanes, lane
+// i receives element (i % 4) of the 8 bytes addressed by lanes 4e + i / 4, e = 0..3.
+__device__ __forceinline__ bf16x4 lds_read_tr_at(uint32_t a) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
+  return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)a));
+}
+
+// 16 bytes per lane from memory straight to LDS: lane l's, from byte lane_off + wave_off of the buffer, go to lds + 16 l (lds
+// and wave_off are wave-uniform).  They are there once the wavefront's wait_loads() and, for other wavefronts, a barrier
+// after it have passed.  Written as assembly because the compiler would make every LDS read after it wait for it, also
+// reads of another tile: the double use of one tile set rests on the reads being ordered by the barriers alone.
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t b, uint32_t lds, uint32_t lane_off, uint32_t wave_off) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds), "v"(lane_off), "s"(b), "s"(wave_off) : "memory");
+}
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // A gathered bf16 [rows, 128] tensor.  kWide: 4 GB or more, which a 32-bit offset does not reach.
 template <bool kWide>
 struct RowTensor {

@@ -524,26 +524,35 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 //            lists them as pieces) through LDS, with a running (max, sum) per row and the output accumulated in
 //            registers across the pieces.  The 64-bit mask of a piece says which tokens of the tile keep its block;
 //            the others see none of its keys.  S^T = K Q^T and O^T = V^T P^T as in the kernels above (K fragments
-//            are 16-byte LDS reads, V^T fragments LDS transpose reads); the next piece is fetched into registers while
-//            the current one computes.  The result, normalised, goes to a wave-private LDS tile with its log-sum-exp.
+//            are 16-byte LDS reads, V^T fragments LDS transpose reads).  K and V go from memory straight to LDS, each
+//            requested as soon as its tile has been read: the next K flies during the PV product, the next V during the
+//            S product and the softmax.  The result, normalised, goes to LDS with its log-sum-exp.
 //   phase 2  is the reduction step of Sec. 3.2 for the same rows: 16 lanes per row gather the partial rows the gather
 //            route left for the row's other kept columns (two rows and eight columns at a time per lane: the few
 //            wavefronts of this kernel need that many loads in flight) and combine them, together with the row of
 //            phase 1, by their log-sum-exps; O, LSE and the optional gated sum of Eq. (2) are written once.  The
 //            rows' kept-column masks and slot positions are fetched at the very start of the kernel and parked in
-//            the wave's LDS tile (free between the Q staging and the end), so that phase 2 starts with its addresses
-//            known and the only memory latency left in it is that of the gathers themselves.
+//            LDS, so that phase 2 starts with its addresses known and the only memory latency left in it is that of the
+//            gathers themselves.
 // Tiles without a dense piece skip phase 1, so with the dense route on this kernel is the merge of every row.
-constexpr int kDnPitch = 152;                                  // bf16 per LDS row of the K / V tiles
+// Phase 2 is bound by memory (65536 tokens, g = 4: 9.4 GB in 1.80 ms; gathers of 1 KB from 8 GB reach 6.0 TB/s), phase 1
+// by the order S product, softmax, PV product inside each of the two wavefronts of a SIMD.  Staging through registers with
+// the piece table read inside the loop took 1.85 ms there and 0.55 instead of 0.505 ms for a window of 512 at 32768 tokens,
+// 1.91 instead of 1.76 ms with 9 of 16 columns dense at g = 7.  A second K tile (requests one piece earlier) gave nothing,
+// three workgroups per CU (168 registers) spill.
+// LDS: the K and the V tile of a piece, row-major and unpadded; the 16-byte chunk c of row r lies at place c ^ (r & 7) of
+// its row, which keeps both access shapes (16-byte reads down a column of rows, transposing reads of 4 rows x 32 bytes)
+// off each other's banks.  Phase 1's result takes the same area afterwards (place c ^ (r & 15)).
+constexpr int kDnRow = kD * 2;
 constexpr int kDnK = 0;
-constexpr int kDnV = kDnK + 64 * kDnPitch * 2;
-constexpr int kDnTiles = kDnV + 64 * kDnPitch * 2;
-constexpr int kDnLse = kDnTiles + 4 * 32 * kTileStride * 2;
-constexpr int kDnBytes = kDnLse + 4 * 32 * 4;                  // 74240: two workgroups per CU
-static_assert(4 * 32 * kTileStride * 2 <= kDnTiles, "phase 1's result must fit the K / V area");
-static_assert((kMaxTopk + 2) * 32 * 4 <= 32 * kTileStride * 2, "a wavefront's index data must fit its LDS tile");
+constexpr int kDnV = kDnK + 64 * kDnRow;
+constexpr int kDnLse = kDnV + 64 * kDnRow;
+constexpr int kDnMeta = kDnLse + 4 * 32 * 4;
+static_assert(4 * 32 * kDnRow <= kDnLse, "phase 1's result must fit the K / V area");
+// words of phase 2's index data of one wavefront: (kept, dense, positions) of every token its 32 rows can touch
+inline __host__ __device__ int dense_meta_words(int g, int topk) { return (31 / g + 2) * (topk + 2); }
+inline int dense_lds_bytes(int g, int topk) { return kDnMeta + 4 * 4 * dense_meta_words(g, topk); }
 constexpr int kMergeBatch = 8;                                 // columns of a row gathered at a time in phase 2
-static_assert(2 * kDnBytes <= 160 * 1024, "two workgroups of the dense forward must fit one CU's LDS");
 
 __global__ void __launch_bounds__(256, 2)
 k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
@@ -555,8 +564,6 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
                   const int32_t* __restrict__ off, bf16_t* __restrict__ O, float* __restrict__ LSE,
                   const float* __restrict__ gate, const bf16_t* Oacc, bf16_t* Oout) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16_t* Ks = reinterpret_cast<bf16_t*>(smem + kDnK);
-  bf16_t* Vs = reinterpret_cast<bf16_t*>(smem + kDnV);
   const int chunks = (kTileTokens * P.g + 127) >> 7;  // 128-row chunks of a tile's rows
   // Workgroups are handed to the chip's 8 XCDs (each with its own L2) round-robin by their index; the work is
   // ordered kv head -> tile -> chunk, and every XCD takes one contiguous eighth of that order, so that the
@@ -567,32 +574,30 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
   const int chunk = lid % chunks, qt = (lid / chunks) % P.t_cap;
   const int j = P.j0 + lid / (chunks * P.t_cap);
   const size_t slot = (size_t)qt * P.hkv + j;
-  // everything the prologue needs from the tables is requested at once (the first piece's slot exists even when the
-  // tile has no dense piece)
+  // everything the prologue needs from the tables is requested at once: lane i holds the tile's piece i and its member
+  // mask (the slots exist whatever the piece count), so that the loop over the pieces waits for no table
   const int nd = d_cnt[slot];
   const int tlen = tile_len[qt];
   const int ttok0 = tile_tok0[qt];
-  const int2 piece0 = d_piece[slot * kDenseMax];
+  const int2 my_piece = d_piece[slot * kDenseMax + (threadIdx.x & (kDenseMax - 1))];
+  const unsigned long long my_mask = d_mask[slot * kDenseMax + (threadIdx.x & (kDenseMax - 1))];
   const int rows_total = tlen * P.g;
   if (chunk * 128 >= rows_total) return;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, qh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: what derives from it stays out of the VGPRs
-  const int crow = lane >> 4, cchunk = (lane & 15) * 8;
-  bf16_t* tile_lds = reinterpret_cast<bf16_t*>(smem + kDnTiles) + wave * 32 * kTileStride;
   float* lse_lds = reinterpret_cast<float*>(smem + kDnLse) + wave * 32;
-  bf16_t* od_lds = Ks + wave * 32 * kTileStride;   // phase 1's result for phase 2 (the K / V area after the last piece)
+  unsigned char* od_lds = smem + wave * 32 * kDnRow;  // phase 1's result for phase 2 (the K / V area after the last piece)
   const int row0 = chunk * 128 + wave * 32;        // first row of this wavefront
   const bool wave_on = row0 < rows_total;          // idle wavefronts still help to stage K / V
   const int hbase = j * P.g;
 
   // Phase 2's index data for this wavefront's tokens: per token (kept columns, dense columns, slot positions).
-  // Requested now (up to 4 words per lane in registers, the rest - many tokens per wave, long rows - later), stored to
-  // the wave's LDS tile once the Q fragments have left it.
+  // Requested now (up to 4 words per lane in registers, the rest - many tokens per wave, long rows - later).
   const int e_lo = div_g(min(row0, rows_total - 1), P.g, P.g_magic);
   const int e_hi = div_g(min(row0 + 31, rows_total - 1), P.g, P.g_magic);
   const int mstride = P.topk + 2;
   const int mwords = wave_on ? (e_hi - e_lo + 1) * mstride : 0;
-  int32_t* meta = reinterpret_cast<int32_t*>(tile_lds);
+  int32_t* meta = reinterpret_cast<int32_t*>(smem + kDnMeta) + wave * dense_meta_words(P.g, P.topk);
   auto meta_word = [&](int i) -> int32_t {
     const int tk = i / mstride, c = i - tk * mstride;
     const size_t tj = (size_t)(ttok0 + e_lo + tk) * P.hkv + j;
@@ -611,50 +616,37 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
 
   if (nd > 0) {  // ---------------------------------------------------------------------------------- phase 1
     const float c2 = P.scale * 1.4426950408889634f;
-    // staging of 64 keys: thread = (key, 32 channels), four 16-byte pieces of K and of V
-    const int skey = tid >> 2, sd0 = (tid & 3) * 32;
-    u32x4 kreg[4], vreg[4];
-    auto fetch = [&](int2 piece) {  // (first key, number of keys)
-      const bool on = skey < piece.y;
-      const size_t o = ((size_t)(piece.x + (on ? skey : 0)) * P.hkv + j) * kD + sd0;
+    // Staging goes from memory straight to LDS (no register, no LDS store instruction): access i of a wavefront fills rows
+    // 16 i + 4 wave + lane / 16, lane l the place l % 16 of its row, so the lane fetches chunk (l % 16) ^ (row & 7).
+    // Rows past the end of a ragged block lie past the end of the buffer and arrive as zero.
+    const int srow = 4 * wave + (lane >> 4);
+    const uint32_t row_bytes = (uint32_t)P.hkv * kDnRow;
+    const uint32_t stage_off = srow * row_bytes + (((lane & 15) ^ (srow & 7)) << 4);
+    auto stage = [&](const bf16_t* X, int lds_off, int step) __attribute__((always_inline)) {
+      UnitRec B;
+      B.tok0 = __builtin_amdgcn_readlane(my_piece.x, step);
+      B.blen = __builtin_amdgcn_readlane(my_piece.y, step);
+      B.j = j;
+      const __amdgpu_buffer_rsrc_t buf = block_buffer(X, P, B);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        kreg[i] = *reinterpret_cast<const u32x4*>(K + o + 8 * i);
-        vreg[i] = *reinterpret_cast<const u32x4*>(V + o + 8 * i);
-        if (!on) {  // rows past the end of a ragged block are zero
-          kreg[i] = u32x4{0, 0, 0, 0};
-          vreg[i] = u32x4{0, 0, 0, 0};
-        }
-      }
+      for (int i = 0; i < 4; ++i)
+        load_to_lds(buf, lds_address(smem + lds_off) + (16 * i + 4 * wave) * kDnRow, stage_off, 16 * i * row_bytes);
     };
-    // this wavefront's 32 rows of Q (coalesced loads) and the first piece are requested together
-    u32x4 qc[8];
-    if (wave_on) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int r = min(row0 + 4 * i + crow, rows_total - 1);
-        const int e = div_g(r, P.g, P.g_magic);
-        const uint32_t grow = (uint32_t)(ttok0 + e) * (uint32_t)P.hq + (uint32_t)(hbase + (r - e * P.g));
-        qc[i] = *reinterpret_cast<const u32x4*>(Q + ((size_t)grow * kD + cchunk));
-      }
-    }
-    fetch(piece0);
-    // Q rows -> wave tile -> B-operand fragments, kept for the whole tile
-    bf16x8 qf[8];
-    if (wave_on) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(&tile_lds[(4 * i + crow) * kTileStride + cchunk]) = qc[i];
-      wave_sync();
-#pragma unroll
-      for (int s = 0; s < 8; ++s)
-        qf[s] = *reinterpret_cast<const bf16x8*>(&tile_lds[col * kTileStride + 16 * s + 8 * qh]);
-      wave_sync();
-      park_meta();  // the tile is free until phase 2
-    }
+    stage(K, kDnK, 0);
+    stage(V, kDnV, 0);
+    // this wavefront's 32 rows of Q as B-operand fragments, kept for the whole tile
     const int r = row0 + col;                        // this lane's row
     const bool valid = r < rows_total;
     const int e_row = div_g(min(r, rows_total - 1), P.g, P.g_magic);
     const int t = ttok0 + e_row;
+    bf16x8 qf[8];
+    {  // (a wavefront without rows goes along with the last row: it sees no key)
+      const uint32_t grow = (uint32_t)t * (uint32_t)P.hq + (uint32_t)(hbase + min(r, rows_total - 1) - e_row * P.g);
+      const bf16_t* src = Q + (size_t)grow * kD + 8 * qh;
+#pragma unroll
+      for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(src + 16 * s);
+      park_meta();
+    }
 
     f32x16 oacc[4];
 #pragma unroll
@@ -663,22 +655,26 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
       for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;            // running maximum (raw scores) and sum of the row
     const int grp = lane >> 4, sl = lane & 15;
-    const int tr_v = ((sl >> 2) + 4 * (grp >> 1)) * kDnPitch + 16 * (grp & 1) + 4 * (sl & 3);
-
-    for (int step = 0; step < nd; ++step) {
-      __syncthreads();  // the previous piece is no longer read
+    // K fragment of contraction step s, keys 32 mb..: chunk 2 s + qh of row 32 mb + col
+    uint32_t kaddr[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        *reinterpret_cast<u32x4*>(&Ks[skey * kDnPitch + sd0 + 8 * i]) = kreg[i];
-        *reinterpret_cast<u32x4*>(&Vs[skey * kDnPitch + sd0 + 8 * i]) = vreg[i];
-      }
-      const int2 piece = d_piece[slot * kDenseMax + step];
-      const unsigned long long members = d_mask[slot * kDenseMax + step];
-      const int ktok0 = piece.x, klen = piece.y;                // first key of the piece and its number of keys
-      if (step + 1 < nd) fetch(d_piece[slot * kDenseMax + step + 1]);  // flies during the compute
-      __syncthreads();  // K, V of the piece staged
-      if (!wave_on) continue;
+    for (int s = 0; s < 4; ++s) kaddr[s] = lds_address(smem + kDnK) + col * kDnRow + (((2 * s + qh) ^ (col & 7)) << 4);
+    // V^T fragments: transposing reads of rows (sl / 4) + 4 (grp / 2) + 16 sp (+ 8), channels 32 db + 16 (grp & 1) + 4 (sl & 3)
+    const int vrow = (sl >> 2) + 4 * (grp >> 1), vchunk = 2 * (grp & 1) + ((sl & 3) >> 1);
+    uint32_t vaddr[2];
+#pragma unroll
+    for (int d = 0; d < 2; ++d) vaddr[d] = lds_address(smem + kDnV) + vrow * kDnRow + (((4 * d + vchunk) ^ (vrow & 7)) << 4) + 8 * (sl & 1);
 
+    wait_loads();
+    __syncthreads();  // the first piece is staged
+    for (int step = 0; step < nd; ++step) {
+      // the reads below differ from these addresses by immediate offsets only
+      asm volatile("" : "+v"(kaddr[0]), "+v"(kaddr[1]), "+v"(kaddr[2]), "+v"(kaddr[3]), "+v"(vaddr[0]), "+v"(vaddr[1]));
+      const unsigned long long members =
+          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_mask, step) |
+          (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_mask >> 32), step) << 32;
+      // first key of the piece and its number of keys
+      const int ktok0 = __builtin_amdgcn_readlane(my_piece.x, step), klen = __builtin_amdgcn_readlane(my_piece.y, step);
       f32x16 sacc[2];
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
@@ -688,7 +684,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
       for (int s = 0; s < 8; ++s)
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb) {
-          const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Ks[(32 * mb + col) * kDnPitch + 16 * s + 8 * qh]);
+          const bf16x8 kf = lds_read_frag(kaddr[s & 3] + 32 * mb * kDnRow + 128 * (s >> 2));
           sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sacc[mb], 0, 0, 0);
         }
       // keys [lo, lim) of the piece are visible to this row: none if the token does not keep the block
@@ -713,11 +709,21 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           }
       }
       m = fmaxf(m, __shfl_xor(m, 32));
-      // online softmax: new running maximum, rescale of what has been accumulated
-      const float m_new = fmaxf(m_run, m);
-      const float mc = (m_new == -INFINITY) ? 0.f : m_new * c2;
-      const float alpha = __builtin_amdgcn_exp2f(fmaf(m_run, c2, -mc));  // exp2(-inf) = 0 on the first visible piece
-      m_run = m_new;
+      // Online softmax.  The reference m_run is the row maximum, but it only follows the running maximum when that has
+      // grown by more than 2^8 in the exponential's domain for some row of the wavefront: until then the probabilities
+      // stay below 2^8 and sums and products are as exact as with the true maximum (fp32, and bf16 has fp32's
+      // exponents), and the rescale of what has been accumulated is skipped.
+      if (__builtin_amdgcn_ballot_w64((m - m_run) * c2 > 8.f) != 0ull) {
+        const float m_new = fmaxf(m_run, m);
+        const float alpha = __builtin_amdgcn_exp2f((m_run - (m_new == -INFINITY ? 0.f : m_new)) * c2);  // exp2(-inf) = 0 at first
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
+      }
+      const float mc = (m_run == -INFINITY) ? 0.f : m_run * c2;
       float l = 0.f;
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
@@ -727,30 +733,33 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           sacc[mb][v] = p;
           l += p;
         }
-      l += __shfl_xor(l, 32);
-      l_run = l_run * alpha + l;
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
+      l_run += l;  // this lane's half of the keys; the halves are added up after the last piece
 
       bf16x8 pf[4];
 #pragma unroll
       for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
         for (int e2 = 0; e2 < 8; ++e2) pf[sp][e2] = (bf16_t)sacc[sp >> 1][8 * (sp & 1) + e2];
+      // K of this piece has been read and, with every wavefront's loads done, V of it is staged: the next K flies during the
+      // PV product, the next V during the S product and the softmax after it
+      wait_loads();
+      __syncthreads();
+      if (step + 1 < nd) stage(K, kDnK, step + 1);
 #pragma unroll
       for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
         for (int db = 0; db < 4; ++db) {
-          const bf16x4 a0 = lds_read_tr_f(&Vs[16 * sp * kDnPitch + tr_v + 32 * db]);
-          const bf16x4 a1 = lds_read_tr_f(&Vs[(16 * sp + 8) * kDnPitch + tr_v + 32 * db]);
+          const uint32_t v0 = vaddr[db & 1] + 16 * sp * kDnRow + 128 * (db >> 1);
+          const bf16x4 a0 = lds_read_tr_at(v0), a1 = lds_read_tr_at(v0 + 8 * kDnRow);
           const bf16x8 vf = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
           oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[sp], oacc[db], 0, 0, 0);
         }
+      wait_loads();
+      __syncthreads();  // V of this piece has been read (after the last piece: the K / V area is free), the next K is staged
+      if (step + 1 < nd) stage(V, kDnV, step + 1);
     }
-    __syncthreads();  // every wavefront is done with the last piece: the K / V area is free
     if (!wave_on) return;
+    l_run += __shfl_xor(l_run, 32);
     // the rows' dense result, normalised, and its log-sum-exp (natural log; -inf for a row that keeps none of the
     // tile's dense blocks) -> this wavefront's quarter of the K / V area, where phase 2 picks them up in its own
     // lane layout
@@ -762,7 +771,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
         uint2 w;
         w.x = pack_bf16x2(oacc[db][4 * a + 0] * inv, oacc[db][4 * a + 1] * inv);
         w.y = pack_bf16x2(oacc[db][4 * a + 2] * inv, oacc[db][4 * a + 3] * inv);
-        *reinterpret_cast<uint2*>(&od_lds[col * kTileStride + 32 * db + 8 * a + 4 * qh]) = w;
+        *reinterpret_cast<uint2*>(od_lds + col * kDnRow + (((4 * db + a) ^ (col & 15)) << 4) + 8 * qh) = w;
       }
     if (qh == 0) {
       const float mcf = (m_run == -INFINITY) ? 0.f : m_run * c2;
@@ -808,7 +817,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
       if (dm != 0u && nd > 0) {  // the row of phase 1 starts the sum
         const float ls = lse_lds[wrow];
         if (ls > -INFINITY) {
-          const uint4 v = *reinterpret_cast<const uint4*>(&od_lds[wrow * kTileStride + 8 * sub]);
+          const uint4 v = *reinterpret_cast<const uint4*>(od_lds + wrow * kDnRow + ((sub ^ (wrow & 15)) << 4));
           M[x] = ls;
           Ls[x] = 1.f;
           acc[x][0] = bf16_lo(v.x); acc[x][1] = bf16_hi(v.x); acc[x][2] = bf16_lo(v.y); acc[x][3] = bf16_hi(v.y);
@@ -987,7 +996,7 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
   auto* main128 = wide ? k_fwd_main128<true> : k_fwd_main128<false>;
   if (P0.dense) {
     static std::atomic<uint64_t> ready_dense;
-    hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge, kDnBytes, ready_dense);
+    hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge, 64 * 1024, ready_dense);
     if (e != hipSuccess) return e;
   }
   {
@@ -1018,7 +1027,7 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
       const int chunks = (kTileTokens * P.g + 127) / 128;
       const int per = (P.nj * P.t_cap * chunks + 7) / 8;
       ProfScope ps(KID_FWD_DENSE, st);
-      hipLaunchKernelGGL(k_fwd_dense_merge, dim3((unsigned)(8 * per)), dim3(256), kDnBytes, st, P, (const bf16_t*)Q,
+      hipLaunchKernelGGL(k_fwd_dense_merge, dim3((unsigned)(8 * per)), dim3(256), dense_lds_bytes(P.g, P.topk), st, P, (const bf16_t*)Q,
                          (const bf16_t*)K, (const bf16_t*)V, p.tile_tok0, p.tile_len, p.d_cnt, p.d_piece, p.d_mask,
                          (const bf16_t*)opart, (const float*)lse_part, p.vmask, p.dmask, p.slotpos, p.off, (bf16_t*)O,
                          LSE, G.gate, (const bf16_t*)G.o_acc, (bf16_t*)G.o_out);
