@@ -16,10 +16,13 @@ class _SelectedAttention(torch.autograd.Function):
         ctx.attn, ctx.cu = attn, cu
         ctx.save_for_backward(q, k, v, o, lse)
         ctx.mark_non_differentiable(lse)
+        ctx.set_materialize_grads(False)  # no zero gradient is made up (and filled on the GPU) for lse
         return o, lse
 
     @staticmethod
     def backward(ctx, do, _dlse):
+        if do is None:  # nothing reaches o
+            return None, None, None, None, None, None, None
         q, k, v, o, lse = ctx.saved_tensors
         dq, dk, dv = ctx.attn.backward(q, k, v, o, lse, do.contiguous(), ctx.cu)
         return dq, dk, dv, None, None, None, None

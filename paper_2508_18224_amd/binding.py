@@ -65,16 +65,21 @@ def _check(rc: int, what: str):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    if t is None:
-        return None
-    if not t.is_cuda or not t.is_contiguous():
+    """Address of a tensor whose device and contiguity have been checked (None stays None)."""
+    return None if t is None else t.data_ptr()
+
+
+def _launch(fn, what: str, dev: torch.device, *args):
+    """fn(*args, current stream of dev) with dev current; every argument has been checked."""
+    if dev.type != "cuda":
         raise NsaSelError("tensors must be contiguous device tensors")
-    return C.c_void_p(t.data_ptr())
-
-
-def _stream(device=None):
-    """The current stream of `device` (of the current device when None), as the void* the C ABI takes."""
-    return C.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    if torch.cuda.current_device() == dev.index:
+        rc = fn(*args, torch._C._cuda_getCurrentRawStream(dev.index))
+    else:
+        with torch.cuda.device(dev):
+            rc = fn(*args, torch._C._cuda_getCurrentRawStream(dev.index))
+    if rc != 0:
+        _check(rc, what)
 
 
 def _nbytes(t: torch.Tensor) -> int:
@@ -83,7 +88,7 @@ def _nbytes(t: torch.Tensor) -> int:
 
 def _device(device) -> torch.device:
     """torch.device with an explicit index ("cuda" means the current device)."""
-    d = torch.device(device)
+    d = device if isinstance(device, torch.device) else torch.device(device)
     if d.type == "cuda" and d.index is None:
         d = torch.device("cuda", torch.cuda.current_device())
     return d
@@ -100,15 +105,17 @@ def expect_tensor(name: str, t, dtype, shape, device, optional: bool = False):
         raise NsaSelError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
         raise NsaSelError(f"{name} must be {dtype}, got {t.dtype}")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise NsaSelError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-    if t.device != _device(device):
-        raise NsaSelError(f"{name} must live on {_device(device)}, got {t.device}")
+    if t.device != device:
+        raise NsaSelError(f"{name} must live on {device}, got {t.device}")
     if not t.is_contiguous():
         raise NsaSelError(f"{name} must be contiguous")
 
 
 def expect_workspace(name: str, t, min_bytes: int, device):
+    """A workspace is any contiguous tensor on the device.  min_bytes = 0 leaves the size to the library, which checks it
+    against the shape before it launches anything."""
     if not isinstance(t, torch.Tensor) or t.device != _device(device) or not t.is_contiguous():
         raise NsaSelError(f"{name} must be a contiguous tensor on {_device(device)}")
     if _nbytes(t) < min_bytes:
@@ -120,18 +127,23 @@ def expect_attention_args(s: "Shape", device, *, q=None, k=None, v=None, idx=Non
     """dtype / shape / device of every tensor of a forward or backward call against the shape `s` (only the
     tensors given are checked; cu is required when the shape packs several sequences)."""
     T, hq, hkv, d = s.total_tokens, s.hq, s.hkv, s.d
-    bf, f32, i32 = torch.bfloat16, torch.float32, torch.int32
-    for name, t, heads in (("q", q, hq), ("k", k, hkv), ("v", v, hkv), ("o", o, hq), ("do", do, hq),
-                           ("o_acc", o_acc, hq), ("o_out", o_out, hq)):
-        expect_tensor(name, t, bf, (T, heads, d), device, optional=True)
-    expect_tensor("lse", lse, f32, (T, hq), device, optional=True)
-    expect_tensor("gate", gate, f32, (T, hq), device, optional=True)
-    expect_tensor("dgate", dgate, f32, (T, hq), device, optional=True)
-    expect_tensor("idx", idx, i32, (T, hkv, s.topk), device, optional=not need_idx)
-    expect_tensor("cu_seqlens", cu, i32, (s.nseq + 1,), device, optional=s.nseq == 1)
+    device = _device(device)
+    bf, f32 = torch.bfloat16, torch.float32
+    rows, kv_rows, per_row = (T, hq, d), (T, hkv, d), (T, hq)
+    for name, t, shape in (("q", q, rows), ("k", k, kv_rows), ("v", v, kv_rows), ("o", o, rows), ("do", do, rows),
+                           ("o_acc", o_acc, rows), ("o_out", o_out, rows)):
+        if t is not None:
+            expect_tensor(name, t, bf, shape, device)
+    for name, t in (("lse", lse), ("gate", gate), ("dgate", dgate)):
+        if t is not None:
+            expect_tensor(name, t, f32, per_row, device)
+    if idx is not None or need_idx:
+        expect_tensor("idx", idx, torch.int32, (T, hkv, s.topk), device)
+    if cu is not None or s.nseq != 1:
+        expect_tensor("cu_seqlens", cu, torch.int32, (s.nseq + 1,), device)
     if grads is not None:
-        for name, t, heads in zip(("dq", "dk", "dv"), grads, (hq, hkv, hkv)):
-            expect_tensor(name, t, bf, (T, heads, d), device)
+        for name, t, shape in zip(("dq", "dk", "dv"), grads, (rows, kv_rows, kv_rows)):
+            expect_tensor(name, t, bf, shape, device)
     if o_out is not None and o is not None and o_out.data_ptr() == o.data_ptr() and T > 0:
         raise NsaSelError("o_out must not be the tensor o")
     if o_acc is not None and o is not None and o_acc.data_ptr() == o.data_ptr() and T > 0:
@@ -154,17 +166,16 @@ def workspace_bytes_min(shape: Shape):
 def build_index(shape: Shape, idx: torch.Tensor, cu: Optional[torch.Tensor], index_ws: torch.Tensor):
     dev = index_ws.device
     expect_attention_args(shape, dev, idx=idx, cu=cu, need_idx=True)
-    expect_workspace("index_ws", index_ws, workspace_bytes(shape)[2], dev)
-    with torch.cuda.device(dev):
-        _check(lib().nsa_sel_build_index(C.byref(shape), _ptr(idx), _ptr(cu), _ptr(index_ws), _nbytes(index_ws),
-                                         _stream(dev)), "nsa_sel_build_index")
+    expect_workspace("index_ws", index_ws, 0, dev)
+    _launch(lib().nsa_sel_build_index, "nsa_sel_build_index", dev, C.byref(shape), _ptr(idx), _ptr(cu), _ptr(index_ws),
+            _nbytes(index_ws))
 
 
 def index_view(shape: Shape, index_ws: torch.Tensor):
     """Byte offsets (from the workspace base) of cnt, off, qent, vmask, and the list stride b_cap."""
     outs = [C.c_void_p() for _ in range(4)]
     bcap = C.c_int32()
-    _check(lib().nsa_sel_index_view(C.byref(shape), _ptr(index_ws), *[C.byref(o) for o in outs], C.byref(bcap)),
+    _check(lib().nsa_sel_index_view(C.byref(shape), index_ws.data_ptr(), *[C.byref(o) for o in outs], C.byref(bcap)),
            "nsa_sel_index_view")
     base = index_ws.data_ptr()
     return [o.value - base for o in outs], bcap.value
@@ -173,34 +184,28 @@ def index_view(shape: Shape, index_ws: torch.Tensor):
 def nsa_sel_fwd(shape, q, k, v, idx, cu, rebuild_index, index_ws, o, lse, ws):
     dev = index_ws.device
     expect_attention_args(shape, dev, q=q, k=k, v=v, idx=idx, cu=cu, o=o, lse=lse, need_idx=bool(rebuild_index))
-    expect_workspace("index_ws", index_ws, workspace_bytes(shape)[2], dev)
-    expect_workspace("ws", ws, workspace_bytes_min(shape)[0], dev)
-    with torch.cuda.device(dev):
-        _check(lib().nsa_sel_fwd(C.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(idx), _ptr(cu), int(rebuild_index),
-                                 _ptr(index_ws), _nbytes(index_ws), _ptr(o), _ptr(lse), _ptr(ws), _nbytes(ws),
-                                 _stream(dev)), "nsa_sel_fwd")
+    expect_workspace("index_ws", index_ws, 0, dev)
+    expect_workspace("ws", ws, 0, dev)
+    _launch(lib().nsa_sel_fwd, "nsa_sel_fwd", dev, C.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(idx), _ptr(cu),
+            int(rebuild_index), _ptr(index_ws), _nbytes(index_ws), _ptr(o), _ptr(lse), _ptr(ws), _nbytes(ws))
 
 
 def nsa_sel_fwd_static(shape, q, k, v, idx, cu, rebuild_index, index_ws, o, lse):
     """nsa_sel_fwd with the partial buffers in the library's own device array (no workspace argument)."""
     dev = index_ws.device
     expect_attention_args(shape, dev, q=q, k=k, v=v, idx=idx, cu=cu, o=o, lse=lse, need_idx=bool(rebuild_index))
-    expect_workspace("index_ws", index_ws, workspace_bytes(shape)[2], dev)
-    with torch.cuda.device(dev):
-        _check(lib().nsa_sel_fwd_static(C.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(idx), _ptr(cu),
-                                        int(rebuild_index), _ptr(index_ws), _nbytes(index_ws), _ptr(o), _ptr(lse),
-                                        _stream(dev)), "nsa_sel_fwd_static")
+    expect_workspace("index_ws", index_ws, 0, dev)
+    _launch(lib().nsa_sel_fwd_static, "nsa_sel_fwd_static", dev, C.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(idx),
+            _ptr(cu), int(rebuild_index), _ptr(index_ws), _nbytes(index_ws), _ptr(o), _ptr(lse))
 
 
 def nsa_sel_bwd(shape, q, k, v, o, lse, do, cu, index_ws, dq, dk, dv, ws):
     dev = index_ws.device
     expect_attention_args(shape, dev, q=q, k=k, v=v, cu=cu, o=o, lse=lse, do=do, grads=(dq, dk, dv))
-    expect_workspace("index_ws", index_ws, workspace_bytes(shape)[2], dev)
-    expect_workspace("ws", ws, workspace_bytes_min(shape)[1], dev)
-    with torch.cuda.device(dev):
-        _check(lib().nsa_sel_bwd(C.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(do), _ptr(cu),
-                                 _ptr(index_ws), _nbytes(index_ws), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(ws), _nbytes(ws),
-                                 _stream(dev)), "nsa_sel_bwd")
+    expect_workspace("index_ws", index_ws, 0, dev)
+    expect_workspace("ws", ws, 0, dev)
+    _launch(lib().nsa_sel_bwd, "nsa_sel_bwd", dev, C.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(do),
+            _ptr(cu), _ptr(index_ws), _nbytes(index_ws), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(ws), _nbytes(ws))
 
 
 def select_blocks(scores: torch.Tensor, cu: Optional[torch.Tensor], topk: int, *, block: int = 64,
@@ -217,9 +222,8 @@ def select_blocks(scores: torch.Tensor, cu: Optional[torch.Tensor], topk: int, *
     expect_tensor("scores", scores, torch.float32, (T, hkv, stride), dev)
     expect_tensor("cu_seqlens", cu, torch.int32, (nseq + 1,), dev, optional=True)
     expect_tensor("out", out, torch.int32, (T, hkv, topk), dev)
-    with torch.cuda.device(dev):
-        _check(lib().nsa_sel_select_blocks(C.byref(shape), _ptr(scores), stride, _ptr(cu), n_sink, n_local, _ptr(out),
-                                           _stream(dev)), "nsa_sel_select_blocks")
+    _launch(lib().nsa_sel_select_blocks, "nsa_sel_select_blocks", dev, C.byref(shape), _ptr(scores), stride, _ptr(cu), n_sink,
+            n_local, _ptr(out))
     return out
 
 
@@ -233,9 +237,7 @@ def window_blocks(total_tokens: int, hkv: int, window: int, cu: Optional[torch.T
     dev = _device(device)
     out = torch.empty(total_tokens, hkv, topk, dtype=torch.int32, device=dev)
     expect_tensor("cu_seqlens", cu, torch.int32, (nseq + 1,), dev, optional=True)
-    with torch.cuda.device(dev):
-        _check(lib().nsa_sel_select_blocks(C.byref(shape), None, 0, _ptr(cu), 0, topk, _ptr(out), _stream(dev)),
-               "nsa_sel_select_blocks")
+    _launch(lib().nsa_sel_select_blocks, "nsa_sel_select_blocks", dev, C.byref(shape), None, 0, _ptr(cu), 0, topk, _ptr(out))
     return out
 
 
@@ -272,17 +274,16 @@ def calibration_copy(dst: torch.Tensor, src: torch.Tensor):
     nbytes = _nbytes(src)
     if _nbytes(dst) < nbytes or dst.device != src.device:
         raise NsaSelError("calibration_copy: dst must be on src's device and at least as large")
-    with torch.cuda.device(src.device):
-        _check(lib().nsa_sel_calibration_copy(_ptr(dst), _ptr(src), nbytes, _stream(src.device)),
-               "nsa_sel_calibration_copy")
+    if not dst.is_contiguous() or not src.is_contiguous():
+        raise NsaSelError("calibration_copy: tensors must be contiguous")
+    _launch(lib().nsa_sel_calibration_copy, "nsa_sel_calibration_copy", src.device, _ptr(dst), _ptr(src), nbytes)
 
 
 def mfma_probe(iters: int, sink: torch.Tensor) -> float:
     """Enqueue the MFMA probe kernel; returns the FLOPs it performs."""
     fl = C.c_double()
     expect_tensor("sink", sink, torch.float32, tuple(sink.shape), sink.device)
-    with torch.cuda.device(sink.device):
-        _check(lib().nsa_sel_mfma_probe(int(iters), _ptr(sink), C.byref(fl), _stream(sink.device)), "nsa_sel_mfma_probe")
+    _launch(lib().nsa_sel_mfma_probe, "nsa_sel_mfma_probe", sink.device, int(iters), _ptr(sink), C.byref(fl))
     return fl.value
 
 
@@ -334,10 +335,16 @@ class SelAttention:
     def build_index(self, idx, cu=None):
         build_index(self.shape, idx, cu, self.index_ws)
 
+    def _new(self, heads, dtype=torch.bfloat16):
+        """An uninitialised output: [tokens, heads, 128] bf16, or [tokens, heads] fp32, on the object's device."""
+        s = self.shape
+        size = (s.total_tokens, heads, 128) if dtype is torch.bfloat16 else (s.total_tokens, heads)
+        return torch.empty(size, dtype=dtype, device=self.device)
+
     def forward(self, q, k, v, idx, cu=None, rebuild_index=True, out=None, lse=None):
         s = self.shape
-        o = torch.empty(s.total_tokens, s.hq, 128, dtype=torch.bfloat16, device=self.device) if out is None else out
-        l = torch.empty(s.total_tokens, s.hq, dtype=torch.float32, device=self.device) if lse is None else lse
+        o = self._new(s.hq) if out is None else out
+        l = self._new(s.hq, torch.float32) if lse is None else lse
         nsa_sel_fwd(s, q, k, v, idx, cu, rebuild_index, self.index_ws, o, l, self.fwd_ws)
         return o, l
 
@@ -345,17 +352,15 @@ class SelAttention:
         """(O, LSE) by nsa_sel_fwd_static: the forward that keeps its partial results in the library's own device
         array instead of this object's workspace (small shapes only)."""
         s = self.shape
-        o = torch.empty(s.total_tokens, s.hq, 128, dtype=torch.bfloat16, device=self.device) if out is None else out
-        l = torch.empty(s.total_tokens, s.hq, dtype=torch.float32, device=self.device) if lse is None else lse
+        o = self._new(s.hq) if out is None else out
+        l = self._new(s.hq, torch.float32) if lse is None else lse
         nsa_sel_fwd_static(s, q, k, v, idx, cu, rebuild_index, self.index_ws, o, l)
         return o, l
 
     def backward(self, q, k, v, o, lse, do, cu=None, out=None):
         s = self.shape
         if out is None:
-            dq = torch.empty_like(q)
-            dk = torch.empty_like(k)
-            dv = torch.empty_like(v)
+            dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         else:
             dq, dk, dv = out
         if self.bwd_ws is None:
@@ -366,42 +371,35 @@ class SelAttention:
     def forward_query_outer(self, q, k, v, idx, cu=None):
         """(O, LSE) by the query-outer kernel (nsa_sel_fwd_query_outer): the loop order of the original NSA kernel."""
         s = self.shape
-        o = torch.empty(s.total_tokens, s.hq, 128, dtype=torch.bfloat16, device=self.device)
-        l = torch.empty(s.total_tokens, s.hq, dtype=torch.float32, device=self.device)
+        o, l = self._new(s.hq), self._new(s.hq, torch.float32)
         expect_attention_args(s, self.device, q=q, k=k, v=v, idx=idx, cu=cu, need_idx=True)
-        with torch.cuda.device(self.device):
-            _check(lib().nsa_sel_fwd_query_outer(C.byref(s), _ptr(q), _ptr(k), _ptr(v), _ptr(idx), _ptr(cu), _ptr(o),
-                                                 _ptr(l), _stream(self.device)), "nsa_sel_fwd_query_outer")
+        _launch(lib().nsa_sel_fwd_query_outer, "nsa_sel_fwd_query_outer", self.device, C.byref(s), _ptr(q), _ptr(k), _ptr(v),
+                _ptr(idx), _ptr(cu), _ptr(o), _ptr(l))
         return o, l
 
     def forward_gated(self, q, k, v, idx, gate, o_acc=None, cu=None, rebuild_index=True, out=None):
         """(O_out, O, LSE) with O_out = O_acc + gate * O (nsa_sel_fwd_gated); `out` may be the O_acc tensor."""
         s = self.shape
-        o = torch.empty(s.total_tokens, s.hq, 128, dtype=torch.bfloat16, device=self.device)
-        l = torch.empty(s.total_tokens, s.hq, dtype=torch.float32, device=self.device)
-        o_out = torch.empty_like(o) if out is None else out
+        o, l = self._new(s.hq), self._new(s.hq, torch.float32)
+        o_out = self._new(s.hq) if out is None else out
         expect_attention_args(s, self.device, q=q, k=k, v=v, idx=idx, cu=cu, gate=gate, o_acc=o_acc, o_out=o_out, o=o,
                               need_idx=bool(rebuild_index))
-        with torch.cuda.device(self.device):
-            _check(lib().nsa_sel_fwd_gated(C.byref(s), _ptr(q), _ptr(k), _ptr(v), _ptr(idx), _ptr(cu),
-                                           int(rebuild_index), _ptr(self.index_ws), _nbytes(self.index_ws), _ptr(o),
-                                           _ptr(l), _ptr(gate), _ptr(o_acc), _ptr(o_out), _ptr(self.fwd_ws),
-                                           _nbytes(self.fwd_ws), _stream(self.device)), "nsa_sel_fwd_gated")
+        _launch(lib().nsa_sel_fwd_gated, "nsa_sel_fwd_gated", self.device, C.byref(s), _ptr(q), _ptr(k), _ptr(v), _ptr(idx),
+                _ptr(cu), int(rebuild_index), _ptr(self.index_ws), _nbytes(self.index_ws), _ptr(o), _ptr(l), _ptr(gate),
+                _ptr(o_acc), _ptr(o_out), _ptr(self.fwd_ws), _nbytes(self.fwd_ws))
         return o_out, o, l
 
     def backward_gated(self, q, k, v, o, lse, do_out, gate, cu=None):
         """(dQ, dK, dV, dgate) of nsa_sel_bwd_gated."""
         s = self.shape
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
-        dgate = torch.empty(s.total_tokens, s.hq, dtype=torch.float32, device=self.device)
+        dgate = self._new(s.hq, torch.float32)
         expect_attention_args(s, self.device, q=q, k=k, v=v, cu=cu, o=o, lse=lse, do=do_out, gate=gate)
         if self.bwd_ws is None:
             raise NsaSelError("this SelAttention was created with bwd=False")
-        with torch.cuda.device(self.device):
-            _check(lib().nsa_sel_bwd_gated(C.byref(s), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(do_out),
-                                           _ptr(gate), _ptr(cu), _ptr(self.index_ws), _nbytes(self.index_ws), _ptr(dq),
-                                           _ptr(dk), _ptr(dv), _ptr(dgate), _ptr(self.bwd_ws), _nbytes(self.bwd_ws),
-                                           _stream(self.device)), "nsa_sel_bwd_gated")
+        _launch(lib().nsa_sel_bwd_gated, "nsa_sel_bwd_gated", self.device, C.byref(s), _ptr(q), _ptr(k), _ptr(v), _ptr(o),
+                _ptr(lse), _ptr(do_out), _ptr(gate), _ptr(cu), _ptr(self.index_ws), _nbytes(self.index_ws), _ptr(dq),
+                _ptr(dk), _ptr(dv), _ptr(dgate), _ptr(self.bwd_ws), _nbytes(self.bwd_ws))
         return dq, dk, dv, dgate
 
     def dense_entries(self):
