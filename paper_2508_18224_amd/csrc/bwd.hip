@@ -926,35 +926,49 @@ k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const uint32_t* __
   *reinterpret_cast<uint4*>(dQ + row * kD + 8 * sub) = o;
 }
 
-// grid (n_lists, 2, B_K / 8): y = 0 -> dK, 1 -> dV; z = group of 8 keys, so that the units of a long list (the sink
-// block's list has 32 of them) are walked by B_K / 8 workgroups side by side.  Thread = 4 consecutive channels of
-// one key; the sum runs in unit order.
+// grid (ceil(lists / per), 2, B_K / 8): y = 0 -> dK, 1 -> dV; z = group of 8 keys, so that the units of a long list (the sink
+// block's list has 32 of them) are walked by B_K / 8 workgroups side by side.  Thread = 4 consecutive channels of one
+// key; the sum runs in unit order, four units in flight.  Most lists fit one unit, which wrote the final values itself:
+// a workgroup looks at `per` <= 64 lists at once (one per lane) and walks only those that need it, so that a launch is
+// some thousand workgroups and not one per list and key group (25 900 lists: 414 000 workgroups, 174 us).
 __global__ void __launch_bounds__(256)
-k_bwd_dkv_reduce(Problem P, const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ blk_tok0,
+k_bwd_dkv_reduce(Problem P, int per, const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ blk_tok0,
                  const int32_t* __restrict__ blk_len, const float* __restrict__ dkv_part, bf16_t* __restrict__ dK,
                  bf16_t* __restrict__ dV) {
-  const int L = P.j0 * P.b_cap + blockIdx.x, which = blockIdx.y;  // lists of the pass's KV heads
-  const int ubase = nu_scan[P.j0 * P.b_cap];
-  const int j = L / P.b_cap, gb = L - j * P.b_cap;
-  const int blen = blk_len[gb];
-  if (blen == 0) return;
-  const int tok0 = blk_tok0[gb];
-  const int u0 = nu_scan[L], u1 = nu_scan[L + 1];
-  if (u1 - u0 == 1) return;  // a single unit wrote the final values itself
+  const int which = blockIdx.y, lane = threadIdx.x & 63;
+  const int n_lists = P.nj * P.b_cap, l0 = blockIdx.x * per;
+  const int ubase = P.j0 > 0 ? nu_scan[P.j0 * P.b_cap] : 0;
+  const int mine = P.j0 * P.b_cap + min(l0 + lane, n_lists - 1);  // lists of the pass's KV heads
+  const int my_u0 = nu_scan[mine], my_nu = nu_scan[mine + 1] - my_u0;
+  unsigned long long todo = __builtin_amdgcn_ballot_w64(lane < per && l0 + lane < n_lists && my_nu != 1);
   bf16_t* out = which ? dV : dK;
   const int d4 = (threadIdx.x & 31) * 4;
   const int key = 8 * blockIdx.z + (threadIdx.x >> 5);
-  if (key < blen) {
+  const size_t unit_stride = (size_t)2 * P.bk * kD;
+  while (todo != 0ull) {
+    const int i = __builtin_ctzll(todo);
+    todo &= todo - 1ull;
+    const int u0 = __builtin_amdgcn_readlane(my_u0, i), nu = __builtin_amdgcn_readlane(my_nu, i);
+    const int jl = (l0 + i) / P.b_cap, gb = l0 + i - jl * P.b_cap;
+    if (key >= blk_len[gb]) continue;
+    const float* src = dkv_part + (size_t)(u0 - ubase) * unit_stride + (size_t)which * P.bk * kD + key * kD + d4;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int u = u0; u < u1; ++u) {
-      const float4 x =
-          *reinterpret_cast<const float4*>(dkv_part + ((size_t)(u - ubase) * 2 + which) * P.bk * kD + key * kD + d4);
+    int u = 0;
+    for (; u + 4 <= nu; u += 4, src += 4 * unit_stride) {
+      float4 x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[q] = *reinterpret_cast<const float4*>(src + q * unit_stride);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { acc.x += x[q].x; acc.y += x[q].y; acc.z += x[q].z; acc.w += x[q].w; }
+    }
+    for (; u < nu; ++u, src += unit_stride) {
+      const float4 x = *reinterpret_cast<const float4*>(src);
       acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
     }
     uint2 w;
     w.x = pack_bf16x2(acc.x, acc.y);
     w.y = pack_bf16x2(acc.z, acc.w);
-    *reinterpret_cast<uint2*>(out + ((size_t)(tok0 + key) * P.hkv + j) * kD + d4) = w;
+    *reinterpret_cast<uint2*>(out + ((size_t)(blk_tok0[gb] + key) * P.hkv + P.j0 + jl) * kD + d4) = w;
   }
 }
 
@@ -1012,7 +1026,8 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
     hipLaunchKernelGGL(k_bwd_dq_reduce, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, P,
                        (const bf16_t*)dqpart, p.vmask, p.slotpos, p.off, (bf16_t*)dQ); }
     ProfScope ps(KID_BWD_DKV_REDUCE, st);
-    hipLaunchKernelGGL(k_bwd_dkv_reduce, dim3(P.nj * P.b_cap, 2, P.bk / 8), dim3(256), 0, st, P, p.u_nu, p.blk_tok0, p.blk_len,
+    const int lists = P.nj * P.b_cap, per = max(1, min(64, lists * (P.bk / 4) / 4096));
+    hipLaunchKernelGGL(k_bwd_dkv_reduce, dim3((lists + per - 1) / per, 2, P.bk / 8), dim3(256), 0, st, P, per, p.u_nu, p.blk_tok0, p.blk_len,
                        (const float*)dkv_part, (bf16_t*)dK, (bf16_t*)dV);
   }
   return hipGetLastError();

@@ -14,7 +14,7 @@ namespace nsa {
 constexpr int kBlock = 64;         // tokens of the smaller of the two block sizes (B_K = 64 or 2 * 64)
 constexpr int kD = 128;            // head dimension
 constexpr int kMaxUnit = 2048;     // most list entries of one work unit (the size used for long inputs)
-constexpr int kMinUnit = 256;
+constexpr int kMinUnit = 256;       // the smallest a caller may ask for (the library itself goes lower for tiny inputs)
 constexpr int kMaxTopk = 32;
 constexpr int kSlotBatch = 4;      // slots of a row the two reduction kernels gather at a time
 constexpr int kTileTokens = 64;    // query tokens of a tile of the dense forward path (whatever B_K is)
@@ -113,12 +113,18 @@ struct Problem {
   float scale;
 };
 
-// List entries per work unit.  Long inputs use kMaxUnit (splitting lists further only adds dK/dV partial sums);
-// short inputs use smaller units so that the ~512 workgroup slots of the chip each get several units and the sink
-// block's list (every token) does not become one slot's whole share.  Sizes swept on the paper's 8K .. 64K grid.
-inline int work_unit_entries(int64_t total_pairs) {
-  int u = kMinUnit;
-  while (u < kMaxUnit && (int64_t)u * 2 * 2048 <= total_pairs) u *= 2;  // largest power of two <= pairs / 2048
+// List entries per work unit.  Long inputs use kMaxUnit (splitting lists further only adds dK/dV partial sums); shorter
+// ones use smaller units so that the ~512 workgroup slots of the chip each get several and the sink block's list (every
+// token) does not become one slot's whole share: the largest power of two <= pairs / 2048, swept on the paper's
+// 8K .. 64K grid.  Below 2048 x 256 pairs that would cut lists into many partial sums for nothing, so it stops at 256 -
+// unless there would then be fewer than 400 units, or, for units of more than 1024 rows, fewer than 1024: slots that
+// would stand idle are worth the partial sums.  Measured, forward + backward main + dK/dV reduction: 1024 tokens x 1 kv
+// head, g = 4, top-k 8: 73 / 49 / 41 / 39 us for units of 256 / 128 / 64 / 32; 2048 x 2, g = 4, top-k 16: 79 / 71 / 86 /
+// 110; 8192 x 1, g = 8: 297 / 259 / 298; but 4096 x 2, g = 4: 117 / 131 and 16384 x 1, g = 4: 269 / 311 for 256 / 128.
+inline int work_unit_entries(int64_t total_pairs, int g) {
+  int u = 32;
+  while (u < kMaxUnit && (int64_t)u * 2 * (u < kMinUnit ? 400 : 2048) <= total_pairs) u *= 2;
+  if (u == kMinUnit && u * g > 1024 && total_pairs < (int64_t)u * 1024) u /= 2;
   return u;
 }
 
