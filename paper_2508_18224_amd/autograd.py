@@ -21,9 +21,9 @@ class _SelectedAttention(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, do, _dlse):
-        if do is None:  # nothing reaches o
-            return None, None, None, None, None, None, None
         q, k, v, o, lse = ctx.saved_tensors
+        if do is None:  # nothing reaches o: its gradient is zero
+            do = torch.zeros_like(o)
         dq, dk, dv = ctx.attn.backward(q, k, v, o, lse, do.contiguous(), ctx.cu)
         return dq, dk, dv, None, None, None, None
 

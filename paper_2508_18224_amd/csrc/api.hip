@@ -47,7 +47,7 @@ static IndexLayout make_layout(const nsa_sel_shape* s) {
   L.n_chunks = index_chunks(L.t_cap);
   L.n_groups = (L.b_cap + 63) / 64;
   L.p_max = (int64_t)s->total_tokens * s->hkv * L.topk;
-  L.unit = s->unit != 0 ? s->unit : work_unit_entries(L.p_max, s->hq / s->hkv);
+  L.unit = s->unit != 0 ? s->unit : work_unit_entries(L.p_max, s->hq / s->hkv, s->block);
   L.units_max = (int32_t)units_bound(L.hkv, L.b_cap, L.T, L.topk, L.unit);
   // dense route: on request, or by default where it pays: with g = 1 a (tile, kv head) has only 64 rows to share a
   // K / V piece, which costs more than the gather route saves (measured: +4 % per step at g = 1, -1 % .. -8 % at

@@ -118,13 +118,18 @@ struct Problem {
 // token) does not become one slot's whole share: the largest power of two <= pairs / 2048, swept on the paper's
 // 8K .. 64K grid.  Below 2048 x 256 pairs that would cut lists into many partial sums for nothing, so it stops at 256 -
 // unless there would then be fewer than 400 units, or, for units of more than 1024 rows, fewer than 1024: slots that
-// would stand idle are worth the partial sums.  Measured, forward + backward main + dK/dV reduction: 1024 tokens x 1 kv
-// head, g = 4, top-k 8: 73 / 49 / 41 / 39 us for units of 256 / 128 / 64 / 32; 2048 x 2, g = 4, top-k 16: 79 / 71 / 86 /
-// 110; 8192 x 1, g = 8: 297 / 259 / 298; but 4096 x 2, g = 4: 117 / 131 and 16384 x 1, g = 4: 269 / 311 for 256 / 128.
-inline int work_unit_entries(int64_t total_pairs, int g) {
-  int u = 32;
-  while (u < kMaxUnit && (int64_t)u * 2 * (u < kMinUnit ? 400 : 2048) <= total_pairs) u *= 2;
-  if (u == kMinUnit && u * g > 1024 && total_pairs < (int64_t)u * 1024) u /= 2;
+// would stand idle are worth the partial sums, down to the size at which a unit's fp32 dK/dV sums (2 x 64 rows of 512
+// bytes) take the room of its partial dQ rows (unit x g rows of 256 bytes): beyond it the backward workspace would be
+// mostly sums.  Measured, forward + backward main + dK/dV reduction: 1024 tokens x 1 kv head, g = 4, top-k 8:
+// 73 / 49 / 41 us for units of 256 / 128 / 64; 2048 x 2, g = 4, top-k 16: 79 / 71 / 86; 8192 x 1, g = 8: 297 / 259 for
+// 256 / 128; but 4096 x 2, g = 4: 117 / 131 and 16384 x 1, g = 4: 269 / 311.  Blocks of 128 tokens stay at 256: their
+// backward has half the workgroup slots, and its sums are twice as large.
+inline int work_unit_entries(int64_t total_pairs, int g, int bk) {
+  int u = bk == kBlock ? 32 : kMinUnit;
+  while (u < kMaxUnit && (u * g < 4 * kBlock || (int64_t)u * 2 * (u < kMinUnit ? 400 : 2048) <= total_pairs) &&
+         (u < kMinUnit || (int64_t)u * 2 * 2048 <= total_pairs))
+    u *= 2;
+  if (bk == kBlock && u == kMinUnit && u * g > 1024 && total_pairs < (int64_t)u * 1024) u /= 2;
   return u;
 }
 
