@@ -709,21 +709,13 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           }
       }
       m = fmaxf(m, __shfl_xor(m, 32));
-      // Online softmax.  The reference m_run is the row maximum, but it only follows the running maximum when that has
-      // grown by more than 2^8 in the exponential's domain for some row of the wavefront: until then the probabilities
-      // stay below 2^8 and sums and products are as exact as with the true maximum (fp32, and bf16 has fp32's
-      // exponents), and the rescale of what has been accumulated is skipped.
-      if (__builtin_amdgcn_ballot_w64((m - m_run) * c2 > 8.f) != 0ull) {
-        const float m_new = fmaxf(m_run, m);
-        const float alpha = __builtin_amdgcn_exp2f((m_run - (m_new == -INFINITY ? 0.f : m_new)) * c2);  // exp2(-inf) = 0 at first
-        m_run = m_new;
-        l_run *= alpha;
-#pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
-      }
-      const float mc = (m_run == -INFINITY) ? 0.f : m_run * c2;
+      // Online softmax: new running maximum, rescale of what has been accumulated.  For every piece, also where no maximum of
+      // the wavefront has grown much: a rescale put off until some row's has would make a row's rounding depend on the
+      // rows it shares the wavefront with.
+      const float m_new = fmaxf(m_run, m);
+      const float mc = (m_new == -INFINITY) ? 0.f : m_new * c2;
+      const float alpha = __builtin_amdgcn_exp2f(fmaf(m_run, c2, -mc));  // exp2(-inf) = 0 on the first visible piece
+      m_run = m_new;
       float l = 0.f;
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
@@ -733,7 +725,12 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           sacc[mb][v] = p;
           l += p;
         }
-      l_run += l;  // this lane's half of the keys; the halves are added up after the last piece
+      l += __shfl_xor(l, 32);
+      l_run = l_run * alpha + l;
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
 
       bf16x8 pf[4];
 #pragma unroll
@@ -759,7 +756,6 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
       if (step + 1 < nd) stage(V, kDnV, step + 1);
     }
     if (!wave_on) return;
-    l_run += __shfl_xor(l_run, 32);
     // the rows' dense result, normalised, and its log-sum-exp (natural log; -inf for a row that keeps none of the
     // tile's dense blocks) -> this wavefront's quarter of the K / V area, where phase 2 picks them up in its own
     // lane layout

@@ -132,3 +132,29 @@ def test_default_routing_policy():
                                   block=w.block, window=window, bwd=False)        # dense=None: the library picks
         c.forward()
         assert bool(c.attn.dense_entries().any()) == expect, (name, window)
+
+
+@pytest.mark.parametrize("step", [0.5, 6.0, 10.0])
+def test_climbing_maxima_and_independence_of_the_other_rows(step):
+    """The running maximum of every second token climbs by `step` (log2 domain) from piece to piece, that of its neighbours
+    stays flat: the result matches the oracle, and a row's bits do not depend on the rows it shares a wavefront with."""
+    print("case dense climbing maxima", step, flush=True)
+    T, window = 1024, 512
+    w = wl.realise(wl.Workload("climb", [T], hq=2, hkv=1, topk=1, seed=36))
+    w.idx = wl.window_block_indices([T], 1, window)                # the most recent block first: pieces go back in time
+    w.topk = w.idx.shape[2]
+    q, k = wl.bf16_bits_to_f32(w.q).copy(), wl.bf16_bits_to_f32(w.k).copy()
+    # channel 0 carries the climb: older blocks score higher by `step` / (scale log2 e) for a query of 1 there
+    level = step / (1.4426950408889634 * 128 ** -0.5)
+    k[:, :, 0] = level / 16 * (T // 64 - np.arange(T) // 64)[:, None]
+    q *= 0.25
+    q[0::2, :, 0], q[1::2, :, 0] = 16.0, 0.0
+    w.q, w.k = wl.f32_to_bf16_bits(q), wl.f32_to_bf16_bits(k)
+    _check(w, window=window, expect_dense=(0.9, 1.0))
+    o, lse = Case(w, bwd=False, window=window).forward()
+    q[1::2, :, 0] = 48.0                                           # now the neighbours climb three times as fast
+    w.q = wl.f32_to_bf16_bits(q)
+    _check(w, window=window)
+    o2, lse2 = Case(w, bwd=False, window=window).forward()
+    assert torch.equal(o[0::2], o2[0::2]) and torch.equal(lse[0::2], lse2[0::2])
+    assert not torch.equal(o[1::2], o2[1::2])
