@@ -290,15 +290,17 @@ __device__ __forceinline__ bf16x4 lds_read_tr_at(uint32_t a) {
   return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)a));
 }
 
-// 16 bytes per lane from memory straight to LDS: lane l's, from byte lane_off + wave_off of the buffer, go to lds + 16 l (lds
-// and wave_off are wave-uniform).  They are there once the wavefront's wait_loads() and, for other wavefronts, a barrier
+// 16 bytes per lane from memory straight to LDS: lane l's, from byte `off` of the buffer, go to lds + 16 l (lds is
+// wave-uniform); lanes past the end of the buffer get zero.  The whole offset is per lane: the instruction's scalar offset is
+// left out of the bounds check, or taken off the buffer's size before it, so a row step put there could read past the end.
+// The bytes are there once the wavefront's wait_loads() and, for other wavefronts, a barrier
 // after it have passed.  Written as assembly because the compiler would make every LDS read after it wait for it, also
 // reads of another tile: the double use of one tile set rests on the reads being ordered by the barriers alone.
 // The load takes its LDS address from m0 and needs a wait state after the scalar write of m0; inside an assembly block the
 // compiler inserts none, hence the s_nop.
-__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t b, uint32_t lds, uint32_t lane_off, uint32_t wave_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds), "v"(lane_off), "s"(b), "s"(wave_off) : "memory", "m0");
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t b, uint32_t lds, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(lds), "v"(off), "s"(b) : "memory", "m0");
 }
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

@@ -630,7 +630,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
       const __amdgpu_buffer_rsrc_t buf = block_buffer(X, P, B);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        load_to_lds(buf, lds_address(smem + lds_off) + (16 * i + 4 * wave) * kDnRow, stage_off, 16 * i * row_bytes);
+        load_to_lds(buf, lds_address(smem + lds_off) + (16 * i + 4 * wave) * kDnRow, stage_off + 16 * i * row_bytes);
     };
     stage(K, kDnK, 0);
     stage(V, kDnV, 0);

@@ -158,3 +158,37 @@ def test_climbing_maxima_and_independence_of_the_other_rows(step):
     o2, lse2 = Case(w, bwd=False, window=window).forward()
     assert torch.equal(o[0::2], o2[0::2]) and torch.equal(lse[0::2], lse2[0::2])
     assert not torch.equal(o[1::2], o2[1::2])
+
+
+@pytest.mark.parametrize("block,dense", [(64, True), (128, True), (64, False), (128, False)])
+def test_rows_past_a_ragged_block_are_never_used(block, dense):
+    """Short ragged blocks of packed sequences with several KV heads: NaN in the K and V of every second sequence and behind
+    the last token leaves the results of the other sequences as they are, bit for bit - a masked key still meets its V row
+    as 0 * V, so one foreign row would show."""
+    print("case dense ragged guard", block, dense, flush=True)
+    seqlens = [65, 70, 1, 85, 17, 112, 130, 33, 81]
+    w = wl.realise(wl.Workload("guard", seqlens, hq=4, hkv=2, topk=4, block=block, sink=True, seed=37))
+    T = w.total_tokens
+    seq = torch.from_numpy(np.repeat(np.arange(len(seqlens)), seqlens)).cuda()
+    c = Case(w, dense=dense)
+    rO, rL = orc.forward(*c.host_f64()[:3], w.idx, w.cu_seqlens, block=block)
+    o0, lse0 = c.forward()
+    g0 = c.backward(o0, lse0)
+    assert_close("O", to_f64(o0), rO, TOL_O)
+    if dense:
+        assert c.attn.dense_entries().any()
+    clean = (c.k, c.v)
+    for bad in (0, 1):
+        padded = []
+        for x in clean:
+            p = torch.full((T + 128, 2, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+            p[:T] = x
+            p[:T][seq % 2 == bad] = float("nan")
+            padded.append(p)
+        c.k, c.v = padded[0][:T], padded[1][:T]
+        o, lse = c.forward()
+        grads = c.backward(o, lse)
+        good = seq % 2 != bad
+        assert torch.equal(o[good], o0[good]) and torch.equal(lse[good], lse0[good]) and bool(torch.isfinite(o[good]).all())
+        for a, b in zip(grads, g0):
+            assert torch.equal(a[good], b[good])
