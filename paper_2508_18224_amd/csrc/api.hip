@@ -2,7 +2,7 @@
 #include "common.h"
 
 namespace nsa {
-int index_chunks(int t_cap);
+int index_chunks(int T, int nseq);
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -23,10 +23,13 @@ static int check_shape(const nsa_sel_shape* s) {
   if (s->nseq > (1 << 20)) return NSA_SEL_EUNSUPPORTED;
   if ((int64_t)s->total_tokens * s->hq >= ((int64_t)1 << 31)) return NSA_SEL_EUNSUPPORTED;  // 32-bit row indices
   const int64_t b_cap = (int64_t)s->total_tokens / s->block + s->nseq;
-  // block count: the inversion keeps a counter per block of a sequence in LDS
+  // Block count.  What the inversion needs is a counter per block in LDS (4 bytes, next to 32 KB of the dense detection);
+  // the limit is the tighter one of three words per block and two tiles of rows, which callers have been held to.
   if (b_cap * 12 + 2 * 64 * (int64_t)(s->topk + 1) * 4 > 160 * 1024) return NSA_SEL_EUNSUPPORTED;
   const int64_t p_max = (int64_t)s->total_tokens * s->hkv * s->topk;
   if (p_max >= ((int64_t)1 << 31) - 4096) return NSA_SEL_EUNSUPPORTED;
+  // Counters of the inversion, reckoned in chunks of 512 tokens: the layout has at most a quarter more and three (see
+  // index_by_token) and addresses them in 64 bits.
   const int64_t n_chunks = ((int64_t)s->total_tokens + 511) / 512;
   if (b_cap * s->hkv * (n_chunks > 0 ? n_chunks : 1) >= ((int64_t)1 << 31) - 4096) return NSA_SEL_EUNSUPPORTED;
   return NSA_SEL_OK;
@@ -44,7 +47,7 @@ static IndexLayout make_layout(const nsa_sel_shape* s) {
   L.b_cap = s->total_tokens / s->block + s->nseq;
   L.n_lists = s->hkv * L.b_cap;
   L.t_cap = s->total_tokens / kTileTokens + s->nseq;
-  L.n_chunks = index_chunks(L.t_cap);
+  L.n_chunks = index_chunks(L.T, L.nseq);
   L.n_groups = (L.b_cap + 63) / 64;
   L.p_max = (int64_t)s->total_tokens * s->hkv * L.topk;
   L.unit = s->unit != 0 ? s->unit : work_unit_entries(L.p_max, s->hq / s->hkv, s->block);

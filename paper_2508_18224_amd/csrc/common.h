@@ -133,6 +133,14 @@ inline int work_unit_entries(int64_t total_pairs, int g, int bk) {
   return u;
 }
 
+// Whether the inversion walks a packed batch 64 consecutive tokens at a time instead of by query tile, one wavefront each.  By
+// tile it has T / 64 + nseq wavefronts and a row of counters (one per block) for every eight of them: while sequences average
+// 256 tokens that is at most 1.25 x what the tokens alone need, far beyond it grows with the square of nseq.  The 16 keep
+// small batches by tile, where the launch that finds the dense pairs by itself would be felt.  Measured by tile / by token:
+// 65536 tokens x 8 kv heads, top-k 16, in 273 sequences 110 / 113 us, in 1024 104 / 102, in 4096 214 / 142 us; 160000
+// tokens in 10000 sequences 1128 / 420 us and 938 / 438 MB of index workspace.
+inline bool index_by_token(int T, int nseq) { return nseq > 16 + T / 256; }
+
 // Upper bound of the work units of nj KV heads (one per non-empty list plus one per full unit of entries); the
 // real count is only known on the device.
 inline int64_t units_bound(int nj, int b_cap, int T, int topk, int unit) {

@@ -4,7 +4,7 @@
 // (token, kv head, column), the entry's position in its list, which is where its partial result lives in the
 // compact partial buffers (the role of the paper's O_i), plus the work-unit tables of the attention kernels.
 //
-// Three launches (a fourth, k_prep, for packed batches):
+// Three launches (for packed batches k_prep before them, and k_dense where the tokens are walked without regard to sequences):
 //   k_hist     per (kv head, chunk, block) counts, kept columns per token, dense (query tile, KV block) pairs
 //   k_prefix   per list: prefix over the chunks, length; per 64 lists: sums
 //   k_scatter  exclusive scan of the list lengths (redone by every workgroup from the 64-list sums), list entries and
@@ -12,6 +12,9 @@
 // Everything is organised by query tile: 64 consecutive tokens of one sequence, one wavefront, lane = token.  A chunk
 // is kTilesPerChunk tiles = one workgroup.  The counters are stored chunk-major, [kv head][chunk][block], so that
 // the histogram and the scatter of one (chunk, kv head) touch one contiguous row.
+// Batches of many short sequences (index_by_token) would have a tile, mostly empty, per sequence, and counters that grow with
+// the square of the number of sequences: there a wavefront takes 64 consecutive tokens whatever sequences they belong to
+// (the lists come out the same), and only the dense pairs, which are defined by query tile, are found tile by tile, in k_dense.
 // Lists come out ascending without a sort and without order-dependent atomics: a token's rank inside its tile is a
 // popcount over a 64-bit membership mask, the tiles of a chunk are ordered by a byte count per (block, tile).
 //
@@ -31,13 +34,24 @@ struct IndexGeom {
   int32_t nseq, T, hkv, k, bk, causal, window, b_cap, t_cap, n_chunks, n_groups, unit, dense;
 };
 
-// A query tile: its first token and length (0: none), its sequence's bounds and first global block.
+// The tokens of a wavefront: the first one and their number (0: none); bounds and first global block of their sequence.  In
+// a query tile the latter are the same for all lanes; by token they are those of the lane's token (of the last one past it).
 struct Tile {
   int tok0, len, c0, c1, bb;
 };
 
-__device__ __forceinline__ Tile load_tile(const IndexGeom& G, int qt, const int32_t* cu, const IndexPtrs& p) {
+template <bool kByToken>
+__device__ __forceinline__ Tile load_tile(const IndexGeom& G, int qt, int lane, const int32_t* cu, const IndexPtrs& p) {
   Tile t = {0, 0, 0, 0, 0};
+  if constexpr (kByToken) {
+    t.tok0 = qt * kTileTokens;
+    t.len = max(min(G.T - t.tok0, kTileTokens), 0);
+    if (t.len == 0) return t;
+    int s;
+    seq_bounds(cu, G.nseq, G.T, t.tok0 + min(lane, t.len - 1), s, t.c0, t.c1);
+    t.bb = p.blk_base[s];
+    return t;
+  }
   if (qt >= G.t_cap) return t;
   if (G.nseq == 1) {
     t.tok0 = qt * kTileTokens;
@@ -55,17 +69,17 @@ __device__ __forceinline__ Tile load_tile(const IndexGeom& G, int qt, const int3
   return t;
 }
 
-// One past the last global block the tile's tokens can keep.
-__device__ __forceinline__ int tile_blocks_end(const IndexGeom& G, const Tile& t) {
-  return t.bb + (G.causal ? (t.tok0 + t.len - 1 - t.c0) / G.bk + 1 : (t.c1 - t.c0 + G.bk - 1) / G.bk);
+// Last block of its sequence the token can keep, -1 if none.
+__device__ __forceinline__ int last_block(const IndexGeom& G, const Tile& t, int tok) {
+  return G.causal ? (tok - t.c0) / G.bk : (t.c1 - t.c0 + G.bk - 1) / G.bk - 1;
 }
 
 // The window [lo, hi) of global blocks the tokens of a chunk can keep; block-wide (every wavefront passes its own tile).
+// Blocks ascend with the tokens: the first lane knows where a tile's begin, the last where they end.
 __device__ __forceinline__ void chunk_window(const IndexGeom& G, const Tile& t, int wave, int* s_win, int& lo, int& hi) {
-  if ((threadIdx.x & 63) == 0) {
-    s_win[2 * wave] = t.len > 0 ? t.bb : 0x7fffffff;
-    s_win[2 * wave + 1] = t.len > 0 ? tile_blocks_end(G, t) : 0;
-  }
+  const int lane = threadIdx.x & 63;
+  if (lane == 0) s_win[2 * wave] = t.len > 0 ? t.bb : 0x7fffffff;
+  if (lane == 63) s_win[2 * wave + 1] = t.len > 0 ? t.bb + last_block(G, t, t.tok0 + t.len - 1) + 1 : 0;
   __syncthreads();
   lo = 0x7fffffff;
   hi = 0;
@@ -269,12 +283,47 @@ __device__ __forceinline__ uint32_t dense_detect(const IndexGeom& G, const Tile&
   return dm;
 }
 
+// The same for every tile of the grid's, also the empty ones at its end, with the lanes' dense columns recorded.
+template <int KMAX>
+__device__ __forceinline__ void dense_tile(const IndexGeom& G, const Tile& t, const int32_t (&row)[KMAX], uint32_t vm, int lane,
+                                           int qt, int j, int32_t* hash, const IndexPtrs& p) {
+  const size_t slot = (size_t)qt * G.hkv + j;
+  if (t.len > 0) {
+    const uint32_t dm = dense_detect<KMAX>(G, t, row, vm, lane, slot, hash, p);
+    if (lane < t.len) p.dmask[(size_t)(t.tok0 + lane) * G.hkv + j] = dm;
+  } else if (lane == 0) {
+    p.d_cnt[slot] = 0;
+  }
+}
+
+// Detection as a launch of its own, where the histogram does not go by query tile.  grid (ceil(t_cap / kTilesPerChunk), hkv).
+// Dynamic LDS: kTilesPerChunk * kDenseHash ints.
+template <int KMAX>
+__global__ void __launch_bounds__(kChunkThreads) k_dense(IndexGeom G, const int32_t* __restrict__ idx,
+                                                         const int32_t* __restrict__ cu, IndexPtrs p) {
+  extern __shared__ __attribute__((aligned(16))) int32_t lds[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), j = blockIdx.y;
+  const int qt = blockIdx.x * kTilesPerChunk + wave;
+  if (qt >= G.t_cap) return;  // no block-wide barrier below
+  const Tile t = load_tile<false>(G, qt, lane, cu, p);
+  int32_t row[KMAX];
+#pragma unroll
+  for (int m = 0; m < KMAX; ++m) row[m] = -1;
+  uint32_t vm = 0;
+  if (lane < t.len) {
+    const size_t at = (size_t)(t.tok0 + lane) * G.hkv + j;
+    load_row<KMAX>(idx + at * G.k, G.k, rows_are_vec4(idx, G.k), row);
+    vm = p.vmask[at];
+  }
+  dense_tile<KMAX>(G, t, row, vm, lane, qt, j, lds + wave * kDenseHash, p);
+}
+
 // ------------------------------------------------------------------------------------------------ histogram
 // grid (n_chunks, hkv).  chunk_off[(j*n_chunks + chunk)*b_cap + gb] = number of tokens of the chunk that keep block gb
 // for kv head j; the whole row is written (zeros outside the chunk's window), so the array needs no clearing.  The rows
 // of idx stay in registers (one 16-byte load per four columns); the duplicate test is k^2/2 register compares.
-// Dynamic LDS: b_cap ints, with the dense route + kTilesPerChunk * kDenseHash ints.
-template <int KMAX>
+// Dynamic LDS: b_cap ints, with the dense route (by tile) + kTilesPerChunk * kDenseHash ints.
+template <int KMAX, bool kByToken>
 __global__ void __launch_bounds__(kChunkThreads) k_hist(IndexGeom G, const int32_t* __restrict__ idx,
                                                         const int32_t* __restrict__ cu, IndexPtrs p) {
   extern __shared__ __attribute__((aligned(16))) int32_t lds[];
@@ -282,7 +331,7 @@ __global__ void __launch_bounds__(kChunkThreads) k_hist(IndexGeom G, const int32
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int chunk = blockIdx.x, j = blockIdx.y;
   const int qt = chunk * kTilesPerChunk + wave;
-  const Tile t = load_tile(G, qt, cu, p);
+  const Tile t = load_tile<kByToken>(G, qt, lane, cu, p);
   const int tok = t.tok0 + lane;
   const bool live = lane < t.len;
   int32_t row[KMAX];
@@ -292,7 +341,7 @@ __global__ void __launch_bounds__(kChunkThreads) k_hist(IndexGeom G, const int32
   int gb_lo, gb_hi;
   chunk_window(G, t, wave, s_win, gb_lo, gb_hi);
   int32_t* hash = lds + wave * kDenseHash;
-  int32_t* hist = lds + (G.dense ? kTilesPerChunk * kDenseHash : 0);
+  int32_t* hist = lds + (G.dense && !kByToken ? kTilesPerChunk * kDenseHash : 0);
   for (int i = tid; i < gb_hi - gb_lo; i += kChunkThreads) hist[i] = 0;
   if (G.nseq == 1 && j == 0) {  // block and tile tables of a single sequence
     if (lane == 0 && qt < G.t_cap) {
@@ -310,7 +359,7 @@ __global__ void __launch_bounds__(kChunkThreads) k_hist(IndexGeom G, const int32
   // wholly before the token's window, and not a repeat of an earlier column.
   uint32_t vm = 0;
   if (live) {
-    const int last = G.causal ? (tok - t.c0) / G.bk : (t.c1 - t.c0 + G.bk - 1) / G.bk - 1;
+    const int last = last_block(G, t, tok);
     // oldest key a window of G.window tokens shows to this token: position tok - c0 - window + 1 of its sequence
     const int first = G.window > 0 ? max(tok - t.c0 - G.window + 1, 0) / G.bk : 0;
 #pragma unroll
@@ -327,15 +376,8 @@ __global__ void __launch_bounds__(kChunkThreads) k_hist(IndexGeom G, const int32
 #pragma unroll
   for (int m = 0; m < KMAX; ++m)
     if (m < G.k) count_column(hist, base + row[m], (vm >> m) & 1u, lane);
-  if (G.dense && qt < G.t_cap) {
-    const size_t slot = (size_t)qt * G.hkv + j;
-    if (t.len > 0) {
-      const uint32_t dm = dense_detect<KMAX>(G, t, row, vm, lane, slot, hash, p);
-      if (live) p.dmask[(size_t)tok * G.hkv + j] = dm;
-    } else if (lane == 0) {
-      p.d_cnt[slot] = 0;
-    }
-  }
+  if constexpr (!kByToken)
+    if (G.dense && qt < G.t_cap) dense_tile<KMAX>(G, t, row, vm, lane, qt, j, hash, p);
   __syncthreads();
   int32_t* out = p.chunk_off + ((size_t)j * G.n_chunks + chunk) * G.b_cap;
   for (int i = tid; i < G.b_cap; i += kChunkThreads) out[i] = (i >= gb_lo && i < gb_hi) ? hist[i - gb_lo] : 0;
@@ -454,7 +496,7 @@ __device__ __forceinline__ int2 block_scan(int2 v, int2* s_red, int2& total) {
 // as the wavefront's byte of the block's word; a token's position is list offset + entries of earlier chunks +
 // the bytes of the wavefronts before its own + popcount(mask below its lane).
 // Dynamic LDS: win * (8 masks + 1 word of bytes + 1 offset) = 76 win bytes.
-template <int KMAX>
+template <int KMAX, bool kByToken>
 __global__ void __launch_bounds__(kChunkThreads) k_scatter(IndexGeom G, int win, const int32_t* __restrict__ idx,
                                                            const int32_t* __restrict__ cu, IndexPtrs p) {
   extern __shared__ __attribute__((aligned(16))) int32_t lds[];
@@ -496,7 +538,7 @@ __global__ void __launch_bounds__(kChunkThreads) k_scatter(IndexGeom G, int win,
     return;
   }
   const int chunk = blockIdx.x - 1;
-  const Tile t = load_tile(G, chunk * kTilesPerChunk + wave, cu, p);
+  const Tile t = load_tile<kByToken>(G, chunk * kTilesPerChunk + wave, lane, cu, p);
   const int tok = t.tok0 + lane;
   const bool live = lane < t.len;
   int32_t row[KMAX];
@@ -592,30 +634,35 @@ __global__ void __launch_bounds__(kChunkThreads) k_scatter(IndexGeom G, int win,
   }
 }
 
-template <int KMAX>
+template <int KMAX, bool kByToken>
 static hipError_t launch_inversion(const IndexGeom& G, const int32_t* idx, const int32_t* cu, const IndexPtrs& p,
                                    hipStream_t st) {
-  const int lds_hist = 4 * (G.b_cap + (G.dense ? kTilesPerChunk * kDenseHash : 0));
+  const int lds_dense = 4 * kTilesPerChunk * kDenseHash, lds_hist = 4 * G.b_cap + (G.dense && !kByToken ? lds_dense : 0);
   const int win = min((G.b_cap + 63) & ~63, kScatterWindow);
   const int lds_scat = 76 * win;
   if (lds_hist > 60 * 1024 || lds_scat > 60 * 1024) {  // beyond the default 64 KB
     static std::atomic<uint64_t> ready_hist, ready_scat;
-    hipError_t e = allow_dynamic_lds((const void*)k_hist<KMAX>, 150 * 1024, ready_hist);
-    if (e == hipSuccess) e = allow_dynamic_lds((const void*)k_scatter<KMAX>, 150 * 1024, ready_scat);
+    hipError_t e = allow_dynamic_lds((const void*)(k_hist<KMAX, kByToken>), 150 * 1024, ready_hist);
+    if (e == hipSuccess) e = allow_dynamic_lds((const void*)(k_scatter<KMAX, kByToken>), 150 * 1024, ready_scat);
     if (e != hipSuccess) return e;
   }
   {
     ProfScope ps(KID_INDEX_HIST, st);
-    hipLaunchKernelGGL(k_hist<KMAX>, dim3(G.n_chunks, G.hkv), dim3(kChunkThreads), lds_hist, st, G, idx, cu, p);
+    hipLaunchKernelGGL((k_hist<KMAX, kByToken>), dim3(G.n_chunks, G.hkv), dim3(kChunkThreads), lds_hist, st, G, idx, cu, p);
   }
-  if (G.dense) ProfScope in_hist(KID_INDEX_DENSE, st);  // part of the launch above: recorded, with no time of its own
+  if (G.dense) {
+    ProfScope ps(KID_INDEX_DENSE, st);  // by tile: part of the launch above, recorded with no time of its own
+    if constexpr (kByToken)
+      hipLaunchKernelGGL(k_dense<KMAX>, dim3((G.t_cap + kTilesPerChunk - 1) / kTilesPerChunk, G.hkv), dim3(kChunkThreads),
+                         lds_dense, st, G, idx, cu, p);
+  }
   {
     ProfScope ps(KID_INDEX_SCAN, st);
     hipLaunchKernelGGL(k_prefix, dim3(G.n_groups, G.hkv), dim3(64 * kPrefixWaves), 0, st, G, p.chunk_off, p.cnt,
                        p.group_sum);
   }
   ProfScope ps(KID_INDEX_SCATTER, st);
-  hipLaunchKernelGGL(k_scatter<KMAX>, dim3(G.n_chunks + 1, G.hkv), dim3(kChunkThreads), lds_scat, st, G, win, idx, cu, p);
+  hipLaunchKernelGGL((k_scatter<KMAX, kByToken>), dim3(G.n_chunks + 1, G.hkv), dim3(kChunkThreads), lds_scat, st, G, win, idx, cu, p);
   return hipGetLastError();
 }
 
@@ -641,11 +688,19 @@ hipError_t launch_build_index(const IndexLayout& L, const int32_t* idx, const in
     hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, G, cu, p);
   }
   // rows of idx live in registers: a variant per width
-  if (G.k <= 8) return launch_inversion<8>(G, idx, cu, p, st);
-  if (G.k <= 16) return launch_inversion<16>(G, idx, cu, p, st);
-  return launch_inversion<32>(G, idx, cu, p, st);
+  if (index_by_token(L.T, L.nseq)) {
+    if (G.k <= 8) return launch_inversion<8, true>(G, idx, cu, p, st);
+    if (G.k <= 16) return launch_inversion<16, true>(G, idx, cu, p, st);
+    return launch_inversion<32, true>(G, idx, cu, p, st);
+  }
+  if (G.k <= 8) return launch_inversion<8, false>(G, idx, cu, p, st);
+  if (G.k <= 16) return launch_inversion<16, false>(G, idx, cu, p, st);
+  return launch_inversion<32, false>(G, idx, cu, p, st);
 }
 
-int index_chunks(int t_cap) { return (t_cap + kTilesPerChunk - 1) / kTilesPerChunk; }
+int index_chunks(int T, int nseq) {
+  const int tiles = index_by_token(T, nseq) ? (T + kTileTokens - 1) / kTileTokens : T / kTileTokens + nseq;
+  return (tiles + kTilesPerChunk - 1) / kTilesPerChunk;
+}
 
 }  // namespace nsa

@@ -168,3 +168,18 @@ def test_static_forward_refuses_large_shapes_before_any_gpu_call():
     assert b"nsa_sel_fwd_static" in L.nsa_sel_strerror(-5)
     assert L.nsa_sel_fwd_static(ctypes.byref(fits), None, a, a, a, None, 1, a, 1 << 40, a, a, None) == -1
     assert L.nsa_sel_fwd_static(ctypes.byref(fits), a, a, a, a, None, 1, a, 16, a, a, None) == -3
+
+
+@pytest.mark.parametrize("tokens,nseq,hkv,topk", [(160000, 10000, 8, 16), (100000, 8192, 8, 16), (100000, 10000, 64, 4),
+                                                  (65536, 4096, 8, 16), (65536, 272, 8, 16), (65536, 273, 8, 16),
+                                                  (65536, 8, 8, 16), (2000, 16, 2, 16), (12800, 12800, 8, 1)])
+def test_index_workspace_of_many_sequences(tokens, nseq, hkv, topk):
+    """The index workspace is its per-entry, per-token and per-list tables plus one counter per list and 512 tokens (a
+    quarter more and three at most): nothing in it grows with the square of the number of sequences."""
+    nsa, _ = _lib()
+    got = nsa.workspace_bytes(nsa.Shape(tokens, nseq, 4 * hkv, hkv, 128, 64, topk, 1, 0.0, 0))[2]
+    blocks, tiles, pairs = tokens // 64 + nseq, tokens // 64 + nseq, tokens * hkv * topk
+    lists, units = hkv * blocks, hkv * blocks + pairs // 32        # units of 32 entries are the smallest
+    counters = lists * (1.25 * tokens / 512 + 3)
+    tables = 12 * pairs + 8 * tokens * hkv + 20 * lists + 32 * units + 8 * blocks + 16 * tiles + tiles * hkv * (16 * 32 + 4)
+    assert got <= 4 * counters + tables + 32 * 256

@@ -80,3 +80,42 @@ def test_inversion_bit_exact_full_size(name, heads):
     if w.sink:
         assert np.all(cnt[:, 0] == w.total_tokens)
     assert int(off[-1]) == int(cnt.sum())
+
+
+@pytest.mark.parametrize("dense", [True, False])
+@pytest.mark.parametrize("extra,topk,block,causal", [(0, 5, 64, True), (1, 5, 64, True), (1, 8, 64, False),
+                                                     (40, 20, 128, True), (700, 8, 64, True)])
+def test_inversion_of_many_short_sequences(extra, topk, block, causal, dense):
+    """Packed batches on both sides of the line (16 + tokens / 256 sequences) beyond which the inversion walks the tokens
+    without regard to sequences, with empty and one-token sequences and 64-token runs that several sequences share.  The
+    dense pairs do not depend on the walk either: the same sequences in batches of few have the same dense entries."""
+    import paper_2508_18224_amd as nsa
+    print("many sequences", extra, topk, block, causal, dense, flush=True)
+    tokens = 2560
+    nseq = 16 + tokens // 256 + extra
+    rng = np.random.default_rng(91 + extra)
+    cuts = np.sort(rng.integers(0, tokens + 1, nseq - 1))
+    cuts[:3] = 0                                                   # empty sequences in front and, by chance, elsewhere
+    w = wl.Workload("many", [int(n) for n in np.diff([0, *cuts, tokens])], hq=4, hkv=2, topk=topk, block=block, causal=causal,
+                    seed=92)
+    wl.realise(w, tensors=False)
+    _compare(w)
+
+    def dense_of(idx, cu):                                         # {(token, kv head, column)} of the dense entries
+        attn = nsa.SelAttention(len(idx), w.hq, w.hkv, topk, nseq=len(cu) - 1, causal=causal, bwd=False, block=block,
+                                dense=dense)
+        attn.build_index(torch.from_numpy(idx).cuda(), torch.from_numpy(cu).cuda())
+        cnt, off, qlist, qslot, _, bcap = attn.index_arrays()
+        head = np.repeat(np.arange(w.hkv), cnt.sum(axis=1))
+        on = attn.dense_entries()
+        return set(zip(qlist[on].tolist(), head[on].tolist(), qslot[on].tolist()))
+
+    got = dense_of(w.idx, w.cu_seqlens)
+    assert bool(got) == dense
+    few, cu = set(), w.cu_seqlens
+    for s in range(0, nseq, 8):
+        a, b = int(cu[s]), int(cu[min(s + 8, nseq)])
+        if b > a:
+            part = (cu[s:min(s + 8, nseq) + 1] - a).astype(np.int32)
+            few |= {(t + a, j, m) for t, j, m in dense_of(np.ascontiguousarray(w.idx[a:b]), part)}
+    assert got == few
