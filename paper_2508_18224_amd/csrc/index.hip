@@ -69,9 +69,10 @@ __device__ __forceinline__ Tile load_tile(const IndexGeom& G, int qt, int lane, 
   return t;
 }
 
-// Last block of its sequence the token can keep, -1 if none.
+// Last block of its sequence the token can keep, -1 if none.  (A token past the last sequence's end lies past its blocks.)
 __device__ __forceinline__ int last_block(const IndexGeom& G, const Tile& t, int tok) {
-  return G.causal ? (tok - t.c0) / G.bk : (t.c1 - t.c0 + G.bk - 1) / G.bk - 1;
+  const int last = (t.c1 - t.c0 + G.bk - 1) / G.bk - 1;
+  return G.causal ? min((tok - t.c0) / G.bk, last) : last;
 }
 
 // The window [lo, hi) of global blocks the tokens of a chunk can keep; block-wide (every wavefront passes its own tile).
@@ -134,15 +135,16 @@ __device__ __forceinline__ void count_column(int32_t* table, int x, bool on, int
 // ------------------------------------------------------------------------------------------------ prep
 // Packed batches: blk_base[s] / tile_base[s] = number of KV blocks / query tiles of sequences < s; per global block its
 // first token and its key count, per tile its first token, length and sequence.  One workgroup.  (For a single sequence
-// the tables are closed forms that k_hist writes.)
+// the tables are closed forms that k_hist writes.)  The tiles cover every token up to T, whatever the last of cu says: tokens
+// past it (a padded batch) are queries of the last sequence, so that no row of the per-token tables stays unwritten.
 __global__ void __launch_bounds__(1024) k_prep(IndexGeom G, const int32_t* __restrict__ cu, IndexPtrs p) {
   __shared__ int s_sum[2][16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int carry_b = 0, carry_t = 0;
   for (int s0 = 0; s0 < G.nseq; s0 += 1024) {
     const int s = s0 + tid;
-    const int len = s < G.nseq ? cu[s + 1] - cu[s] : 0;
-    const int nb = (len + G.bk - 1) / G.bk, nt = (len + kTileTokens - 1) / kTileTokens;
+    const int len = s < G.nseq ? cu[s + 1] - cu[s] : 0, queries = s == G.nseq - 1 ? max(G.T - cu[s], 0) : len;
+    const int nb = (len + G.bk - 1) / G.bk, nt = (queries + kTileTokens - 1) / kTileTokens;
     int ib = nb, it = nt;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -192,7 +194,7 @@ __global__ void __launch_bounds__(1024) k_prep(IndexGeom G, const int32_t* __res
     if (qt < carry_t) {
       s = owner(p.tile_base, qt);
       tok0 = cu[s] + (qt - p.tile_base[s]) * kTileTokens;
-      len = min(kTileTokens, cu[s + 1] - tok0);
+      len = min(kTileTokens, (s == G.nseq - 1 ? G.T : cu[s + 1]) - tok0);
     }
     p.tile_tok0[qt] = tok0;
     p.tile_len[qt] = len;

@@ -73,3 +73,29 @@ def test_no_tokens_at_all():
                        0, None)
     assert rc == 0
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dense", [True, False])
+@pytest.mark.parametrize("singles", [0, 40])
+def test_tokens_past_the_last_sequence(singles, dense):
+    """A padded batch, cu_seqlens ending before total_tokens: the tokens past it are queries of the last sequence, and every
+    row of the result is written.  With the keys of the padding never selected that is what the oracle gives for a last
+    sequence that reaches to the end; 40 one-token sequences in front take the inversion's walk by token."""
+    print("case padded batch", singles, dense, flush=True)
+    seqlens = [1] * singles + [130, 192 + 178]                     # the last sequence: 192 tokens and 178 of padding
+    w = wl.realise(wl.Workload("padded", seqlens, hq=4, hkv=2, topk=6, sink=True, seed=84))
+    T, end = w.total_tokens, w.total_tokens - 178
+    last = w.idx[end - 192:]
+    last[last >= 3] = -1                                           # the padding's own blocks
+    c = Case(w, dense=dense)
+    c.cu[-1] = end
+    o, lse = c.forward()
+    dq, dk, dv = c.backward(o, lse)
+    Q, K, V, dO = c.host_f64()
+    rO, rL = orc.forward(Q, K, V, w.idx, w.cu_seqlens)
+    rq, rk, rv = orc.backward(Q, K, V, dO, w.idx, w.cu_seqlens)
+    assert_close("O", to_f64(o), rO, TOL_O)
+    assert np.abs(to_f64(lse) - rL)[np.isfinite(rL)].max() <= TOL_LSE
+    assert_close("dQ", to_f64(dq), rq, TOL_GRAD)
+    assert_close("dK", to_f64(dk[:end]), rk[:end], TOL_GRAD)
+    assert_close("dV", to_f64(dv[:end]), rv[:end], TOL_GRAD)
