@@ -90,7 +90,9 @@ int nsa_sel_workspace_bytes(const nsa_sel_shape* shape, size_t* fwd_bytes, size_
  * also accept a ws smaller than the sizes above, down to the minima reported here (the partial results of ONE KV
  * head with its g query heads; for the backward plus the per-row statistics of all heads).  The library then
  * works through the KV heads in groups of as many heads as ws_bytes holds, one group after the other on the
- * stream, reusing the buffers; results are bit-identical to the single-pass ones.  Either output may be NULL. */
+ * stream, reusing the buffers (the backward of tiny inputs, whose work units are smaller than 256 entries, through the
+ * KV blocks of a head in ranges where the dK/dV sums of all its units do not fit); results are bit-identical to the
+ * single-pass ones.  Either output may be NULL. */
 int nsa_sel_workspace_bytes_min(const nsa_sel_shape* shape, size_t* fwd_bytes, size_t* bwd_bytes);
 
 /* Index inversion (Sec. 3.2: the index tensors are computed from the selection tensor T before the attention kernels run):

@@ -300,14 +300,6 @@ class SelAttention:
         fb, bb, ib = workspace_bytes(self.shape)
         if ws_cap_bytes is not None:
             fmin, bmin = workspace_bytes_min(self.shape)
-            if unit == 0 and bwd and int(ws_cap_bytes) < bmin:
-                # the smaller work units the library takes for tiny inputs need room for more dK/dV partial sums
-                coarse = Shape.from_buffer_copy(self.shape)
-                coarse.unit = 256
-                if workspace_bytes_min(coarse)[1] < bmin:
-                    self.shape = coarse
-                    fb, bb, ib = workspace_bytes(self.shape)
-                    fmin, bmin = workspace_bytes_min(self.shape)
             fb = min(fb, max(fmin, int(ws_cap_bytes)))
             bb = min(bb, max(bmin, int(ws_cap_bytes)))
         self.device = _device(device)

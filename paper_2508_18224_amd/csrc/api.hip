@@ -50,7 +50,7 @@ static IndexLayout make_layout(const nsa_sel_shape* s) {
   L.n_chunks = index_chunks(L.T, L.nseq);
   L.n_groups = (L.b_cap + 63) / 64;
   L.p_max = (int64_t)s->total_tokens * s->hkv * L.topk;
-  L.unit = s->unit != 0 ? s->unit : work_unit_entries(L.p_max, s->hq / s->hkv, s->block);
+  L.unit = s->unit != 0 ? s->unit : work_unit_entries(L.p_max, L.topk, s->hq / s->hkv, s->block);
   L.units_max = (int32_t)units_bound(L.hkv, L.b_cap, L.T, L.topk, L.unit);
   // dense route: on request, or by default where it pays: with g = 1 a (tile, kv head) has only 64 rows to share a
   // K / V piece, which costs more than the gather route saves (measured: +4 % per step at g = 1, -1 % .. -8 % at
@@ -101,6 +101,9 @@ static Problem make_problem(const nsa_sel_shape* s, const IndexLayout& L) {
   P.g_magic = P.g == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint64_t)P.g + 1);
   P.j0 = 0;
   P.nj = s->hkv;
+  P.l0 = 0;
+  P.l1 = L.n_lists;
+  P.units_max = L.units_max;
   P.scale = s->scale > 0.f ? s->scale : 0.08838834764831845f;  // 1/sqrt(128)
   return P;
 }
@@ -116,10 +119,18 @@ static size_t fwd_ws_bytes(const nsa_sel_shape* s, int nj) {
   return align256(rows * kD * 2) + align256(rows * 4);
 }
 
+// Without the dK/dV sums: partial dQ rows and the statistics of all rows.
+static size_t bwd_rows_bytes(const nsa_sel_shape* s, int nj) {
+  return align256(partial_rows(s, nj) * kD * 2) + align256((size_t)s->total_tokens * s->hq * 8);
+}
+static size_t unit_sums_bytes(const IndexLayout& L) { return (size_t)2 * L.bk * kD * 4; }
+
 static size_t bwd_ws_bytes(const nsa_sel_shape* s, const IndexLayout& L, int nj) {
-  const size_t rows = partial_rows(s, nj);
-  return align256(rows * kD * 2) + align256((size_t)s->total_tokens * s->hq * 8) +
-         align256((size_t)units_bound(nj, L.b_cap, L.T, L.topk, L.unit) * 2 * L.bk * kD * 4);
+  return bwd_rows_bytes(s, nj) + align256((size_t)units_bound(nj, L.b_cap, L.T, L.topk, L.unit) * unit_sums_bytes(L));
+}
+
+static size_t bwd_ws_bytes_min(const nsa_sel_shape* s, const IndexLayout& L) {
+  return bwd_rows_bytes(s, 1) + align256((size_t)bwd_units_min(L.b_cap, L.T, L.topk, L.unit) * unit_sums_bytes(L));
 }
 
 // Largest number of KV heads per pass that `bytes` can hold; 0 when not even one fits.
@@ -150,7 +161,7 @@ int nsa_sel_workspace_bytes_min(const nsa_sel_shape* shape, size_t* fwd_bytes, s
   if (rc) return rc;
   IndexLayout L = make_layout(shape);
   if (fwd_bytes) *fwd_bytes = fwd_ws_bytes(shape, 1);
-  if (bwd_bytes) *bwd_bytes = bwd_ws_bytes(shape, L, 1);
+  if (bwd_bytes) *bwd_bytes = bwd_ws_bytes_min(shape, L);
   return NSA_SEL_OK;
 }
 
@@ -304,16 +315,22 @@ static int bwd_impl(const nsa_sel_shape* shape, const void* Q, const void* K, co
     return NSA_SEL_EINVAL;
   if (!cu_seqlens && shape->nseq != 1) return NSA_SEL_EINVAL;
   IndexLayout L = make_layout(shape);
-  const int hpp = heads_that_fit(shape->hkv, ws_bytes, [&](int nj) { return bwd_ws_bytes(shape, L, nj); });
-  if (index_bytes < L.total || hpp < 1) return NSA_SEL_EWORKSPACE;
+  int hpp = heads_that_fit(shape->hkv, ws_bytes, [&](int nj) { return bwd_ws_bytes(shape, L, nj); });
+  if (index_bytes < L.total || (hpp < 1 && ws_bytes < bwd_ws_bytes_min(shape, L))) return NSA_SEL_EWORKSPACE;
   if (shape->total_tokens == 0) return NSA_SEL_OK;
+  int lists = 0;
+  if (hpp < 1) {  // the dK/dV sums of one KV head do not fit: as many of its lists at a time as surely do
+    hpp = 1;
+    const size_t slots = (ws_bytes - bwd_rows_bytes(shape, 1)) / unit_sums_bytes(L);
+    lists = (int)(slots / (size_t)((L.T + L.unit - 1) / L.unit));
+  }
   Problem P = make_problem(shape, L);
   const size_t rows = partial_rows(shape, hpp);
   char* w = (char*)ws;
   void* dqpart = w;
   float* delta = (float*)(w + align256(rows * kD * 2));
   float* dkv_part = (float*)((char*)delta + align256((size_t)shape->total_tokens * shape->hq * 8));
-  return launch_bwd(P, L, hpp, Q, K, V, O, LSE, dO, index_ws, dqpart, delta, dkv_part, dQ, dK, dV, G,
+  return launch_bwd(P, L, hpp, lists, Q, K, V, O, LSE, dO, index_ws, dqpart, delta, dkv_part, dQ, dK, dV, G,
                     (hipStream_t)stream) == hipSuccess
              ? NSA_SEL_OK
              : NSA_SEL_EHIP;

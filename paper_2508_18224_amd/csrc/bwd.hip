@@ -936,11 +936,11 @@ k_bwd_dkv_reduce(Problem P, int per, const int32_t* __restrict__ nu_scan, const 
                  const int32_t* __restrict__ blk_len, const float* __restrict__ dkv_part, bf16_t* __restrict__ dK,
                  bf16_t* __restrict__ dV) {
   const int which = blockIdx.y, lane = threadIdx.x & 63;
-  const int n_lists = P.nj * P.b_cap, l0 = blockIdx.x * per;
-  const int ubase = P.j0 > 0 ? nu_scan[P.j0 * P.b_cap] : 0;
-  const int mine = P.j0 * P.b_cap + min(l0 + lane, n_lists - 1);  // lists of the pass's KV heads
+  const int l0 = P.l0 + blockIdx.x * per;
+  const int ubase = P.l0 > 0 ? nu_scan[P.l0] : 0;
+  const int mine = min(l0 + lane, P.l1 - 1);
   const int my_u0 = nu_scan[mine], my_nu = nu_scan[mine + 1] - my_u0;
-  unsigned long long todo = __builtin_amdgcn_ballot_w64(lane < per && l0 + lane < n_lists && my_nu != 1);
+  unsigned long long todo = __builtin_amdgcn_ballot_w64(lane < per && l0 + lane < P.l1 && my_nu != 1);
   bf16_t* out = which ? dV : dK;
   const int d4 = (threadIdx.x & 31) * 4;
   const int key = 8 * blockIdx.z + (threadIdx.x >> 5);
@@ -949,7 +949,7 @@ k_bwd_dkv_reduce(Problem P, int per, const int32_t* __restrict__ nu_scan, const 
     const int i = __builtin_ctzll(todo);
     todo &= todo - 1ull;
     const int u0 = __builtin_amdgcn_readlane(my_u0, i), nu = __builtin_amdgcn_readlane(my_nu, i);
-    const int jl = (l0 + i) / P.b_cap, gb = l0 + i - jl * P.b_cap;
+    const int j = (l0 + i) / P.b_cap, gb = l0 + i - j * P.b_cap;
     if (key >= blk_len[gb]) continue;
     const float* src = dkv_part + (size_t)(u0 - ubase) * unit_stride + (size_t)which * P.bk * kD + key * kD + d4;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -968,7 +968,7 @@ k_bwd_dkv_reduce(Problem P, int per, const int32_t* __restrict__ nu_scan, const 
     uint2 w;
     w.x = pack_bf16x2(acc.x, acc.y);
     w.y = pack_bf16x2(acc.z, acc.w);
-    *reinterpret_cast<uint2*>(out + ((size_t)(blk_tok0[gb] + key) * P.hkv + P.j0 + jl) * kD + d4) = w;
+    *reinterpret_cast<uint2*>(out + ((size_t)(blk_tok0[gb] + key) * P.hkv + j) * kD + d4) = w;
   }
 }
 
@@ -984,8 +984,8 @@ extern "C" int nsa_sel_pipe_timing_read(unsigned long long* out, int reset) {
   return 0;
 }
 #endif
-hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pass, const void* Q, const void* K,
-                      const void* V, const void* O, const float* LSE, const void* dO, const void* index_ws,
+hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pass, int lists_per_pass, const void* Q,
+                      const void* K, const void* V, const void* O, const float* LSE, const void* dO, const void* index_ws,
                       void* dqpart, float* delta, float* dkv_part, void* dQ, void* dK, void* dV, const GateArgs& G,
                       hipStream_t st) {
   IndexPtrs p = index_ptrs(L, const_cast<void*>(index_ws));
@@ -1011,24 +1011,35 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
                        dim3(256), 0, st, P0, (const bf16_t*)O,
                        (const bf16_t*)dO, LSE, (float2*)delta, G.gate, G.dgate);
   }
-  // KV heads are processed heads_per_pass at a time, every pass reusing the partial-dQ and unit-partial buffers
+  // KV heads are processed heads_per_pass at a time, every pass reusing the partial-dQ and unit-sum buffers; of one head,
+  // where its unit sums do not fit, lists_per_pass lists at a time, every range reusing the unit sums.
   for (int j0 = 0; j0 < P0.hkv; j0 += heads_per_pass) {
     Problem P = P0;
     P.j0 = j0;
     P.nj = min(heads_per_pass, P0.hkv - j0);
-    const unsigned units_max = (unsigned)units_bound(P.nj, P.b_cap, P.T, P.topk, P.unit);
-    const int64_t rows = (int64_t)P.T * P.nj * P.g;
-    { ProfScope ps(KID_BWD_MAIN, st);
-    hipLaunchKernelGGL(main_kernel, dim3(units_max), dim3(main_threads), main_lds, st, P, (const bf16_t*)Q,
-                       (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, (const float2*)delta, p.u_rec, p.u_nu,
-                       p.off, p.qent, (bf16_t*)dqpart, dkv_part, (bf16_t*)dK, (bf16_t*)dV); }
-    { ProfScope ps(KID_BWD_DQ_REDUCE, st);
-    hipLaunchKernelGGL(k_bwd_dq_reduce, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, P,
-                       (const bf16_t*)dqpart, p.vmask, p.slotpos, p.off, (bf16_t*)dQ); }
-    ProfScope ps(KID_BWD_DKV_REDUCE, st);
-    const int lists = P.nj * P.b_cap, per = max(1, min(64, lists * (P.bk / 4) / 4096));
-    hipLaunchKernelGGL(k_bwd_dkv_reduce, dim3((lists + per - 1) / per, 2, P.bk / 8), dim3(256), 0, st, P, per, p.u_nu, p.blk_tok0, p.blk_len,
-                       (const float*)dkv_part, (bf16_t*)dK, (bf16_t*)dV);
+    const int first = j0 * P.b_cap, end = (j0 + P.nj) * P.b_cap;
+    const int step = lists_per_pass > 0 ? lists_per_pass : end - first;
+    for (P.l0 = first; P.l0 < end; P.l0 += step) {
+      P.l1 = min(P.l0 + step, end);
+      // upper bound of the work units of the launch (the real count is only known on the device): also what the workspace holds
+      const int64_t bound = units_bound(P.nj, P.b_cap, P.T, P.topk, P.unit);
+      const unsigned units_max =
+          (unsigned)(lists_per_pass > 0 ? min(bound, (int64_t)step * ((P.T + P.unit - 1) / P.unit)) : bound);
+      { ProfScope ps(KID_BWD_MAIN, st);
+      hipLaunchKernelGGL(main_kernel, dim3(units_max), dim3(main_threads), main_lds, st, P, (const bf16_t*)Q,
+                         (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, (const float2*)delta, p.u_rec, p.u_nu,
+                         p.off, p.qent, (bf16_t*)dqpart, dkv_part, (bf16_t*)dK, (bf16_t*)dV); }
+      if (P.l1 == end) {
+        const int64_t rows = (int64_t)P.T * P.nj * P.g;
+        ProfScope ps(KID_BWD_DQ_REDUCE, st);
+        hipLaunchKernelGGL(k_bwd_dq_reduce, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, P,
+                           (const bf16_t*)dqpart, p.vmask, p.slotpos, p.off, (bf16_t*)dQ);
+      }
+      ProfScope ps(KID_BWD_DKV_REDUCE, st);
+      const int lists = P.l1 - P.l0, per = max(1, min(64, lists * (P.bk / 4) / 4096));
+      hipLaunchKernelGGL(k_bwd_dkv_reduce, dim3((lists + per - 1) / per, 2, P.bk / 8), dim3(256), 0, st, P, per, p.u_nu,
+                         p.blk_tok0, p.blk_len, (const float*)dkv_part, (bf16_t*)dK, (bf16_t*)dV);
+    }
   }
   return hipGetLastError();
 }

@@ -110,6 +110,8 @@ struct Problem {
   int32_t dense;   // 1: the dense forward path is on (the index carries dense flags and tables)
   int32_t t_cap;   // stride of the per-(tile, kv head) dense tables
   int32_t j0, nj;  // KV heads [j0, j0 + nj) handled by this launch (all of them unless the workspace is capped)
+  int32_t l0, l1;  // lists [l0, l1): those of the heads, or a range of one head's (see launch_bwd)
+  int32_t units_max;  // last index the table of work units has room for
   float scale;
 };
 
@@ -124,8 +126,10 @@ struct Problem {
 // 73 / 49 / 41 us for units of 256 / 128 / 64; 2048 x 2, g = 4, top-k 16: 79 / 71 / 86; 8192 x 1, g = 8: 297 / 259 for
 // 256 / 128; but 4096 x 2, g = 4: 117 / 131 and 16384 x 1, g = 4: 269 / 311.  Blocks of 128 tokens stay at 256: their
 // backward has half the workgroup slots, and its sums are twice as large.
-inline int work_unit_entries(int64_t total_pairs, int g, int bk) {
-  int u = bk == kBlock ? 32 : kMinUnit;
+// Units of 32 need a top-k of 4: a list of every token must not have more units than the smallest backward workspace has room
+// for (see bwd_units_min).
+inline int work_unit_entries(int64_t total_pairs, int topk, int g, int bk) {
+  int u = bk == kBlock ? (topk < 4 ? 64 : 32) : kMinUnit;
   while (u < kMaxUnit && (u * g < 4 * kBlock || (int64_t)u * 2 * (u < kMinUnit ? 400 : 2048) <= total_pairs) &&
          (u < kMinUnit || (int64_t)u * 2 * 2048 <= total_pairs))
     u *= 2;
@@ -145,6 +149,14 @@ inline bool index_by_token(int T, int nseq) { return nseq > 16 + T / 256; }
 // real count is only known on the device.
 inline int64_t units_bound(int nj, int b_cap, int T, int topk, int unit) {
   return (int64_t)nj * b_cap + (int64_t)nj * T * topk / unit + 1;
+}
+
+// Work units whose dK/dV sums the smallest backward workspace holds: those of one KV head at units of at least kMinUnit.  The
+// smaller units of tiny inputs have more; where they do not fit, the backward goes through the head's lists in ranges.  One
+// list always fits: it has at most ceil(T / unit) units, and that is no more than the blocks of T tokens (units of 64 and
+// 128) or, for units of 32, the blocks and T topk / 256.
+inline int64_t bwd_units_min(int b_cap, int T, int topk, int unit) {
+  return units_bound(1, b_cap, T, topk, unit < kMinUnit ? kMinUnit : unit);
 }
 
 // ---- optional per-kernel timing (off unless nsa_sel_profile_enable was called) ---------------------------
@@ -192,8 +204,9 @@ hipError_t launch_fwd(const Problem& P, const IndexLayout& L, int heads_per_pass
 // the same forward in query-outer loop order (no workspaces, no index): see qouter.hip
 hipError_t launch_fwd_query_outer(const Problem& P, const void* Q, const void* K, const void* V, const int32_t* idx,
                                   const int32_t* cu, void* O, float* LSE, hipStream_t st);
-hipError_t launch_bwd(const Problem& P, const IndexLayout& L, int heads_per_pass, const void* Q, const void* K,
-                      const void* V, const void* O, const float* LSE, const void* dO, const void* index_ws,
+// lists_per_pass: lists of a KV head whose dK/dV sums the workspace can hold at once (only with one head per pass; 0: all)
+hipError_t launch_bwd(const Problem& P, const IndexLayout& L, int heads_per_pass, int lists_per_pass, const void* Q,
+                      const void* K, const void* V, const void* O, const float* LSE, const void* dO, const void* index_ws,
                       void* dqpart, float* delta, float* dkv_part, void* dQ, void* dK, void* dV, const GateArgs& G,
                       hipStream_t st);
 
@@ -268,16 +281,17 @@ __device__ __forceinline__ bf16x8 load_frag(__amdgpu_buffer_rsrc_t b, uint32_t o
 
 // The unit of this workgroup, or false when the launch (sized by an upper bound) has no unit left for it.  The record is
 // requested before the unit count is known: the two loads are independent and every index up to the bound is allocated.
-// base = the pass's first unit, pos0 = its first list position (partial rows are relative to it).
+// base = the launch's first unit, pos0 = the first list position of its KV heads (partial rows are relative to it).
 __device__ __forceinline__ bool load_unit(const Problem& P, const UnitRec* __restrict__ u_rec,
                                           const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off,
                                           UnitRec& U, int& base, int& pos0) {
-  base = P.j0 > 0 ? nu_scan[P.j0 * P.b_cap] : 0;
+  base = P.l0 > 0 ? nu_scan[P.l0] : 0;
   pos0 = P.j0 > 0 ? off[P.j0 * P.b_cap] : 0;
   const int u = base + (int)blockIdx.x;
-  const int4 a = *reinterpret_cast<const int4*>(u_rec + u);
-  const int2 b = *reinterpret_cast<const int2*>(&u_rec[u].j);
-  const int end = nu_scan[(P.j0 + P.nj) * P.b_cap];
+  const int ur = min(u, P.units_max);
+  const int4 a = *reinterpret_cast<const int4*>(u_rec + ur);
+  const int2 b = *reinterpret_cast<const int2*>(&u_rec[ur].j);
+  const int end = nu_scan[P.l1];
   U.e0 = a.x; U.ne = a.y; U.tok0 = a.z; U.blen = a.w; U.j = b.x; U.n_units = b.y;
   asm volatile("" : "+s"(U.e0), "+s"(U.ne), "+s"(U.tok0), "+s"(U.blen), "+s"(U.j), "+s"(U.n_units));  // requested here
   return u < end;

@@ -1007,6 +1007,8 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
     Problem P = P0;
     P.j0 = j0;
     P.nj = min(heads_per_pass, P0.hkv - j0);
+    P.l0 = j0 * P.b_cap;
+    P.l1 = (j0 + P.nj) * P.b_cap;
     // upper bound of the work units of the pass (the real count is only known on the device)
     const unsigned units_max = (unsigned)units_bound(P.nj, P.b_cap, P.T, P.topk, P.unit);
     if (P.bk == 128) {

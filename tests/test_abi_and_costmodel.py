@@ -183,3 +183,45 @@ def test_index_workspace_of_many_sequences(tokens, nseq, hkv, topk):
     counters = lists * (1.25 * tokens / 512 + 3)
     tables = 12 * pairs + 8 * tokens * hkv + 20 * lists + 32 * units + 8 * blocks + 16 * tiles + tiles * hkv * (16 * 32 + 4)
     assert got <= 4 * counters + tables + 32 * 256
+
+
+def _unit_of(nsa, T, nseq, hkv, g, topk, block):
+    """Work-unit size the library picks, from the size of the backward workspace: partial dQ rows, row statistics and one
+    slot of 2 x block x 128 fp32 sums per possible unit (one per list and one per `unit` entries)."""
+    def up(x):
+        return (x + 255) // 256 * 256
+    bwd = nsa.workspace_bytes(nsa.Shape(T, nseq, g * hkv, hkv, 128, block, topk, 1, 0.0, 0))[1]
+    sums = bwd - up(T * g * hkv * topk * 256) - up(T * g * hkv * 8)
+    units, rest = divmod(sums, 2 * block * 128 * 4)
+    fits = [u for u in (32, 64, 128, 256, 512, 1024, 2048)
+            if hkv * (T // block + nseq) + T * hkv * topk // u + 1 == units]
+    assert rest == 0 and len(fits) == 1, (units, fits)
+    return fits[0]
+
+
+@pytest.mark.parametrize("pairs_per_topk,g,topk,block,unit", [
+    # tiny inputs: the smallest unit of 256 rows (32 at g = 8, 64 at 4 and 5, 128 at 2, 256 at 1), of 64 entries below a top-k of 4
+    (1024, 8, 8, 64, 32), (1024, 4, 8, 64, 64), (1024, 5, 8, 64, 64), (1024, 2, 8, 64, 128), (1024, 1, 8, 64, 256),
+    (1024, 8, 3, 64, 64), (1024, 8, 4, 64, 32),
+    # doubled while 400 units remain
+    (1599, 8, 16, 64, 32), (1600, 8, 16, 64, 64), (3199, 4, 16, 64, 64), (3200, 4, 16, 64, 128), (6399, 2, 16, 64, 128),
+    (6400, 2, 16, 64, 256),
+    # units of 256 entries and more than 1024 rows are halved below 1024 units; not at g = 4
+    (16383, 5, 16, 64, 128), (16384, 5, 16, 64, 256), (8192, 4, 16, 64, 256),
+    # then as before: the largest power of two <= pairs / 2048, at most 2048; blocks of 128 tokens never below 256
+    (65535, 4, 16, 64, 256), (65536, 4, 16, 64, 512), (262144, 4, 16, 64, 2048), (524288, 4, 16, 64, 2048),
+    (1024, 8, 8, 128, 256), (131072, 4, 8, 128, 512)])
+def test_work_unit_the_library_picks(pairs_per_topk, g, topk, block, unit):
+    nsa, _ = _lib()
+    assert _unit_of(nsa, pairs_per_topk, 1, 1, g, topk, block) == unit
+
+
+def test_smallest_backward_workspace_is_that_of_units_of_256():
+    """However small the library's work units are, a workspace that holds one KV head at units of 256 entries is accepted."""
+    import random
+    nsa, _ = _lib()
+    rng = random.Random(5)
+    for _ in range(3000):
+        T, nseq, hkv, g = rng.randint(1, 9000), rng.choice([1, 1, 2, 50]), rng.randint(1, 8), rng.randint(1, 8)
+        args = (T, nseq, g * hkv, hkv, 128, rng.choice([64, 128]), rng.randint(1, 32), 1, 0.0, 0, 0)
+        assert nsa.workspace_bytes_min(nsa.Shape(*args, 0))[1] <= nsa.workspace_bytes_min(nsa.Shape(*args, 256))[1], args

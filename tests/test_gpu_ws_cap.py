@@ -56,3 +56,25 @@ def test_workspace_below_minimum_is_rejected():
     case.attn.fwd_ws = torch.empty(fmin - 256, dtype=torch.uint8, device="cuda")
     with pytest.raises(nsa.NsaSelError):
         case.forward()
+
+
+@pytest.mark.parametrize("seqlens,hq,hkv,topk", [([1024], 4, 1, 8), ([2000], 8, 2, 16), ([700, 1, 333], 16, 2, 4),
+                                                 ([1200], 8, 1, 3), ([2000], 2, 1, 16)])
+def test_capped_workspace_of_tiny_inputs_matches_single_pass(seqlens, hq, hkv, topk):
+    """The smaller work units of tiny inputs have more dK/dV sums than the smallest backward workspace holds: the KV blocks
+    of a head are gone through in ranges, with the same units and so the same bits."""
+    print("case capped tiny", seqlens, hq, hkv, topk, flush=True)
+    w = wl.realise(wl.Workload("tiny_cap", seqlens, hq=hq, hkv=hkv, topk=topk, sink=True, seed=93))
+    full = Case(w)
+    ref = _run(full)
+    _, bmin = nsa.workspace_bytes_min(full.attn.shape)
+    one_head = nsa.Shape.from_buffer_copy(full.attn.shape)
+    one_head.unit = 256
+    assert bmin <= nsa.workspace_bytes_min(one_head)[1]
+    for cap in (bmin, bmin + 5 * 65536):
+        capped = Case(w)
+        capped.attn = nsa.SelAttention(w.total_tokens, w.hq, w.hkv, w.topk, nseq=len(w.seqlens), ws_cap_bytes=cap, dense=True)
+        assert capped.attn.shape.unit == 0 and capped.attn.bwd_ws.numel() == cap < full.attn.bwd_ws.numel()
+        capped.attn.bwd_ws.fill_(0x7F)
+        for nm, a, b in zip(("O", "LSE", "dQ", "dK", "dV"), _run(capped), ref):
+            assert _same_bits(a, b), f"{nm} differs between the capped and the full workspace"
