@@ -308,13 +308,19 @@ class SelAttention:
         self.bwd_ws = torch.empty(bb, dtype=torch.uint8, device=self.device) if bwd else None
 
     @classmethod
-    def autotuned(cls, q, k, v, idx, do, cu=None, *, topk, candidates=(256, 512, 1024, 2048), reps=3, **kw):
+    def autotuned(cls, q, k, v, idx, do, cu=None, *, topk, candidates=None, reps=3, **kw):
         """The paper picks its query batch size by timing the candidates once per configuration (App. E); this does
         the same for the work-unit size: builds one object per candidate, times `reps` forward + backward steps on
-        the given tensors with device events, and returns (best object, {unit: ms})."""
+        the given tensors with device events, and returns (best object, {unit: ms}).  candidates: None takes 256, 512, 1024
+        and 2048, and for tiny inputs, where the library by itself (unit 0) goes below what a caller can ask for, 0, 256,
+        512 and 1024."""
         T, hq = q.shape[0], q.shape[1]
         hkv = k.shape[1]
         nseq = 1 if cu is None else cu.numel() - 1
+        if candidates is None:
+            own, asked = (Shape(T, nseq, hq, hkv, 128, kw.get("block", 64), topk, 1, 0.0, 0, 0, unit) for unit in (0, 256))
+            finer = workspace_bytes(own)[1] > workspace_bytes(asked)[1]  # more units, more dK/dV sums
+            candidates = (0, 256, 512, 1024) if finer else (256, 512, 1024, 2048)
         timings = {}
         for unit in candidates:
             a = cls(T, hq, hkv, topk, nseq=nseq, unit=unit, **kw)

@@ -90,3 +90,28 @@ def test_work_unit_size_changes_speed_not_results():
             assert torch.equal(o, ref[0]) and torch.equal(lse, ref[1]) and torch.equal(dq, ref[2])
     best, timings = nsa.SelAttention.autotuned(c.q, c.k, c.v, c.idx, c.do, c.cu, topk=w.topk, reps=2)
     assert best.shape.unit in timings and len(timings) == 4
+
+
+@pytest.mark.parametrize("seqlens,hq,hkv,topk", [([1024], 8, 1, 4), ([1024], 4, 1, 8), ([700, 333], 4, 2, 8)])
+def test_units_below_256_entries(seqlens, hq, hkv, topk):
+    """Tiny inputs, for which the library takes units of 32, 64 and 128 entries: O, LSE and dQ are those of units of 256 bit
+    for bit, dK/dV match the oracle, and the autotuner times them too and keeps the fastest."""
+    print("case tiny units", seqlens, hq, hkv, topk, flush=True)
+    import paper_2508_18224_amd as nsa
+    from gpu_util import Case, TOL_GRAD, assert_close, to_f64
+    from oracle import nsa_sel_oracle as orc
+    w = wl.realise(wl.Workload("tiny_units", seqlens, hq=hq, hkv=hkv, topk=topk, sink=True, seed=94))
+    c = Case(w)
+    Q, K, V, dO = c.host_f64()
+    _, rk, rv = orc.backward(Q, K, V, dO, w.idx, w.cu_seqlens)
+    outs = []
+    for unit in (0, 256):
+        a = nsa.SelAttention(w.total_tokens, hq, hkv, topk, nseq=len(seqlens), unit=unit)
+        o, lse = a.forward(c.q, c.k, c.v, c.idx, c.cu)
+        dq, dk, dv = a.backward(c.q, c.k, c.v, o, lse, c.do, c.cu)
+        assert_close("dK", to_f64(dk), rk, TOL_GRAD)
+        assert_close("dV", to_f64(dv), rv, TOL_GRAD)
+        outs.append((o, lse, dq))
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    best, timings = nsa.SelAttention.autotuned(c.q, c.k, c.v, c.idx, c.do, c.cu, topk=topk, reps=2)
+    assert set(timings) == {0, 256, 512, 1024} and best.shape.unit == min(timings, key=timings.get)
