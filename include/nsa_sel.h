@@ -196,8 +196,7 @@ int nsa_sel_select_blocks(const nsa_sel_shape* shape, const float* scores, int64
  * events on the caller's stream, up to `capacity` launches (later ones are not recorded); capacity <= 0 turns
  * it off and frees the events.  nsa_sel_profile_collect waits for the recorded events, writes per kernel kind
  * its name, the summed milliseconds and the number of launches into the HOST arrays (each of max_kernels
- * entries), clears the record and returns the number of kinds written (or a negative code).  Launches of a group
- * that consists of several small kernels (the scans) are timed as one.
+ * entries), clears the record and returns the number of kinds written (or a negative code).
  * RESTRICTION: the record is one process-wide table (host memory; the event objects are created by enable and
  * destroyed by enable(0)).  While profiling is on, the library must be driven from ONE host thread on ONE stream:
  * calls from a second thread race on the table, and launches on a second stream would interleave their records

@@ -652,12 +652,12 @@ static hipError_t launch_inversion(const IndexGeom& G, const int32_t* idx, const
     ProfScope ps(KID_INDEX_HIST, st);
     hipLaunchKernelGGL((k_hist<KMAX, kByToken>), dim3(G.n_chunks, G.hkv), dim3(kChunkThreads), lds_hist, st, G, idx, cu, p);
   }
-  if (G.dense) {
-    ProfScope ps(KID_INDEX_DENSE, st);  // by tile: part of the launch above, recorded with no time of its own
-    if constexpr (kByToken)
+  if constexpr (kByToken)
+    if (G.dense) {
+      ProfScope ps(KID_INDEX_DENSE, st);
       hipLaunchKernelGGL(k_dense<KMAX>, dim3((G.t_cap + kTilesPerChunk - 1) / kTilesPerChunk, G.hkv), dim3(kChunkThreads),
                          lds_dense, st, G, idx, cu, p);
-  }
+    }
   {
     ProfScope ps(KID_INDEX_SCAN, st);
     hipLaunchKernelGGL(k_prefix, dim3(G.n_groups, G.hkv), dim3(64 * kPrefixWaves), 0, st, G, p.chunk_off, p.cnt,

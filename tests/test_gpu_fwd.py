@@ -52,7 +52,12 @@ def test_profile_records_only_selected_kernels():
     nsa.profile_select(None)
     c.forward()
     every = {n for n, v in nsa.profile_collect().items() if v[1]}
-    assert {"fwd_main", "fwd_dense", "index_dense", "index_scatter", "index_scan"} <= every   # fwd_dense: dense pairs + merge
+    # a kind is a launch: fwd_dense is dense pairs + merge; the dense pairs are found inside the histogram's launch ...
+    assert every == {"index_hist", "index_scan", "index_scatter", "fwd_main", "fwd_dense"}
+    many = Case(wl.realise(wl.Workload("many", [40] * 60, hq=4, hkv=2, topk=1, seed=22)), bwd=False)
+    many.forward()   # ... and by a launch of their own in batches of many short sequences
+    every = {n for n, v in nsa.profile_collect().items() if v[1]}
+    assert every == {"index_prep", "index_hist", "index_dense", "index_scan", "index_scatter", "fwd_main", "fwd_dense"}
     nsa.profile_enable(0)
     c.forward()
     assert not any(v[1] for v in nsa.profile_collect().values())
