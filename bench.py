@@ -23,18 +23,18 @@ sys.path.insert(0, ROOT)
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0
 
-# kernel kinds of nsa_sel_profile_collect -> kernel names in the rocprofv3 summaries under profiles/
+# kernel kinds of nsa_sel_profile_collect -> kernel names in the rocprofv3 summaries under profiles/ (template arguments left out)
 KERNEL_NAMES = {
     "fwd_main": ("nsa::k_fwd_main", "nsa::k_fwd_main128"), "fwd_merge": ("nsa::k_fwd_merge",),
     "fwd_dense": ("nsa::k_fwd_dense_merge",),
-    "bwd_main": ("nsa::k_bwd_tiled<2>", "nsa::k_bwd_pipe128"), "bwd_delta": ("nsa::k_bwd_delta",),
+    "bwd_main": ("nsa::k_bwd_tiled", "nsa::k_bwd_pipe128"), "bwd_delta": ("nsa::k_bwd_delta",),
     "bwd_dq_reduce": ("nsa::k_bwd_dq_reduce",), "bwd_dkv_reduce": ("nsa::k_bwd_dkv_reduce",),
 }
 NOT_IN_STEP = ("nsa::k_select_blocks", "k_calib_copy", "nsa::k_mfma_probe", "nsa::k_fwd_query_outer")
 
 
 def measured_traffic(workload: str):
-    """{kernel name: HBM bytes per launch} from the committed rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE summary of
+    """{kernel name without template arguments: HBM bytes per launch} from the committed rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE summary of
     this workload (profiles/hot_path_<workload>.txt, the table headed 'HBM traffic per launch', already scaled by the
     copy-kernel calibration).  The counters cannot be read inside a timing run, so the summary is the source; a
     workload without one has no traffic figure and the caller says so loudly."""
@@ -49,7 +49,7 @@ def measured_traffic(workload: str):
             parts = line.split()
             if len(parts) == 4 and parts[0] != "kernel":
                 try:
-                    out[parts[0]] = float(parts[3]) * 1e9
+                    out[parts[0].split("<")[0]] = float(parts[3]) * 1e9
                 except ValueError:
                     pass
     return out, path
