@@ -105,10 +105,10 @@ def expect_tensor(name: str, t, dtype, shape, device, optional: bool = False):
         raise NsaSelError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
         raise NsaSelError(f"{name} must be {dtype}, got {t.dtype}")
-    if t.shape != shape:
+    if t.shape != shape and tuple(t.shape) != tuple(shape):
         raise NsaSelError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-    if t.device != device:
-        raise NsaSelError(f"{name} must live on {device}, got {t.device}")
+    if t.device != device and t.device != _device(device):
+        raise NsaSelError(f"{name} must live on {_device(device)}, got {t.device}")
     if not t.is_contiguous():
         raise NsaSelError(f"{name} must be contiguous")
 
@@ -173,6 +173,8 @@ def build_index(shape: Shape, idx: torch.Tensor, cu: Optional[torch.Tensor], ind
 
 def index_view(shape: Shape, index_ws: torch.Tensor):
     """Byte offsets (from the workspace base) of cnt, off, qent, vmask, and the list stride b_cap."""
+    if index_ws is None or not index_ws.is_cuda or not index_ws.is_contiguous():
+        raise NsaSelError("tensors must be contiguous device tensors")
     outs = [C.c_void_p() for _ in range(4)]
     bcap = C.c_int32()
     _check(lib().nsa_sel_index_view(C.byref(shape), index_ws.data_ptr(), *[C.byref(o) for o in outs], C.byref(bcap)),

@@ -225,3 +225,22 @@ def test_smallest_backward_workspace_is_that_of_units_of_256():
         T, nseq, hkv, g = rng.randint(1, 9000), rng.choice([1, 1, 2, 50]), rng.randint(1, 8), rng.randint(1, 8)
         args = (T, nseq, g * hkv, hkv, 128, rng.choice([64, 128]), rng.randint(1, 32), 1, 0.0, 0, 0)
         assert nsa.workspace_bytes_min(nsa.Shape(*args, 0))[1] <= nsa.workspace_bytes_min(nsa.Shape(*args, 256))[1], args
+
+
+def test_binding_accepts_and_refuses_by_value():
+    """A shape is a sequence of sizes and a device may be named by a string; a host tensor is no index workspace."""
+    import torch
+    from paper_2508_18224_amd.binding import expect_tensor
+    nsa, _ = _lib()
+    t = torch.zeros(3, 4)
+    for shape in ((3, 4), [3, 4], torch.Size([3, 4])):
+        for device in ("cpu", torch.device("cpu"), t.device):
+            expect_tensor("t", t, torch.float32, shape, device)
+    with pytest.raises(nsa.NsaSelError):
+        expect_tensor("t", t, torch.float32, [4, 3], "cpu")
+    with pytest.raises(nsa.NsaSelError):
+        expect_tensor("t", t, torch.float32, (3, 4), "meta")
+    shape = nsa.Shape(1024, 1, 4, 1, 128, 64, 8, 1, 0.0, 0)
+    for ws in (None, torch.zeros(nsa.workspace_bytes(shape)[2], dtype=torch.uint8)):
+        with pytest.raises(nsa.NsaSelError):
+            nsa.index_view(shape, ws)
