@@ -99,3 +99,35 @@ def test_tokens_past_the_last_sequence(singles, dense):
     assert_close("dQ", to_f64(dq), rq, TOL_GRAD)
     assert_close("dK", to_f64(dk[:end]), rk[:end], TOL_GRAD)
     assert_close("dV", to_f64(dv[:end]), rv[:end], TOL_GRAD)
+
+
+@pytest.mark.parametrize("block,window", [(64, 0), (64, 512), (128, 0), (128, 512)])
+def test_query_tensors_beyond_4_gb(block, window):
+    """Q, O, dO and dQ of 4.6 GB, whose rows 32-bit offsets do not reach (64 heads, 280 000 tokens in two sequences): every
+    output is that of the two sequences taken alone, 2.3 GB each, bit for bit - same lists, same work units."""
+    print("case beyond 4 GB", block, window, flush=True)
+    hq, hkv, lengths = 64, 8, [139000, 141000]
+    T, cuts = sum(lengths), [0, lengths[0], sum(lengths)]
+    gen = torch.Generator(device="cuda").manual_seed(85)
+
+    def normal(heads):
+        return torch.randn(T, heads, 128, generator=gen, device="cuda", dtype=torch.float32).to(torch.bfloat16)
+    q, k, v, do = normal(hq), normal(hkv), normal(hkv), normal(hq)
+    cu = torch.tensor(cuts, dtype=torch.int32, device="cuda")
+    if window:
+        idx = nsa.window_blocks(T, hkv, window, cu, block=block)
+    else:  # own block, sink, and one earlier block
+        own = torch.cat([torch.arange(n, device="cuda") // block for n in lengths])[:, None]
+        pick = (torch.rand(T, hkv, generator=gen, device="cuda") * own).long()
+        idx = torch.stack([own.expand(T, hkv), torch.zeros_like(pick), pick], dim=2).to(torch.int32).contiguous()
+
+    def step(a, b, cu):
+        attn = nsa.SelAttention(b - a, hq, hkv, idx.shape[2], nseq=1 if cu is None else 2, block=block, window=window,
+                                unit=2048, dense=True, ws_cap_bytes=1)
+        o, lse = attn.forward(q[a:b], k[a:b], v[a:b], idx[a:b], cu)
+        return (o, lse, *attn.backward(q[a:b], k[a:b], v[a:b], o, lse, do[a:b], cu))
+    whole = step(0, T, cu)
+    for a, b in zip(cuts, cuts[1:]):
+        for nm, x, y in zip(("O", "LSE", "dQ", "dK", "dV"), step(a, b, None), whole):
+            assert torch.equal(x, y[a:b]), nm
+    assert bool(torch.isfinite(whole[0][::997].float()).all())

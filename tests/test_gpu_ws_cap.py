@@ -78,3 +78,21 @@ def test_capped_workspace_of_tiny_inputs_matches_single_pass(seqlens, hq, hkv, t
         capped.attn.bwd_ws.fill_(0x7F)
         for nm, a, b in zip(("O", "LSE", "dQ", "dK", "dV"), _run(capped), ref):
             assert _same_bits(a, b), f"{nm} differs between the capped and the full workspace"
+
+
+@pytest.mark.parametrize("tokens,block", [(9900, 64), (9990, 128)])
+def test_reduction_by_ranges_of_lists_matches_one_list_each(tokens, block):
+    """The dK/dV reduction gives a workgroup lists x block / 4 / 4096 lists: three of 775 (of 395 blocks of 128 tokens)
+    with all KV heads in one pass, the last range short, and one of 155 (79) with a KV head per pass.  Same bits."""
+    print("case list ranges", tokens, block, flush=True)
+    w = wl.realise(wl.Workload("ranges", [tokens], hq=5, hkv=5, topk=4, block=block, sink=True, seed=95))
+    lists = 5 * (tokens // block + 1)
+    per = lists * (block // 4) // 4096
+    assert per == 3 and lists % per and lists // 5 * (block // 4) < 2 * 4096
+    full = Case(w)
+    ref = _run(full)
+    capped = Case(w)
+    capped.attn = nsa.SelAttention(tokens, 5, 5, 4, block=block, ws_cap_bytes=1, dense=True)
+    capped.attn.bwd_ws.fill_(0x7F)
+    for nm, a, b in zip(("O", "LSE", "dQ", "dK", "dV"), _run(capped), ref):
+        assert _same_bits(a, b), nm
