@@ -32,17 +32,6 @@ namespace nsa {
 // 45 % of LDS cycles were bank conflicts, 8 % kernel time).
 constexpr int kRowStride = 152;
 
-// ds_read_b64_tr_b16: every lane passes the address of 8 bytes (four 16-bit elements); within each group of
-// 16 lanes, lane i receives element (i % 4) of the 8 bytes addressed by lanes 4e + i / 4, for e = 0..3.  With
-// lane s of a group pointing at row (s / 4), columns 4 (s % 4).. of a row-major tile, lane i gets column i of
-// four consecutive rows: the MFMA operand layout (lane = column, elements = rows) without a transposed copy.
-__device__ __forceinline__ bf16x4 lds_read_tr(const bf16_t* p) {
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-  const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(uintptr_t)(uint32_t)(uintptr_t)p);
-  return __builtin_bit_cast(bf16x4, v);
-}
-
 __device__ __forceinline__ void wave_sync_bwd() {  // orders a wavefront's own LDS traffic
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -53,7 +42,7 @@ __device__ __forceinline__ void wave_sync_bwd() {  // orders a wavefront's own L
 // head), so it is laid out head-major, [kv head][token][head of the group]: one kv head's pairs (8 g bytes a token, 2 MB
 // at 65536 tokens and g = 4) stay in an XCD's L2 while the main kernels work on that head.  In token-major order every
 // gather of 8 g bytes fetched a line of its own (2 GB per pass at 65536 tokens, 32 kv heads, g = 1).
-// A workgroup takes kDeltaTokens tokens x kDeltaHeads query heads: rows are read in memory order (16 lanes x 16 bytes a
+// A workgroup takes kDeltaTokens tokens x the query heads of kDeltaKv KV heads: rows are read in memory order (16 lanes x 16 bytes a
 // row, four rows per lane in flight), the pairs are turned around in LDS and leave as runs of 8 g kDeltaTokens bytes.
 constexpr int kDeltaTokens = 8;
 constexpr int kDeltaKv = 8;   // kv heads per workgroup: at most 64 query heads

@@ -305,12 +305,15 @@ __device__ __forceinline__ bf16x8 lds_read_frag(uint32_t a) {
   return *(__attribute__((address_space(3))) const bf16x8*)a;
 }
 // ds_read_b64_tr_b16: every lane passes the address of 8 bytes (four 16-bit elements); within each group of 16 lanes, lane
-// i receives element (i % 4) of the 8 bytes addressed by lanes 4e + i / 4, e = 0..3.
+// i receives element (i % 4) of the 8 bytes addressed by lanes 4e + i / 4, e = 0..3.  With lane s of a group pointing at row
+// (s / 4), columns 4 (s % 4).. of a row-major tile, lane i gets column i of four consecutive rows: the MFMA operand layout
+// (lane = column, elements = rows) without a transposed copy.
 __device__ __forceinline__ bf16x4 lds_read_tr_at(uint32_t a) {
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
   return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)a));
 }
+__device__ __forceinline__ bf16x4 lds_read_tr(const bf16_t* p) { return lds_read_tr_at((uint32_t)(uintptr_t)p); }
 
 // 16 bytes per lane from memory straight to LDS: lane l's, from byte `off` of the buffer, go to lds + 16 l (lds is
 // wave-uniform); lanes past the end of the buffer get zero.  The whole offset is per lane: the instruction's scalar offset is

@@ -329,15 +329,6 @@ constexpr int kF128Cnts = kF128Epos + kMaxUnit * 2;
 constexpr int kF128Bytes = kF128Cnts + (kMaxUnit / 64) * 4;
 static_assert(kF128Bytes <= 160 * 1024, "forward 128-key tile set must fit the CU's LDS");
 
-// ds_read_b64_tr_b16: every lane passes the address of 8 bytes (four 16-bit elements); within each group of 16
-// lanes, lane i receives element (i % 4) of the 8 bytes addressed by lanes 4e + i / 4, e = 0..3.
-__device__ __forceinline__ bf16x4 lds_read_tr_f(const bf16_t* p) {
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-  const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(uintptr_t)(uint32_t)(uintptr_t)p);
-  return __builtin_bit_cast(bf16x4, v);
-}
-
 template <bool kWide>
 __global__ void __launch_bounds__(64 * kWaves128)
 k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
@@ -487,8 +478,8 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
       const int k0 = 32 * (sp >> 1) + 16 * (sp & 1);
 #pragma unroll
       for (int db = 0; db < 4; ++db) {
-        const bf16x4 a0 = lds_read_tr_f(&Vs[k0 * kPitch128 + tr_v + 32 * db]);
-        const bf16x4 a1 = lds_read_tr_f(&Vs[(k0 + 8) * kPitch128 + tr_v + 32 * db]);
+        const bf16x4 a0 = lds_read_tr(&Vs[k0 * kPitch128 + tr_v + 32 * db]);
+        const bf16x4 a1 = lds_read_tr(&Vs[(k0 + 8) * kPitch128 + tr_v + 32 * db]);
         const bf16x8 vf = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
         oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[sp], oacc[db], 0, 0, 0);
       }
