@@ -64,7 +64,7 @@ typedef struct {
                              listing the blocks a window can touch (the token's own and the ceil((w-1)/block)
                              before it; nsa_sel_select_blocks with scores = NULL writes that table) the path
                              computes the sliding-window term of Eq. (2), softmax over the last w tokens       */
-  int32_t unit;           /* 0: the library picks.  Else the list entries one workgroup works through (a work
+  int32_t unit;           /* 0: the library picks (for tiny inputs also below 256).  Else the list entries one workgroup works through (a work
                              unit; the knob that corresponds to the paper's query batch size B_Q, App. E, which
                              it picks by online profiling): a power of two in [256, 2048].  It changes speed and
                              the workspace sizes, not results (dK/dV only in their fp32 summation order)      */

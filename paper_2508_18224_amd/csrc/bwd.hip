@@ -127,8 +127,8 @@ k_bwd_delta(Problem P, const bf16_t* __restrict__ O, const bf16_t* __restrict__ 
 // A row's place in memory is worked out once, by the lane that owns it, one tile before its loads are issued, and handed
 // to the lanes that move it; rows move through buffer instructions without branches (see RowTensor), so the wait for a
 // tile's rows does not wait for the stores of the tile before.  That took 40 % of the vector instructions out of the loop
-// and a full drain of the memory queue out of every tile: 4.59 -> 4.25 ms at 65536 tokens, g = 4 (26.5 GB: 6.2 TB/s of the
-// 7.2 TB/s that plain gather + store kernels reach between the XCDs and the memory side).
+// and a full drain of the memory queue out of every tile: 4.59 -> 4.2 ms at 65536 tokens, g = 4 (26.2 GB between the XCDs
+// and the memory side: 6.2 TB/s; LDS pipe busy 69 % of the time, matrix pipe 34 %).
 constexpr int kTile = 64;      // rows per tile
 constexpr int kPStride = 72;   // bf16 per row of the P^T / dS^T tiles: 64 rows + 8 pad
 constexpr int kEntSeg = 1024;  // list entries whose token ids are resident in LDS
@@ -422,7 +422,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 // Q / dO tiles and P^T / dS^T tiles are double-buffered in LDS (154 KB in all), so the S-waves' MFMA and exponential work
 // on tile n runs beside the A-waves' LDS-bound products on tile n - 1 on the same SIMD; two block-wide barriers per
 // tile order the hand-over.  Rows are requested three tiles ahead into two register sets and staged after the second
-// barrier.  Measured at 65536 tokens, g = 4, (128, 8): 3.5 ms against 4.1 ms for the eight-waves-in-step kernel, 3.25 ms
+// barrier.  Measured at 65536 tokens, g = 4, (128, 8): 3.5 ms against 4.1 ms for the eight-waves-in-step kernel, 3.3 ms
 // since rows move by buffer instructions (no 64-bit address per access on the P/dS waves' staging path).
 struct PipeLds {
   static constexpr int QB = kTile * kRowStride * 2;   // one Q or dO tile: 19456 bytes

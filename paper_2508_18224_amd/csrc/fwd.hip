@@ -133,10 +133,9 @@ constexpr int kF64Bytes = kF64Cnts + (kMaxUnit / 64) * 4;
 static_assert(2 * kF64Bytes <= 160 * 1024, "two workgroups of the 64-key forward must fit one CU's LDS");
 
 // Bound by the traffic between the XCDs and the memory side: 14.3 GB per launch at 65536 tokens, g = 4, which this kernel
-// moves at 6.9 TB/s (plain gather + store kernels reach 7.2).  Rows move by branch-free buffer instructions with the
-// row's place worked out once per tile and lane: with branches around the stores and 64-bit addresses per access every
-// wait for the next rows also drained the stores and the tile cost twice the address arithmetic (2.14 -> 2.06 ms; at
-// 8192 tokens, g = 1: 367 -> 330 us).
+// moves at 7.0 TB/s.  Rows move by branch-free buffer instructions with the row's place worked out once per tile and lane: with
+// branches around the stores and 64-bit addresses per access every wait for the next rows also drained the stores and the tile
+// cost a third more vector instructions (2.14 -> 2.04 ms; at 8192 tokens, g = 1: 367 -> 330 us).
 template <bool kWide>
 __global__ void __launch_bounds__(256, 2)  // two workgroups per CU: 256 registers per wavefront
 k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
@@ -526,14 +525,15 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 //            LDS, so that phase 2 starts with its addresses known and the only memory latency left in it is that of the
 //            gathers themselves.
 // Tiles without a dense piece skip phase 1, so with the dense route on this kernel is the merge of every row.
-// Phase 2 is bound by memory (65536 tokens, g = 4: 9.4 GB in 1.80 ms; gathers of 1 KB from 8 GB reach 6.0 TB/s), phase 1
-// by the order S product, softmax, PV product inside each of the two wavefronts of a SIMD.  Staging through registers with
-// the piece table read inside the loop took 1.85 ms there and 0.55 instead of 0.505 ms for a window of 512 at 32768 tokens,
-// 1.91 instead of 1.76 ms with 9 of 16 columns dense at g = 7.  A second K tile (requests one piece earlier) gave nothing,
-// three workgroups per CU (168 registers) spill.
+// Phase 2 is bound by memory (65536 tokens, g = 4: 9.15 GB in 1.79 ms for the whole kernel), phase 1 by the order S product,
+// softmax, PV product inside each of the two wavefronts of a SIMD.  Staging through registers with the piece table read inside the
+// loop took 1.87 ms there, 1.10 instead of 1.05 ms for a window of 512 at 65536 tokens and 1.88 instead of 1.81 ms with 9 of 16
+// columns dense at g = 7.  A second K tile (requests one piece earlier) gave nothing; three workgroups per CU leave 168
+// registers, 30 of them spilled.
 // LDS: the K and the V tile of a piece, row-major and unpadded; the 16-byte chunk c of row r lies at place c ^ (r & 7) of
-// its row, which keeps both access shapes (16-byte reads down a column of rows, transposing reads of 4 rows x 32 bytes)
-// off each other's banks.  Phase 1's result takes the same area afterwards (place c ^ (r & 15)).
+// its row, which spreads both access shapes (16-byte reads down a column of rows, transposing reads of 4 rows x 32 bytes)
+// over the banks.  (The LDS pipe is busy 10 % of the kernel's time, half of that in conflicts.)  Phase 1's result takes the same
+// area afterwards (place c ^ (r & 15)).
 constexpr int kDnRow = kD * 2;
 constexpr int kDnK = 0;
 constexpr int kDnV = kDnK + 64 * kDnRow;
@@ -887,7 +887,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
 // 16 lanes per (token, head) row, 8 output channels per lane.  Slots are taken kSlotBatch at a time: positions,
 // partial log-sum-exps and partial rows of a batch are all requested before any of them is used; batches are chained
 // by the usual running-max rescale.  Small batches keep the register count low, and the many resident waves that
-// result hide the gather latency better than long batches did (16 -> 4: 1.87 -> 1.80 ms at the headline shape).
+// result hide the gather latency better than long batches did (16 -> 4: 1.87 -> 1.80 ms at 65536 tokens, g = 4).
 __global__ void __launch_bounds__(256)
 k_fwd_merge(Problem P, const bf16_t* __restrict__ opart, const float* __restrict__ lse_part,
             const uint32_t* __restrict__ vmask, const int32_t* __restrict__ slotpos,

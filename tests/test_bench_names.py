@@ -19,3 +19,5 @@ def test_kernel_names_of_the_bench_exist_and_are_found_in_the_summaries():
         traffic, _ = bench.measured_traffic(workload)
         for kind in ("fwd_main", "bwd_main", "bwd_delta", "bwd_dq_reduce"):
             assert any(n in traffic for n in bench.KERNEL_NAMES[kind]), (path, kind)
+        # every kernel a summary gives bytes for is one of the sources'
+        assert {n.replace("nsa::", "") for n in traffic} <= kernels, (path, traffic)
