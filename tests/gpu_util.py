@@ -5,7 +5,7 @@ import torch
 import paper_2508_18224_amd as nsa
 import workloads as wl
 
-# spec tolerances, read as |gpu - ref| <= atol + rtol * |ref| per element, plus a Frobenius-norm bound
+# parity tolerances, read as |gpu - ref| <= atol + rtol * |ref| per element, plus a Frobenius-norm bound
 TOL_O = (2e-2, 1e-2)
 TOL_GRAD = (4e-2, 2e-2)
 TOL_LSE = 1e-3

@@ -1,6 +1,6 @@
 """The library's HOST code (argument validation, workspace layout arithmetic, error paths) under AddressSanitizer and
 UndefinedBehaviorSanitizer: a sanitizer build of the library (device code unchanged, host pass instrumented) driven by a
-small C program over ~10^4 shapes, no GPU involved.  GPU-side sanitizers are not available on this machine."""
+small C program over ~10^4 shapes, no GPU involved.  Device code is not instrumented."""
 import os
 import shutil
 import subprocess
