@@ -122,3 +122,36 @@ def test_selection_gated_and_window_steps_replay_from_a_hip_graph():
         torch.cuda.synchronize()
         for k, (got, ref) in enumerate(zip(outs, refs[rep])):
             assert torch.equal(_bits(got), _bits(ref)), f"output {k} of replay with variant {rep} differs from eager"
+
+
+@pytest.mark.parametrize("kind", ["many sequences", "capped tiny"])
+def test_other_launch_sequences_replay_from_a_hip_graph(kind):
+    """The inversion by token with its launch for the dense pairs, and the backward that goes through a head's KV blocks in
+    ranges: the host picks both from the shape and the workspace size alone, so they replay like the plain step."""
+    import paper_2508_18224_amd as nsa
+    print("case graph", kind, flush=True)
+    base = wl.Workload("graph", [37] * 40 if kind == "many sequences" else [1000], hq=8, hkv=2, topk=6, sink=True, seed=61)
+    variants = [wl.realise(dataclasses.replace(base, seed=base.seed + 100 * i)) for i in range(2)]
+    refs = [_eager(w) for w in variants]
+    case = Case(variants[0])
+    if kind == "capped tiny":
+        cap = nsa.workspace_bytes_min(case.attn.shape)[1]
+        case.attn = nsa.SelAttention(base.seqlens[0], base.hq, base.hkv, base.topk, ws_cap_bytes=cap, dense=True)
+        assert case.attn.bwd_ws.numel() == cap
+    case.backward(*case.forward())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        o, lse = case.attn.forward(case.q, case.k, case.v, case.idx, case.cu)
+        outs = (o, lse, *case.attn.backward(case.q, case.k, case.v, o, lse, case.do, case.cu))
+    for rep in (1, 0, 1):
+        w = variants[rep]
+        for dst, bits in ((case.q, w.q), (case.k, w.k), (case.v, w.v), (case.do, w.do)):
+            dst.copy_(dev_bf16(bits))
+        case.idx.copy_(torch.from_numpy(w.idx).cuda())
+        for buf in (case.attn.index_ws, case.attn.fwd_ws, case.attn.bwd_ws):
+            buf.fill_(0x5A)
+        _ = (case.q.float() @ case.q.float().transpose(1, 2)).sum().item()
+        graph.replay()
+        torch.cuda.synchronize()
+        for nm, got, ref in zip(("O", "LSE", "dQ", "dK", "dV"), outs, refs[rep]):
+            assert torch.equal(_bits(got), _bits(ref)), f"{nm} of replay with variant {rep} differs from eager"
