@@ -874,45 +874,57 @@ k_bwd_pipe128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
     pipe_role<kWin, kWide, false>(P, U, smem, wave - 4, Q, K, V, dO, stats, qent, dqpart, dkv_part, dK, dV);
 }
 
-__global__ void __launch_bounds__(256)
-k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const uint32_t* __restrict__ vmask,
-                const int32_t* __restrict__ slotpos, const int32_t* __restrict__ off, bf16_t* __restrict__ dQ) {
-  // rows of the pass: (token, head of the KV heads [j0, j0 + nj))
-  const int hp = P.nj * P.g;
-  const int64_t prow = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+// dQ of every (token, head) row from its columns' partial rows: plain sums, in column order.  Rows and workgroups: see "the two
+// reduction kernels" in common.h.  (k_fwd_merge is the same with weights.)
+template <int kRows, int kThreads>
+__global__ void __launch_bounds__(kThreads)
+k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const int32_t* __restrict__ slotpos,
+                const int32_t* __restrict__ off, bf16_t* __restrict__ dQ) {
+  constexpr int kBatch = 8;  // independent 256-byte gathers in flight per row
   const int sub = threadIdx.x & 15;
-  if (prow >= (int64_t)P.T * hp) return;
-  const int t = (int)(prow / hp);
-  const int h = P.j0 * P.g + (int)(prow - (int64_t)t * hp);
-  const int64_t row = (int64_t)t * P.hq + h;
-  const int j = h / P.g, hh = h - j * P.g;
   const int pos0 = off[P.j0 * P.b_cap];
-  const uint32_t vm = vmask[(size_t)t * P.hkv + j];
-  const int32_t* sp = slotpos + ((size_t)t * P.hkv + j) * P.topk;
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int m0 = 0; m0 < P.topk; m0 += kSlotBatch) {  // kSlotBatch independent 256-byte gathers in flight per row
-    uint4 x[kSlotBatch];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  u32x4* const out = reinterpret_cast<u32x4*>(smem) + threadIdx.x;
+  ReduceRow R = reduce_row<kRows, kThreads>(P, 0);
+  SlotRow slots = load_slots(slotpos, P, R);
+#pragma unroll 1
+  for (int q = 0; q < kRows; ++q) {
+    const ReduceRow R_next = reduce_row<kRows, kThreads>(P, min(q + 1, kRows - 1));
+    const SlotRow slots_next = load_slots(slotpos, P, R_next);
+    const bf16_t* base = dqpart + R.hh * kD + 8 * sub;
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int pos = pos0;  // of the last kept column: dropped ones gather it again
+    for (int m0 = 0; m0 < P.topk; m0 += kBatch) {
+      int at[kBatch];
+      u32x4 x[kBatch];
 #pragma unroll
-    for (int i = 0; i < kSlotBatch; ++i) {
-      const int m = m0 + i;
-      const bool on = m < P.topk && ((vm >> m) & 1u);
-      x[i] = on ? *reinterpret_cast<const uint4*>(dqpart + ((size_t)(sp[on ? m : 0] - pos0) * P.g + hh) * kD + 8 * sub)
-                : make_uint4(0, 0, 0, 0);
-    }
+      for (int i = 0; i < kBatch; ++i) at[i] = slot_of(slots, m0 + i);
 #pragma unroll
-    for (int i = 0; i < kSlotBatch; ++i) {
-      acc[0] += bf16_lo(x[i].x); acc[1] += bf16_hi(x[i].x);
-      acc[2] += bf16_lo(x[i].y); acc[3] += bf16_hi(x[i].y);
-      acc[4] += bf16_lo(x[i].z); acc[5] += bf16_hi(x[i].z);
-      acc[6] += bf16_lo(x[i].w); acc[7] += bf16_hi(x[i].w);
+      for (int i = 0; i < kBatch; ++i) {
+        pos = at[i] >= 0 ? at[i] : pos;
+        asm volatile("" : "+v"(at[i]), "+v"(pos));  // keeps the loads free of branches
+        x[i] = load_streaming(base + (size_t)(pos - pos0) * P.g * kD);
+      }
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        if (at[i] < 0) x[i] = u32x4{0, 0, 0, 0};
+        acc[0] += bf16_lo(x[i].x); acc[1] += bf16_hi(x[i].x);
+        acc[2] += bf16_lo(x[i].y); acc[3] += bf16_hi(x[i].y);
+        acc[4] += bf16_lo(x[i].z); acc[5] += bf16_hi(x[i].z);
+        acc[6] += bf16_lo(x[i].w); acc[7] += bf16_hi(x[i].w);
+      }
     }
+    out[q * kThreads] = u32x4{pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]), pack_bf16x2(acc[4], acc[5]),
+                              pack_bf16x2(acc[6], acc[7])};
+    R = R_next;
+    slots = slots_next;
   }
-  uint4 o;
-  o.x = pack_bf16x2(acc[0], acc[1]);
-  o.y = pack_bf16x2(acc[2], acc[3]);
-  o.z = pack_bf16x2(acc[4], acc[5]);
-  o.w = pack_bf16x2(acc[6], acc[7]);
-  *reinterpret_cast<uint4*>(dQ + row * kD + 8 * sub) = o;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kRows; ++q) {
+    const ReduceRow R = reduce_row<kRows, kThreads>(P, q);
+    if (R.on) store_streaming(dQ + ((int64_t)R.t * P.hq + R.j * P.g + R.hh) * kD + 8 * sub, out[q * kThreads]);
+  }
 }
 
 // grid (ceil(lists / per), 2, B_K / 8): y = 0 -> dK, 1 -> dV; z = group of 8 keys, so that the units of a long list (the sink
@@ -991,7 +1003,11 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
   const int main_lds = b128 ? PipeLds::Bytes : BwdLds::Bytes;
   {
     static std::atomic<uint64_t> ready[8];
+    static std::atomic<uint64_t> ready_reduce;
     hipError_t e = allow_dynamic_lds((const void*)main_kernel, main_lds, ready[win + 2 * wide + 4 * b128]);
+    if (e == hipSuccess)
+      e = allow_dynamic_lds((const void*)(k_bwd_dq_reduce<kBurstRows, kBurstThreads>), reduce_lds(kBurstThreads, kBurstRows, 1, false),
+                            ready_reduce);
     if (e != hipSuccess) return e;
   }
   {
@@ -1019,10 +1035,16 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
                          (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, (const float2*)delta, p.u_rec, p.u_nu,
                          p.off, p.qent, (bf16_t*)dqpart, dkv_part, (bf16_t*)dK, (bf16_t*)dV); }
       if (P.l1 == end) {
-        const int64_t rows = (int64_t)P.T * P.nj * P.g;
         ProfScope ps(KID_BWD_DQ_REDUCE, st);
-        hipLaunchKernelGGL(k_bwd_dq_reduce, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, P,
-                           (const bf16_t*)dqpart, p.vmask, p.slotpos, p.off, (bf16_t*)dQ);
+        auto launch = [&](auto rows, auto threads) {
+          constexpr int kRows = decltype(rows)::value, kThreads = decltype(threads)::value;
+          hipLaunchKernelGGL((k_bwd_dq_reduce<kRows, kThreads>), dim3(reduce_groups<kRows, kThreads>(P)), dim3(kThreads),
+                             reduce_lds(kThreads, kRows, 1, false), st, P, (const bf16_t*)dqpart, p.slotpos, p.off, (bf16_t*)dQ);
+        };
+        if (reduce_in_bursts(P))
+          launch(std::integral_constant<int, kBurstRows>{}, std::integral_constant<int, kBurstThreads>{});
+        else
+          launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 256>{});
       }
       ProfScope ps(KID_BWD_DKV_REDUCE, st);
       const int lists = P.l1 - P.l0, per = max(1, min(64, lists * (P.bk / 4) / 4096));

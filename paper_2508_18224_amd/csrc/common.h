@@ -16,7 +16,6 @@ constexpr int kD = 128;            // head dimension
 constexpr int kMaxUnit = 2048;     // most list entries of one work unit (the size used for long inputs)
 constexpr int kMinUnit = 256;       // the smallest a caller may ask for (the library itself goes lower for tiny inputs)
 constexpr int kMaxTopk = 32;
-constexpr int kSlotBatch = 4;      // slots of a row the two reduction kernels gather at a time
 constexpr int kTileTokens = 64;    // query tokens of a tile of the dense forward path (whatever B_K is)
 constexpr int kDenseMax = 32;      // most 64-key pieces one (query tile, kv head) routes through the dense path
 constexpr int kDenseHash = 1024;   // per-wavefront counters of the detection pass (block id modulo this)
@@ -237,11 +236,12 @@ __device__ __forceinline__ int div_g(int r, int g, uint32_t g_magic) {
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __builtin_bit_cast(float, u << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __builtin_bit_cast(float, u & 0xffff0000u); }
 
-// 16-byte store with the non-temporal hint: partial rows are written once and read once much later, so they
-// should not displace the gathered Q / dO rows from the caches.
-__device__ __forceinline__ void store_streaming(bf16_t* dst, uint4 v) {
-  u32x4 x = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(dst));
+// 16-byte accesses with the non-temporal hint.
+__device__ __forceinline__ u32x4 load_streaming(const bf16_t* src) {
+  return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src));
+}
+__device__ __forceinline__ void store_streaming(bf16_t* dst, u32x4 v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
 }
 
 // ---- rows of 256 bytes through buffer instructions ------------------------------------------------------
@@ -344,6 +344,63 @@ struct RowTensor {
   }
 };
 inline bool rows_are_wide(int64_t rows) { return rows * (kD * 2) >= ((int64_t)1 << 32) - 65536; }
+
+// ---- the two reduction kernels ---------------------------------------------------------------------------
+// k_fwd_merge and k_bwd_dq_reduce read sixteen rows for every row they write, and what bounds them is the memory side: a kernel that
+// only gathers these rows reads 7.0 TB/s with non-temporal loads (6.2 with plain ones), and the sixteenth of writes takes it
+// down to 5.4 when they are strewn among the reads, to 5.7 as non-temporal stores, and to 6.4 when a workgroup keeps 128 KB of results
+// and writes them at once.  So a workgroup parks its rows in LDS and writes them after its last gather: dQ reduction at
+// 65536 tokens, g = 4: 1.72 -> 1.50 ms, at 8192, g = 1: 222 -> 182 us; merge there 233 -> 207 us.  Inputs with fewer than 2^18
+// rows would leave compute units without such a workgroup and take 16 rows a workgroup instead, written as they are done (4877 tokens,
+// 8 heads, top-k 8: 24 -> 19 us for either kernel, from the columns being gathered side by side).
+// Rows of a pass are (token, head of its KV heads), token-major.  A workgroup of kThreads threads takes kRows * kThreads / 16
+// consecutive ones, 16 lanes a row, and every XCD (they get workgroups in turn) works through one contiguous eighth of them, so
+// that its L2 keeps the lines of log-sum-exps that neighbouring tokens share.
+struct ReduceRow {
+  int t, j, hh;   // token, KV head, head of the group; rows past the last one repeat it
+  bool on;
+};
+template <int kRows, int kThreads>
+__device__ __forceinline__ ReduceRow reduce_row(const Problem& P, int q) {
+  const uint32_t hp = (uint32_t)(P.nj * P.g), rows = (uint32_t)P.T * hp;  // total_tokens * hq < 2^31 is checked on the host
+  const uint32_t blk = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const uint32_t r = (blk * kRows + q) * (kThreads / 16) + (threadIdx.x >> 4), rc = min(r, rows - 1);
+  ReduceRow x;
+  x.t = (int)(rc / hp);
+  const int h = (int)(rc - (uint32_t)x.t * hp);
+  x.j = h / P.g;
+  x.hh = h - x.j * P.g;
+  x.j += P.j0;
+  x.on = r < rows;
+  return x;
+}
+// Positions of the row's columns in the partial rows (-1: not kept, or past the last column): lane sub of the 16 holds columns
+// sub and 16 + sub.
+struct SlotRow {
+  int lo, hi;
+};
+__device__ __forceinline__ SlotRow load_slots(const int32_t* __restrict__ slotpos, const Problem& P, const ReduceRow& R) {
+  const int32_t* sp = slotpos + ((size_t)R.t * P.hkv + R.j) * P.topk;
+  const int sub = threadIdx.x & 15;
+  SlotRow s;
+  s.lo = sp[min(sub, P.topk - 1)];
+  s.hi = P.topk > 16 ? sp[min(16 + sub, P.topk - 1)] : -1;
+  if (sub >= P.topk) s.lo = -1;
+  if (16 + sub >= P.topk) s.hi = -1;
+  return s;
+}
+__device__ __forceinline__ int slot_of(const SlotRow& s, int m) {  // m is wave-uniform
+  return (int)lane_value((uint32_t)(m < 16 ? s.lo : s.hi), (int)(threadIdx.x & 48) + (m & 15));
+}
+constexpr int kBurstThreads = 1024, kBurstRows = 8, kBurstRowsGated = 4;  // gated: two tensors share the LDS
+inline bool reduce_in_bursts(const Problem& P) { return (int64_t)P.T * P.nj * P.g >= (1 << 18); }
+// LDS of a workgroup: 16 bytes a thread and row for every tensor written, and a float a row for LSE.
+constexpr int reduce_lds(int threads, int rows, int tensors, bool lse) { return rows * threads * (16 * tensors) + (lse ? rows * threads / 4 : 0); }
+template <int kRows, int kThreads>
+inline unsigned reduce_groups(const Problem& P) {
+  const int64_t rows = (int64_t)P.T * P.nj * P.g, per = kRows * kThreads / 16;
+  return (unsigned)(((rows + per - 1) / per + 7) / 8 * 8);
+}
 
 // Sequence bounds of token t in a packed batch (cu may be null for a single sequence).
 __device__ __forceinline__ void seq_bounds(const int32_t* cu, int nseq, int T, int t, int& s, int& c0, int& c1) {

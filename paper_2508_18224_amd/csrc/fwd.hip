@@ -20,6 +20,7 @@
 // k_fwd_merge: per (token, head) combines the kept slots: LSE = ln sum_s exp(lse_s), O = sum_s exp(lse_s-LSE) O_s.
 //   This replaces the paper's separate statistics pre-pass: per-slot log-sum-exps make the merge exact.
 #include "common.h"
+#include <type_traits>
 
 namespace nsa {
 
@@ -523,9 +524,12 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 //            phase 1, by their log-sum-exps; O, LSE and the optional gated sum of Eq. (2) are written once.  The
 //            rows' kept-column masks and slot positions are fetched at the very start of the kernel and parked in
 //            LDS, so that phase 2 starts with its addresses known and the only memory latency left in it is that of the
-//            gathers themselves.
+//            gathers themselves.  A row's columns are taken from its bit mask, so that dense ones cost no place in a batch; the
+//            finished rows wait in LDS until the workgroup writes them all (see "the two reduction kernels" in common.h).  With
+//            the columns in place, plain loads and every row written as it was done: 1.79 instead of 1.69 ms at 65536 tokens, g = 4,
+//            1.78 instead of 1.65 with 9 of 16 columns dense at g = 7, 1.02 instead of 0.93 gated at 32768 tokens.
 // Tiles without a dense piece skip phase 1, so with the dense route on this kernel is the merge of every row.
-// Phase 2 is bound by memory (65536 tokens, g = 4: 9.15 GB in 1.79 ms for the whole kernel), phase 1 by the order S product,
+// Phase 2 is bound by memory (65536 tokens, g = 4: 9.15 GB in 1.69 ms for the whole kernel), phase 1 by the order S product,
 // softmax, PV product inside each of the two wavefronts of a SIMD.  Staging through registers with the piece table read inside the
 // loop took 1.87 ms there, 1.10 instead of 1.05 ms for a window of 512 at 65536 tokens and 1.88 instead of 1.81 ms with 9 of 16
 // columns dense at g = 7.  A second K tile (requests one piece earlier) gave nothing; three workgroups per CU leave 168
@@ -542,8 +546,8 @@ constexpr int kDnMeta = kDnLse + 4 * 32 * 4;
 static_assert(4 * 32 * kDnRow <= kDnLse, "phase 1's result must fit the K / V area");
 // words of phase 2's index data of one wavefront: (kept, dense, positions) of every token its 32 rows can touch
 inline __host__ __device__ int dense_meta_words(int g, int topk) { return (31 / g + 2) * (topk + 2); }
-inline int dense_lds_bytes(int g, int topk) { return kDnMeta + 4 * 4 * dense_meta_words(g, topk); }
-constexpr int kMergeBatch = 8;                                 // columns of a row gathered at a time in phase 2
+inline int dense_lds_bytes(int g, int topk, bool gated) { return kDnMeta + 16 * dense_meta_words(g, topk) + (gated ? 4 * 32 * kDnRow : 0); }
+constexpr int kMergeBatch = 7;                                 // columns of a row gathered at a time in phase 2
 
 __global__ void __launch_bounds__(256, 2)
 k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
@@ -746,231 +750,257 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
       __syncthreads();  // V of this piece has been read (after the last piece: the K / V area is free), the next K is staged
       if (step + 1 < nd) stage(V, kDnV, step + 1);
     }
-    if (!wave_on) return;
-    // the rows' dense result, normalised, and its log-sum-exp (natural log; -inf for a row that keeps none of the
-    // tile's dense blocks) -> this wavefront's quarter of the K / V area, where phase 2 picks them up in its own
-    // lane layout
-    const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
+    if (wave_on) {
+      // the rows' dense result, normalised, and its log-sum-exp (natural log; -inf for a row that keeps none of the
+      // tile's dense blocks) -> this wavefront's quarter of the K / V area, where phase 2 picks them up in its own
+      // lane layout
+      const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+      for (int db = 0; db < 4; ++db)
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        uint2 w;
-        w.x = pack_bf16x2(oacc[db][4 * a + 0] * inv, oacc[db][4 * a + 1] * inv);
-        w.y = pack_bf16x2(oacc[db][4 * a + 2] * inv, oacc[db][4 * a + 3] * inv);
-        *reinterpret_cast<uint2*>(od_lds + col * kDnRow + (((4 * db + a) ^ (col & 15)) << 4) + 8 * qh) = w;
+        for (int a = 0; a < 4; ++a) {
+          uint2 w;
+          w.x = pack_bf16x2(oacc[db][4 * a + 0] * inv, oacc[db][4 * a + 1] * inv);
+          w.y = pack_bf16x2(oacc[db][4 * a + 2] * inv, oacc[db][4 * a + 3] * inv);
+          *reinterpret_cast<uint2*>(od_lds + col * kDnRow + (((4 * db + a) ^ (col & 15)) << 4) + 8 * qh) = w;
+        }
+      if (qh == 0) {
+        const float mcf = (m_run == -INFINITY) ? 0.f : m_run * c2;
+        lse_lds[col] = l_run > 0.f ? (mcf + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f : -INFINITY;
       }
-    if (qh == 0) {
-      const float mcf = (m_run == -INFINITY) ? 0.f : m_run * c2;
-      lse_lds[col] = l_run > 0.f ? (mcf + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f : -INFINITY;
+      wave_sync();
     }
-    wave_sync();
   }
-  if (!wave_on) return;
-
   // ------------------------------------------------------------------------------------------------ phase 2
-  if (nd == 0) park_meta();
   // lane-derived indices of this phase, recomputed here so that they do not occupy registers during phase 1
   int lane_b = threadIdx.x & 63;
   asm volatile("" : "+v"(lane_b));
   const int sub = lane_b & 15, crow_b = lane_b >> 4;
-  const int pos0 = off[P.j0 * P.b_cap];  // first list position of the pass: partial rows are relative to it
-  for (int pass = 0; pass < 4; ++pass) {
-    // two rows per lane group: wave rows 4 pass + crow and 16 more
-    bool ok[2];
-    int hh[2];
-    int64_t grow[2];
-    uint32_t vm_all[2], vm[2];
-    const int32_t* sp[2];  // the row's slot positions (LDS)
-    float acc[2][8], M[2], Ls[2];
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      const int wrow = 4 * pass + crow_b + 16 * x;
-      const int rr = row0 + wrow;
-      ok[x] = rr < rows_total;
-      const int rc = min(rr, rows_total - 1);
-      const int e = div_g(rc, P.g, P.g_magic);
-      hh[x] = rc - e * P.g;
-      grow[x] = (int64_t)(ttok0 + e) * P.hq + hbase + hh[x];
-      const int32_t* mrow = meta + (e - e_lo) * mstride;
-      vm_all[x] = ok[x] ? (uint32_t)mrow[0] : 0u;
-      const uint32_t dm = ok[x] ? (uint32_t)mrow[1] : 0u;
-      vm[x] = vm_all[x] & ~dm;
-      sp[x] = mrow + 2;
-      M[x] = -INFINITY;
-      Ls[x] = 0.f;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) acc[x][c] = 0.f;
-      if (dm != 0u && nd > 0) {  // the row of phase 1 starts the sum
-        const float ls = lse_lds[wrow];
-        if (ls > -INFINITY) {
-          const uint4 v = *reinterpret_cast<const uint4*>(od_lds + wrow * kDnRow + ((sub ^ (wrow & 15)) << 4));
-          M[x] = ls;
-          Ls[x] = 1.f;
-          acc[x][0] = bf16_lo(v.x); acc[x][1] = bf16_hi(v.x); acc[x][2] = bf16_lo(v.y); acc[x][3] = bf16_hi(v.y);
-          acc[x][4] = bf16_lo(v.z); acc[x][5] = bf16_hi(v.z); acc[x][6] = bf16_lo(v.w); acc[x][7] = bf16_hi(v.w);
-        }
-      }
-    }
-    for (int m0 = 0; m0 < P.topk; m0 += kMergeBatch) {
-      if (((vm[0] | vm[1]) >> m0) == 0u) break;  // no kept column left in either row
-      uint4 xv[2][kMergeBatch];
-      float ls[2][kMergeBatch];
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int i = 0; i < kMergeBatch; ++i) {
-          const int m = m0 + i;
-          const bool on = m < P.topk && ((vm[x] >> m) & 1u);
-          const size_t pr = on ? (size_t)(sp[x][m] - pos0) * P.g + hh[x] : (size_t)0;
-          xv[x][i] = on ? *reinterpret_cast<const uint4*>(opart + pr * kD + 8 * sub) : make_uint4(0, 0, 0, 0);
-          ls[x][i] = on ? lse_part[pr] : -INFINITY;
-        }
+  unsigned char* gated_lds = smem + kDnMeta + 16 * dense_meta_words(P.g, P.topk) + wave * 32 * kDnRow;
+  if (wave_on) {
+    if (nd == 0) park_meta();
+    const int pos0 = off[P.j0 * P.b_cap];  // first list position of the pass: partial rows are relative to it
+    for (int pass = 0; pass < 4; ++pass) {
+      // two rows per lane group: wave rows 4 pass + crow and 16 more
+      int hh[2];
+      uint32_t vm_all[2], vm[2];
+      const int32_t* sp[2];  // the row's slot positions (LDS)
+      float acc[2][8], M[2], Ls[2];
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
-        float Mb = M[x];
+        const int wrow = 4 * pass + crow_b + 16 * x;
+        const int rr = row0 + wrow;
+        const bool ok = rr < rows_total;
+        const int rc = min(rr, rows_total - 1);
+        const int e = div_g(rc, P.g, P.g_magic);
+        hh[x] = rc - e * P.g;
+        const int32_t* mrow = meta + (e - e_lo) * mstride;
+        vm_all[x] = ok ? (uint32_t)mrow[0] : 0u;
+        const uint32_t dm = ok ? (uint32_t)mrow[1] : 0u;
+        vm[x] = vm_all[x] & ~dm;
+        sp[x] = mrow + 2;
+        M[x] = -INFINITY;
+        Ls[x] = 0.f;
 #pragma unroll
-        for (int i = 0; i < kMergeBatch; ++i) Mb = fmaxf(Mb, ls[x][i]);
-        if (Mb == -INFINITY) continue;  // no kept column in this batch or before it
-        const float rescale = __expf(M[x] - Mb);  // 0 on the first non-empty batch
-        Ls[x] *= rescale;
+        for (int c = 0; c < 8; ++c) acc[x][c] = 0.f;
+        if (dm != 0u && nd > 0) {  // the row of phase 1 starts the sum
+          const float ls = lse_lds[wrow];
+          if (ls > -INFINITY) {
+            const uint4 v = *reinterpret_cast<const uint4*>(od_lds + wrow * kDnRow + ((sub ^ (wrow & 15)) << 4));
+            M[x] = ls;
+            Ls[x] = 1.f;
+            acc[x][0] = bf16_lo(v.x); acc[x][1] = bf16_hi(v.x); acc[x][2] = bf16_lo(v.y); acc[x][3] = bf16_hi(v.y);
+            acc[x][4] = bf16_lo(v.z); acc[x][5] = bf16_hi(v.z); acc[x][6] = bf16_lo(v.w); acc[x][7] = bf16_hi(v.w);
+          }
+        }
+      }
+      while (__builtin_amdgcn_ballot_w64((vm[0] | vm[1]) != 0u) != 0ull) {  // the next columns of some row
+        u32x4 xv[2][kMergeBatch];
+        float ls[2][kMergeBatch];
+        int at[2][kMergeBatch];  // position, -1 past the row's last column
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[x][c] *= rescale;
-        M[x] = Mb;
+        for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int i = 0; i < kMergeBatch; ++i) {
-          const float w = __expf(ls[x][i] - Mb);  // exp(-inf) = 0 for columns that are off
-          Ls[x] += w;
-          acc[x][0] += w * bf16_lo(xv[x][i].x); acc[x][1] += w * bf16_hi(xv[x][i].x);
-          acc[x][2] += w * bf16_lo(xv[x][i].y); acc[x][3] += w * bf16_hi(xv[x][i].y);
-          acc[x][4] += w * bf16_lo(xv[x][i].z); acc[x][5] += w * bf16_hi(xv[x][i].z);
-          acc[x][6] += w * bf16_lo(xv[x][i].w); acc[x][7] += w * bf16_hi(xv[x][i].w);
+          for (int i = 0; i < kMergeBatch; ++i) {
+            at[x][i] = vm[x] != 0u ? sp[x][__builtin_ctz(vm[x] | 0x80000000u)] : -1;
+            vm[x] &= vm[x] - 1u;
+          }
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int i = 0; i < kMergeBatch; ++i) {
+            xv[x][i] = u32x4{0, 0, 0, 0};
+            ls[x][i] = -INFINITY;
+            if (at[x][i] >= 0) {
+              const size_t pr = (size_t)(at[x][i] - pos0) * P.g + hh[x];
+              xv[x][i] = load_streaming(opart + pr * kD + 8 * sub);
+              ls[x][i] = lse_part[pr];
+            }
+          }
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          float Mb = M[x];
+#pragma unroll
+          for (int i = 0; i < kMergeBatch; ++i) Mb = fmaxf(Mb, ls[x][i]);
+          if (Mb == -INFINITY) continue;  // no kept column in this batch or before it
+          const float rescale = __expf(M[x] - Mb);  // 0 on the first non-empty batch
+          Ls[x] *= rescale;
+#pragma unroll
+          for (int c = 0; c < 8; ++c) acc[x][c] *= rescale;
+          M[x] = Mb;
+#pragma unroll
+          for (int i = 0; i < kMergeBatch; ++i) {
+            const float w = __expf(ls[x][i] - Mb);  // exp(-inf) = 0 for columns that are off
+            Ls[x] += w;
+            acc[x][0] += w * bf16_lo(xv[x][i].x); acc[x][1] += w * bf16_hi(xv[x][i].x);
+            acc[x][2] += w * bf16_lo(xv[x][i].y); acc[x][3] += w * bf16_hi(xv[x][i].y);
+            acc[x][4] += w * bf16_lo(xv[x][i].z); acc[x][5] += w * bf16_hi(xv[x][i].z);
+            acc[x][6] += w * bf16_lo(xv[x][i].w); acc[x][7] += w * bf16_hi(xv[x][i].w);
+          }
+        }
+      }
+      // the finished rows wait in LDS, in the place of phase 1's, until the workgroup writes all of them
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const int wrow = 4 * pass + crow_b + 16 * x;
+        const bool empty = vm_all[x] == 0u;  // nothing visible: O = 0, LSE = -inf, and the gated sum is what the other branches gave
+        const float inv = empty ? 0.f : 1.f / Ls[x];
+        const int place = wrow * kDnRow + ((sub ^ (wrow & 15)) << 4);
+        *reinterpret_cast<u32x4*>(od_lds + place) =
+            u32x4{pack_bf16x2(acc[x][0] * inv, acc[x][1] * inv), pack_bf16x2(acc[x][2] * inv, acc[x][3] * inv),
+                  pack_bf16x2(acc[x][4] * inv, acc[x][5] * inv), pack_bf16x2(acc[x][6] * inv, acc[x][7] * inv)};
+        if (sub == 0) lse_lds[wrow] = empty ? -INFINITY : M[x] + __logf(Ls[x]);
+        if (gate != nullptr) {
+          // Eq. (2): O_out = O_acc + gate * O, from the fp32 result (Oout may be the buffer Oacc points to: every lane
+          // reads its own 16 bytes before it writes them)
+          const int e = div_g(min(row0 + wrow, rows_total - 1), P.g, P.g_magic);
+          const int64_t grow = (int64_t)(ttok0 + e) * P.hq + hbase + hh[x];
+          const float tau = gate[grow] * inv;
+          u32x4 a = {0, 0, 0, 0};
+          if (Oacc != nullptr) a = *reinterpret_cast<const u32x4*>(Oacc + grow * kD + 8 * sub);
+          if (!empty) {
+            a.x = pack_bf16x2(bf16_lo(a.x) + tau * acc[x][0], bf16_hi(a.x) + tau * acc[x][1]);
+            a.y = pack_bf16x2(bf16_lo(a.y) + tau * acc[x][2], bf16_hi(a.y) + tau * acc[x][3]);
+            a.z = pack_bf16x2(bf16_lo(a.z) + tau * acc[x][4], bf16_hi(a.z) + tau * acc[x][5]);
+            a.w = pack_bf16x2(bf16_lo(a.w) + tau * acc[x][6], bf16_hi(a.w) + tau * acc[x][7]);
+          }
+          *reinterpret_cast<u32x4*>(gated_lds + place) = a;
         }
       }
     }
+  }
+  __syncthreads();
+  if (!wave_on) return;
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      if (!ok[x]) continue;
-      bf16_t* orow = O + grow[x] * kD + 8 * sub;
-      if (vm_all[x] == 0u) {  // nothing visible: O = 0, LSE = -inf, and the gated sum is what the other branches gave
-        *reinterpret_cast<uint4*>(orow) = make_uint4(0, 0, 0, 0);
-        if (sub == 0) LSE[grow[x]] = -INFINITY;
-        if (gate != nullptr)
-          *reinterpret_cast<uint4*>(Oout + grow[x] * kD + 8 * sub) =
-              Oacc != nullptr ? *reinterpret_cast<const uint4*>(Oacc + grow[x] * kD + 8 * sub) : make_uint4(0, 0, 0, 0);
-        continue;
-      }
-      const float inv = 1.f / Ls[x];
-      uint4 o;
-      o.x = pack_bf16x2(acc[x][0] * inv, acc[x][1] * inv);
-      o.y = pack_bf16x2(acc[x][2] * inv, acc[x][3] * inv);
-      o.z = pack_bf16x2(acc[x][4] * inv, acc[x][5] * inv);
-      o.w = pack_bf16x2(acc[x][6] * inv, acc[x][7] * inv);
-      *reinterpret_cast<uint4*>(orow) = o;
-      if (sub == 0) LSE[grow[x]] = M[x] + __logf(Ls[x]);
-      if (gate != nullptr) {
-        // Eq. (2): O_out = O_acc + gate * O, from the fp32 result (Oout may be the buffer Oacc points to: every lane
-        // reads its own 16 bytes before it writes them)
-        const float tau = gate[grow[x]] * inv;
-        uint4 a = make_uint4(0, 0, 0, 0);
-        if (Oacc != nullptr) a = *reinterpret_cast<const uint4*>(Oacc + grow[x] * kD + 8 * sub);
-        o.x = pack_bf16x2(bf16_lo(a.x) + tau * acc[x][0], bf16_hi(a.x) + tau * acc[x][1]);
-        o.y = pack_bf16x2(bf16_lo(a.y) + tau * acc[x][2], bf16_hi(a.y) + tau * acc[x][3]);
-        o.z = pack_bf16x2(bf16_lo(a.z) + tau * acc[x][4], bf16_hi(a.z) + tau * acc[x][5]);
-        o.w = pack_bf16x2(bf16_lo(a.w) + tau * acc[x][6], bf16_hi(a.w) + tau * acc[x][7]);
-        *reinterpret_cast<uint4*>(Oout + grow[x] * kD + 8 * sub) = o;
-      }
-    }
+  for (int q = 0; q < 8; ++q) {
+    const int wrow = 4 * q + crow_b;
+    if (row0 + wrow >= rows_total) break;
+    const int e = div_g(row0 + wrow, P.g, P.g_magic);
+    const int64_t grow = (int64_t)(ttok0 + e) * P.hq + hbase + (row0 + wrow - e * P.g);
+    const int place = wrow * kDnRow + ((sub ^ (wrow & 15)) << 4);
+    store_streaming(O + grow * kD + 8 * sub, *reinterpret_cast<const u32x4*>(od_lds + place));
+    if (sub == 0) LSE[grow] = lse_lds[wrow];
+    if (gate != nullptr) store_streaming(Oout + grow * kD + 8 * sub, *reinterpret_cast<const u32x4*>(gated_lds + place));
   }
 }
 
-// 16 lanes per (token, head) row, 8 output channels per lane.  Slots are taken kSlotBatch at a time: positions,
-// partial log-sum-exps and partial rows of a batch are all requested before any of them is used; batches are chained
-// by the usual running-max rescale.  Small batches keep the register count low, and the many resident waves that
-// result hide the gather latency better than long batches did (16 -> 4: 1.87 -> 1.80 ms at 65536 tokens, g = 4).
-__global__ void __launch_bounds__(256)
+// The reduction alone (dense route off); rows and workgroups: see "the two reduction kernels" in common.h.  16 lanes per (token,
+// head) row, 8 output channels per lane; columns are taken kBatch at a time, all their log-sum-exps and rows requested, without
+// branches, before any is used, the positions of the next row before this one's; batches are chained by the usual running-max
+// rescale.
+template <int kRows, int kThreads, bool kGate>
+__global__ void __launch_bounds__(kThreads)
 k_fwd_merge(Problem P, const bf16_t* __restrict__ opart, const float* __restrict__ lse_part,
-            const uint32_t* __restrict__ vmask, const int32_t* __restrict__ slotpos,
-            const int32_t* __restrict__ off, bf16_t* __restrict__ O,
+            const int32_t* __restrict__ slotpos, const int32_t* __restrict__ off, bf16_t* __restrict__ O,
             float* __restrict__ LSE, const float* __restrict__ gate, const bf16_t* Oacc, bf16_t* Oout) {
-  // rows of the pass: (token, head of the KV heads [j0, j0 + nj))
-  const int hp = P.nj * P.g;
-  const int64_t prow = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+  constexpr int kBatch = 8;  // columns of a row gathered at a time
   const int sub = threadIdx.x & 15;
-  if (prow >= (int64_t)P.T * hp) return;
-  const int t = (int)(prow / hp);
-  const int h = P.j0 * P.g + (int)(prow - (int64_t)t * hp);
-  const int64_t row = (int64_t)t * P.hq + h;
-  const int j = h / P.g, hh = h - j * P.g;
   const int pos0 = off[P.j0 * P.b_cap];
-  const uint32_t vm = vmask[(size_t)t * P.hkv + j];
-  bf16_t* orow = O + row * kD + 8 * sub;
-  if (vm == 0u) {
-    *reinterpret_cast<uint4*>(orow) = make_uint4(0, 0, 0, 0);
-    if (sub == 0) LSE[row] = -INFINITY;
-    if (gate != nullptr)  // nothing to add: the gated sum is what the other branches gave
-      *reinterpret_cast<uint4*>(Oout + row * kD + 8 * sub) =
-          Oacc != nullptr ? *reinterpret_cast<const uint4*>(Oacc + row * kD + 8 * sub) : make_uint4(0, 0, 0, 0);
-    return;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  // what the workgroup's rows leave with: the sum, LSE, and with a gate the gated sum
+  u32x4* const out = reinterpret_cast<u32x4*>(smem) + threadIdx.x;
+  u32x4* const gated = out + kRows * kThreads;
+  float* const lse = reinterpret_cast<float*>(smem + kRows * kThreads * (kGate ? 32 : 16)) + (threadIdx.x >> 4);
+  ReduceRow R = reduce_row<kRows, kThreads>(P, 0);
+  SlotRow slots = load_slots(slotpos, P, R);
+#pragma unroll 1
+  for (int q = 0; q < kRows; ++q) {
+    const ReduceRow R_next = reduce_row<kRows, kThreads>(P, min(q + 1, kRows - 1));
+    const SlotRow slots_next = load_slots(slotpos, P, R_next);
+    const int64_t row = (int64_t)R.t * P.hq + R.j * P.g + R.hh;
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    float M = -INFINITY, Ls = 0.f;
+    int pos = -1;  // of the last kept column: dropped ones gather it again
+    for (int m0 = 0; m0 < P.topk; m0 += kBatch) {
+      int at[kBatch];
+      u32x4 x[kBatch];
+      float ls[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) at[i] = slot_of(slots, m0 + i);
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        pos = at[i] >= 0 ? at[i] : pos;
+        asm volatile("" : "+v"(at[i]), "+v"(pos));  // keeps the loads free of branches
+        const size_t pr = (size_t)(max(pos, pos0) - pos0) * P.g + R.hh;
+        x[i] = load_streaming(opart + pr * kD + 8 * sub);
+        ls[i] = lse_part[pr];
+      }
+      float Mb = M;
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        if (at[i] < 0) {
+          x[i] = u32x4{0, 0, 0, 0};
+          ls[i] = -INFINITY;
+        }
+        Mb = fmaxf(Mb, ls[i]);
+      }
+      const float Mf = Mb == -INFINITY ? 0.f : Mb;  // no kept slot in this batch or before it: all factors below are 0
+      const float rescale = __expf(M - Mf);         // 0 on the first non-empty batch
+      Ls *= rescale;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[c] *= rescale;
+      M = Mb;
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const float w = __expf(ls[i] - Mf);  // exp(-inf) = 0 for slots that are off
+        Ls += w;
+        acc[0] += w * bf16_lo(x[i].x); acc[1] += w * bf16_hi(x[i].x);
+        acc[2] += w * bf16_lo(x[i].y); acc[3] += w * bf16_hi(x[i].y);
+        acc[4] += w * bf16_lo(x[i].z); acc[5] += w * bf16_hi(x[i].z);
+        acc[6] += w * bf16_lo(x[i].w); acc[7] += w * bf16_hi(x[i].w);
+      }
+    }
+    const bool empty = pos < 0;  // nothing visible: O = 0, LSE = -inf, and the gated sum is what the other branches gave
+    const float inv = empty ? 0.f : 1.f / Ls;
+    out[q * kThreads] = u32x4{pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),
+                              pack_bf16x2(acc[4] * inv, acc[5] * inv), pack_bf16x2(acc[6] * inv, acc[7] * inv)};
+    if (sub == 0) lse[q * (kThreads / 16)] = empty ? -INFINITY : M + __logf(Ls);
+    if constexpr (kGate) {
+      // Eq. (2): O_out = O_acc + gate * O, from the fp32 result (Oout may be the buffer Oacc points to: every lane
+      // reads its own 16 bytes before it writes them)
+      const float tau = gate[row] * inv;
+      u32x4 a = {0, 0, 0, 0};
+      if (Oacc != nullptr) a = *reinterpret_cast<const u32x4*>(Oacc + row * kD + 8 * sub);
+      if (!empty) {
+        a.x = pack_bf16x2(bf16_lo(a.x) + tau * acc[0], bf16_hi(a.x) + tau * acc[1]);
+        a.y = pack_bf16x2(bf16_lo(a.y) + tau * acc[2], bf16_hi(a.y) + tau * acc[3]);
+        a.z = pack_bf16x2(bf16_lo(a.z) + tau * acc[4], bf16_hi(a.z) + tau * acc[5]);
+        a.w = pack_bf16x2(bf16_lo(a.w) + tau * acc[6], bf16_hi(a.w) + tau * acc[7]);
+      }
+      gated[q * kThreads] = a;
+    }
+    R = R_next;
+    slots = slots_next;
   }
-  const int32_t* sp = slotpos + ((size_t)t * P.hkv + j) * P.topk;
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  float M = -INFINITY, Ls = 0.f;
-  for (int m0 = 0; m0 < P.topk; m0 += kSlotBatch) {
-    size_t pr[kSlotBatch];
-    uint4 x[kSlotBatch];
-    float ls[kSlotBatch];
+  __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kSlotBatch; ++i) {
-      const int m = m0 + i;
-      const bool on = m < P.topk && ((vm >> m) & 1u);
-      pr[i] = on ? (size_t)(sp[m] - pos0) * P.g + hh : (size_t)0;
-    }
-#pragma unroll
-    for (int i = 0; i < kSlotBatch; ++i) {
-      const int m = m0 + i;
-      const bool on = m < P.topk && ((vm >> m) & 1u);
-      x[i] = on ? *reinterpret_cast<const uint4*>(opart + pr[i] * kD + 8 * sub) : make_uint4(0, 0, 0, 0);
-      ls[i] = on ? lse_part[pr[i]] : -INFINITY;
-    }
-    float Mb = M;
-#pragma unroll
-    for (int i = 0; i < kSlotBatch; ++i) Mb = fmaxf(Mb, ls[i]);
-    if (Mb == -INFINITY) continue;  // no kept slot in this batch or before it
-    const float rescale = __expf(M - Mb);  // 0 on the first non-empty batch
-    Ls *= rescale;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] *= rescale;
-    M = Mb;
-#pragma unroll
-    for (int i = 0; i < kSlotBatch; ++i) {
-      const float w = __expf(ls[i] - M);  // exp(-inf) = 0 for slots that are off
-      Ls += w;
-      acc[0] += w * bf16_lo(x[i].x); acc[1] += w * bf16_hi(x[i].x);
-      acc[2] += w * bf16_lo(x[i].y); acc[3] += w * bf16_hi(x[i].y);
-      acc[4] += w * bf16_lo(x[i].z); acc[5] += w * bf16_hi(x[i].z);
-      acc[6] += w * bf16_lo(x[i].w); acc[7] += w * bf16_hi(x[i].w);
-    }
-  }
-  const float inv = 1.f / Ls;
-  uint4 o;
-  o.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
-  o.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
-  o.z = pack_bf16x2(acc[4] * inv, acc[5] * inv);
-  o.w = pack_bf16x2(acc[6] * inv, acc[7] * inv);
-  *reinterpret_cast<uint4*>(orow) = o;
-  if (sub == 0) LSE[row] = M + __logf(Ls);
-  if (gate != nullptr) {
-    // Eq. (2): O_out = O_acc + gate * O, from the fp32 result (Oout may be the buffer Oacc points to: every lane
-    // reads its own 16 bytes before it writes them)
-    const float tau = gate[row] * inv;
-    uint4 a = make_uint4(0, 0, 0, 0);
-    if (Oacc != nullptr) a = *reinterpret_cast<const uint4*>(Oacc + row * kD + 8 * sub);
-    o.x = pack_bf16x2(bf16_lo(a.x) + tau * acc[0], bf16_hi(a.x) + tau * acc[1]);
-    o.y = pack_bf16x2(bf16_lo(a.y) + tau * acc[2], bf16_hi(a.y) + tau * acc[3]);
-    o.z = pack_bf16x2(bf16_lo(a.z) + tau * acc[4], bf16_hi(a.z) + tau * acc[5]);
-    o.w = pack_bf16x2(bf16_lo(a.w) + tau * acc[6], bf16_hi(a.w) + tau * acc[7]);
-    *reinterpret_cast<uint4*>(Oout + row * kD + 8 * sub) = o;
+  for (int q = 0; q < kRows; ++q) {
+    const ReduceRow R = reduce_row<kRows, kThreads>(P, q);
+    if (!R.on) continue;
+    const int64_t row = (int64_t)R.t * P.hq + R.j * P.g + R.hh;
+    store_streaming(O + row * kD + 8 * sub, out[q * kThreads]);
+    if (sub == 0) LSE[row] = lse[q * (kThreads / 16)];
+    if constexpr (kGate) store_streaming(Oout + row * kD + 8 * sub, gated[q * kThreads]);
   }
 }
 
@@ -983,7 +1013,15 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
   auto* main128 = wide ? k_fwd_main128<true> : k_fwd_main128<false>;
   if (P0.dense) {
     static std::atomic<uint64_t> ready_dense;
-    hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge, 64 * 1024, ready_dense);
+    hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge, 96 * 1024, ready_dense);
+    if (e != hipSuccess) return e;
+  } else {
+    static std::atomic<uint64_t> ready_merge[2];
+    hipError_t e = allow_dynamic_lds((const void*)(k_fwd_merge<kBurstRows, kBurstThreads, false>),
+                                     reduce_lds(kBurstThreads, kBurstRows, 1, true), ready_merge[0]);
+    if (e == hipSuccess)
+      e = allow_dynamic_lds((const void*)(k_fwd_merge<kBurstRowsGated, kBurstThreads, true>),
+                            reduce_lds(kBurstThreads, kBurstRowsGated, 2, true), ready_merge[1]);
     if (e != hipSuccess) return e;
   }
   {
@@ -1016,16 +1054,31 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
       const int chunks = (kTileTokens * P.g + 127) / 128;
       const int per = (P.nj * P.t_cap * chunks + 7) / 8;
       ProfScope ps(KID_FWD_DENSE, st);
-      hipLaunchKernelGGL(k_fwd_dense_merge, dim3((unsigned)(8 * per)), dim3(256), dense_lds_bytes(P.g, P.topk), st, P, (const bf16_t*)Q,
+      hipLaunchKernelGGL(k_fwd_dense_merge, dim3((unsigned)(8 * per)), dim3(256), dense_lds_bytes(P.g, P.topk, G.gate != nullptr), st, P, (const bf16_t*)Q,
                          (const bf16_t*)K, (const bf16_t*)V, p.tile_tok0, p.tile_len, p.d_cnt, p.d_piece, p.d_mask,
                          (const bf16_t*)opart, (const float*)lse_part, p.vmask, p.dmask, p.slotpos, p.off, (bf16_t*)O,
                          LSE, G.gate, (const bf16_t*)G.o_acc, (bf16_t*)G.o_out);
     } else {
-      const int64_t rows = (int64_t)P.T * P.nj * P.g;
       ProfScope ps(KID_FWD_MERGE, st);
-      hipLaunchKernelGGL(k_fwd_merge, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, P, (const bf16_t*)opart,
-                         (const float*)lse_part, p.vmask, p.slotpos, p.off, (bf16_t*)O, LSE, G.gate,
-                         (const bf16_t*)G.o_acc, (bf16_t*)G.o_out);
+      auto launch = [&](auto rows, auto threads, auto gated) {
+        constexpr int kRows = decltype(rows)::value, kThreads = decltype(threads)::value;
+        constexpr bool kGate = decltype(gated)::value;
+        hipLaunchKernelGGL((k_fwd_merge<kRows, kThreads, kGate>), dim3(reduce_groups<kRows, kThreads>(P)), dim3(kThreads),
+                           reduce_lds(kThreads, kRows, kGate ? 2 : 1, true), st, P, (const bf16_t*)opart,
+                           (const float*)lse_part, p.slotpos, p.off, (bf16_t*)O, LSE, G.gate, (const bf16_t*)G.o_acc,
+                           (bf16_t*)G.o_out);
+      };
+      using std::integral_constant;
+      const integral_constant<int, kBurstThreads> burst;
+      const integral_constant<int, 1> one;
+      const integral_constant<int, 256> few;
+      if (reduce_in_bursts(P)) {
+        if (G.gate != nullptr) launch(integral_constant<int, kBurstRowsGated>{}, burst, std::true_type{});
+        else launch(integral_constant<int, kBurstRows>{}, burst, std::false_type{});
+      } else {
+        if (G.gate != nullptr) launch(one, few, std::true_type{});
+        else launch(one, few, std::false_type{});
+      }
     }
   }
   return hipGetLastError();

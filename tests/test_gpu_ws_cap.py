@@ -96,3 +96,35 @@ def test_reduction_by_ranges_of_lists_matches_one_list_each(tokens, block):
     capped.attn.bwd_ws.fill_(0x7F)
     for nm, a, b in zip(("O", "LSE", "dQ", "dK", "dV"), _run(capped), ref):
         assert _same_bits(a, b), nm
+
+
+@pytest.mark.parametrize("seqlens,hq,hkv,topk,block,dense", [([8201], 32, 32, 5, 64, False), ([3000, 1, 5200], 33, 11, 17, 64, False),
+                                                             ([9001], 30, 6, 32, 128, False), ([9001], 30, 6, 3, 64, True)])
+def test_reduction_in_bursts_matches_row_by_row(seqlens, hq, hkv, topk, block, dense):
+    """From 2^18 rows a pass the two reductions write a workgroup's rows at once, below that as they are done: one pass takes the
+    former (the last workgroup of it part empty), a KV head per pass the latter.  Same sums in the same order, same bits; gated
+    and plain, more and fewer columns than a batch."""
+    print("case bursts", seqlens, hq, hkv, topk, block, dense, flush=True)
+    w = wl.realise(wl.Workload("bursts", seqlens, hq=hq, hkv=hkv, topk=topk, block=block, sink=True, seed=96))
+    rows = w.total_tokens * hq
+    assert rows >= 1 << 18 and rows % 512 and rows // hkv < 1 << 18
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    gate = torch.rand(w.total_tokens, hq, generator=gen, device="cuda")
+    gate[::7] = 0
+    acc = torch.randn(w.total_tokens, hq, 128, generator=gen, device="cuda").to(torch.bfloat16)
+    outs = []
+    for cap in (None, 1):
+        case = Case(w)
+        case.attn = nsa.SelAttention(w.total_tokens, hq, hkv, topk, nseq=len(seqlens), block=block, ws_cap_bytes=cap, dense=dense)
+        for ws in (case.attn.fwd_ws, case.attn.bwd_ws):
+            ws.fill_(0x7F)
+        got = _run(case)
+        case.attn.fwd_ws.fill_(0x7F)
+        got += [x.clone() for x in case.attn.forward_gated(case.q, case.k, case.v, case.idx, gate, acc, case.cu)]
+        outs.append(got)
+    for nm, a, b in zip(("O", "LSE", "dQ", "dK", "dV", "gated O_out", "gated O", "gated LSE"), *outs):
+        assert _same_bits(a, b), nm
+    assert _same_bits(outs[0][0], outs[0][6]) and _same_bits(outs[0][1], outs[0][7])
+    plain = acc.float() + gate[..., None] * outs[0][0].float()
+    # two bf16 roundings apart: the library adds the sum before it is rounded
+    assert ((outs[0][5].float() - plain).abs() <= 2.0 ** -7 * (plain.abs() + outs[0][0].float().abs())).all()
