@@ -304,6 +304,19 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 __device__ __forceinline__ bf16x8 lds_read_frag(uint32_t a) {
   return *(__attribute__((address_space(3))) const bf16x8*)a;
 }
+__device__ __forceinline__ u32x4 lds_read_16(uint32_t a) { return *(__attribute__((address_space(3))) const u32x4*)a; }
+__device__ __forceinline__ void lds_write_16(uint32_t a, u32x4 v) { *(__attribute__((address_space(3))) u32x4*)a = v; }
+__device__ __forceinline__ void lds_write_8(uint32_t a, uint2 v) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  *(__attribute__((address_space(3))) u32x2*)a = u32x2{v.x, v.y};
+}
+// Rows of 128 bf16 lie in LDS unpadded, the 16-byte chunk c of row r at place c ^ row_turn(r).  That spreads over all 64 banks both
+// shapes in which the matrix operands are read: 16 bytes of one chunk in 16 consecutive rows (the low four bits of r all count),
+// and the transposing read, which takes four consecutive rows x 64 bytes in a cycle (their two low bits select the quarter of the
+// row).  Measured per CU: 256 bytes a clock for the former and twice the 128 of a 304-byte pitch for the latter, for which no
+// padding serves both (64 at 256 + 16, 64 with c ^ (r & 15)).  Where rows of a read differ by multiples of 16, its places differ by
+// an immediate offset; other steps flip bits of the address.
+__device__ __forceinline__ int row_turn(int r) { return (r & 3) << 2 | ((r >> 2) & 3); }
 // ds_read_b64_tr_b16: every lane passes the address of 8 bytes (four 16-bit elements); within each group of 16 lanes, lane
 // i receives element (i % 4) of the 8 bytes addressed by lanes 4e + i / 4, e = 0..3.  With lane s of a group pointing at row
 // (s / 4), columns 4 (s % 4).. of a row-major tile, lane i gets column i of four consecutive rows: the MFMA operand layout

@@ -534,10 +534,9 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 // loop took 1.87 ms there, 1.10 instead of 1.05 ms for a window of 512 at 65536 tokens and 1.88 instead of 1.81 ms with 9 of 16
 // columns dense at g = 7.  A second K tile (requests one piece earlier) gave nothing; three workgroups per CU leave 168
 // registers, 30 of them spilled.
-// LDS: the K and the V tile of a piece, row-major and unpadded; the 16-byte chunk c of row r lies at place c ^ (r & 7) of
-// its row, which spreads both access shapes (16-byte reads down a column of rows, transposing reads of 4 rows x 32 bytes)
-// over the banks.  (The LDS pipe is busy 10 % of the kernel's time, half of that in conflicts.)  Phase 1's result takes the same
-// area afterwards (place c ^ (r & 15)).
+// LDS: the K and the V tile of a piece, row-major and unpadded, their rows turned (see row_turn): 0.55 -> 0.51 ms for a window of
+// 512 at 32768 tokens, 6.3 -> 6.1 ms at 131072, g = 8, against a turn of the low three bits, which left the transposing reads at a
+// quarter of their rate.  Phase 1's result takes the same area afterwards (place c ^ (r & 15)).
 constexpr int kDnRow = kD * 2;
 constexpr int kDnK = 0;
 constexpr int kDnV = kDnK + 64 * kDnRow;
@@ -612,11 +611,11 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
   if (nd > 0) {  // ---------------------------------------------------------------------------------- phase 1
     const float c2 = P.scale * 1.4426950408889634f;
     // Staging goes from memory straight to LDS (no register, no LDS store instruction): access i of a wavefront fills rows
-    // 16 i + 4 wave + lane / 16, lane l the place l % 16 of its row, so the lane fetches chunk (l % 16) ^ (row & 7).
+    // 16 i + 4 wave + lane / 16, lane l the place l % 16 of its row, so the lane fetches chunk (l % 16) ^ row_turn(row).
     // Rows past the end of a ragged block lie past the end of the buffer and arrive as zero.
     const int srow = 4 * wave + (lane >> 4);
     const uint32_t row_bytes = (uint32_t)P.hkv * kDnRow;
-    const uint32_t stage_off = srow * row_bytes + (((lane & 15) ^ (srow & 7)) << 4);
+    const uint32_t stage_off = srow * row_bytes + (((lane & 15) ^ row_turn(srow)) << 4);
     auto stage = [&](const bf16_t* X, int lds_off, int step) __attribute__((always_inline)) {
       UnitRec B;
       B.tok0 = __builtin_amdgcn_readlane(my_piece.x, step);
@@ -651,20 +650,26 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
     float m_run = -INFINITY, l_run = 0.f;            // running maximum (raw scores) and sum of the row
     const int grp = lane >> 4, sl = lane & 15;
     // K fragment of contraction step s, keys 32 mb..: chunk 2 s + qh of row 32 mb + col
-    uint32_t kaddr[4];
+    uint32_t kaddr[8];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) kaddr[s] = lds_address(smem + kDnK) + col * kDnRow + (((2 * s + qh) ^ (col & 7)) << 4);
+    for (int s = 0; s < 8; ++s) kaddr[s] = lds_address(smem + kDnK) + col * kDnRow + (((2 * s + qh) ^ row_turn(col)) << 4);
     // V^T fragments: transposing reads of rows (sl / 4) + 4 (grp / 2) + 16 sp (+ 8), channels 32 db + 16 (grp & 1) + 4 (sl & 3)
     const int vrow = (sl >> 2) + 4 * (grp >> 1), vchunk = 2 * (grp & 1) + ((sl & 3) >> 1);
-    uint32_t vaddr[2];
+    uint32_t vaddr[2][4];
 #pragma unroll
-    for (int d = 0; d < 2; ++d) vaddr[d] = lds_address(smem + kDnV) + vrow * kDnRow + (((4 * d + vchunk) ^ (vrow & 7)) << 4) + 8 * (sl & 1);
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int d = 0; d < 4; ++d)
+        vaddr[h][d] = lds_address(smem + kDnV) + (vrow + 8 * h) * kDnRow + (((4 * d + vchunk) ^ row_turn(vrow + 8 * h)) << 4) + 8 * (sl & 1);
 
     wait_loads();
     __syncthreads();  // the first piece is staged
     for (int step = 0; step < nd; ++step) {
       // the reads below differ from these addresses by immediate offsets only
-      asm volatile("" : "+v"(kaddr[0]), "+v"(kaddr[1]), "+v"(kaddr[2]), "+v"(kaddr[3]), "+v"(vaddr[0]), "+v"(vaddr[1]));
+      asm volatile("" : "+v"(kaddr[0]), "+v"(kaddr[1]), "+v"(kaddr[2]), "+v"(kaddr[3]), "+v"(kaddr[4]), "+v"(kaddr[5]),
+                   "+v"(kaddr[6]), "+v"(kaddr[7]));
+      asm volatile("" : "+v"(vaddr[0][0]), "+v"(vaddr[0][1]), "+v"(vaddr[0][2]), "+v"(vaddr[0][3]), "+v"(vaddr[1][0]),
+                   "+v"(vaddr[1][1]), "+v"(vaddr[1][2]), "+v"(vaddr[1][3]));
       const unsigned long long members =
           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_mask, step) |
           (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_mask >> 32), step) << 32;
@@ -679,7 +684,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
       for (int s = 0; s < 8; ++s)
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb) {
-          const bf16x8 kf = lds_read_frag(kaddr[s & 3] + 32 * mb * kDnRow + 128 * (s >> 2));
+          const bf16x8 kf = lds_read_frag(kaddr[s] + 32 * mb * kDnRow);
           sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sacc[mb], 0, 0, 0);
         }
       // keys [lo, lim) of the piece are visible to this row: none if the token does not keep the block
@@ -741,8 +746,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
       for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
         for (int db = 0; db < 4; ++db) {
-          const uint32_t v0 = vaddr[db & 1] + 16 * sp * kDnRow + 128 * (db >> 1);
-          const bf16x4 a0 = lds_read_tr_at(v0), a1 = lds_read_tr_at(v0 + 8 * kDnRow);
+          const bf16x4 a0 = lds_read_tr_at(vaddr[0][db] + 16 * sp * kDnRow), a1 = lds_read_tr_at(vaddr[1][db] + 16 * sp * kDnRow);
           const bf16x8 vf = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
           oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[sp], oacc[db], 0, 0, 0);
         }
