@@ -9,7 +9,7 @@
 //                     P.unit list entries): four wavefronts and half of a CU's LDS, so two workgroups share a CU and
 //                     cover each other's barriers and waits.  The waves share tiles of 64 gathered rows and take three
 //                     roles per tile (see the comment above the kernel): S = Q K_i^T, dP = dO V_i^T,
-//                     P = exp(S - LSE), dS = P (dP - delta) scale; then dV_i += P^T dO and dK_i += dS^T Q
+//                     P = exp(S - LSE), dS = P (dP - delta); then dV_i += P^T dO and dK_i += dS^T Q
 //                     (accumulators in registers for the whole unit) and dQ^T = K_i^T dS^T.  Operands are row-major
 //                     tiles in LDS; "lane = column" operands are LDS transpose reads.  Partial dQ rows go to the
 //                     compact buffer at the rows' list position; the unit's dK_i, dV_i go out as bf16 (list fitted
@@ -26,10 +26,8 @@
 
 namespace nsa {
 
-// bf16 per row of the K / Q / dO tiles in LDS: 128 + 24 pad.  A 304-byte row pitch puts the rows
-// of both access shapes used here (16-byte operand reads down a column of rows, and the 4-row x 32-byte footprint
-// of a transposing read) on disjoint banks; with 128 + 8 the transposing reads conflicted two-way (measured:
-// 45 % of LDS cycles were bank conflicts, 8 % kernel time).
+// bf16 per row of the 128-key kernel's Q / dO tiles in LDS: 128 + 24 pad.  With a 304-byte pitch the 16-byte operand reads
+// run at the full 256 bytes a clock and the transposing reads at half of it; with 128 + 8 the latter at a quarter (8 % kernel time).
 constexpr int kRowStride = 152;
 
 __device__ __forceinline__ void wave_sync_bwd() {  // orders a wavefront's own LDS traffic
@@ -122,26 +120,32 @@ k_bwd_delta(Problem P, const bf16_t* __restrict__ O, const bf16_t* __restrict__ 
 //               P^T / dS^T operand read)
 //   rows/chans  dQ^T for rows 32 rb.. and channels 64 kb..; the same wave stages / prefetches that part of the Q and dO
 //               tiles and stores that part of dQ
-// K_i, Q, dO (304-byte pitch) and P^T, dS^T (144-byte pitch) are row-major tiles in LDS; "lane = column" operands
-// are LDS transpose reads.  The list's token ids are kept in LDS 1024 entries at a time.
+// K_i, Q, dO (turned rows of 256 bytes, see row_turn) and P^T, dS^T (144-byte pitch) are row-major tiles in LDS; "lane =
+// column" operands are LDS transpose reads.  The S product starts from -LSE / scale and the dP product from -delta of its rows, so
+// that P = 2^(S scale log2 e) and dS = P dP need no subtraction; dS, dK and dQ go without the softmax scale, which dK
+// gets when the unit is done and dQ in the reduction; keys are hidden in a branch that tiles seeing the whole block skip.  The list's token ids are kept in LDS 1024 entries at a time.
 // A row's place in memory is worked out once, by the lane that owns it, one tile before its loads are issued, and handed
 // to the lanes that move it; rows move through buffer instructions without branches (see RowTensor), so the wait for a
 // tile's rows does not wait for the stores of the tile before.  That took 40 % of the vector instructions out of the loop
-// and a full drain of the memory queue out of every tile: 4.59 -> 4.2 ms at 65536 tokens, g = 4 (26.2 GB between the XCDs
-// and the memory side: 6.2 TB/s; LDS pipe busy 69 % of the time, matrix pipe 34 %).
+// and a full drain of the memory queue out of every tile: 4.59 -> 4.2 ms at 65536 tokens, g = 4.  What bounds the kernel is on
+// the CU, LDS first (with the gathers served by one XCD's L2 and the stores dropped it still took 3.7 ms of 4.4): the leaner
+// elementwise part gave 4.50 -> 4.36 ms on one chip, the turned rows in place of a 304-byte pitch 4.16 -> 3.99 ms on another (8192
+// tokens, g = 1: 580 -> 544 us; g = 7, 65536 tokens: 3.46 -> 3.34 ms).  Staging the next tile before the dQ rows are stored,
+// through the P^T / dS^T area, gave nothing (g = 1: +4 %).
 constexpr int kTile = 64;      // rows per tile
 constexpr int kPStride = 72;   // bf16 per row of the P^T / dS^T tiles: 64 rows + 8 pad
 constexpr int kEntSeg = 1024;  // list entries whose token ids are resident in LDS
 
 struct BwdLds {
+  static constexpr int Row = kD * 2;
   static constexpr int K = 0;
-  static constexpr int Q = K + 64 * kRowStride * 2;
-  static constexpr int DO = Q + kTile * kRowStride * 2;
-  static constexpr int Pt = DO + kTile * kRowStride * 2;
+  static constexpr int Q = K + 64 * Row;
+  static constexpr int DO = Q + kTile * Row;
+  static constexpr int Pt = DO + kTile * Row;
   static constexpr int DSt = Pt + 64 * kPStride * 2;
   static constexpr int Ent = DSt + 64 * kPStride * 2;
-  static constexpr int Rec = Ent + kEntSeg * 4;      // per row of the tile: LSE (log2 domain), delta * scale, visible keys
-  static constexpr int Bytes = Rec + 3 * kTile * 4;  // 81664
+  static constexpr int Rec = Ent + kEntSeg * 4;      // per row of the tile: -LSE / scale, -delta, visible keys
+  static constexpr int Bytes = Rec + 3 * kTile * 4;  // 72448
 };
 static_assert(2 * BwdLds::Bytes <= 160 * 1024, "two workgroups of the 64-key backward must fit one CU's LDS");
 
@@ -151,11 +155,12 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
             const bf16_t* __restrict__ dO, const float2* __restrict__ stats, const UnitRec* __restrict__ u_rec,
             const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off, const int2* __restrict__ qent,
             bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
   int32_t* ent = reinterpret_cast<int32_t*>(smem + BwdLds::Ent);
   UnitRec U;
   int ubase, pos0;
   if (!load_unit(P, u_rec, nu_scan, off, U, ubase, pos0)) return;
+  constexpr int kRow = BwdLds::Row;
   const int j = U.j, ne = U.ne, tok0 = U.tok0, blen = U.blen;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, qh = lane >> 5, rb = wave >> 1, kb = wave & 1;
@@ -177,7 +182,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
   for (int i = 0; i < kEntSeg / 256; ++i) ent[tid + 256 * i] = ids[i];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-    *reinterpret_cast<bf16x8*>(smem + BwdLds::K + (tid >> 2) * (kRowStride * 2) + (tid & 3) * 64 + 16 * i) = kreg[i];
+    *reinterpret_cast<bf16x8*>(smem + BwdLds::K + (tid >> 2) * kRow + (((4 * (tid & 3) + i) ^ row_turn(tid >> 2)) << 4)) = kreg[i];
 
   f32x16 dkacc[2], dvacc[2];
 #pragma unroll
@@ -187,23 +192,26 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
       dkacc[cb][v] = 0.f;
       dvacc[cb][v] = 0.f;
     }
-  const float c2 = P.scale * 1.4426950408889634f;
+  // (a scale whose reciprocal would overflow leaves no trace of the scores in P: any other such scale does as well)
+  const float c2 = fmaxf(P.scale * 1.4426950408889634f, 1e-30f), start = -1.f / c2;
+  constexpr uint32_t kAllSeen = kWin ? 64u << 16 : 64u;
 
   // this lane's places in the LDS tiles (everything else is an immediate offset)
   const int grp = lane >> 4, sl = lane & 15, srow = lane >> 3;
-  unsigned char* const stage = smem + BwdLds::Q + (32 * rb + srow) * (kRowStride * 2) + 128 * kb + 16 * (lane & 7);
-  const unsigned char* const qfrag = smem + BwdLds::Q + (32 * rb + col) * (kRowStride * 2) + 16 * qh;
-  const unsigned char* const kfrag = smem + BwdLds::K + (32 * kb + col) * (kRowStride * 2) + 16 * qh;
+  const uint32_t lds = lds_address(smem);
+  const uint32_t stage = lds + BwdLds::Q + (32 * rb + srow) * kRow + (((8 * kb + (lane & 7)) ^ row_turn(srow)) << 4);
+  const uint32_t frag = col * kRow + ((qh ^ row_turn(col)) << 4);
+  uint32_t qfrag = lds + BwdLds::Q + 32 * rb * kRow + frag, kfrag = lds + BwdLds::K + 32 * kb * kRow + frag;
   const float* const rec_rd = reinterpret_cast<const float*>(smem + BwdLds::Rec) + 32 * rb + 4 * qh;
   float* const rec_wr = reinterpret_cast<float*>(smem + BwdLds::Rec) + 32 * rb + col;
   unsigned char* const pt_wr = smem + BwdLds::Pt + (32 * kb + col) * (kPStride * 2) + (32 * rb + 4 * qh) * 2;
   const unsigned char* const pt_rd = smem + BwdLds::Pt + (32 * rb + col) * (kPStride * 2) + 16 * qh;
   // transposing reads of four rows x 16 columns (see lds_read_tr), for the two row pitches
-  const bf16_t* const tr_row = reinterpret_cast<const bf16_t*>(smem + BwdLds::Q) +
-                               ((sl >> 2) + 8 * (grp >> 1)) * kRowStride + 16 * (grp & 1) + 4 * (sl & 3) + 64 * kb;
+  const int tr_r = (sl >> 2) + 8 * (grp >> 1);
+  uint32_t tr_row = lds + tr_r * kRow + (((8 * kb + 2 * (grp & 1) + ((sl & 3) >> 1)) ^ row_turn(tr_r)) << 4) + 8 * (sl & 1);
   const bf16_t* const tr_ds = reinterpret_cast<const bf16_t*>(smem + BwdLds::DSt) +
                               ((sl >> 2) + 8 * (grp >> 1)) * kPStride + 16 * (grp & 1) + 4 * (sl & 3) + 32 * rb;
-  unsigned char* const dq_wr = smem + BwdLds::Q + (32 * rb + col) * (kRowStride * 2) + 128 * kb + 8 * qh;
+  uint32_t dq_wr = lds + BwdLds::Q + (32 * rb + col) * kRow + (((8 * kb) ^ row_turn(col)) << 4) + 8 * qh;
   constexpr int kDoOff = BwdLds::DO - BwdLds::Q, kDsOff = BwdLds::DSt - BwdLds::Pt;
 
   const RowTensor<kWide> Qrows(Q, (int64_t)P.T * P.hq), dOrows(dO, (int64_t)P.T * P.hq);
@@ -264,14 +272,18 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
     do {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        *reinterpret_cast<u32x4*>(stage + 8 * i * (kRowStride * 2)) = qc[i];
-        *reinterpret_cast<u32x4*>(stage + kDoOff + 8 * i * (kRowStride * 2)) = dc[i];
+        const uint32_t to = (stage ^ (32 * (i & 1))) + 8 * i * kRow;
+        lds_write_16(to, qc[i]);
+        lds_write_16(to + kDoOff, dc[i]);
       }
       if (kb == 0 && qh == 0) {  // this row's record, for the lanes of the rows/keys role (which hold keys, not rows)
-        rec_wr[0] = st.x;
-        rec_wr[kTile] = st.y * P.scale;
+        rec_wr[0] = st.x * start;
+        rec_wr[kTile] = -st.y;
         reinterpret_cast<uint32_t*>(rec_wr)[2 * kTile] = vis_c;
       }
+      // the reads below are these addresses with bits flipped and immediate offsets added
+      asm volatile("" : "+v"(qfrag), "+v"(kfrag), "+v"(tr_row), "+v"(dq_wr));
+      const bool part_seen = __builtin_amdgcn_ballot_w64(vis_c != kAllSeen) != 0ull;  // some row does not see the whole block
       issue_rows(row_n, sidx_n);  // the next tile's rows fly while this one computes (past the last: its last row, unused)
       vis_c = vis_n;
       __syncthreads();  // Q / dO tile and the row records staged by all waves
@@ -280,30 +292,44 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
          // 8 (v >> 2) + 4 qh + (v & 3), so four consecutive rows of P^T / dS^T leave each lane as one 8-byte LDS store
         f32x16 sacc, dpacc;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          sacc[v] = 0.f;
-          dpacc[v] = 0.f;
+        for (int a = 0; a < 4; ++a) {
+          const f32x4 s4 = *reinterpret_cast<const f32x4*>(rec_rd + 8 * a);
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(rec_rd + kTile + 8 * a);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            sacc[4 * a + c] = s4[c];
+            dpacc[4 * a + c] = d4[c];
+          }
         }
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-          const bf16x8 qf = *reinterpret_cast<const bf16x8*>(qfrag + 32 * s);
-          const bf16x8 dof = *reinterpret_cast<const bf16x8*>(qfrag + kDoOff + 32 * s);
-          const bf16x8 kfa = *reinterpret_cast<const bf16x8*>(kfrag + 32 * s);
+          const bf16x8 qf = lds_read_frag(qfrag ^ (32 * s));
+          const bf16x8 dof = lds_read_frag((qfrag ^ (32 * s)) + kDoOff);
+          const bf16x8 kfa = lds_read_frag(kfrag ^ (32 * s));
           sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kfa, sacc, 0, 0, 0);
           dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dof, vf[s], dpacc, 0, 0, 0);
         }
-        const uint32_t key = 32 * kb + col;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sacc[v] = __builtin_amdgcn_exp2f(sacc[v] * c2);
+        if (part_seen) {
+          const uint32_t key = 32 * kb + col;
+#pragma unroll
+          for (int a = 0; a < 4; ++a) {
+            const u32x4 vis4 = *reinterpret_cast<const u32x4*>(rec_rd + 2 * kTile + 8 * a);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const bool seen = kWin ? key - (vis4[c] & 0xffffu) < (vis4[c] >> 16) : (int)key < (int)vis4[c];
+              sacc[4 * a + c] = seen ? sacc[4 * a + c] : 0.f;
+            }
+          }
+        }
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-          const f32x4 lse4 = *reinterpret_cast<const f32x4*>(rec_rd + 8 * a);
-          const f32x4 dls4 = *reinterpret_cast<const f32x4*>(rec_rd + kTile + 8 * a);
-          const u32x4 vis4 = *reinterpret_cast<const u32x4*>(rec_rd + 2 * kTile + 8 * a);
           float p[4], ds[4];
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            const bool seen = kWin ? key - (vis4[c] & 0xffffu) < (vis4[c] >> 16) : (int)key < (int)vis4[c];
-            p[c] = seen ? __builtin_amdgcn_exp2f(fmaf(sacc[4 * a + c], c2, -lse4[c])) : 0.f;
-            ds[c] = p[c] * fmaf(dpacc[4 * a + c], P.scale, -dls4[c]);  // P (dP - delta) scale
+            p[c] = sacc[4 * a + c];
+            ds[c] = p[c] * dpacc[4 * a + c];  // P (dP - delta)
           }
           uint2 pw, sw2;
           pw.x = pack_bf16x2(p[0], p[1]);
@@ -323,10 +349,10 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
           const bf16x8 sa = *reinterpret_cast<const bf16x8*>(pt_rd + kDsOff + 32 * qs);
 #pragma unroll
           for (int cb = 0; cb < 2; ++cb) {
-            const bf16_t* q_tr = tr_row + (16 * qs * kRowStride + 32 * cb);
-            const bf16_t* do_tr = q_tr + kDoOff / 2;
-            const bf16x4 d0 = lds_read_tr(do_tr), d1 = lds_read_tr(do_tr + 4 * kRowStride);
-            const bf16x4 q0 = lds_read_tr(q_tr), q1 = lds_read_tr(q_tr + 4 * kRowStride);
+            const uint32_t lo = (tr_row ^ (64 * cb)) + BwdLds::Q + 16 * qs * kRow;  // four rows, and the four below
+            const uint32_t hi = (tr_row ^ (64 * cb + 16)) + BwdLds::Q + (16 * qs + 4) * kRow;
+            const bf16x4 d0 = lds_read_tr_at(lo + kDoOff), d1 = lds_read_tr_at(hi + kDoOff);
+            const bf16x4 q0 = lds_read_tr_at(lo), q1 = lds_read_tr_at(hi);
             const bf16x8 dob = __builtin_shufflevector(d0, d1, 0, 1, 2, 3, 4, 5, 6, 7);
             const bf16x8 qb = __builtin_shufflevector(q0, q1, 0, 1, 2, 3, 4, 5, 6, 7);
             dvacc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa, dob, dvacc[cb], 0, 0, 0);
@@ -346,8 +372,8 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
           const bf16x8 dsb = __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
           for (int db = 0; db < 2; ++db) {
-            const bf16_t* k_tr = tr_row - (BwdLds::Q - BwdLds::K) / 2 + (16 * sp * kRowStride + 32 * db);
-            const bf16x4 a0 = lds_read_tr(k_tr), a1 = lds_read_tr(k_tr + 4 * kRowStride);
+            const bf16x4 a0 = lds_read_tr_at((tr_row ^ (64 * db)) + BwdLds::K + 16 * sp * kRow);
+            const bf16x4 a1 = lds_read_tr_at((tr_row ^ (64 * db + 16)) + BwdLds::K + (16 * sp + 4) * kRow);
             const bf16x8 ktf = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
             dqacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf, dsb, dqacc[db], 0, 0, 0);
           }
@@ -362,14 +388,14 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
           uint2 w;
           w.x = pack_bf16x2(dqacc[db][4 * a + 0], dqacc[db][4 * a + 1]);
           w.y = pack_bf16x2(dqacc[db][4 * a + 2], dqacc[db][4 * a + 3]);
-          *reinterpret_cast<uint2*>(dq_wr + 64 * db + 16 * a) = w;
+          lds_write_8(dq_wr ^ (64 * db + 16 * a), w);
         }
       wave_sync_bwd();
       const __amdgpu_buffer_rsrc_t dq_buf =
           buffer_of(dq_unit + (size_t)tile0 * kD, (uint32_t)min(rows_end - tile0, kTile) * (kD * 2));
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(stage + 8 * i * (kRowStride * 2)), dq_buf,
+        __builtin_amdgcn_raw_buffer_store_b128(lds_read_16((stage ^ (32 * (i & 1))) + 8 * i * kRow), dq_buf,
                                                dq_lane + 8 * i * (kD * 2), 0, kNonTemporal);
       wave_sync_bwd();
       tile0 += kTile;
@@ -386,7 +412,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
       for (int v = 0; v < 16; ++v) {
         const int key = 32 * rb + 8 * (v >> 2) + 4 * qh + (v & 3);
         if (key < blen) {
-          outk[(size_t)key * P.hkv * kD] = (bf16_t)dkacc[cb][v];
+          outk[(size_t)key * P.hkv * kD] = (bf16_t)(dkacc[cb][v] * P.scale);
           outv[(size_t)key * P.hkv * kD] = (bf16_t)dvacc[cb][v];
         }
       }
@@ -401,7 +427,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int key = 32 * rb + 8 * (v >> 2) + 4 * qh + (v & 3);
-      outk[key * kD] = dkacc[cb][v];
+      outk[key * kD] = dkacc[cb][v] * P.scale;
       outv[key * kD] = dvacc[cb][v];
     }
   }
@@ -413,7 +439,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 // accumulation), MFMA, VALU and LDS time add up and every LDS read waits out its latency: two waves per SIMD cannot
 // cover each other.  Here the waves specialise and work one tile apart:
 //   waves 0-3 (S-waves, one per SIMD): wave w keeps the K and V fragments of keys 32 w.. in registers and computes, for
-//       the 64 rows of tile n, S = Q K^T, dP = dO V^T, P = exp(S - LSE), dS = P (dP - delta) scale, and writes
+//       the 64 rows of tile n, S = Q K^T, dP = dO V^T, P = exp(S - LSE), dS = P (dP - delta), and writes
 //       P^T, dS^T (bf16, [key][row]) to LDS; they also request and stage the gathered Q / dO rows;
 //   waves 4-7 (A-waves, the other wave of each SIMD): wave a keeps the fp32 dK, dV accumulators of keys 32 a.. (all 128
 //       channels) and the K^T fragments of channels 32 a.., and for tile n - 1 computes dV += P^T dO, then
@@ -433,7 +459,7 @@ struct PipeLds {
   static constexpr int DSt0 = Pt0 + 2 * PB;
   static constexpr int Ent = DSt0 + 2 * PB;
   static constexpr int St0 = Ent + kEntSeg * 4;       // per-row records of a staged tile, two buffers: three arrays
-  static constexpr int SB = 3 * kTile * 4;            // of 64: LSE (log2 domain), delta * scale, visible key range
+  static constexpr int SB = 3 * kTile * 4;            // of 64: LSE (log2 domain), delta, visible key range
   static constexpr int Tb0 = St0 + 2 * SB;            // per row of the tile to request next: row of Q / dO, place in
   static constexpr int Bytes = Tb0 + kTile * 12;      // the kv head's statistics, visible keys; 157952 in all
 };
@@ -575,7 +601,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
     if ((tid & 3) == 0) {
       float* rec = reinterpret_cast<float*>(smem + PipeLds::St0 + buf * PipeLds::SB) + ((tid & 255) >> 2);
       rec[0] = st_set[set].x;
-      rec[kTile] = st_set[set].y * P.scale;
+      rec[kTile] = st_set[set].y;
       reinterpret_cast<int*>(rec)[2 * kTile] = vis_set[set];
     }
   };
@@ -639,24 +665,32 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
           const int key = 32 * sw + col;
           const bf16_t* q0 = Qs + col * kRowStride + 8 * qh;
           const bf16_t* d0 = dOs + col * kRowStride + 8 * qh;
-          f32x4 lse4, dls4;
-          u32x4 vis4;
-          auto probs = [&](int rb, int st) __attribute__((always_inline)) {  // P = exp(S scale - LSE) on visible keys
-            const int a = st >> 1, r4 = 32 * rb + 8 * a + 4 * qh;
-            if ((st & 1) == 0) {
-              lse4 = *reinterpret_cast<const f32x4*>(rec + r4);
-              vis4 = *reinterpret_cast<const u32x4*>(rec + 2 * kTile + r4);
-            }
+          f32x4 lse4, dl4;
+          const bool part_seen =
+              __builtin_amdgcn_ballot_w64(reinterpret_cast<const uint32_t*>(rec)[2 * kTile + lane] != 128u << 16) != 0ull;
+          auto probs = [&](int rb, int st) __attribute__((always_inline)) {  // P = exp(S scale - LSE)
+            const int a = st >> 1;
+            if ((st & 1) == 0) lse4 = *reinterpret_cast<const f32x4*>(rec + 32 * rb + 8 * a + 4 * qh);
 #pragma unroll
-            for (int c = 2 * (st & 1); c < 2 * (st & 1) + 2; ++c) {
-              const bool seen = (uint32_t)key - (vis4[c] & 0xffffu) < (vis4[c] >> 16);
-              pv[rb][4 * a + c] = seen ? __builtin_amdgcn_exp2f(fmaf(sacc[rb][4 * a + c], c2, -lse4[c])) : 0.f;
+            for (int c = 2 * (st & 1); c < 2 * (st & 1) + 2; ++c)
+              pv[rb][4 * a + c] = __builtin_amdgcn_exp2f(fmaf(sacc[rb][4 * a + c], c2, -lse4[c]));
+          };
+          auto hide = [&](int rb) __attribute__((always_inline)) {  // P = 0 at keys the row does not see
+            if (!part_seen) return;
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+              const u32x4 vis4 = *reinterpret_cast<const u32x4*>(rec + 2 * kTile + 32 * rb + 8 * a + 4 * qh);
+#pragma unroll
+              for (int c = 0; c < 4; ++c) {
+                const bool seen = (uint32_t)key - (vis4[c] & 0xffffu) < (vis4[c] >> 16);
+                pv[rb][4 * a + c] = seen ? pv[rb][4 * a + c] : 0.f;
+              }
             }
           };
-          auto emit = [&](int rb, int st) __attribute__((always_inline)) {  // dS = P (dP - delta) scale; bf16 to LDS
+          auto emit = [&](int rb, int st) __attribute__((always_inline)) {  // dS = P (dP - delta); bf16 to LDS
             const int a = st >> 1, r4 = 32 * rb + 8 * a + 4 * qh;
             if ((st & 1) == 0) {
-              dls4 = *reinterpret_cast<const f32x4*>(rec + kTile + r4);
+              dl4 = *reinterpret_cast<const f32x4*>(rec + kTile + r4);
               uint2 pw;
               pw.x = pack_bf16x2(pv[rb][4 * a + 0], pv[rb][4 * a + 1]);
               pw.y = pack_bf16x2(pv[rb][4 * a + 2], pv[rb][4 * a + 3]);
@@ -664,7 +698,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
             } else {
               float ds[4];
 #pragma unroll
-              for (int c = 0; c < 4; ++c) ds[c] = pv[rb][4 * a + c] * fmaf(dpacc[rb][4 * a + c], P.scale, -dls4[c]);
+              for (int c = 0; c < 4; ++c) ds[c] = pv[rb][4 * a + c] * (dpacc[rb][4 * a + c] - dl4[c]);
               uint2 sw2;
               sw2.x = pack_bf16x2(ds[0], ds[1]);
               sw2.y = pack_bf16x2(ds[2], ds[3]);
@@ -689,8 +723,9 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
             probs(0, st);
             __builtin_amdgcn_sched_barrier(0);
           }
+          hide(0);
 #pragma unroll
-          for (int st = 0; st < 8; ++st) {  // S, rows 32..63; refill with dO, rows 32..63; dS of rows 0..31
+          for (int st = 0; st < 8; ++st) {  // S, rows 32..63; refill with dO, rows 32..63; P, dS of rows 0..31 to LDS
             sacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[st], kf[st], sacc[1], 0, 0, 0);
             fr[st] = *reinterpret_cast<const bf16x8*>(d0 + 32 * kRowStride + 16 * st);
             emit(0, st);
@@ -702,6 +737,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
             probs(1, st);
             __builtin_amdgcn_sched_barrier(0);
           }
+          hide(1);
 #pragma unroll
           for (int st = 0; st < 8; ++st) emit(1, st);
         }
@@ -835,7 +871,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
         for (int v = 0; v < 16; ++v) {
           const int key = 32 * sw + 8 * (v >> 2) + 4 * qh + (v & 3);
           if (key < blen) {
-            outk[(size_t)key * P.hkv * kD] = (bf16_t)dkacc[cb][v];
+            outk[(size_t)key * P.hkv * kD] = (bf16_t)(dkacc[cb][v] * P.scale);
             outv[(size_t)key * P.hkv * kD] = (bf16_t)dvacc[cb][v];
           }
         }
@@ -850,7 +886,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int key = 32 * sw + 8 * (v >> 2) + 4 * qh + (v & 3);
-        outk[key * kD] = dkacc[cb][v];
+        outk[key * kD] = dkacc[cb][v] * P.scale;
         outv[key * kD] = dvacc[cb][v];
       }
     }
@@ -914,6 +950,8 @@ k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const int32_t* __r
         acc[6] += bf16_lo(x[i].w); acc[7] += bf16_hi(x[i].w);
       }
     }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[c] *= P.scale;
     out[q * kThreads] = u32x4{pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]), pack_bf16x2(acc[4], acc[5]),
                               pack_bf16x2(acc[6], acc[7])};
     R = R_next;

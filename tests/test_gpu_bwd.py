@@ -86,3 +86,21 @@ def test_two_calls_share_nothing_but_the_index():
     g1 = c.backward(o1, l1)
     g2 = c.backward(o1, l1)
     assert all(torch.equal(a, b) for a, b in zip(g1, g2))
+
+
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("scale", [1e-30, 1e-6, 0.3])
+def test_backward_far_scales(scale, block):
+    """The 64-key kernel starts its products from LSE / scale and both kernels leave the scale out of dS: a tiny scale (P is
+    uniform) and a large one (P nearly one-hot).  dQ and dK carry it as a factor and are compared with the default scale in its
+    place: that is what the tolerance, a bound on sums of rounded dS times it, was stated for."""
+    print("case far scale", scale, block, flush=True)
+    w = wl.realise(wl.Workload("scale", [1100, 77], hq=6, hkv=2, topk=6, sink=True, block=block, seed=97))
+    c = Case(w, scale=scale)
+    o, lse = c.forward()
+    dq, dk, dv = (to_f64(x) for x in c.backward(o, lse))
+    Q, K, V, dO = c.host_f64()
+    rq, rk, rv = orc.backward(Q, K, V, dO, w.idx, w.cu_seqlens, scale=scale, block=block)
+    f = 128 ** -0.5 / scale
+    for nm, a, b in (("dQ", dq * f, rq * f), ("dK", dk * f, rk * f), ("dV", dv, rv)):
+        assert_close(nm, a, b, TOL_GRAD)
