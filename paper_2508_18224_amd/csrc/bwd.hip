@@ -26,10 +26,6 @@
 
 namespace nsa {
 
-// bf16 per row of the 128-key kernel's Q / dO tiles in LDS: 128 + 24 pad.  With a 304-byte pitch the 16-byte operand reads
-// run at the full 256 bytes a clock and the transposing reads at half of it; with 128 + 8 the latter at a quarter (8 % kernel time).
-constexpr int kRowStride = 152;
-
 __device__ __forceinline__ void wave_sync_bwd() {  // orders a wavefront's own LDS traffic
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -445,13 +441,16 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 //       channels) and the K^T fragments of channels 32 a.., and for tile n - 1 computes dV += P^T dO, then
 //       dQ^T = K^T dS^T (channels 32 a.., all 128 keys; its 64-byte slice of every dQ row is stored at once), then
 //       dK += dS^T Q; they also work out the row addresses of tile n + 3 for the S-waves.
-// Q / dO tiles and P^T / dS^T tiles are double-buffered in LDS (154 KB in all), so the S-waves' MFMA and exponential work
+// Q / dO tiles (turned rows, see row_turn) and P^T / dS^T tiles are double-buffered in LDS (142 KB in all), so the S-waves' MFMA and exponential work
 // on tile n runs beside the A-waves' LDS-bound products on tile n - 1 on the same SIMD; two block-wide barriers per
 // tile order the hand-over.  Rows are requested three tiles ahead into two register sets and staged after the second
 // barrier.  Measured at 65536 tokens, g = 4, (128, 8): 3.5 ms against 4.1 ms for the eight-waves-in-step kernel, 3.3 ms
-// since rows move by buffer instructions (no 64-bit address per access on the P/dS waves' staging path).
+// since rows move by buffer instructions (no 64-bit address per access on the P/dS waves' staging path), 3.30 -> 3.20 ms with
+// turned rows, the softmax scale out of dS and one compare a key.  The masks in a branch instead (3.25 ms) or products that
+// start from the row statistics as in the 64-key kernel (+1.5 %) break up the order the P/dS waves' steps are issued in.
 struct PipeLds {
-  static constexpr int QB = kTile * kRowStride * 2;   // one Q or dO tile: 19456 bytes
+  static constexpr int Row = kD * 2;
+  static constexpr int QB = kTile * Row;              // one Q or dO tile: 16384 bytes
   static constexpr int PB = 128 * kPStride * 2;       // one P^T or dS^T tile: 18432 bytes
   static constexpr int Q0 = 0;
   static constexpr int DO0 = Q0 + 2 * QB;
@@ -461,7 +460,7 @@ struct PipeLds {
   static constexpr int St0 = Ent + kEntSeg * 4;       // per-row records of a staged tile, two buffers: three arrays
   static constexpr int SB = 3 * kTile * 4;            // of 64: LSE (log2 domain), delta, visible key range
   static constexpr int Tb0 = St0 + 2 * SB;            // per row of the tile to request next: row of Q / dO, place in
-  static constexpr int Bytes = Tb0 + kTile * 12;      // the kv head's statistics, visible keys; 157952 in all
+  static constexpr int Bytes = Tb0 + kTile * 12;      // the kv head's statistics, visible keys; 145664 in all
 };
 static_assert(PipeLds::Bytes <= 160 * 1024, "the pipelined 128-key backward must fit one CU's LDS");
 constexpr int kDqPitch = 36;  // bf16 per row of an A-wave's dQ staging (64 rows x 32 channels + pad = 4608 bytes)
@@ -503,7 +502,11 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
   const float c2 = P.scale * 1.4426950408889634f;
   const int hbase = j * P.g;
   const int grp = lane >> 4, sl = lane & 15;
-  int tr_lane = ((sl >> 2) + 8 * (grp >> 1)) * kRowStride + 16 * (grp & 1) + 4 * (sl & 3);
+  // this lane's place in the Q / dO tiles (turned rows, see row_turn): as operand rows, and in a transposing read of four rows
+  constexpr int kRow = PipeLds::Row;
+  const int tr_r = (sl >> 2) + 8 * (grp >> 1);
+  uint32_t tr_lane = lds_address(smem) + tr_r * kRow + (((2 * (grp & 1) + ((sl & 3) >> 1)) ^ row_turn(tr_r)) << 4) + 8 * (sl & 1);
+  uint32_t frag_lane = lds_address(smem) + col * kRow + ((qh ^ row_turn(col)) << 4);
   int tr_lane_p = ((sl >> 2) + 8 * (grp >> 1)) * kPStride + 16 * (grp & 1) + 4 * (sl & 3);
   const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
@@ -548,7 +551,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
   const int srow = (tid & 255) >> 4, schunk = (tid & 15) * 8;
   u32x4 qc[kS ? 2 : 1][kS ? 4 : 1], dc[kS ? 2 : 1][kS ? 4 : 1];
   // row record of row (t >> 2) of a requested tile, staged like the rows: (LSE in the log2 domain, delta) and the
-  // block's keys the row sees, [lo, lo + span), as lo | span << 16
+  // block's keys the row sees: [0, lim) as lim, with a window [lo, lo + span) as lo | span << 16
   float2 st_set[2];
   int vis_set[2];
   int seg0 = 0, rows_end = 0;
@@ -572,7 +575,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
       uint32_t* e = row_table + ((tid & 255) >> 2);
       e[0] = (uint32_t)t * (uint32_t)P.hq + (uint32_t)(hbase + (rc - ec * P.g));
       e[kTile] = (uint32_t)t * (uint32_t)P.g + (uint32_t)(rc - ec * P.g);
-      e[2 * kTile] = (uint32_t)(lo | (max(lim - lo, 0) << 16));
+      e[2 * kTile] = kWin ? (uint32_t)(lo | (max(lim - lo, 0) << 16)) : (uint32_t)lim;
     }
   };
   auto issue_rows = [&](auto setc) __attribute__((always_inline)) {
@@ -589,14 +592,13 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
     st_set[set] = head_stats[mine[kTile]];
     vis_set[set] = (int)mine[2 * kTile];
   };
-  auto stage_rows = [&](int buf, auto setc) __attribute__((always_inline)) {
-    constexpr int set = kS ? decltype(setc)::value : 0;
-    bf16_t* Qs = reinterpret_cast<bf16_t*>(smem + PipeLds::Q0 + buf * PipeLds::QB);
-    bf16_t* dOs = reinterpret_cast<bf16_t*>(smem + PipeLds::DO0 + buf * PipeLds::QB);
+  const uint32_t stage = lds_address(smem) + srow * kRow + (((tid & 15) ^ row_turn(srow)) << 4);
+  auto stage_rows = [&](auto bufc, auto setc) __attribute__((always_inline)) {
+    constexpr int set = kS ? decltype(setc)::value : 0, buf = decltype(bufc)::value;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      *reinterpret_cast<u32x4*>(&Qs[(16 * i + srow) * kRowStride + schunk]) = qc[set][i];
-      *reinterpret_cast<u32x4*>(&dOs[(16 * i + srow) * kRowStride + schunk]) = dc[set][i];
+      lds_write_16(stage + PipeLds::Q0 + buf * PipeLds::QB + 16 * i * kRow, qc[set][i]);
+      lds_write_16(stage + PipeLds::DO0 + buf * PipeLds::QB + 16 * i * kRow, dc[set][i]);
     }
     if ((tid & 3) == 0) {
       float* rec = reinterpret_cast<float*>(smem + PipeLds::St0 + buf * PipeLds::SB) + ((tid & 255) >> 2);
@@ -627,7 +629,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
       if constexpr (kS) {
         if (k == 0) {
           issue_rows(Set0{});
-          stage_rows(0, Set0{});
+          stage_rows(Set0{}, Set0{});
         } else if (k == 1) {
           issue_rows(Set1{});
         } else {
@@ -640,15 +642,13 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
     // one pipeline step: S-waves work on tile `it`, A-waves on tile `it - 1`; `par` = parity of `it`
     auto step = [&](const int it, auto par) __attribute__((always_inline)) {
       using Other = std::integral_constant<int, 1 - decltype(par)::value>;
-      asm volatile("" : "+v"(col), "+v"(qh), "+v"(tr_lane), "+v"(tr_lane_p));
+      asm volatile("" : "+v"(col), "+v"(qh), "+v"(tr_lane), "+v"(tr_lane_p), "+v"(frag_lane));
       PT_STAMP(3)
       __syncthreads();  // tile `it` staged; P^T / dS^T of tile `it - 1` complete
       PT_STAMP(0)
       if constexpr (kS) {
         if (it < ntiles) {  // ---- S, dP, P, dS of tile `it`: keys 32 sw.., all 64 rows
-          const int buf = it & 1;
-          const bf16_t* Qs = reinterpret_cast<const bf16_t*>(smem + PipeLds::Q0 + buf * PipeLds::QB);
-          const bf16_t* dOs = reinterpret_cast<const bf16_t*>(smem + PipeLds::DO0 + buf * PipeLds::QB);
+          constexpr int buf = decltype(par)::value;
           bf16_t* Pt = reinterpret_cast<bf16_t*>(smem + PipeLds::Pt0 + buf * PipeLds::PB);
           bf16_t* dSt = reinterpret_cast<bf16_t*>(smem + PipeLds::DSt0 + buf * PipeLds::PB);
           // S = Q K_i^T, dP = dO V_i^T for rows 32 rb.. x keys 32 sw..: lane = key, register v = row 8 (v >> 2) + 4 qh
@@ -663,28 +663,20 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
           bf16x8 fr[8];
           const float* rec = reinterpret_cast<const float*>(smem + PipeLds::St0 + buf * PipeLds::SB);
           const int key = 32 * sw + col;
-          const bf16_t* q0 = Qs + col * kRowStride + 8 * qh;
-          const bf16_t* d0 = dOs + col * kRowStride + 8 * qh;
+          auto q_frag = [&](int rb, int st) { return lds_read_frag((frag_lane ^ (32 * st)) + PipeLds::Q0 + buf * PipeLds::QB + 32 * rb * kRow); };
+          auto d_frag = [&](int rb, int st) { return lds_read_frag((frag_lane ^ (32 * st)) + PipeLds::DO0 + buf * PipeLds::QB + 32 * rb * kRow); };
           f32x4 lse4, dl4;
-          const bool part_seen =
-              __builtin_amdgcn_ballot_w64(reinterpret_cast<const uint32_t*>(rec)[2 * kTile + lane] != 128u << 16) != 0ull;
-          auto probs = [&](int rb, int st) __attribute__((always_inline)) {  // P = exp(S scale - LSE)
-            const int a = st >> 1;
-            if ((st & 1) == 0) lse4 = *reinterpret_cast<const f32x4*>(rec + 32 * rb + 8 * a + 4 * qh);
+          u32x4 vis4;
+          auto probs = [&](int rb, int st) __attribute__((always_inline)) {  // P = exp(S scale - LSE) on visible keys
+            const int a = st >> 1, r4 = 32 * rb + 8 * a + 4 * qh;
+            if ((st & 1) == 0) {
+              lse4 = *reinterpret_cast<const f32x4*>(rec + r4);
+              vis4 = *reinterpret_cast<const u32x4*>(rec + 2 * kTile + r4);
+            }
 #pragma unroll
-            for (int c = 2 * (st & 1); c < 2 * (st & 1) + 2; ++c)
-              pv[rb][4 * a + c] = __builtin_amdgcn_exp2f(fmaf(sacc[rb][4 * a + c], c2, -lse4[c]));
-          };
-          auto hide = [&](int rb) __attribute__((always_inline)) {  // P = 0 at keys the row does not see
-            if (!part_seen) return;
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-              const u32x4 vis4 = *reinterpret_cast<const u32x4*>(rec + 2 * kTile + 32 * rb + 8 * a + 4 * qh);
-#pragma unroll
-              for (int c = 0; c < 4; ++c) {
-                const bool seen = (uint32_t)key - (vis4[c] & 0xffffu) < (vis4[c] >> 16);
-                pv[rb][4 * a + c] = seen ? pv[rb][4 * a + c] : 0.f;
-              }
+            for (int c = 2 * (st & 1); c < 2 * (st & 1) + 2; ++c) {
+              const bool seen = kWin ? (uint32_t)key - (vis4[c] & 0xffffu) < (vis4[c] >> 16) : (uint32_t)key < vis4[c];
+              pv[rb][4 * a + c] = seen ? __builtin_amdgcn_exp2f(fmaf(sacc[rb][4 * a + c], c2, -lse4[c])) : 0.f;
             }
           };
           auto emit = [&](int rb, int st) __attribute__((always_inline)) {  // dS = P (dP - delta); bf16 to LDS
@@ -708,26 +700,25 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
 #pragma unroll
           for (int v = 0; v < 16; ++v) sacc[0][v] = dpacc[0][v] = sacc[1][v] = dpacc[1][v] = 0.f;
 #pragma unroll
-          for (int st = 0; st < 8; ++st) fr[st] = *reinterpret_cast<const bf16x8*>(q0 + 16 * st);
+          for (int st = 0; st < 8; ++st) fr[st] = q_frag(0, st);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int st = 0; st < 8; ++st) {  // S, rows 0..31; refill with dO, rows 0..31
             sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[st], kf[st], sacc[0], 0, 0, 0);
-            fr[st] = *reinterpret_cast<const bf16x8*>(d0 + 16 * st);
+            fr[st] = d_frag(0, st);
             __builtin_amdgcn_sched_barrier(0);
           }
 #pragma unroll
           for (int st = 0; st < 8; ++st) {  // dP, rows 0..31; refill with Q, rows 32..63; P of rows 0..31
             dpacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[st], vf[st], dpacc[0], 0, 0, 0);
-            fr[st] = *reinterpret_cast<const bf16x8*>(q0 + 32 * kRowStride + 16 * st);
+            fr[st] = q_frag(1, st);
             probs(0, st);
             __builtin_amdgcn_sched_barrier(0);
           }
-          hide(0);
 #pragma unroll
           for (int st = 0; st < 8; ++st) {  // S, rows 32..63; refill with dO, rows 32..63; P, dS of rows 0..31 to LDS
             sacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[st], kf[st], sacc[1], 0, 0, 0);
-            fr[st] = *reinterpret_cast<const bf16x8*>(d0 + 32 * kRowStride + 16 * st);
+            fr[st] = d_frag(1, st);
             emit(0, st);
             __builtin_amdgcn_sched_barrier(0);
           }
@@ -737,7 +728,6 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
             probs(1, st);
             __builtin_amdgcn_sched_barrier(0);
           }
-          hide(1);
 #pragma unroll
           for (int st = 0; st < 8; ++st) emit(1, st);
         }
@@ -746,14 +736,12 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
         PT_STAMP(2)
         // unconditional (tiles past the end re-read the list's last row and are never used): with no branch around
         // the loads the compiler's wait counts stay exact and the newer set's loads are left in flight here
-        stage_rows((it + 1) & 1, Other{});
+        stage_rows(Other{}, Other{});
         issue_rows(Other{});
       } else {
-        const int buf = (it - 1) & 1;
+        constexpr int buf = 1 - decltype(par)::value;
         prepare_rows(row_first + (it + 3) * kTile);  // read by the S-waves after this step's second barrier
         if (it >= 1 && it <= ntiles) {  // ---- tile `it - 1`
-          const bf16_t* Qs = reinterpret_cast<const bf16_t*>(smem + PipeLds::Q0 + buf * PipeLds::QB);
-          const bf16_t* dOs = reinterpret_cast<const bf16_t*>(smem + PipeLds::DO0 + buf * PipeLds::QB);
           const bf16_t* Pt = reinterpret_cast<const bf16_t*>(smem + PipeLds::Pt0 + buf * PipeLds::PB);
           const bf16_t* dSt = reinterpret_cast<const bf16_t*>(smem + PipeLds::DSt0 + buf * PipeLds::PB);
           // Three products of 16 MFMAs each, in this order:
@@ -767,21 +755,19 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
           constexpr int kRing = 4;
           const bf16_t* parow = Pt + (32 * sw + col) * kPStride + 8 * qh;   // rows 32 sw.. of P^T: read by this wave only
           const bf16_t* sarow = dSt + (32 * sw + col) * kPStride + 8 * qh;
-          const bf16_t* do_tr = dOs + tr_lane;
-          const bf16_t* q_tr = Qs + tr_lane;
           const bf16_t* ds_tr = dSt + tr_lane_p;
           auto operand = [&](auto opc) __attribute__((always_inline)) {
             constexpr int op = decltype(opc)::value;
-            const bf16_t* p0;
-            constexpr int step = (op >= 16 && op < 32) ? 4 * kPStride : 4 * kRowStride;
-            if constexpr (op < 16)
-              p0 = do_tr + (16 * (op >> 2) * kRowStride + 32 * (op & 3));
-            else if constexpr (op < 32)
-              p0 = ds_tr + (16 * ((op - 16) >> 1) * kPStride + 32 * (op & 1));
-            else
-              p0 = q_tr + (16 * ((op - 32) >> 2) * kRowStride + 32 * (op & 3));
-            const bf16x4 lo4 = lds_read_tr(p0);
-            const bf16x4 hi4 = lds_read_tr(p0 + step);
+            bf16x4 lo4, hi4;
+            if constexpr (op >= 16 && op < 32) {
+              const bf16_t* p0 = ds_tr + (16 * ((op - 16) >> 1) * kPStride + 32 * (op & 1));
+              lo4 = lds_read_tr(p0);
+              hi4 = lds_read_tr(p0 + 4 * kPStride);
+            } else {
+              constexpr int at = (op < 16 ? PipeLds::DO0 : PipeLds::Q0) + buf * PipeLds::QB + 16 * ((op & 15) >> 2) * kRow;
+              lo4 = lds_read_tr_at((tr_lane ^ (64 * (op & 3))) + at);
+              hi4 = lds_read_tr_at((tr_lane ^ (64 * (op & 3) + 16)) + at + 4 * kRow);
+            }
             return __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
           };
           bf16x8 ring[kRing], af[4];  // af: the "lane = row of the result" operand of the first / third product
@@ -899,7 +885,7 @@ k_bwd_pipe128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
               const bf16_t* __restrict__ dO, const float2* __restrict__ stats, const UnitRec* __restrict__ u_rec,
               const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off, const int2* __restrict__ qent,
               bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
   PipeUnit U;
   int ubase;
   if (!load_unit(P, u_rec, nu_scan, off, U, ubase, U.pos0)) return;
