@@ -1,10 +1,9 @@
 // Block selection in front of the attention path: per (token, KV head) the forced sink / most-recent blocks and
 // then the visible blocks with the highest scores (see nsa_sel_select_blocks in nsa_sel.h for the rule).
 //
-// One wavefront owns one row and looks at it in chunks of up to 1024 blocks, 16 scores per lane held in registers
-// as order-preserving unsigned keys.  The fast method (select_by_threshold) bounds the picks from below with the
+// One wavefront takes a row at a time and looks at it in chunks of up to 1024 blocks, 16 scores per lane held in registers.  The fast method (select_by_threshold) bounds the picks from below with the
 // r-th largest lane maximum, compacts the few elements above that bound into the LDS and ranks them against each
-// other: ~400 instructions per row.  Rows where too many scores tie at the bound fall back to the general method
+// other: ~530 instructions per row.  Rows where too many scores tie at the bound fall back to the general method
 // (select_by_rounds): one pick per round, each round two wave-wide reductions.  Each visible score is read from
 // HBM once, with 16-byte loads when the rows are 16-byte aligned.
 #include "common.h"
@@ -12,12 +11,19 @@
 namespace nsa {
 namespace {
 
-constexpr int kSelWaves = 4;                  // rows per workgroup
+constexpr int kSelWaves = 4;                  // wavefronts per workgroup
+// Rows of a wavefront: eight where that leaves every SIMD several wavefronts, else one.  The kernel is bound by the instructions a
+// row takes (270 vector, 260 scalar; a compute unit issues one scalar instruction a clock for its four SIMDs), and a token's
+// bounds and the row's divisions were a fifth of the scalar ones: 65536 tokens x 8 heads x 1024 blocks 399 -> 341 us, most of
+// it from that, the rest from scores compared as floats and a coarser bound.  Against this, 16 rows a wavefront cost 3 %, ending
+// the bound's search early by a branch or requesting the next row ahead (16 more registers and moves) 20 %.
+constexpr int kSelRows = 8;
+constexpr int64_t kSelManyRows = 1 << 16;
 constexpr int kChunkBlocks = 1024;            // blocks examined at a time: 16 keys per lane
 constexpr int kKeys = kChunkBlocks / 64;
 constexpr int kMaxChunks = 16;                // rows of up to 16384 blocks
 constexpr int kCandPerLane = kMaxChunks * kMaxTopk / 64;   // chunk picks each lane holds in the final selection
-constexpr int kTauLowBit = 16;                // the bound is searched on the upper 16 bits of the keys (looser, still a bound)
+constexpr int kTauLowBit = 21;                // the bound is searched on the upper 11 bits of the keys (looser, still a bound)
 constexpr int kMaxSurv = 128;                 // survivors the fast method ranks; rows with more take the general one
 
 // All four steps stay inside a row of 16 lanes (quad swaps, then mirrors of 8 and of 16 lanes), after which every
@@ -167,49 +173,74 @@ __device__ __forceinline__ int select_by_rounds(const RowInfo& R, int lane, uint
 }
 
 // ---- the fast method.  Per chunk of up to 1024 blocks:
-//   1. every lane takes the largest of its keys; tau = the r-th largest of the 64 lane maxima, found bit by bit
+//   1. every lane takes the largest of its scores; tau = the r-th largest of the 64 lane maxima, found bit by bit
 //      with ballots (scalar work).  r = want + (forced blocks) + 3, so at least `want` selectable blocks of the
-//      chunk have a key >= tau (forced blocks and the up to three blocks a 16-byte load brings along past b_vis
-//      are not masked beforehand: they are dropped in step 3), hence no block with a key < tau can be a pick;
-//   2. the elements with key >= tau ("survivors", a few more than r unless many scores tie) are compacted into
-//      an LDS list of (key, ~block) pairs;
-//   3. after all chunks every survivor counts the survivors that beat it; that rank is its output column.
-// Returns false, having written nothing, when the survivors do not fit the list.
+//      chunk have a score >= tau (forced blocks and the up to three blocks a 16-byte load brings along past b_vis
+//      are not masked beforehand: they are dropped in step 3), hence no block with a score < tau can be a pick;
+//   2. the elements not below tau ("survivors", a few more than r unless many scores tie) are compacted into
+//      an LDS list of (score, ~block) pairs;
+//   3. after all chunks the survivors' scores become order-preserving keys and every survivor counts the survivors that beat
+//      it; that rank is its output column.
+// The scores are compared as floats up to step 3, so that only the 64 maxima and the survivors are turned into keys.  A lane's
+// maximum leaves out its NaNs (or reads as -inf for one, which only lowers the bound); a NaN is not below anything and
+// survives; -0 equals +0.  chunk_survivors does steps 1 and 2; n_surv above kMaxSurv says that the survivors do not fit the list.
 template <bool kVec, int E>
 __device__ __forceinline__ void chunk_survivors(const RowInfo& R, int base, int lane, int r, uint64_t* surv, int& n_surv) {
-  uint32_t key[E];
-  load_bits<kVec, E>(R, base, lane, 0u, key);
-  uint32_t lmax = 0;
+  uint32_t x[E];
+  load_bits<kVec, E>(R, base, lane, 0xff800000u, x);
+  float lmax = -__builtin_inff();
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    // +0 turns -0 into +0 and max(., -inf) turns a NaN into -inf, as the order of the scores demands; then the
-    // sign-magnitude bits become an unsigned key of the same order (always > 0).  What was not loaded gets key 0,
-    // "nothing here".
-    const bool hole = blk_of<kVec>(base, lane, kVec ? (e & ~3) : e) >= R.b_vis;   // not loaded
-    float f = __builtin_bit_cast(float, key[e]) + 0.0f;
-    f = __builtin_fmaxf(f, -__builtin_inff());
-    const uint32_t u = __builtin_bit_cast(uint32_t, f);
-    const uint32_t k = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-    key[e] = hole ? 0u : k;
-    lmax = key[e] > lmax ? key[e] : lmax;
-  }
+  for (int e = 0; e < E; e += 2)
+    asm("v_max3_f32 %0, %0, %1, %2" : "+v"(lmax) : "v"(x[e]), "v"(x[e + 1]));
+  const uint32_t key = blk_of<kVec>(base, lane, 0) < R.b_vis ? order_key(__builtin_bit_cast(uint32_t, lmax)) : 0u;
   uint32_t tau = 0;
+#pragma unroll
   for (int bit = 31; bit >= kTauLowBit; --bit) {
     const uint32_t trial = tau | (1u << bit);
-    const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lmax >= trial));
+    const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(key >= trial));
     tau = c >= r ? trial : tau;
   }
-  const uint32_t thr = tau ? tau : 1u;     // fewer than r lanes hold anything: every loaded element survives
+  // tau as a score; below the key of -inf it is a NaN, and everything loaded survives (fewer than r lanes hold anything)
+  const float thr = __builtin_bit_cast(float, (tau & 0x80000000u) ? tau ^ 0x80000000u : ~tau);
+  const uint32_t not_blk = ~(uint32_t)blk_of<kVec>(base, lane, 0);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const bool sv = key[e] >= thr;
+    const bool loaded = blk_of<kVec>(base, lane, kVec ? (e & ~3) : e) < R.b_vis;
+    const bool sv = loaded & !(__builtin_bit_cast(float, x[e]) < thr);
     const uint64_t m = __builtin_amdgcn_ballot_w64(sv);
-    if (m != 0) {
-      const int pos = n_surv + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-      if (sv && pos < kMaxSurv)
-        surv[pos] = ((uint64_t)key[e] << 32) | (uint32_t)~(uint32_t)blk_of<kVec>(base, lane, e);
-      n_surv += __builtin_popcountll(m);
+    // (a list that overflows is discarded: its writes only have to stay inside the wavefront's LDS)
+    const int at = min(n_surv, kMaxChunks * kMaxTopk - 64);
+    const int pos = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)at));
+    if (sv) {
+      uint32_t* to = reinterpret_cast<uint32_t*>(surv + pos);
+      to[0] = not_blk - (uint32_t)blk_of<kVec>(0, 0, e);
+      to[1] = x[e];
     }
+    n_surv += __builtin_popcountll(m);
+  }
+}
+
+// Step 3: the survivors' columns.
+__device__ __forceinline__ void rank_survivors(const RowInfo& R, int lane, uint64_t* surv, int n_surv, int32_t* out_row) {
+  // keys in place of the scores; 0 for what may not be picked, forced blocks and blocks past the visible range, and for the
+  // entries that fill the list up to a multiple of eight
+  for (int q = lane; q < ((n_surv + 7) & ~7); q += 64) {
+    const uint64_t v = surv[q];
+    const int b = (int)~(uint32_t)v;
+    surv[q] = q >= n_surv || b >= R.b_vis || R.forced(b) ? 0 : ((uint64_t)order_key((uint32_t)(v >> 32)) << 32) | (uint32_t)v;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  for (int q0 = 0; q0 < n_surv; q0 += 64) {
+    const int q = q0 + lane;
+    const uint64_t my = q < n_surv ? surv[q] : 0;
+    int rank = 0;
+    for (int s = 0; s < n_surv; s += 8) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) rank += surv[s + i] > my ? 1 : 0;   // same address in every lane: a broadcast
+    }
+    if (my != 0 && rank < R.want) out_row[R.n_forced + rank] = (int32_t)~(uint32_t)my;
   }
 }
 
@@ -227,19 +258,7 @@ __device__ __forceinline__ bool select_by_threshold(const RowInfo& R, int lane, 
     else chunk_survivors<kVec, 4>(R, base, lane, r, surv, n_surv);
     if (n_surv > kMaxSurv) return false;
   }
-  // drop what may not be picked: forced blocks and blocks past the visible range
-  for (int q = lane; q < n_surv; q += 64) {
-    const int b = (int)~(uint32_t)surv[q];
-    if (b >= R.b_vis || R.forced(b)) surv[q] = 0;
-  }
-  for (int q0 = 0; q0 < n_surv; q0 += 64) {
-    const int q = q0 + lane;
-    const uint64_t my = q < n_surv ? surv[q] : 0;
-    int rank = 0;
-#pragma unroll 4
-    for (int s = 0; s < n_surv; ++s) rank += surv[s] > my ? 1 : 0;   // same address in every lane: a broadcast
-    if (my != 0 && rank < R.want) out_row[R.n_forced + rank] = (int32_t)~(uint32_t)my;
-  }
+  rank_survivors(R, lane, surv, n_surv, out_row);
   return true;
 }
 
@@ -248,47 +267,60 @@ __device__ __forceinline__ bool select_by_threshold(const RowInfo& R, int lane, 
 template <bool kVec>
 __global__ void __launch_bounds__(64 * kSelWaves)
 k_select_blocks(const float* __restrict__ scores, int64_t stride, const int32_t* __restrict__ cu, int T, int nseq,
-                int hkv, int bk, int topk, int causal, int n_sink, int n_local, int32_t* __restrict__ idx) {
+                int hkv, int bk, int topk, int causal, int n_sink, int n_local, int per, int32_t* __restrict__ idx) {
   // per wavefront: the survivor list of the fast method, or the chunk picks of the general one
   __shared__ uint64_t lds[kSelWaves][kMaxChunks * kMaxTopk];
   static_assert(kMaxSurv <= kMaxChunks * kMaxTopk, "survivor list must fit");
-  const int lane = threadIdx.x & 63;
+  int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t row = (int64_t)blockIdx.x * kSelWaves + w;
-  if (row >= (int64_t)T * hkv) return;     // whole wavefront leaves together
-  const int t = (int)(row / hkv);
-  int s, c0, c1;
-  seq_bounds(cu, nseq, T, t, s, c0, c1);
-  const int cur = (t - c0) / bk;
-  const int b_s = (c1 - c0 + bk - 1) / bk;
+  // `per` consecutive rows a wavefront (T * hkv < 2^31 is checked on the host); what they share, a token's bounds, is worked out
+  // once per token
+  const uint32_t rows = (uint32_t)T * (uint32_t)hkv, first = ((uint32_t)blockIdx.x * kSelWaves + w) * (uint32_t)per;
+  if (first >= rows) return;               // whole wavefront leaves together
+  const uint32_t end = min(first + (uint32_t)per, rows);
+  int t = (int)(first / (uint32_t)hkv), j = (int)(first - (uint32_t)t * (uint32_t)hkv), t_known = -1;
   RowInfo R;
-  R.b_vis = causal ? (cur + 1 < b_s ? cur + 1 : b_s) : b_s;
-  if ((int64_t)R.b_vis > stride) R.b_vis = (int)stride;   // never read past a row, whatever cu says
-  // forced blocks: sinks 0 .. ns-1, then cur - r0, cur - r0 - 1, ... (nl of them, all >= ns and < b_vis)
-  R.ns = n_sink < R.b_vis ? n_sink : R.b_vis;
-  const int r0 = cur - R.b_vis + 1 > 0 ? cur - R.b_vis + 1 : 0;
-  const int r_last = n_local - 1 < cur - R.ns ? n_local - 1 : cur - R.ns;
-  R.nl = r_last - r0 + 1 > 0 ? r_last - r0 + 1 : 0;
-  R.loc_hi = cur - r0;
-  R.loc_lo = R.loc_hi - R.nl + 1;
-  R.n_forced = R.ns + R.nl < topk ? R.ns + R.nl : topk;
-  R.want = topk - R.n_forced;
-  R.srow = scores + row * stride;
-  int32_t* out_row = idx + row * topk;
-
-  int mine = -1;                           // lane i holds column i of the output row: forced blocks, then -1
-  if (lane < R.n_forced) mine = lane < R.ns ? lane : R.loc_hi - (lane - R.ns);
-  const int n_free = R.b_vis - R.ns - R.nl;                  // selectable blocks
-  int n_picks = R.want < n_free ? R.want : n_free;           // columns the selection fills
-  bool by_rank = true;                     // pick columns already written, each by the lane that ranked there
-  if (n_picks > 0 && scores == nullptr) {
-    n_picks = 0;                           // forced blocks only: the rest of the row is padding
+  R.srow = scores + (int64_t)first * stride;
+  int32_t* out_row = idx + (int64_t)first * topk;
+#pragma unroll 1
+  for (uint32_t row = first; row < end; ++row, R.srow += stride, out_row += topk) {
+    asm volatile("" : "+v"(lane));         // what derives from it is not kept in registers from row to row
+    if (t != t_known) {
+      t_known = t;
+      int s, c0, c1;
+      seq_bounds(cu, nseq, T, t, s, c0, c1);
+      const int cur = (t - c0) / bk;
+      const int b_s = (c1 - c0 + bk - 1) / bk;
+      R.b_vis = causal ? (cur + 1 < b_s ? cur + 1 : b_s) : b_s;
+      if ((int64_t)R.b_vis > stride) R.b_vis = (int)stride;   // never read past a row, whatever cu says
+      // forced blocks: sinks 0 .. ns-1, then cur - r0, cur - r0 - 1, ... (nl of them, all >= ns and < b_vis)
+      R.ns = n_sink < R.b_vis ? n_sink : R.b_vis;
+      const int r0 = cur - R.b_vis + 1 > 0 ? cur - R.b_vis + 1 : 0;
+      const int r_last = n_local - 1 < cur - R.ns ? n_local - 1 : cur - R.ns;
+      R.nl = r_last - r0 + 1 > 0 ? r_last - r0 + 1 : 0;
+      R.loc_hi = cur - r0;
+      R.loc_lo = R.loc_hi - R.nl + 1;
+      R.n_forced = R.ns + R.nl < topk ? R.ns + R.nl : topk;
+      R.want = topk - R.n_forced;
+    }
+    if (++j == hkv) {
+      j = 0;
+      ++t;
+    }
+    int mine = -1;                           // lane i holds column i of the output row: forced blocks, then -1
+    if (lane < R.n_forced) mine = lane < R.ns ? lane : R.loc_hi - (lane - R.ns);
+    const int n_free = R.b_vis - R.ns - R.nl;                  // selectable blocks
+    int n_picks = R.want < n_free ? R.want : n_free;           // columns the selection fills
+    bool by_rank = true;                     // pick columns already written, each by the lane that ranked there
+    if (n_picks > 0 && scores == nullptr) {
+      n_picks = 0;                           // forced blocks only: the rest of the row is padding
+    }
+    if (n_picks > 0) {
+      by_rank = select_by_threshold<kVec>(R, lane, lds[w], out_row);
+      if (!by_rank) mine = select_by_rounds<kVec>(R, lane, reinterpret_cast<uint32_t*>(lds[w]), mine);
+    }
+    if (lane < topk && (!by_rank || lane < R.n_forced || lane >= R.n_forced + n_picks)) out_row[lane] = mine;
   }
-  if (n_picks > 0) {
-    by_rank = select_by_threshold<kVec>(R, lane, lds[w], out_row);
-    if (!by_rank) mine = select_by_rounds<kVec>(R, lane, reinterpret_cast<uint32_t*>(lds[w]), mine);
-  }
-  if (lane < topk && (!by_rank || lane < R.n_forced || lane >= R.n_forced + n_picks)) out_row[lane] = mine;
 }
 
 }  // namespace nsa
@@ -309,7 +341,8 @@ extern "C" int nsa_sel_select_blocks(const nsa_sel_shape* shape, const float* sc
   const int64_t rows = (int64_t)shape->total_tokens * shape->hkv;
   if (rows == 0) return NSA_SEL_OK;
   if (rows * shape->topk >= ((int64_t)1 << 31)) return NSA_SEL_EUNSUPPORTED;
-  const int64_t grid = (rows + kSelWaves - 1) / kSelWaves;
+  const int per = rows >= kSelManyRows ? kSelRows : 1;
+  const int64_t grid = (rows + kSelWaves * per - 1) / (kSelWaves * per);
   if (grid >= ((int64_t)1 << 31)) return NSA_SEL_EUNSUPPORTED;
   hipStream_t st = (hipStream_t)stream;
   ProfScope prof(KID_SELECT_BLOCKS, st);
@@ -317,6 +350,6 @@ extern "C" int nsa_sel_select_blocks(const nsa_sel_shape* shape, const float* sc
   auto kern = vec ? k_select_blocks<true> : k_select_blocks<false>;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * kSelWaves), 0, st, scores, score_stride, cu_seqlens,
                      shape->total_tokens, shape->nseq, shape->hkv, shape->block, shape->topk, shape->causal ? 1 : 0,
-                     (int)n_sink, (int)n_local, idx);
+                     (int)n_sink, (int)n_local, per, idx);
   return hipGetLastError() == hipSuccess ? NSA_SEL_OK : NSA_SEL_EHIP;
 }

@@ -170,3 +170,21 @@ def test_argument_errors():
     assert L.nsa_sel_select_blocks(C.byref(shape2), p(x), 8, None, 1, 2, p(out), None) == -1   # nseq > 1 needs cu
     shape3 = nsa.Shape(0, 1, 1, 1, 128, 64, 4, 1, 0.0, 0)
     assert L.nsa_sel_select_blocks(C.byref(shape3), p(x), 8, None, 1, 2, p(out), None) == 0     # nothing to do
+
+
+@pytest.mark.parametrize("seqlens,hkv,topk,causal,kind,stride", [
+    ([13000, 1, 107], 5, 16, True, "wild", None),     # 65540 rows: eight a wavefront, the last wavefront with four
+    ([13000, 107], 5, 16, True, "wild", 207),         # 65535 rows: one a wavefront
+    ([21846], 3, 32, False, "wild", None),            # a wavefront's rows begin and end inside a token
+    ([70000], 1, 1, True, "ties", 1099),              # eight tokens a wavefront, two chunks
+])
+def test_rows_of_a_wavefront(seqlens, hkv, topk, causal, kind, stride):
+    """From 65536 rows a wavefront takes eight, and scores are compared as floats: infinities, NaN, both zeros and denormals.
+    Oracle on sampled tokens."""
+    print("case rows of a wavefront", seqlens, hkv, topk, causal, kind, stride, flush=True)
+    cu, n = _cu(seqlens), sum(seqlens)
+    x = wl.draw_block_scores(35, seqlens, hkv, kind=kind, stride=stride, trap_future=causal)
+    tokens = np.unique(np.concatenate([np.random.default_rng(9).integers(0, n, 200), np.arange(n - 12, n), np.arange(12)]))
+    ref = tko.select_blocks(x, cu, topk, causal=causal, tokens=tokens)
+    got = _gpu_select(x, cu, topk, causal=causal)
+    assert np.array_equal(got[tokens], ref[tokens])
