@@ -9,7 +9,7 @@
 //                     P.unit list entries): four wavefronts and half of a CU's LDS, so two workgroups share a CU and
 //                     cover each other's barriers and waits.  The waves share tiles of 64 gathered rows and take three
 //                     roles per tile (see the comment above the kernel): S = Q K_i^T, dP = dO V_i^T,
-//                     P = exp(S - LSE), dS = P (dP - delta); then dV_i += P^T dO and dK_i += dS^T Q
+//                     P = exp(S - LSE), dS = P (dP - delta) scale; then dV_i += P^T dO and dK_i += dS^T Q
 //                     (accumulators in registers for the whole unit) and dQ^T = K_i^T dS^T.  Operands are row-major
 //                     tiles in LDS; "lane = column" operands are LDS transpose reads.  Partial dQ rows go to the
 //                     compact buffer at the rows' list position; the unit's dK_i, dV_i go out as bf16 (list fitted
@@ -118,8 +118,10 @@ k_bwd_delta(Problem P, const bf16_t* __restrict__ O, const bf16_t* __restrict__ 
 //               tiles and stores that part of dQ
 // K_i, Q, dO (turned rows of 256 bytes, see row_turn) and P^T, dS^T (144-byte pitch) are row-major tiles in LDS; "lane =
 // column" operands are LDS transpose reads.  The S product starts from -LSE / scale and the dP product from -delta of its rows, so
-// that P = 2^(S scale log2 e) and dS = P dP need no subtraction; dS, dK and dQ go without the softmax scale, which dK
-// gets when the unit is done and dQ in the reduction; keys are hidden in a branch that tiles seeing the whole block skip.  The list's token ids are kept in LDS 1024 entries at a time.
+// that P = 2^(S scale log2 e) and dS = P dP scale need no subtraction; keys are hidden in a branch that tiles seeing the
+// whole block skip.  Of the softmax scale = scale_m scale_2, scale_2 a power of two, dS carries scale_m only; dK gets scale_2
+// when the unit is done, dQ in the reduction.  (Left out altogether the scale would move what is rounded to bf16 by half an octave:
+// dQ of normal inputs at scale 1 / sqrt(128) came out 4 % further from the exact one.)  The list's token ids are kept in LDS 1024 entries at a time.
 // A row's place in memory is worked out once, by the lane that owns it, one tile before its loads are issued, and handed
 // to the lanes that move it; rows move through buffer instructions without branches (see RowTensor), so the wait for a
 // tile's rows does not wait for the stores of the tile before.  That took 40 % of the vector instructions out of the loop
@@ -325,7 +327,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             p[c] = sacc[4 * a + c];
-            ds[c] = p[c] * dpacc[4 * a + c];  // P (dP - delta)
+            ds[c] = p[c] * (dpacc[4 * a + c] * P.scale_m);  // P (dP - delta) scale_m
           }
           uint2 pw, sw2;
           pw.x = pack_bf16x2(p[0], p[1]);
@@ -408,7 +410,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
       for (int v = 0; v < 16; ++v) {
         const int key = 32 * rb + 8 * (v >> 2) + 4 * qh + (v & 3);
         if (key < blen) {
-          outk[(size_t)key * P.hkv * kD] = (bf16_t)(dkacc[cb][v] * P.scale);
+          outk[(size_t)key * P.hkv * kD] = (bf16_t)(dkacc[cb][v] * P.scale_2);
           outv[(size_t)key * P.hkv * kD] = (bf16_t)dvacc[cb][v];
         }
       }
@@ -423,7 +425,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int key = 32 * rb + 8 * (v >> 2) + 4 * qh + (v & 3);
-      outk[key * kD] = dkacc[cb][v] * P.scale;
+      outk[key * kD] = dkacc[cb][v] * P.scale_2;
       outv[key * kD] = dvacc[cb][v];
     }
   }
@@ -435,7 +437,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 // accumulation), MFMA, VALU and LDS time add up and every LDS read waits out its latency: two waves per SIMD cannot
 // cover each other.  Here the waves specialise and work one tile apart:
 //   waves 0-3 (S-waves, one per SIMD): wave w keeps the K and V fragments of keys 32 w.. in registers and computes, for
-//       the 64 rows of tile n, S = Q K^T, dP = dO V^T, P = exp(S - LSE), dS = P (dP - delta), and writes
+//       the 64 rows of tile n, S = Q K^T, dP = dO V^T, P = exp(S - LSE), dS = P (dP - delta) scale_m, and writes
 //       P^T, dS^T (bf16, [key][row]) to LDS; they also request and stage the gathered Q / dO rows;
 //   waves 4-7 (A-waves, the other wave of each SIMD): wave a keeps the fp32 dK, dV accumulators of keys 32 a.. (all 128
 //       channels) and the K^T fragments of channels 32 a.., and for tile n - 1 computes dV += P^T dO, then
@@ -446,7 +448,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 // tile order the hand-over.  Rows are requested three tiles ahead into two register sets and staged after the second
 // barrier.  Measured at 65536 tokens, g = 4, (128, 8): 3.5 ms against 4.1 ms for the eight-waves-in-step kernel, 3.3 ms
 // since rows move by buffer instructions (no 64-bit address per access on the P/dS waves' staging path), 3.30 -> 3.20 ms with
-// turned rows, the softmax scale out of dS and one compare a key.  The masks in a branch instead (3.25 ms) or products that
+// turned rows and one compare a key.  The masks in a branch instead (3.25 ms) or products that
 // start from the row statistics as in the 64-key kernel (+1.5 %) break up the order the P/dS waves' steps are issued in.
 struct PipeLds {
   static constexpr int Row = kD * 2;
@@ -458,7 +460,7 @@ struct PipeLds {
   static constexpr int DSt0 = Pt0 + 2 * PB;
   static constexpr int Ent = DSt0 + 2 * PB;
   static constexpr int St0 = Ent + kEntSeg * 4;       // per-row records of a staged tile, two buffers: three arrays
-  static constexpr int SB = 3 * kTile * 4;            // of 64: LSE (log2 domain), delta, visible key range
+  static constexpr int SB = 3 * kTile * 4;            // of 64: LSE (log2 domain), delta * scale_m, visible key range
   static constexpr int Tb0 = St0 + 2 * SB;            // per row of the tile to request next: row of Q / dO, place in
   static constexpr int Bytes = Tb0 + kTile * 12;      // the kv head's statistics, visible keys; 145664 in all
 };
@@ -603,7 +605,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
     if ((tid & 3) == 0) {
       float* rec = reinterpret_cast<float*>(smem + PipeLds::St0 + buf * PipeLds::SB) + ((tid & 255) >> 2);
       rec[0] = st_set[set].x;
-      rec[kTile] = st_set[set].y;
+      rec[kTile] = st_set[set].y * P.scale_m;
       reinterpret_cast<int*>(rec)[2 * kTile] = vis_set[set];
     }
   };
@@ -679,7 +681,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
               pv[rb][4 * a + c] = seen ? __builtin_amdgcn_exp2f(fmaf(sacc[rb][4 * a + c], c2, -lse4[c])) : 0.f;
             }
           };
-          auto emit = [&](int rb, int st) __attribute__((always_inline)) {  // dS = P (dP - delta); bf16 to LDS
+          auto emit = [&](int rb, int st) __attribute__((always_inline)) {  // dS = P (dP - delta) scale_m; bf16 to LDS
             const int a = st >> 1, r4 = 32 * rb + 8 * a + 4 * qh;
             if ((st & 1) == 0) {
               dl4 = *reinterpret_cast<const f32x4*>(rec + kTile + r4);
@@ -690,7 +692,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
             } else {
               float ds[4];
 #pragma unroll
-              for (int c = 0; c < 4; ++c) ds[c] = pv[rb][4 * a + c] * (dpacc[rb][4 * a + c] - dl4[c]);
+              for (int c = 0; c < 4; ++c) ds[c] = pv[rb][4 * a + c] * fmaf(dpacc[rb][4 * a + c], P.scale_m, -dl4[c]);
               uint2 sw2;
               sw2.x = pack_bf16x2(ds[0], ds[1]);
               sw2.y = pack_bf16x2(ds[2], ds[3]);
@@ -857,7 +859,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
         for (int v = 0; v < 16; ++v) {
           const int key = 32 * sw + 8 * (v >> 2) + 4 * qh + (v & 3);
           if (key < blen) {
-            outk[(size_t)key * P.hkv * kD] = (bf16_t)(dkacc[cb][v] * P.scale);
+            outk[(size_t)key * P.hkv * kD] = (bf16_t)(dkacc[cb][v] * P.scale_2);
             outv[(size_t)key * P.hkv * kD] = (bf16_t)dvacc[cb][v];
           }
         }
@@ -872,7 +874,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int key = 32 * sw + 8 * (v >> 2) + 4 * qh + (v & 3);
-        outk[key * kD] = dkacc[cb][v] * P.scale;
+        outk[key * kD] = dkacc[cb][v] * P.scale_2;
         outv[key * kD] = dvacc[cb][v];
       }
     }
@@ -937,7 +939,7 @@ k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const int32_t* __r
       }
     }
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] *= P.scale;
+    for (int c = 0; c < 8; ++c) acc[c] *= P.scale_2;
     out[q * kThreads] = u32x4{pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]), pack_bf16x2(acc[4], acc[5]),
                               pack_bf16x2(acc[6], acc[7])};
     R = R_next;

@@ -91,7 +91,7 @@ def test_two_calls_share_nothing_but_the_index():
 @pytest.mark.parametrize("block", [64, 128])
 @pytest.mark.parametrize("scale", [1e-30, 1e-6, 0.3])
 def test_backward_far_scales(scale, block):
-    """The 64-key kernel starts its products from LSE / scale and both kernels leave the scale out of dS: a tiny scale (P is
+    """The 64-key kernel starts its products from LSE / scale, and both kernels leave the scale's power of two out of dS: a tiny scale (P is
     uniform) and a large one (P nearly one-hot).  dQ and dK carry it as a factor and are compared with the default scale in its
     place: that is what the tolerance, a bound on sums of rounded dS times it, was stated for."""
     print("case far scale", scale, block, flush=True)
