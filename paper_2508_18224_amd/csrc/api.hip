@@ -54,8 +54,8 @@ static IndexLayout make_layout(const nsa_sel_shape* s) {
   L.unit = s->unit != 0 ? s->unit : work_unit_entries(L.p_max, L.topk, s->hq / s->hkv, s->block);
   L.units_max = (int32_t)units_bound(L.hkv, L.b_cap, L.T, L.topk, L.unit);
   // dense route: on request, or by default where it pays: with g = 1 a (tile, kv head) has only 64 rows to share a
-  // K / V piece, which costs more than the gather route saves (measured: +4 % per step at g = 1, -2 % .. -9 % at
-  // g = 4 .. 8), unless the call is the sliding-window branch, where every pair is dense
+  // K / V piece, which costs more than the gather route saves (measured per step: +7 % .. +10 % at g = 1, even
+  // at g = 2, -2 % .. -9 % at g = 4 .. 8), unless the call is the sliding-window branch, where every pair is dense
   // (and not for inputs so small that the step is a few launch latencies: below 2^18 (token, kv head, column) triples)
   L.dense = s->dense == 1 || (s->dense == 0 && L.p_max >= (1 << 18) && (s->hq / s->hkv >= 2 || s->window > 0)) ? 1 : 0;
   size_t o = 0;
