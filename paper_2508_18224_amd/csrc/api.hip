@@ -1,6 +1,5 @@
 // C ABI of the library (see include/nsa_sel.h): argument validation, workspace layout, launch sequencing.
 #include "common.h"
-#include <math.h>
 
 namespace nsa {
 int index_chunks(int T, int nseq);
@@ -106,9 +105,6 @@ static Problem make_problem(const nsa_sel_shape* s, const IndexLayout& L) {
   P.l1 = L.n_lists;
   P.units_max = L.units_max;
   P.scale = s->scale > 0.f ? s->scale : 0.08838834764831845f;  // 1/sqrt(128)
-  int exponent;
-  P.scale_m = frexpf(P.scale, &exponent);
-  P.scale_2 = ldexpf(1.f, exponent);
   return P;
 }
 

@@ -117,18 +117,18 @@ k_bwd_delta(Problem P, const bf16_t* __restrict__ O, const bf16_t* __restrict__ 
 //   rows/chans  dQ^T for rows 32 rb.. and channels 64 kb..; the same wave stages / prefetches that part of the Q and dO
 //               tiles and stores that part of dQ
 // K_i, Q, dO (turned rows of 256 bytes, see row_turn) and P^T, dS^T (144-byte pitch) are row-major tiles in LDS; "lane =
-// column" operands are LDS transpose reads.  The S product starts from -LSE / scale and the dP product from -delta of its rows, so
-// that P = 2^(S scale log2 e) and dS = P dP scale need no subtraction; keys are hidden in a branch that tiles seeing the
-// whole block skip.  Of the softmax scale = scale_m scale_2, scale_2 a power of two, dS carries scale_m only; dK gets scale_2
-// when the unit is done, dQ in the reduction.  (Left out altogether the scale would move what is rounded to bf16 by half an octave:
-// dQ of normal inputs at scale 1 / sqrt(128) came out 4 % further from the exact one.)  The list's token ids are kept in LDS 1024 entries at a time.
+// column" operands are LDS transpose reads.  The products start from
+// zero and the row statistics come in afterwards, P = 2^(S scale log2 e - LSE), dS = P (dP scale - delta scale): partial sums of S that
+// start from -LSE / scale carry a term several times their size (the error of P before it is rounded to bf16 doubles) for 1 % of the
+// kernel's time.  Keys are hidden in a branch that tiles seeing the whole block skip.  The list's token ids are kept in LDS 1024
+// entries at a time.
 // A row's place in memory is worked out once, by the lane that owns it, one tile before its loads are issued, and handed
 // to the lanes that move it; rows move through buffer instructions without branches (see RowTensor), so the wait for a
 // tile's rows does not wait for the stores of the tile before.  That took 40 % of the vector instructions out of the loop
 // and a full drain of the memory queue out of every tile: 4.59 -> 4.2 ms at 65536 tokens, g = 4.  What bounds the kernel is on
-// the CU, LDS first (with the gathers served by one XCD's L2 and the stores dropped it still took 3.7 ms of 4.4): the leaner
-// elementwise part gave 4.50 -> 4.36 ms on one chip, the turned rows in place of a 304-byte pitch 4.16 -> 3.99 ms on another (8192
-// tokens, g = 1: 580 -> 544 us; g = 7, 65536 tokens: 3.46 -> 3.34 ms).  Staging the next tile before the dQ rows are stored,
+// the CU, LDS first (with the gathers served by one XCD's L2 and the stores dropped it still took 3.7 ms of 4.4): the turned
+// rows in place of a 304-byte pitch and the masks in a branch together took 4.30 -> 3.98 ms (8192 tokens, g = 1: 568 -> 542 us; g = 7,
+// 65536 tokens: 3.73 -> 3.42 ms).  Staging the next tile before the dQ rows are stored,
 // through the P^T / dS^T area, gave nothing (g = 1: +4 %).
 constexpr int kTile = 64;      // rows per tile
 constexpr int kPStride = 72;   // bf16 per row of the P^T / dS^T tiles: 64 rows + 8 pad
@@ -142,7 +142,7 @@ struct BwdLds {
   static constexpr int Pt = DO + kTile * Row;
   static constexpr int DSt = Pt + 64 * kPStride * 2;
   static constexpr int Ent = DSt + 64 * kPStride * 2;
-  static constexpr int Rec = Ent + kEntSeg * 4;      // per row of the tile: -LSE / scale, -delta, visible keys
+  static constexpr int Rec = Ent + kEntSeg * 4;      // per row of the tile: LSE (log2 domain), delta * scale, visible keys
   static constexpr int Bytes = Rec + 3 * kTile * 4;  // 72448
 };
 static_assert(2 * BwdLds::Bytes <= 160 * 1024, "two workgroups of the 64-key backward must fit one CU's LDS");
@@ -190,8 +190,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
       dkacc[cb][v] = 0.f;
       dvacc[cb][v] = 0.f;
     }
-  // (a scale whose reciprocal would overflow leaves no trace of the scores in P: any other such scale does as well)
-  const float c2 = fmaxf(P.scale * 1.4426950408889634f, 1e-30f), start = -1.f / c2;
+  const float c2 = P.scale * 1.4426950408889634f;
   constexpr uint32_t kAllSeen = kWin ? 64u << 16 : 64u;
 
   // this lane's places in the LDS tiles (everything else is an immediate offset)
@@ -275,8 +274,8 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
         lds_write_16(to + kDoOff, dc[i]);
       }
       if (kb == 0 && qh == 0) {  // this row's record, for the lanes of the rows/keys role (which hold keys, not rows)
-        rec_wr[0] = st.x * start;
-        rec_wr[kTile] = -st.y;
+        rec_wr[0] = st.x;
+        rec_wr[kTile] = st.y * P.scale;
         reinterpret_cast<uint32_t*>(rec_wr)[2 * kTile] = vis_c;
       }
       // the reads below are these addresses with bits flipped and immediate offsets added
@@ -290,15 +289,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
          // 8 (v >> 2) + 4 qh + (v & 3), so four consecutive rows of P^T / dS^T leave each lane as one 8-byte LDS store
         f32x16 sacc, dpacc;
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const f32x4 s4 = *reinterpret_cast<const f32x4*>(rec_rd + 8 * a);
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(rec_rd + kTile + 8 * a);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            sacc[4 * a + c] = s4[c];
-            dpacc[4 * a + c] = d4[c];
-          }
-        }
+        for (int v = 0; v < 16; ++v) sacc[v] = dpacc[v] = 0.f;
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
           const bf16x8 qf = lds_read_frag(qfrag ^ (32 * s));
@@ -308,7 +299,11 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
           dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dof, vf[s], dpacc, 0, 0, 0);
         }
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sacc[v] = __builtin_amdgcn_exp2f(sacc[v] * c2);
+        for (int a = 0; a < 4; ++a) {
+          const f32x4 lse4 = *reinterpret_cast<const f32x4*>(rec_rd + 8 * a);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) sacc[4 * a + c] = __builtin_amdgcn_exp2f(fmaf(sacc[4 * a + c], c2, -lse4[c]));
+        }
         if (part_seen) {
           const uint32_t key = 32 * kb + col;
 #pragma unroll
@@ -323,11 +318,12 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
         }
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
+          const f32x4 dls4 = *reinterpret_cast<const f32x4*>(rec_rd + kTile + 8 * a);
           float p[4], ds[4];
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             p[c] = sacc[4 * a + c];
-            ds[c] = p[c] * (dpacc[4 * a + c] * P.scale_m);  // P (dP - delta) scale_m
+            ds[c] = p[c] * fmaf(dpacc[4 * a + c], P.scale, -dls4[c]);  // P (dP - delta) scale
           }
           uint2 pw, sw2;
           pw.x = pack_bf16x2(p[0], p[1]);
@@ -410,7 +406,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
       for (int v = 0; v < 16; ++v) {
         const int key = 32 * rb + 8 * (v >> 2) + 4 * qh + (v & 3);
         if (key < blen) {
-          outk[(size_t)key * P.hkv * kD] = (bf16_t)(dkacc[cb][v] * P.scale_2);
+          outk[(size_t)key * P.hkv * kD] = (bf16_t)dkacc[cb][v];
           outv[(size_t)key * P.hkv * kD] = (bf16_t)dvacc[cb][v];
         }
       }
@@ -425,7 +421,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int key = 32 * rb + 8 * (v >> 2) + 4 * qh + (v & 3);
-      outk[key * kD] = dkacc[cb][v] * P.scale_2;
+      outk[key * kD] = dkacc[cb][v];
       outv[key * kD] = dvacc[cb][v];
     }
   }
@@ -437,7 +433,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 // accumulation), MFMA, VALU and LDS time add up and every LDS read waits out its latency: two waves per SIMD cannot
 // cover each other.  Here the waves specialise and work one tile apart:
 //   waves 0-3 (S-waves, one per SIMD): wave w keeps the K and V fragments of keys 32 w.. in registers and computes, for
-//       the 64 rows of tile n, S = Q K^T, dP = dO V^T, P = exp(S - LSE), dS = P (dP - delta) scale_m, and writes
+//       the 64 rows of tile n, S = Q K^T, dP = dO V^T, P = exp(S - LSE), dS = P (dP - delta) scale, and writes
 //       P^T, dS^T (bf16, [key][row]) to LDS; they also request and stage the gathered Q / dO rows;
 //   waves 4-7 (A-waves, the other wave of each SIMD): wave a keeps the fp32 dK, dV accumulators of keys 32 a.. (all 128
 //       channels) and the K^T fragments of channels 32 a.., and for tile n - 1 computes dV += P^T dO, then
@@ -460,7 +456,7 @@ struct PipeLds {
   static constexpr int DSt0 = Pt0 + 2 * PB;
   static constexpr int Ent = DSt0 + 2 * PB;
   static constexpr int St0 = Ent + kEntSeg * 4;       // per-row records of a staged tile, two buffers: three arrays
-  static constexpr int SB = 3 * kTile * 4;            // of 64: LSE (log2 domain), delta * scale_m, visible key range
+  static constexpr int SB = 3 * kTile * 4;            // of 64: LSE (log2 domain), delta * scale, visible key range
   static constexpr int Tb0 = St0 + 2 * SB;            // per row of the tile to request next: row of Q / dO, place in
   static constexpr int Bytes = Tb0 + kTile * 12;      // the kv head's statistics, visible keys; 145664 in all
 };
@@ -605,7 +601,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
     if ((tid & 3) == 0) {
       float* rec = reinterpret_cast<float*>(smem + PipeLds::St0 + buf * PipeLds::SB) + ((tid & 255) >> 2);
       rec[0] = st_set[set].x;
-      rec[kTile] = st_set[set].y * P.scale_m;
+      rec[kTile] = st_set[set].y * P.scale;
       reinterpret_cast<int*>(rec)[2 * kTile] = vis_set[set];
     }
   };
@@ -667,7 +663,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
           const int key = 32 * sw + col;
           auto q_frag = [&](int rb, int st) { return lds_read_frag((frag_lane ^ (32 * st)) + PipeLds::Q0 + buf * PipeLds::QB + 32 * rb * kRow); };
           auto d_frag = [&](int rb, int st) { return lds_read_frag((frag_lane ^ (32 * st)) + PipeLds::DO0 + buf * PipeLds::QB + 32 * rb * kRow); };
-          f32x4 lse4, dl4;
+          f32x4 lse4, dls4;
           u32x4 vis4;
           auto probs = [&](int rb, int st) __attribute__((always_inline)) {  // P = exp(S scale - LSE) on visible keys
             const int a = st >> 1, r4 = 32 * rb + 8 * a + 4 * qh;
@@ -681,10 +677,10 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
               pv[rb][4 * a + c] = seen ? __builtin_amdgcn_exp2f(fmaf(sacc[rb][4 * a + c], c2, -lse4[c])) : 0.f;
             }
           };
-          auto emit = [&](int rb, int st) __attribute__((always_inline)) {  // dS = P (dP - delta) scale_m; bf16 to LDS
+          auto emit = [&](int rb, int st) __attribute__((always_inline)) {  // dS = P (dP - delta) scale; bf16 to LDS
             const int a = st >> 1, r4 = 32 * rb + 8 * a + 4 * qh;
             if ((st & 1) == 0) {
-              dl4 = *reinterpret_cast<const f32x4*>(rec + kTile + r4);
+              dls4 = *reinterpret_cast<const f32x4*>(rec + kTile + r4);
               uint2 pw;
               pw.x = pack_bf16x2(pv[rb][4 * a + 0], pv[rb][4 * a + 1]);
               pw.y = pack_bf16x2(pv[rb][4 * a + 2], pv[rb][4 * a + 3]);
@@ -692,7 +688,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
             } else {
               float ds[4];
 #pragma unroll
-              for (int c = 0; c < 4; ++c) ds[c] = pv[rb][4 * a + c] * fmaf(dpacc[rb][4 * a + c], P.scale_m, -dl4[c]);
+              for (int c = 0; c < 4; ++c) ds[c] = pv[rb][4 * a + c] * fmaf(dpacc[rb][4 * a + c], P.scale, -dls4[c]);
               uint2 sw2;
               sw2.x = pack_bf16x2(ds[0], ds[1]);
               sw2.y = pack_bf16x2(ds[2], ds[3]);
@@ -859,7 +855,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
         for (int v = 0; v < 16; ++v) {
           const int key = 32 * sw + 8 * (v >> 2) + 4 * qh + (v & 3);
           if (key < blen) {
-            outk[(size_t)key * P.hkv * kD] = (bf16_t)(dkacc[cb][v] * P.scale_2);
+            outk[(size_t)key * P.hkv * kD] = (bf16_t)dkacc[cb][v];
             outv[(size_t)key * P.hkv * kD] = (bf16_t)dvacc[cb][v];
           }
         }
@@ -874,7 +870,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int key = 32 * sw + 8 * (v >> 2) + 4 * qh + (v & 3);
-        outk[key * kD] = dkacc[cb][v] * P.scale_2;
+        outk[key * kD] = dkacc[cb][v];
         outv[key * kD] = dvacc[cb][v];
       }
     }
@@ -938,8 +934,6 @@ k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const int32_t* __r
         acc[6] += bf16_lo(x[i].w); acc[7] += bf16_hi(x[i].w);
       }
     }
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] *= P.scale_2;
     out[q * kThreads] = u32x4{pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]), pack_bf16x2(acc[4], acc[5]),
                               pack_bf16x2(acc[6], acc[7])};
     R = R_next;

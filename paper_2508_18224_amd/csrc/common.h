@@ -112,7 +112,6 @@ struct Problem {
   int32_t l0, l1;  // lists [l0, l1): those of the heads, or a range of one head's (see launch_bwd)
   int32_t units_max;  // last index the table of work units has room for
   float scale;
-  float scale_m, scale_2;  // scale = scale_m scale_2, scale_2 a power of two
 };
 
 // List entries per work unit.  Long inputs use kMaxUnit (splitting lists further only adds dK/dV partial sums); shorter

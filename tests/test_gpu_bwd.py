@@ -91,9 +91,8 @@ def test_two_calls_share_nothing_but_the_index():
 @pytest.mark.parametrize("block", [64, 128])
 @pytest.mark.parametrize("scale", [1e-30, 1e-6, 0.3])
 def test_backward_far_scales(scale, block):
-    """The 64-key kernel starts its products from LSE / scale, and both kernels leave the scale's power of two out of dS: a tiny scale (P is
-    uniform) and a large one (P nearly one-hot).  dQ and dK carry it as a factor and are compared with the default scale in its
-    place: that is what the tolerance, a bound on sums of rounded dS times it, was stated for."""
+    """A tiny scale (P is uniform) and a large one (P nearly one-hot).  dQ and dK carry the scale as a factor and are compared with the
+    default scale in its place: that is what the tolerance, a bound on sums of rounded dS times it, was stated for."""
     print("case far scale", scale, block, flush=True)
     w = wl.realise(wl.Workload("scale", [1100, 77], hq=6, hkv=2, topk=6, sink=True, block=block, seed=97))
     c = Case(w, scale=scale)
@@ -104,3 +103,22 @@ def test_backward_far_scales(scale, block):
     f = 128 ** -0.5 / scale
     for nm, a, b in (("dQ", dq * f, rq * f), ("dK", dk * f, rk * f), ("dV", dv, rv)):
         assert_close(nm, a, b, TOL_GRAD)
+
+
+@pytest.mark.parametrize("scale", [0.0, 1e-3, 0.3])
+@pytest.mark.parametrize("causal,hq,hkv", [(True, 8, 2), (False, 3, 3)])
+def test_both_block_sizes_take_the_same_products(causal, hq, hkv, scale):
+    """Sequences of at most 64 tokens are one block whatever the block size.  Both main kernels sum the products from zero, over the
+    channels and then over the rows in the same order, and bring LSE and delta in afterwards, so from the same O and LSE they
+    give the same bits; sums that start from the statistics carry a larger term and round elsewhere."""
+    print("case same products", causal, hq, hkv, scale, flush=True)
+    seqlens = [64, 1, 63, 17, 64, 40] * 6
+    grads, stats = [], None
+    for block in (64, 128):
+        w = wl.realise(wl.Workload("same", seqlens, hq=hq, hkv=hkv, topk=2, causal=causal, block=block, seed=43))
+        c = Case(w, scale=scale)
+        stats = stats or c.forward()
+        c.forward()
+        grads.append(c.backward(*stats))
+    for nm, a, b in zip(("dQ", "dK", "dV"), *grads):
+        assert torch.equal(a, b), f"{nm}: {int((a != b).sum())} of {a.numel()} differ"
