@@ -116,6 +116,20 @@ __device__ __forceinline__ void load_bits(const RowInfo& R, int base, int lane, 
   }
 }
 
+// What lies in a wavefront's LDS is written and read as 32-bit words by all methods.  An entry of the survivor list is the pair
+// (score bits or key, ~block), in the order in which its two words compare as one number.
+struct alignas(8) Survivor {
+  uint32_t not_blk, score;
+  __device__ __forceinline__ uint64_t both() const { return (uint64_t)score << 32 | not_blk; }
+};
+
+// Orders a wavefront's own LDS traffic: what its lanes wrote before is what any of them reads after, and the other way round.
+__device__ __forceinline__ void wave_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- the general method: `want` rounds of "take the largest remaining key".  Exact for any input, also when
 // most scores are equal; ~150 instructions per pick, so it only serves rows the fast method hands over.
 template <bool kVec>
@@ -152,9 +166,7 @@ __device__ __forceinline__ int select_by_rounds(const RowInfo& R, int lane, uint
   }
   if (n_chunks > 1) {
     // final selection over the chunk picks (written by lane 0 of this wavefront, read by all of its lanes)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync_lds();
     uint32_t key[kCandPerLane];
     int32_t blk[kCandPerLane];
 #pragma unroll
@@ -185,7 +197,7 @@ __device__ __forceinline__ int select_by_rounds(const RowInfo& R, int lane, uint
 // maximum leaves out its NaNs (or reads as -inf for one, which only lowers the bound); a NaN is not below anything and
 // survives; -0 equals +0.  chunk_survivors does steps 1 and 2; n_surv above kMaxSurv says that the survivors do not fit the list.
 template <bool kVec, int E>
-__device__ __forceinline__ void chunk_survivors(const RowInfo& R, int base, int lane, int r, uint64_t* surv, int& n_surv) {
+__device__ __forceinline__ void chunk_survivors(const RowInfo& R, int base, int lane, int r, Survivor* surv, int& n_surv) {
   uint32_t x[E];
   load_bits<kVec, E>(R, base, lane, 0xff800000u, x);
   float lmax = -__builtin_inff();
@@ -212,40 +224,39 @@ __device__ __forceinline__ void chunk_survivors(const RowInfo& R, int base, int 
     const int at = min(n_surv, kMaxChunks * kMaxTopk - 64);
     const int pos = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)at));
     if (sv) {
-      uint32_t* to = reinterpret_cast<uint32_t*>(surv + pos);
-      to[0] = not_blk - (uint32_t)blk_of<kVec>(0, 0, e);
-      to[1] = x[e];
+      surv[pos].not_blk = not_blk - (uint32_t)blk_of<kVec>(0, 0, e);
+      surv[pos].score = x[e];
     }
     n_surv += __builtin_popcountll(m);
   }
 }
 
 // Step 3: the survivors' columns.
-__device__ __forceinline__ void rank_survivors(const RowInfo& R, int lane, uint64_t* surv, int n_surv, int32_t* out_row) {
+__device__ __forceinline__ void rank_survivors(const RowInfo& R, int lane, Survivor* surv, int n_surv, int32_t* out_row) {
   // keys in place of the scores; 0 for what may not be picked, forced blocks and blocks past the visible range, and for the
   // entries that fill the list up to a multiple of eight
   for (int q = lane; q < ((n_surv + 7) & ~7); q += 64) {
-    const uint64_t v = surv[q];
-    const int b = (int)~(uint32_t)v;
-    surv[q] = q >= n_surv || b >= R.b_vis || R.forced(b) ? 0 : ((uint64_t)order_key((uint32_t)(v >> 32)) << 32) | (uint32_t)v;
+    Survivor v = surv[q];
+    const int b = (int)~v.not_blk;
+    v.score = order_key(v.score);
+    if (q >= n_surv || b >= R.b_vis || R.forced(b)) v.score = v.not_blk = 0;
+    surv[q] = v;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  wave_sync_lds();
   for (int q0 = 0; q0 < n_surv; q0 += 64) {
     const int q = q0 + lane;
-    const uint64_t my = q < n_surv ? surv[q] : 0;
+    const uint64_t my = q < n_surv ? surv[q].both() : 0;
     int rank = 0;
     for (int s = 0; s < n_surv; s += 8) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) rank += surv[s + i] > my ? 1 : 0;   // same address in every lane: a broadcast
+      for (int i = 0; i < 8; ++i) rank += surv[s + i].both() > my ? 1 : 0;   // same address in every lane: a broadcast
     }
     if (my != 0 && rank < R.want) out_row[R.n_forced + rank] = (int32_t)~(uint32_t)my;
   }
 }
 
 template <bool kVec>
-__device__ __forceinline__ bool select_by_threshold(const RowInfo& R, int lane, uint64_t* surv, int32_t* out_row) {
+__device__ __forceinline__ bool select_by_threshold(const RowInfo& R, int lane, Survivor* surv, int32_t* out_row) {
   const int r = R.want + R.ns + R.nl + 3;   // <= topk + 3 whenever want > 0
   const int n_chunks = (R.b_vis + kChunkBlocks - 1) / kChunkBlocks;
   int n_surv = 0;
@@ -258,6 +269,7 @@ __device__ __forceinline__ bool select_by_threshold(const RowInfo& R, int lane, 
     else chunk_survivors<kVec, 4>(R, base, lane, r, surv, n_surv);
     if (n_surv > kMaxSurv) return false;
   }
+  wave_sync_lds();
   rank_survivors(R, lane, surv, n_surv, out_row);
   return true;
 }
@@ -269,7 +281,7 @@ __global__ void __launch_bounds__(64 * kSelWaves)
 k_select_blocks(const float* __restrict__ scores, int64_t stride, const int32_t* __restrict__ cu, int T, int nseq,
                 int hkv, int bk, int topk, int causal, int n_sink, int n_local, int per, int32_t* __restrict__ idx) {
   // per wavefront: the survivor list of the fast method, or the chunk picks of the general one
-  __shared__ uint64_t lds[kSelWaves][kMaxChunks * kMaxTopk];
+  __shared__ Survivor lds[kSelWaves][kMaxChunks * kMaxTopk];
   static_assert(kMaxSurv <= kMaxChunks * kMaxTopk, "survivor list must fit");
   int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -318,6 +330,7 @@ k_select_blocks(const float* __restrict__ scores, int64_t stride, const int32_t*
     if (n_picks > 0) {
       by_rank = select_by_threshold<kVec>(R, lane, lds[w], out_row);
       if (!by_rank) mine = select_by_rounds<kVec>(R, lane, reinterpret_cast<uint32_t*>(lds[w]), mine);
+      wave_sync_lds();                       // the next row writes there
     }
     if (lane < topk && (!by_rank || lane < R.n_forced || lane >= R.n_forced + n_picks)) out_row[lane] = mine;
   }
