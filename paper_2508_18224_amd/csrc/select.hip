@@ -3,7 +3,7 @@
 //
 // One wavefront takes a row at a time and looks at it in chunks of up to 1024 blocks, 16 scores per lane held in registers.  The fast method (select_by_threshold) bounds the picks from below with the
 // r-th largest lane maximum, compacts the few elements above that bound into the LDS and ranks them against each
-// other: ~530 instructions per row.  Rows where too many scores tie at the bound fall back to the general method
+// other: ~530 instructions per row.  Rows where too many scores agree in the bound's bits fall back to the general method
 // (select_by_rounds): one pick per round, each round two wave-wide reductions.  Each visible score is read from
 // HBM once, with 16-byte loads when the rows are 16-byte aligned.
 #include "common.h"
@@ -15,7 +15,7 @@ constexpr int kSelWaves = 4;                  // wavefronts per workgroup
 // Rows of a wavefront: eight where that leaves every SIMD several wavefronts, else one.  The kernel is bound by the instructions a
 // row takes (270 vector, 260 scalar; a compute unit issues one scalar instruction a clock for its four SIMDs), and a token's
 // bounds and the row's divisions were a fifth of the scalar ones: 65536 tokens x 8 heads x 1024 blocks 399 -> 341 us, most of
-// it from that, the rest from scores compared as floats and a coarser bound.  Against this, 16 rows a wavefront cost 3 %, ending
+// it from that, the rest from scores compared as floats.  Against this, 16 rows a wavefront cost 3 %, ending
 // the bound's search early by a branch or requesting the next row ahead (16 more registers and moves) 20 %.
 constexpr int kSelRows = 8;
 constexpr int64_t kSelManyRows = 1 << 16;
@@ -23,7 +23,10 @@ constexpr int kChunkBlocks = 1024;            // blocks examined at a time: 16 k
 constexpr int kKeys = kChunkBlocks / 64;
 constexpr int kMaxChunks = 16;                // rows of up to 16384 blocks
 constexpr int kCandPerLane = kMaxChunks * kMaxTopk / 64;   // chunk picks each lane holds in the final selection
-constexpr int kTauLowBit = 21;                // the bound is searched on the upper 11 bits of the keys (looser, still a bound)
+// The bound is searched on the upper 16 bits of the keys: sign, exponent and 7 bits of the score.  Two bits of it, a grid of a quarter
+// octave, let everything within 25 % of the bound survive, and ordinary scores of a narrower range than exp(1.5 z) outgrew the list of
+// survivors: exp(0.1 z) took 1470 us at 65536 tokens x 8 heads x 1024 blocks instead of 344, uniform ones 592 instead of 343.
+constexpr int kTauLowBit = 16;
 constexpr int kMaxSurv = 128;                 // survivors the fast method ranks; rows with more take the general one
 
 // All four steps stay inside a row of 16 lanes (quad swaps, then mirrors of 8 and of 16 lanes), after which every
@@ -189,13 +192,13 @@ __device__ __forceinline__ int select_by_rounds(const RowInfo& R, int lane, uint
 //      with ballots (scalar work).  r = want + (forced blocks) + 3, so at least `want` selectable blocks of the
 //      chunk have a score >= tau (forced blocks and the up to three blocks a 16-byte load brings along past b_vis
 //      are not masked beforehand: they are dropped in step 3), hence no block with a score < tau can be a pick;
-//   2. the elements not below tau ("survivors", a few more than r unless many scores tie) are compacted into
+//   2. the elements not below tau ("survivors", a few more than r unless many scores agree in the bits of tau) are compacted into
 //      an LDS list of (score, ~block) pairs;
 //   3. after all chunks the survivors' scores become order-preserving keys and every survivor counts the survivors that beat
 //      it; that rank is its output column.
 // The scores are compared as floats up to step 3, so that only the 64 maxima and the survivors are turned into keys.  A lane's
-// maximum leaves out its NaNs (or reads as -inf for one, which only lowers the bound); a NaN is not below anything and
-// survives; -0 equals +0.  chunk_survivors does steps 1 and 2; n_surv above kMaxSurv says that the survivors do not fit the list.
+// maximum leaves out its NaNs (or reads as -inf for one, which only lowers the bound), and a NaN survives only where -inf does;
+// -0 equals +0.  chunk_survivors does steps 1 and 2; n_surv above kMaxSurv says that the survivors do not fit the list.
 template <bool kVec, int E>
 __device__ __forceinline__ void chunk_survivors(const RowInfo& R, int base, int lane, int r, Survivor* surv, int& n_surv) {
   uint32_t x[E];
@@ -206,19 +209,26 @@ __device__ __forceinline__ void chunk_survivors(const RowInfo& R, int base, int 
     asm("v_max3_f32 %0, %0, %1, %2" : "+v"(lmax) : "v"(x[e]), "v"(x[e + 1]));
   const uint32_t key = blk_of<kVec>(base, lane, 0) < R.b_vis ? order_key(__builtin_bit_cast(uint32_t, lmax)) : 0u;
   uint32_t tau = 0;
+  if (E > 4 || R.b_vis - base > (kVec ? 4 : 1) * (r - 1)) {  // else fewer than r lanes hold anything
 #pragma unroll
-  for (int bit = 31; bit >= kTauLowBit; --bit) {
-    const uint32_t trial = tau | (1u << bit);
-    const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(key >= trial));
-    tau = c >= r ? trial : tau;
+    for (int bit = 31; bit >= kTauLowBit; --bit) {
+      const uint32_t trial = tau | (1u << bit);
+      const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(key >= trial));
+      tau = c >= r ? trial : tau;
+    }
   }
-  // tau as a score; below the key of -inf it is a NaN, and everything loaded survives (fewer than r lanes hold anything)
-  const float thr = __builtin_bit_cast(float, (tau & 0x80000000u) ? tau ^ 0x80000000u : ~tau);
+  // tau as a score; with fewer than r lanes that hold more than -inf everything loaded survives, its NaNs as the -inf they rank with
+  float thr = __builtin_bit_cast(float, (tau & 0x80000000u) ? tau ^ 0x80000000u : ~tau);
+  if (tau <= 0x007fffffu) {  // the key of -inf
+    thr = -__builtin_inff();
+#pragma unroll
+    for (int e = 0; e < E; ++e) x[e] = __builtin_bit_cast(uint32_t, __builtin_fmaxf(__builtin_bit_cast(float, x[e]), thr));
+  }
   const uint32_t not_blk = ~(uint32_t)blk_of<kVec>(base, lane, 0);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const bool loaded = blk_of<kVec>(base, lane, kVec ? (e & ~3) : e) < R.b_vis;
-    const bool sv = loaded & !(__builtin_bit_cast(float, x[e]) < thr);
+    const bool sv = loaded & (__builtin_bit_cast(float, x[e]) >= thr);
     const uint64_t m = __builtin_amdgcn_ballot_w64(sv);
     // (a list that overflows is discarded: its writes only have to stay inside the wavefront's LDS)
     const int at = min(n_surv, kMaxChunks * kMaxTopk - 64);
