@@ -12,13 +12,17 @@ namespace nsa {
 namespace {
 
 constexpr int kSelWaves = 4;                  // wavefronts per workgroup
-// Rows of a wavefront: eight where that leaves every SIMD several wavefronts, else one.  The kernel is bound by the instructions a
-// row takes (270 vector, 260 scalar; a compute unit issues one scalar instruction a clock for its four SIMDs), and a token's
-// bounds and the row's divisions were a fifth of the scalar ones: 65536 tokens x 8 heads x 1024 blocks 399 -> 341 us, most of
-// it from that, the rest from scores compared as floats.  Against this, 16 rows a wavefront cost 3 %, ending
-// the bound's search early by a branch or requesting the next row ahead (16 more registers and moves) 20 %.
-constexpr int kSelRows = 8;
-constexpr int64_t kSelManyRows = 1 << 16;
+// Rows of a wavefront: one, or eight in a loop.  The kernel is bound by the instructions a row takes (270 vector, 260 scalar; a
+// compute unit issues one scalar instruction a clock for its four SIMDs), and a token's bounds and the row's divisions are a fifth of
+// the scalar ones: eight rows share them where a token has several heads.  Against that the loop keeps more alive than the scalar
+// registers hold, and eight rows in turn need more rows before every SIMD has wavefronts enough.  Measured, one -> eight, 64 ..
+// 1024 blocks, causal: 8 heads 65536 rows 36.8 .. 40.2 -> 40.6 .. 39.5 us, 131072 rows 74.8 .. 78.2 -> 77.9 .. 74.0, 524288 rows 296 ..
+// 385 -> 291 .. 340; 2 heads 65536 rows 38.2 .. 42.6 -> 44.8 .. 48.5, 131072 rows 76.2 .. 94.2 -> 84.2 .. 96.0, 262144 rows 150 ..
+// 210 -> 158 .. 200; one head 131072 rows 76.8 .. 105.9 -> 89.3 .. 113.8, 524288 rows 299 .. 446 -> 328 .. 430.  16 rows cost
+// 3 % against eight, ending the bound's search early by a branch or requesting the next row ahead (16 more registers
+// and moves) 20 %.
+constexpr uint32_t kSelRows = 8;
+inline bool eight_rows(int64_t rows, int hkv) { return rows >= (hkv > 1 ? 1 << 17 : 1 << 19); }
 constexpr int kChunkBlocks = 1024;            // blocks examined at a time: 16 keys per lane
 constexpr int kKeys = kChunkBlocks / 64;
 constexpr int kMaxChunks = 16;                // rows of up to 16384 blocks
@@ -286,27 +290,28 @@ __device__ __forceinline__ bool select_by_threshold(const RowInfo& R, int lane, 
 
 }  // namespace
 
-template <bool kVec>
+template <bool kVec, bool kMany>
 __global__ void __launch_bounds__(64 * kSelWaves)
 k_select_blocks(const float* __restrict__ scores, int64_t stride, const int32_t* __restrict__ cu, int T, int nseq,
-                int hkv, int bk, int topk, int causal, int n_sink, int n_local, int per, int32_t* __restrict__ idx) {
+                int hkv, int bk, int topk, int causal, int n_sink, int n_local, int32_t* __restrict__ idx) {
   // per wavefront: the survivor list of the fast method, or the chunk picks of the general one
   __shared__ Survivor lds[kSelWaves][kMaxChunks * kMaxTopk];
   static_assert(kMaxSurv <= kMaxChunks * kMaxTopk, "survivor list must fit");
   int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // `per` consecutive rows a wavefront (T * hkv < 2^31 is checked on the host); what they share, a token's bounds, is worked out
+  constexpr uint32_t kRows = kMany ? kSelRows : 1;
+  // consecutive rows a wavefront (T * hkv < 2^31 is checked on the host); what they share, a token's bounds, is worked out
   // once per token
-  const uint32_t rows = (uint32_t)T * (uint32_t)hkv, first = ((uint32_t)blockIdx.x * kSelWaves + w) * (uint32_t)per;
+  const uint32_t rows = (uint32_t)T * (uint32_t)hkv, first = ((uint32_t)blockIdx.x * kSelWaves + w) * kRows;
   if (first >= rows) return;               // whole wavefront leaves together
-  const uint32_t end = min(first + (uint32_t)per, rows);
+  const uint32_t end = kMany ? min(first + kRows, rows) : first + 1;
   int t = (int)(first / (uint32_t)hkv), j = (int)(first - (uint32_t)t * (uint32_t)hkv), t_known = -1;
   RowInfo R;
   R.srow = scores + (int64_t)first * stride;
   int32_t* out_row = idx + (int64_t)first * topk;
 #pragma unroll 1
-  for (uint32_t row = first; row < end; ++row, R.srow += stride, out_row += topk) {
-    asm volatile("" : "+v"(lane));         // what derives from it is not kept in registers from row to row
+  for (uint32_t row = first; kMany ? row < end : row == first; ++row, R.srow += stride, out_row += topk) {
+    if constexpr (kMany) asm volatile("" : "+v"(lane));  // what derives from it is not kept in registers from row to row
     if (t != t_known) {
       t_known = t;
       int s, c0, c1;
@@ -364,15 +369,17 @@ extern "C" int nsa_sel_select_blocks(const nsa_sel_shape* shape, const float* sc
   const int64_t rows = (int64_t)shape->total_tokens * shape->hkv;
   if (rows == 0) return NSA_SEL_OK;
   if (rows * shape->topk >= ((int64_t)1 << 31)) return NSA_SEL_EUNSUPPORTED;
-  const int per = rows >= kSelManyRows ? kSelRows : 1;
+  const bool many = eight_rows(rows, shape->hkv);
+  const int64_t per = many ? kSelRows : 1;
   const int64_t grid = (rows + kSelWaves * per - 1) / (kSelWaves * per);
   if (grid >= ((int64_t)1 << 31)) return NSA_SEL_EUNSUPPORTED;
   hipStream_t st = (hipStream_t)stream;
   ProfScope prof(KID_SELECT_BLOCKS, st);
   const bool vec = (score_stride & 3) == 0 && ((uintptr_t)scores & 15) == 0;
-  auto kern = vec ? k_select_blocks<true> : k_select_blocks<false>;
+  auto kern = many ? (vec ? k_select_blocks<true, true> : k_select_blocks<false, true>)
+                   : (vec ? k_select_blocks<true, false> : k_select_blocks<false, false>);
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * kSelWaves), 0, st, scores, score_stride, cu_seqlens,
                      shape->total_tokens, shape->nseq, shape->hkv, shape->block, shape->topk, shape->causal ? 1 : 0,
-                     (int)n_sink, (int)n_local, per, idx);
+                     (int)n_sink, (int)n_local, idx);
   return hipGetLastError() == hipSuccess ? NSA_SEL_OK : NSA_SEL_EHIP;
 }

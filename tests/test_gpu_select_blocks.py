@@ -173,14 +173,20 @@ def test_argument_errors():
 
 
 @pytest.mark.parametrize("seqlens,hkv,topk,causal,kind,stride", [
-    ([13000, 1, 107], 5, 16, True, "wild", None),     # 65540 rows: eight a wavefront, the last wavefront with four
-    ([13000, 107], 5, 16, True, "wild", 207),         # 65535 rows: one a wavefront
-    ([21846], 3, 32, False, "wild", None),            # a wavefront's rows begin and end inside a token
-    ([70000], 1, 1, True, "ties", 1099),              # eight tokens a wavefront, two chunks
+    ([13000, 1, 107], 5, 16, True, "wild", None),
+    ([13000, 107], 5, 16, True, "wild", 207),
+    ([21846], 3, 32, False, "wild", None),
+    ([70000], 1, 1, True, "ties", 1099),              # two chunks
+    ([26000, 1, 214], 5, 16, True, "wild", None),     # 131075 rows: eight a wavefront, the last wavefront with three
+    ([26000, 214], 5, 16, True, "wild", 407),         # 131070 rows: one a wavefront
+    ([43691], 3, 32, False, "wild", None),            # a wavefront's rows begin and end inside a token
+    ([70000], 2, 1, True, "ties", 1099),              # four tokens a wavefront, two chunks
+    ([1000] * 524 + [289], 1, 16, True, "wild", 16),  # 524289 rows of one head: eight a wavefront, fewer lanes than the bound counts
+    ([1000] * 524 + [287], 1, 16, True, "wild", 17),  # 524287: one
 ])
 def test_rows_of_a_wavefront(seqlens, hkv, topk, causal, kind, stride):
-    """From 65536 rows a wavefront takes eight, and scores are compared as floats: infinities, NaN, both zeros and denormals.
-    Oracle on sampled tokens."""
+    """From 131072 rows (524288 with one head) a wavefront takes eight, and scores are compared as floats: infinities, NaN, both zeros and
+    denormals.  Oracle on sampled tokens."""
     print("case rows of a wavefront", seqlens, hkv, topk, causal, kind, stride, flush=True)
     cu, n = _cu(seqlens), sum(seqlens)
     x = wl.draw_block_scores(35, seqlens, hkv, kind=kind, stride=stride, trap_future=causal)
