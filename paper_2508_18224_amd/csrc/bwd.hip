@@ -913,26 +913,37 @@ k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const int32_t* __r
     const SlotRow slots_next = load_slots(slotpos, P, R_next);
     const bf16_t* base = dqpart + R.hh * kD + 8 * sub;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int pos = pos0;  // of the last kept column: dropped ones gather it again
-    for (int m0 = 0; m0 < P.topk; m0 += kBatch) {
+    int pos = pos0;  // of the last kept column
+    const KeptColumns kept(slots);
+    auto gather = [&](int m0, auto all_kept) __attribute__((always_inline)) {
       int at[kBatch];
       u32x4 x[kBatch];
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) at[i] = slot_of(slots, m0 + i);
+      for (int i = 0; i < kBatch; ++i) at[i] = slot_of(slots, m0, i);
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        pos = at[i] >= 0 ? at[i] : pos;
-        asm volatile("" : "+v"(at[i]), "+v"(pos));  // keeps the loads free of branches
-        x[i] = load_streaming(base + (size_t)(pos - pos0) * P.g * kD);
+        x[i] = u32x4{0, 0, 0, 0};
+        if constexpr (kRows > 1) {
+          pos = at[i] >= 0 ? at[i] : pos;
+          asm volatile("" : "+v"(at[i]), "+v"(pos));  // keeps the loads free of branches
+        } else {
+          pos = at[i];
+        }
+        if (kRows > 1 || all_kept || at[i] >= 0) x[i] = load_streaming(base + (size_t)(uint32_t)(pos - pos0) * (uint32_t)P.g * kD);
       }
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        if (at[i] < 0) x[i] = u32x4{0, 0, 0, 0};
+        if (kRows > 1 && at[i] < 0) x[i] = u32x4{0, 0, 0, 0};
         acc[0] += bf16_lo(x[i].x); acc[1] += bf16_hi(x[i].x);
         acc[2] += bf16_lo(x[i].y); acc[3] += bf16_hi(x[i].y);
         acc[4] += bf16_lo(x[i].z); acc[5] += bf16_hi(x[i].z);
         acc[6] += bf16_lo(x[i].w); acc[7] += bf16_hi(x[i].w);
       }
+    };
+    for (int m0 = 0; m0 < P.topk; m0 += kBatch) {
+      const uint64_t eight = kept.eight_from(m0);
+      if (kRows == 1 && eight == KeptColumns::kAll) gather(m0, std::true_type{});
+      else if (kRows > 1 || eight != 0) gather(m0, std::false_type{});
     }
     out[q * kThreads] = u32x4{pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]), pack_bf16x2(acc[4], acc[5]),
                               pack_bf16x2(acc[6], acc[7])};

@@ -402,9 +402,22 @@ __device__ __forceinline__ SlotRow load_slots(const int32_t* __restrict__ slotpo
   if (16 + sub >= P.topk) s.hi = -1;
   return s;
 }
-__device__ __forceinline__ int slot_of(const SlotRow& s, int m) {  // m is wave-uniform
-  return (int)lane_value((uint32_t)(m < 16 ? s.lo : s.hi), (int)(threadIdx.x & 48) + (m & 15));
+__device__ __forceinline__ int slot_of(const SlotRow& s, int m0, int i) {  // of column m0 + i: m0 a wave-uniform multiple of 8, i < 8
+  return (int)lane_value((uint32_t)(m0 < 16 ? s.lo : s.hi), (int)(threadIdx.x & 48) + (m0 & 8) + i);
 }
+// The kept columns of a wavefront's four rows, 16 bits a row.  Columns are gathered eight at a time.  In bursts, which serve
+// sequences long enough that nearly all rows keep all columns, a dropped column requests the kept one before it again, without
+// a branch.  One row at a time, batches of which no row keeps anything are skipped and dropped columns request nothing; batches
+// that all four rows keep whole go without branches.  6762 tokens in 23 sequences, 16 heads, g = 1, top-k 16, merge / dQ
+// reduction: 58 / 51 us as in the bursts, now 39 / 36.  (In the bursts of long sequences the second way costs up to 8 %.)
+struct KeptColumns {
+  uint64_t lo, hi;
+  __device__ __forceinline__ explicit KeptColumns(const SlotRow& s)
+      : lo(__builtin_amdgcn_ballot_w64(s.lo >= 0)), hi(__builtin_amdgcn_ballot_w64(s.hi >= 0)) {}
+  __device__ __forceinline__ bool none() const { return (((lo | hi) >> (threadIdx.x & 48)) & 0xffffu) == 0; }  // of this lane's row
+  static constexpr uint64_t kAll = 0x00ff00ff00ff00ffull;
+  __device__ __forceinline__ uint64_t eight_from(int m) const { return ((m < 16 ? lo : hi) >> (m & 8)) & kAll; }  // m a multiple of 8
+};
 constexpr int kBurstThreads = 1024, kBurstRows = 8, kBurstRowsGated = 4;  // gated: two tensors share the LDS
 inline bool reduce_in_bursts(const Problem& P) { return (int64_t)P.T * P.nj * P.g >= (1 << 18); }
 // LDS of a workgroup: 16 bytes a thread and row for every tensor written, and a float a row for LSE.

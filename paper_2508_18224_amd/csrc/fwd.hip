@@ -909,8 +909,8 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
 }
 
 // The reduction alone (dense route off); rows and workgroups: see "the two reduction kernels" in common.h.  16 lanes per (token,
-// head) row, 8 output channels per lane; columns are taken kBatch at a time, all their log-sum-exps and rows requested, without
-// branches, before any is used, the positions of the next row before this one's; batches are chained by the usual running-max
+// head) row, 8 output channels per lane; columns are taken kBatch at a time (see KeptColumns), all their log-sum-exps and rows
+// requested before any is used, the positions of the next row before this one's; batches are chained by the usual running-max
 // rescale.
 template <int kRows, int kThreads, bool kGate>
 __global__ void __launch_bounds__(kThreads)
@@ -934,25 +934,34 @@ k_fwd_merge(Problem P, const bf16_t* __restrict__ opart, const float* __restrict
     const int64_t row = (int64_t)R.t * P.hq + R.j * P.g + R.hh;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     float M = -INFINITY, Ls = 0.f;
-    int pos = -1;  // of the last kept column: dropped ones gather it again
-    for (int m0 = 0; m0 < P.topk; m0 += kBatch) {
+    int pos = pos0;  // of the last kept column
+    const KeptColumns kept(slots);
+    auto gather = [&](int m0, auto all_kept) __attribute__((always_inline)) {
       int at[kBatch];
       u32x4 x[kBatch];
       float ls[kBatch];
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) at[i] = slot_of(slots, m0 + i);
+      for (int i = 0; i < kBatch; ++i) at[i] = slot_of(slots, m0, i);
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        pos = at[i] >= 0 ? at[i] : pos;
-        asm volatile("" : "+v"(at[i]), "+v"(pos));  // keeps the loads free of branches
-        const size_t pr = (size_t)(max(pos, pos0) - pos0) * P.g + R.hh;
-        x[i] = load_streaming(opart + pr * kD + 8 * sub);
-        ls[i] = lse_part[pr];
+        x[i] = u32x4{0, 0, 0, 0};
+        ls[i] = -INFINITY;
+        if constexpr (kRows > 1) {
+          pos = at[i] >= 0 ? at[i] : pos;
+          asm volatile("" : "+v"(at[i]), "+v"(pos));  // keeps the loads free of branches
+        } else {
+          pos = at[i];
+        }
+        if (kRows > 1 || all_kept || at[i] >= 0) {
+          const size_t pr = (size_t)(uint32_t)(pos - pos0) * (uint32_t)P.g + (uint32_t)R.hh;
+          x[i] = load_streaming(opart + pr * kD + 8 * sub);
+          ls[i] = lse_part[pr];
+        }
       }
       float Mb = M;
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
-        if (at[i] < 0) {
+        if (kRows > 1 && at[i] < 0) {
           x[i] = u32x4{0, 0, 0, 0};
           ls[i] = -INFINITY;
         }
@@ -973,8 +982,13 @@ k_fwd_merge(Problem P, const bf16_t* __restrict__ opart, const float* __restrict
         acc[4] += w * bf16_lo(x[i].z); acc[5] += w * bf16_hi(x[i].z);
         acc[6] += w * bf16_lo(x[i].w); acc[7] += w * bf16_hi(x[i].w);
       }
+    };
+    for (int m0 = 0; m0 < P.topk; m0 += kBatch) {
+      const uint64_t eight = kept.eight_from(m0);
+      if (kRows == 1 && eight == KeptColumns::kAll) gather(m0, std::true_type{});
+      else if (kRows > 1 || eight != 0) gather(m0, std::false_type{});
     }
-    const bool empty = pos < 0;  // nothing visible: O = 0, LSE = -inf, and the gated sum is what the other branches gave
+    const bool empty = kept.none();  // nothing visible: O = 0, LSE = -inf, and the gated sum is what the other branches gave
     const float inv = empty ? 0.f : 1.f / Ls;
     out[q * kThreads] = u32x4{pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),
                               pack_bf16x2(acc[4] * inv, acc[5] * inv), pack_bf16x2(acc[6] * inv, acc[7] * inv)};
