@@ -905,11 +905,13 @@ k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const int32_t* __r
   const int pos0 = off[P.j0 * P.b_cap];
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u32x4* const out = reinterpret_cast<u32x4*>(smem) + threadIdx.x;
-  ReduceRow R = reduce_row<kRows, kThreads>(P, 0);
+  const ReduceSpan span = reduce_span<kRows, kThreads>(P);
+  if (span.count == 0) return;  // the whole workgroup
+  ReduceRow R = reduce_row<kThreads>(P, span.first);
   SlotRow slots = load_slots(slotpos, P, R);
 #pragma unroll 1
-  for (int q = 0; q < kRows; ++q) {
-    const ReduceRow R_next = reduce_row<kRows, kThreads>(P, min(q + 1, kRows - 1));
+  for (int q = 0; q < span.count; ++q) {
+    const ReduceRow R_next = reduce_row<kThreads>(P, span.first + min(q + 1, span.count - 1));
     const SlotRow slots_next = load_slots(slotpos, P, R_next);
     const bf16_t* base = dqpart + R.hh * kD + 8 * sub;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -953,7 +955,8 @@ k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const int32_t* __r
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < kRows; ++q) {
-    const ReduceRow R = reduce_row<kRows, kThreads>(P, q);
+    if (q >= span.count) break;
+    const ReduceRow R = reduce_row<kThreads>(P, span.first + q);
     if (R.on) store_streaming(dQ + ((int64_t)R.t * P.hq + R.j * P.g + R.hh) * kD + 8 * sub, out[q * kThreads]);
   }
 }
@@ -1072,7 +1075,7 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
           hipLaunchKernelGGL((k_bwd_dq_reduce<kRows, kThreads>), dim3(reduce_groups<kRows, kThreads>(P)), dim3(kThreads),
                              reduce_lds(kThreads, kRows, 1, false), st, P, (const bf16_t*)dqpart, p.slotpos, p.off, (bf16_t*)dQ);
         };
-        if (reduce_in_bursts(P))
+        if (dq_in_bursts(P))
           launch(std::integral_constant<int, kBurstRows>{}, std::integral_constant<int, kBurstThreads>{});
         else
           launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 256>{});

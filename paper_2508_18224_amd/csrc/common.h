@@ -363,21 +363,35 @@ inline bool rows_are_wide(int64_t rows) { return rows * (kD * 2) >= ((int64_t)1 
 // only gathers these rows reads 7.0 TB/s with non-temporal loads (6.2 with plain ones), and the sixteenth of writes takes it
 // down to 5.4 when they are strewn among the reads, to 5.7 as non-temporal stores, and to 6.4 when a workgroup keeps 128 KB of results
 // and writes them at once.  So a workgroup parks its rows in LDS and writes them after its last gather: dQ reduction at
-// 65536 tokens, g = 4: 1.72 -> 1.50 ms, at 8192, g = 1: 222 -> 182 us; merge there 233 -> 207 us.  Inputs with fewer than 2^18
-// rows would leave compute units without such a workgroup and take 16 rows a workgroup instead, written as they are done (4877 tokens,
-// 8 heads, top-k 8: 24 -> 19 us for either kernel, from the columns being gathered side by side).
-// Rows of a pass are (token, head of its KV heads), token-major.  A workgroup of kThreads threads takes kRows * kThreads / 16
-// consecutive ones, 16 lanes a row, and every XCD (they get workgroups in turn) works through one contiguous eighth of them, so
-// that its L2 keeps the lines of log-sum-exps that neighbouring tokens share.
+// 65536 tokens, g = 4: 1.72 -> 1.50 ms, at 8192, g = 1: 222 -> 182 us; merge there 233 -> 207 us.  Small inputs, and sequences too
+// short for their rows to have most columns, leave a burst little to read between its writes and take 16 rows a workgroup instead,
+// written as they are done: merge_in_bursts and dq_in_bursts say where either is faster.
+// Rows of a pass are (token, head of its KV heads), token-major.  A workgroup of kThreads threads takes at most kRows steps of
+// kThreads / 16 consecutive ones, 16 lanes a row, and every XCD (they get workgroups in turn) works through one contiguous eighth of
+// them, so that its L2 keeps the lines of log-sum-exps that neighbouring tokens share.  The LDS holds one burst workgroup a compute
+// unit: up to four turns of all 256 of them the steps are spread evenly, so that no turn is nearly empty (16875 tokens, 16 heads: merge 256
+// -> 224 us, dQ reduction 222 -> 205; 25000: 348 -> 315, 314 -> 285); beyond that full workgroups are as fast or up to 5 % faster.
+struct ReduceSpan {
+  uint32_t first;  // of the workgroup's steps, kThreads / 16 consecutive rows each
+  int count;       // at most kRows
+};
+template <int kRows, int kThreads>
+__device__ __forceinline__ ReduceSpan reduce_span(const Problem& P) {
+  constexpr uint32_t kStep = kThreads / 16;
+  const uint32_t steps = ((uint32_t)P.T * (uint32_t)(P.nj * P.g) + kStep - 1) / kStep;  // total_tokens * hq < 2^31 is checked on the host
+  const uint32_t blk = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if constexpr (kRows == 1) return {blk, blk < steps ? 1 : 0};
+  const uint32_t each = steps / gridDim.x, more = steps - each * gridDim.x;
+  return {blk * each + min(blk, more), (int)(each + (blk < more ? 1 : 0))};
+}
 struct ReduceRow {
   int t, j, hh;   // token, KV head, head of the group; rows past the last one repeat it
   bool on;
 };
-template <int kRows, int kThreads>
-__device__ __forceinline__ ReduceRow reduce_row(const Problem& P, int q) {
-  const uint32_t hp = (uint32_t)(P.nj * P.g), rows = (uint32_t)P.T * hp;  // total_tokens * hq < 2^31 is checked on the host
-  const uint32_t blk = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  const uint32_t r = (blk * kRows + q) * (kThreads / 16) + (threadIdx.x >> 4), rc = min(r, rows - 1);
+template <int kThreads>
+__device__ __forceinline__ ReduceRow reduce_row(const Problem& P, uint32_t step) {
+  const uint32_t hp = (uint32_t)(P.nj * P.g), rows = (uint32_t)P.T * hp;
+  const uint32_t r = step * (kThreads / 16) + (threadIdx.x >> 4), rc = min(r, rows - 1);
   ReduceRow x;
   x.t = (int)(rc / hp);
   const int h = (int)(rc - (uint32_t)x.t * hp);
@@ -419,13 +433,25 @@ struct KeptColumns {
   __device__ __forceinline__ uint64_t eight_from(int m) const { return ((m < 16 ? lo : hi) >> (m & 8)) & kAll; }  // m a multiple of 8
 };
 constexpr int kBurstThreads = 1024, kBurstRows = 8, kBurstRowsGated = 4;  // gated: two tensors share the LDS
-inline bool reduce_in_bursts(const Problem& P) { return (int64_t)P.T * P.nj * P.g >= (1 << 18); }
+inline bool reduce_in_bursts(const Problem& P, int64_t rows, int64_t tokens) {  // at least: rows of the pass, mean length of a sequence
+  return (int64_t)P.T * P.nj * P.g >= rows && P.T >= tokens * P.nseq;
+}
+// The merge: by what it reads, rows * top-k; gated it has two tensors to write and half the rows a workgroup.  (one row at a time ->
+// bursts, us; 16 heads, g = 1: top-k 16 8192 tokens 109 -> 109, 12500 169 -> 168, 16384 224 -> 208; top-k 8 25000 tokens 175 -> 185, 33080
+// 252 -> 240; gated, top-k 16 25000 376 -> 396, 33080 523 -> 490.)  Sequences of 870 / 1440 / 2030 tokens in the mean, 35000 in all: top-k
+// 8 220 -> 230 / 223 -> 229 / 244 -> 239, top-k 16 377 -> 390 / 381 -> 399 / 451 -> 429, top-k 32 594 -> 656 / 609 -> 689 / 784 -> 772.
+inline bool merge_in_bursts(const Problem& P, bool gated) { return reduce_in_bursts(P, (gated ? 1 << 23 : 1 << 22) / P.topk, 1536); }
+// The dQ reduction: a row of the sum is half the work of a merged one.  (16 heads, g = 1, top-k 16: 5600 tokens 69 -> 68, 8192 101 -> 92, 12500
+// 159 -> 140.)  Sequences of 470 / 670 / 870 tokens: top-k 8 165 -> 173 / 196 -> 188 / 212 -> 200, top-k 16 221 -> 273 / 307 -> 297 / 347 -> 322;
+// of 670 / 870 / 2030 tokens: top-k 32 418 -> 497 / 542 -> 538 / 722 -> 651.
+inline bool dq_in_bursts(const Problem& P) { return reduce_in_bursts(P, 1 << 17, (int64_t)P.topk * P.bk * 5 / 8); }
 // LDS of a workgroup: 16 bytes a thread and row for every tensor written, and a float a row for LSE.
 constexpr int reduce_lds(int threads, int rows, int tensors, bool lse) { return rows * threads * (16 * tensors) + (lse ? rows * threads / 4 : 0); }
 template <int kRows, int kThreads>
 inline unsigned reduce_groups(const Problem& P) {
-  const int64_t rows = (int64_t)P.T * P.nj * P.g, per = kRows * kThreads / 16;
-  return (unsigned)(((rows + per - 1) / per + 7) / 8 * 8);
+  constexpr int64_t kStep = kThreads / 16, kTurn = kRows == 1 ? 8 : 256;
+  const int64_t steps = ((int64_t)P.T * P.nj * P.g + kStep - 1) / kStep, turns = (steps + kTurn * kRows - 1) / (kTurn * kRows);
+  return (unsigned)(kRows == 1 || turns <= 4 ? turns * kTurn : ((steps + kRows - 1) / kRows + 7) / 8 * 8);
 }
 
 // Sequence bounds of token t in a packed batch (cu may be null for a single sequence).

@@ -925,11 +925,13 @@ k_fwd_merge(Problem P, const bf16_t* __restrict__ opart, const float* __restrict
   u32x4* const out = reinterpret_cast<u32x4*>(smem) + threadIdx.x;
   u32x4* const gated = out + kRows * kThreads;
   float* const lse = reinterpret_cast<float*>(smem + kRows * kThreads * (kGate ? 32 : 16)) + (threadIdx.x >> 4);
-  ReduceRow R = reduce_row<kRows, kThreads>(P, 0);
+  const ReduceSpan span = reduce_span<kRows, kThreads>(P);
+  if (span.count == 0) return;  // the whole workgroup
+  ReduceRow R = reduce_row<kThreads>(P, span.first);
   SlotRow slots = load_slots(slotpos, P, R);
 #pragma unroll 1
-  for (int q = 0; q < kRows; ++q) {
-    const ReduceRow R_next = reduce_row<kRows, kThreads>(P, min(q + 1, kRows - 1));
+  for (int q = 0; q < span.count; ++q) {
+    const ReduceRow R_next = reduce_row<kThreads>(P, span.first + min(q + 1, span.count - 1));
     const SlotRow slots_next = load_slots(slotpos, P, R_next);
     const int64_t row = (int64_t)R.t * P.hq + R.j * P.g + R.hh;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -1013,7 +1015,8 @@ k_fwd_merge(Problem P, const bf16_t* __restrict__ opart, const float* __restrict
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < kRows; ++q) {
-    const ReduceRow R = reduce_row<kRows, kThreads>(P, q);
+    if (q >= span.count) break;
+    const ReduceRow R = reduce_row<kThreads>(P, span.first + q);
     if (!R.on) continue;
     const int64_t row = (int64_t)R.t * P.hq + R.j * P.g + R.hh;
     store_streaming(O + row * kD + 8 * sub, out[q * kThreads]);
@@ -1090,7 +1093,7 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
       const integral_constant<int, kBurstThreads> burst;
       const integral_constant<int, 1> one;
       const integral_constant<int, 256> few;
-      if (reduce_in_bursts(P)) {
+      if (merge_in_bursts(P, G.gate != nullptr)) {
         if (G.gate != nullptr) launch(integral_constant<int, kBurstRowsGated>{}, burst, std::true_type{});
         else launch(integral_constant<int, kBurstRows>{}, burst, std::false_type{});
       } else {

@@ -1,4 +1,4 @@
-"""The two reduction kernels: what dropped columns cost them."""
+"""The two reduction kernels: what dropped columns cost them, and their rows written in bursts."""
 import numpy as np
 import pytest
 import torch
@@ -29,7 +29,7 @@ def _reduction_times(seqlens, topk):
     return best, float((w.idx >= 0).mean()) * topk
 
 
-@pytest.mark.parametrize("sequences", [24])
+@pytest.mark.parametrize("sequences", [24, 100])  # below and above the rows from which long sequences are written in bursts
 def test_dropped_columns_are_not_gathered(sequences):
     """Rows of short sequences keep few of their columns: the reductions take the time of the rows they read and write, here about
     a sixth of what rows with all 32 columns take, not that of the columns there could be (which took half of it)."""
@@ -42,3 +42,38 @@ def test_dropped_columns_are_not_gathered(sequences):
     assert rows < 0.25
     for a, b in zip(short, full):
         assert a < 1.7 * rows * b
+
+
+@pytest.mark.parametrize("seqlens,heads,topk", [
+    ([8200], 16, 9),             # dQ in bursts, two turns of the chip, workgroups of four and five steps; merged row by row
+    ([16399], 16, 16),           # both: three turns, five and six steps, the last one part empty
+    ([4000, 1, 12500], 32, 16),  # five turns of full workgroups; gated in bursts too
+])
+def test_bursts_of_rows_with_holes_match_row_by_row(seqlens, heads, topk):
+    """Columns dropped anywhere in a row, rows that keep none, whole tokens that keep none: one pass writes in bursts, a KV head per
+    pass row by row.  Same sums in the same order, same bits."""
+    print("case holes", seqlens, heads, topk, flush=True)
+    w = wl.realise(wl.Workload("holes", seqlens, hq=heads, hkv=heads, topk=topk, sink=True, seed=98), tensors=False)
+    rng = np.random.default_rng(9)
+    tokens = w.total_tokens
+    w.idx[rng.random(w.idx.shape) < 0.3] = -1
+    w.idx[rng.random(w.idx.shape[:2]) < 0.05] = -1
+    w.idx[rng.integers(0, tokens, 300)] = -1
+    w.idx[..., topk // 2] = w.idx[..., 0]
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v, do, acc = (torch.randn(tokens, heads, 128, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(5))
+    gate = torch.rand(tokens, heads, generator=gen, device="cuda")
+    idx, cu = torch.from_numpy(w.idx).cuda(), torch.from_numpy(w.cu_seqlens).cuda()
+    outs = []
+    for cap in (None, 1):
+        attn = nsa.SelAttention(tokens, heads, heads, topk, nseq=len(seqlens), ws_cap_bytes=cap, dense=False)
+        for ws in (attn.fwd_ws, attn.bwd_ws):
+            ws.fill_(0x7F)
+        o, lse = attn.forward(q, k, v, idx, cu)
+        got = [o, lse, *attn.backward(q, k, v, o, lse, do, cu), *attn.forward_gated(q, k, v, idx, gate, acc, cu)]
+        outs.append([x.clone() for x in got])
+    for nm, a, b in zip(("O", "LSE", "dQ", "dK", "dV", "gated O_out", "gated O", "gated LSE"), *outs):
+        assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32),
+                           b.view(torch.int16 if b.dtype == torch.bfloat16 else torch.int32)), nm
+    none = idx.eq(-1).all(dim=2)
+    assert bool((outs[0][0][none] == 0).all()) and bool(torch.isneginf(outs[0][1][none]).all()) and bool((outs[0][2][none] == 0).all())
