@@ -119,8 +119,8 @@ k_bwd_delta(Problem P, const bf16_t* __restrict__ O, const bf16_t* __restrict__ 
 // K_i, Q, dO (turned rows of 256 bytes, see row_turn) and P^T, dS^T (144-byte pitch) are row-major tiles in LDS; "lane =
 // column" operands are LDS transpose reads.  The products start from
 // zero and the row statistics come in afterwards, P = 2^(S scale log2 e - LSE), dS = P (dP scale - delta scale): partial sums of S that
-// start from -LSE / scale carry a term several times their size (the error of P before it is rounded to bf16 doubles) for 1 % of the
-// kernel's time.  Keys are hidden in a branch that tiles seeing the whole block skip.  The list's token ids are kept in LDS 1024
+// start from -LSE / scale carry a term several times their size (the error of P before it is rounded to bf16 doubles) and are no
+// faster (4.07 and 4.08 ms at 65536 tokens, g = 4).  Keys are hidden in a branch that tiles seeing the whole block skip.  The list's token ids are kept in LDS 1024
 // entries at a time.
 // A row's place in memory is worked out once, by the lane that owns it, one tile before its loads are issued, and handed
 // to the lanes that move it; rows move through buffer instructions without branches (see RowTensor), so the wait for a
@@ -304,6 +304,12 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 #pragma unroll
           for (int c = 0; c < 4; ++c) sacc[4 * a + c] = __builtin_amdgcn_exp2f(fmaf(sacc[4 * a + c], c2, -lse4[c]));
         }
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {  // (dP - delta) scale, ahead of the branch so that the reads run beside the products
+          const f32x4 dls4 = *reinterpret_cast<const f32x4*>(rec_rd + kTile + 8 * a);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) dpacc[4 * a + c] = fmaf(dpacc[4 * a + c], P.scale, -dls4[c]);
+        }
         if (part_seen) {
           const uint32_t key = 32 * kb + col;
 #pragma unroll
@@ -318,12 +324,11 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
         }
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-          const f32x4 dls4 = *reinterpret_cast<const f32x4*>(rec_rd + kTile + 8 * a);
           float p[4], ds[4];
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             p[c] = sacc[4 * a + c];
-            ds[c] = p[c] * fmaf(dpacc[4 * a + c], P.scale, -dls4[c]);  // P (dP - delta) scale
+            ds[c] = p[c] * dpacc[4 * a + c];
           }
           uint2 pw, sw2;
           pw.x = pack_bf16x2(p[0], p[1]);
