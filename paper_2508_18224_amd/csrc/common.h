@@ -438,13 +438,19 @@ inline bool reduce_in_bursts(const Problem& P, int64_t rows, int64_t tokens) {  
 }
 // The merge: by what it reads, rows * top-k; gated it has two tensors to write and half the rows a workgroup.  (one row at a time ->
 // bursts, us; 16 heads, g = 1: top-k 16 8192 tokens 109 -> 109, 12500 169 -> 168, 16384 224 -> 208; top-k 8 25000 tokens 175 -> 185, 33080
-// 252 -> 240; gated, top-k 16 25000 376 -> 396, 33080 523 -> 490.)  Sequences of 870 / 1440 / 2030 tokens in the mean, 35000 in all: top-k
-// 8 220 -> 230 / 223 -> 229 / 244 -> 239, top-k 16 377 -> 390 / 381 -> 399 / 451 -> 429, top-k 32 594 -> 656 / 609 -> 689 / 784 -> 772.
-inline bool merge_in_bursts(const Problem& P, bool gated) { return reduce_in_bursts(P, (gated ? 1 << 23 : 1 << 22) / P.topk, 1536); }
+// 252 -> 240; gated, top-k 16 25000 376 -> 396, 33080 523 -> 490; top-k 5 and 6 62500 286 -> 334 and 334 -> 357.)  Sequences of 870 / 1440 /
+// 2030 tokens in the mean, 35000 in all: top-k 8 220 -> 230 / 223 -> 229 / 244 -> 239, top-k 16 377 -> 390 / 381 -> 399 / 451 -> 429, top-k
+// 32 594 -> 656 / 609 -> 689 / 784 -> 772.
+inline bool merge_in_bursts(const Problem& P, bool gated) {
+  return P.topk >= 8 && reduce_in_bursts(P, (gated ? 1 << 23 : 1 << 22) / P.topk, 1536);
+}
 // The dQ reduction: a row of the sum is half the work of a merged one.  (16 heads, g = 1, top-k 16: 5600 tokens 69 -> 68, 8192 101 -> 92, 12500
-// 159 -> 140.)  Sequences of 470 / 670 / 870 tokens: top-k 8 165 -> 173 / 196 -> 188 / 212 -> 200, top-k 16 221 -> 273 / 307 -> 297 / 347 -> 322;
-// of 670 / 870 / 2030 tokens: top-k 32 418 -> 497 / 542 -> 538 / 722 -> 651.
-inline bool dq_in_bursts(const Problem& P) { return reduce_in_bursts(P, 1 << 17, (int64_t)P.topk * P.bk * 5 / 8); }
+// 159 -> 140; top-k 8 8192 tokens 56 -> 54; top-k 6 25000 tokens 133 -> 138, 37500 200 -> 192; top-k 5 25000 tokens 113 -> 129, 62500 282 -> 291.)
+// Sequences of 470 / 670 / 870 tokens: top-k 8 165 -> 173 / 196 -> 188 / 212 -> 200, top-k 16 221 -> 273 / 307 -> 297 / 347 -> 322; of 670 / 870 /
+// 2030 tokens: top-k 32 418 -> 497 / 542 -> 538 / 722 -> 651.
+inline bool dq_in_bursts(const Problem& P) {
+  return P.topk >= 6 && reduce_in_bursts(P, P.topk >= 8 ? 1 << 17 : 1 << 19, (int64_t)P.topk * P.bk * 5 / 8);
+}
 // LDS of a workgroup: 16 bytes a thread and row for every tensor written, and a float a row for LSE.
 constexpr int reduce_lds(int threads, int rows, int tensors, bool lse) { return rows * threads * (16 * tensors) + (lse ? rows * threads / 4 : 0); }
 template <int kRows, int kThreads>

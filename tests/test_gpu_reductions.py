@@ -46,6 +46,7 @@ def test_dropped_columns_are_not_gathered(sequences):
 
 @pytest.mark.parametrize("seqlens,heads,topk", [
     ([8200], 16, 9),             # dQ in bursts, two turns of the chip, workgroups of four and five steps; merged row by row
+    ([16399], 32, 6),            # dQ in bursts, full workgroups
     ([16399], 16, 16),           # both: three turns, five and six steps, the last one part empty
     ([4000, 1, 12500], 32, 16),  # five turns of full workgroups; gated in bursts too
 ])

@@ -101,9 +101,9 @@ def test_reduction_by_ranges_of_lists_matches_one_list_each(tokens, block):
 @pytest.mark.parametrize("seqlens,hq,hkv,topk,block,dense", [([8201], 32, 32, 5, 64, False), ([3000, 1, 5200], 33, 11, 17, 64, False),
                                                              ([9001], 30, 6, 32, 128, False), ([9001], 30, 6, 3, 64, True)])
 def test_reduction_in_bursts_matches_row_by_row(seqlens, hq, hkv, topk, block, dense):
-    """From 2^17 rows a pass the dQ reduction writes a workgroup's rows at once, below that as they are done: one pass takes the
-    former (the last workgroup of it part empty), a KV head per pass the latter.  Same sums in the same order, same bits; gated
-    and plain, more and fewer columns than a batch.  (The merge follows from 2^22 gathered rows: test_gpu_reductions.py.)"""
+    """From 2^17 rows a pass and eight columns on the dQ reduction writes a workgroup's rows at once, else as they are done: one pass takes
+    the former with 17 and 32 columns (the last workgroup of it part empty), a KV head per pass and fewer columns the latter.  Same sums
+    in the same order, same bits; gated and plain, more and fewer columns than a batch.  (The merge in bursts: test_gpu_reductions.py.)"""
     print("case bursts", seqlens, hq, hkv, topk, block, dense, flush=True)
     w = wl.realise(wl.Workload("bursts", seqlens, hq=hq, hkv=hkv, topk=topk, block=block, sink=True, seed=96))
     rows = w.total_tokens * hq
