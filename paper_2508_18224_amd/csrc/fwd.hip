@@ -545,9 +545,16 @@ constexpr int kDnMeta = kDnLse + 4 * 32 * 4;
 static_assert(4 * 32 * kDnRow <= kDnLse, "phase 1's result must fit the K / V area");
 // words of phase 2's index data of one wavefront: (kept, dense, positions) of every token its 32 rows can touch
 inline __host__ __device__ int dense_meta_words(int g, int topk) { return (31 / g + 2) * (topk + 2); }
-inline int dense_lds_bytes(int g, int topk, bool gated) { return kDnMeta + 16 * dense_meta_words(g, topk) + (gated ? 4 * 32 * kDnRow : 0); }
+inline int dense_lds_bytes(int g, int topk, bool parked_gated) {
+  return kDnMeta + 16 * dense_meta_words(g, topk) + (parked_gated ? 4 * 32 * kDnRow : 0);
+}
+// Whether finished rows wait in LDS until the workgroup writes them.  With a gate that takes another 32 KB, and where two workgroups
+// would no longer fit a compute unit (g = 1, top-k above 28) rows are written as they are done: 16384 tokens, 16 heads, g = 1, top-k 32, gated:
+// 1119 us with one workgroup a unit, 689 so.
+inline bool rows_wait(int g, int topk, bool gated) { return !gated || dense_lds_bytes(g, topk, true) <= 80 * 1024; }
 constexpr int kMergeBatch = 7;                                 // columns of a row gathered at a time in phase 2
 
+template <bool kWait>
 __global__ void __launch_bounds__(256, 2)
 k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
                   const int32_t* __restrict__ tile_tok0, const int32_t* __restrict__ tile_len,
@@ -863,22 +870,32 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           }
         }
       }
-      // the finished rows wait in LDS, in the place of phase 1's, until the workgroup writes all of them
+      // the finished rows wait in LDS, in the place of phase 1's, until the workgroup writes all of them (see rows_wait)
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
         const int wrow = 4 * pass + crow_b + 16 * x;
+        if (!kWait && row0 + wrow >= rows_total) continue;
         const bool empty = vm_all[x] == 0u;  // nothing visible: O = 0, LSE = -inf, and the gated sum is what the other branches gave
         const float inv = empty ? 0.f : 1.f / Ls[x];
         const int place = wrow * kDnRow + ((sub ^ (wrow & 15)) << 4);
-        *reinterpret_cast<u32x4*>(od_lds + place) =
-            u32x4{pack_bf16x2(acc[x][0] * inv, acc[x][1] * inv), pack_bf16x2(acc[x][2] * inv, acc[x][3] * inv),
-                  pack_bf16x2(acc[x][4] * inv, acc[x][5] * inv), pack_bf16x2(acc[x][6] * inv, acc[x][7] * inv)};
-        if (sub == 0) lse_lds[wrow] = empty ? -INFINITY : M[x] + __logf(Ls[x]);
+        const u32x4 o = {pack_bf16x2(acc[x][0] * inv, acc[x][1] * inv), pack_bf16x2(acc[x][2] * inv, acc[x][3] * inv),
+                         pack_bf16x2(acc[x][4] * inv, acc[x][5] * inv), pack_bf16x2(acc[x][6] * inv, acc[x][7] * inv)};
+        const float lse = empty ? -INFINITY : M[x] + __logf(Ls[x]);
+        auto row_of = [&]() {
+          const int e = div_g(min(row0 + wrow, rows_total - 1), P.g, P.g_magic);
+          return (int64_t)(ttok0 + e) * P.hq + hbase + hh[x];
+        };
+        if constexpr (kWait) {
+          *reinterpret_cast<u32x4*>(od_lds + place) = o;
+          if (sub == 0) lse_lds[wrow] = lse;
+        } else {
+          store_streaming(O + row_of() * kD + 8 * sub, o);
+          if (sub == 0) LSE[row_of()] = lse;
+        }
         if (gate != nullptr) {
           // Eq. (2): O_out = O_acc + gate * O, from the fp32 result (Oout may be the buffer Oacc points to: every lane
           // reads its own 16 bytes before it writes them)
-          const int e = div_g(min(row0 + wrow, rows_total - 1), P.g, P.g_magic);
-          const int64_t grow = (int64_t)(ttok0 + e) * P.hq + hbase + hh[x];
+          const int64_t grow = row_of();
           const float tau = gate[grow] * inv;
           u32x4 a = {0, 0, 0, 0};
           if (Oacc != nullptr) a = *reinterpret_cast<const u32x4*>(Oacc + grow * kD + 8 * sub);
@@ -888,11 +905,13 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
             a.z = pack_bf16x2(bf16_lo(a.z) + tau * acc[x][4], bf16_hi(a.z) + tau * acc[x][5]);
             a.w = pack_bf16x2(bf16_lo(a.w) + tau * acc[x][6], bf16_hi(a.w) + tau * acc[x][7]);
           }
-          *reinterpret_cast<u32x4*>(gated_lds + place) = a;
+          if constexpr (kWait) *reinterpret_cast<u32x4*>(gated_lds + place) = a;
+          else store_streaming(Oout + grow * kD + 8 * sub, a);
         }
       }
     }
   }
+  if constexpr (!kWait) return;
   __syncthreads();
   if (!wave_on) return;
 #pragma unroll
@@ -1033,8 +1052,9 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
   auto* main64 = wide ? k_fwd_main<true> : k_fwd_main<false>;
   auto* main128 = wide ? k_fwd_main128<true> : k_fwd_main128<false>;
   if (P0.dense) {
-    static std::atomic<uint64_t> ready_dense;
-    hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge, 96 * 1024, ready_dense);
+    static std::atomic<uint64_t> ready_dense[2];
+    hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge<true>, 80 * 1024, ready_dense[0]);
+    if (e == hipSuccess) e = allow_dynamic_lds((const void*)k_fwd_dense_merge<false>, 80 * 1024, ready_dense[1]);
     if (e != hipSuccess) return e;
   } else {
     static std::atomic<uint64_t> ready_merge[2];
@@ -1075,7 +1095,9 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
       const int chunks = (kTileTokens * P.g + 127) / 128;
       const int per = (P.nj * P.t_cap * chunks + 7) / 8;
       ProfScope ps(KID_FWD_DENSE, st);
-      hipLaunchKernelGGL(k_fwd_dense_merge, dim3((unsigned)(8 * per)), dim3(256), dense_lds_bytes(P.g, P.topk, G.gate != nullptr), st, P, (const bf16_t*)Q,
+      const bool gated = G.gate != nullptr, wait = rows_wait(P.g, P.topk, gated);
+      auto* kern = wait ? k_fwd_dense_merge<true> : k_fwd_dense_merge<false>;
+      hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per)), dim3(256), dense_lds_bytes(P.g, P.topk, gated && wait), st, P, (const bf16_t*)Q,
                          (const bf16_t*)K, (const bf16_t*)V, p.tile_tok0, p.tile_len, p.d_cnt, p.d_piece, p.d_mask,
                          (const bf16_t*)opart, (const float*)lse_part, p.vmask, p.dmask, p.slotpos, p.off, (bf16_t*)O,
                          LSE, G.gate, (const bf16_t*)G.o_acc, (bf16_t*)G.o_out);

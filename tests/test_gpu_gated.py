@@ -137,3 +137,39 @@ def test_selected_and_window_branches_gated_into_one_output():
     assert_dgate_close("dgate sel", to_f64(dg1), dO, r_sel)
     assert_dgate_close("dgate win", to_f64(dg2), dO, O_w)
     assert np.allclose(rg1, (dO * r_sel).sum(axis=2)) and np.allclose(rg2, (dO * O_w).sum(axis=2))
+
+
+@pytest.mark.parametrize("seqlens,topk", [([3000, 1, 333], 28), ([3000, 1, 333], 29), ([16384], 32)])
+def test_gated_dense_route_one_head_per_kv_head_and_many_columns(seqlens, topk):
+    """g = 1 on the dense route: up to 28 columns a workgroup's finished rows wait in LDS, from 29 on they are written as they are done,
+    since two workgroups would not fit a compute unit with them.  In place, against the plain output (the library adds before it
+    rounds: two bf16 roundings apart) and, at the largest, against the time without a gate: 1.05 times that, and 1.8 times with one
+    workgroup a unit.  Compared on the fastest of several."""
+    print("case gated g1", seqlens, topk, flush=True)
+    w = wl.realise(wl.Workload("gated_g1", seqlens, hq=16, hkv=16, topk=topk, sink=True, seed=47), tensors=False)
+    tokens = w.total_tokens
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    q, k, v, acc = (torch.randn(tokens, 16, 128, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    gate = torch.rand(tokens, 16, generator=gen, device="cuda")
+    idx, cu = torch.from_numpy(w.idx).cuda(), torch.from_numpy(w.cu_seqlens).cuda()
+    idx[5::50, 3] = -1                                          # rows that keep nothing
+    attn = nsa.SelAttention(tokens, 16, 16, topk, nseq=len(seqlens), bwd=False, dense=True)
+    o, lse = attn.forward(q, k, v, idx, cu)
+    buf = acc.clone()
+    o_out, o_g, lse_g = attn.forward_gated(q, k, v, idx, gate, buf, cu, out=buf)
+    assert o_out.data_ptr() == buf.data_ptr() and torch.equal(o, o_g) and torch.equal(lse, lse_g)
+    plain = acc.float() + gate[..., None] * o.float()
+    assert ((o_out.float() - plain).abs() <= 2.0 ** -7 * (plain.abs() + o.float().abs())).all()
+    assert torch.equal(o_out[5::50, 3], acc[5::50, 3])
+    if tokens < 16384:
+        return
+    best = [float("inf")] * 2
+    for _ in range(6):
+        for i, run in enumerate((lambda: attn.forward(q, k, v, idx, cu), lambda: attn.forward_gated(q, k, v, idx, gate, acc, cu))):
+            nsa.binding.profile_enable(16)
+            run()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], nsa.binding.profile_collect()["fwd_dense"][0])
+    nsa.binding.profile_enable(0)
+    print("plain, gated", best, flush=True)
+    assert best[1] < 1.5 * best[0]
