@@ -519,7 +519,7 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 //            requested as soon as its tile has been read: the next K flies during the PV product, the next V during the
 //            S product and the softmax.  The result, normalised, goes to LDS with its log-sum-exp.
 //   phase 2  is the reduction step of Sec. 3.2 for the same rows: 16 lanes per row gather the partial rows the gather
-//            route left for the row's other kept columns (two rows and eight columns at a time per lane: the few
+//            route left for the row's other kept columns (two rows and up to eight columns at a time per lane: the few
 //            wavefronts of this kernel need that many loads in flight) and combine them, together with the row of
 //            phase 1, by their log-sum-exps; O, LSE and the optional gated sum of Eq. (2) are written once.  The
 //            rows' kept-column masks and slot positions are fetched at the very start of the kernel and parked in
@@ -552,7 +552,16 @@ inline int dense_lds_bytes(int g, int topk, bool parked_gated) {
 // would no longer fit a compute unit (g = 1, top-k above 28) rows are written as they are done: 16384 tokens, 16 heads, g = 1, top-k 32, gated:
 // 1119 us with one workgroup a unit, 689 so.
 inline bool rows_wait(int g, int topk, bool gated) { return !gated || dense_lds_bytes(g, topk, true) <= 80 * 1024; }
-constexpr int kMergeBatch = 7;                                 // columns of a row gathered at a time in phase 2
+// Columns of a row gathered next in phase 2 when `left` are: at most eight, as few rounds as possible, of like size.  A place in a
+// round that no row fills costs nearly as much as a column: 16384 tokens, g = 4, with 15 columns to gather 431 us in rounds of
+// seven, 425 of eight, 411 of five, 403 as eight and seven; with 14 columns 396, 419, 405 and 395; with 30 columns 779, 783, 772 and 762; with
+// 7 columns 226, 238, 249 and 226; with 2 columns 212 in one of seven and 192 in one of four.
+constexpr int kMergeBatch = 8;
+__device__ __forceinline__ int batch_of(int left) {
+  constexpr int b = kMergeBatch;
+  return left <= b ? left : left <= 2 * b ? (left + 1) / 2 : left <= 3 * b ? (left + 2) / 3 : (left + 3) / 4;
+}
+static_assert(4 * kMergeBatch >= kMaxTopk, "at most four rounds");
 
 template <bool kWait>
 __global__ void __launch_bounds__(256, 2)
@@ -825,21 +834,22 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           }
         }
       }
-      while (__builtin_amdgcn_ballot_w64((vm[0] | vm[1]) != 0u) != 0ull) {  // the next columns of some row
-        u32x4 xv[2][kMergeBatch];
-        float ls[2][kMergeBatch];
-        int at[2][kMergeBatch];  // position, -1 past the row's last column
+      auto gather = [&](auto count) __attribute__((always_inline)) {  // the next `count` columns of both rows
+        constexpr int kBatch = decltype(count)::value;
+        u32x4 xv[2][kBatch];
+        float ls[2][kBatch];
+        int at[2][kBatch];  // position, -1 past the row's last column
 #pragma unroll
         for (int x = 0; x < 2; ++x)
 #pragma unroll
-          for (int i = 0; i < kMergeBatch; ++i) {
+          for (int i = 0; i < kBatch; ++i) {
             at[x][i] = vm[x] != 0u ? sp[x][__builtin_ctz(vm[x] | 0x80000000u)] : -1;
             vm[x] &= vm[x] - 1u;
           }
 #pragma unroll
         for (int x = 0; x < 2; ++x)
 #pragma unroll
-          for (int i = 0; i < kMergeBatch; ++i) {
+          for (int i = 0; i < kBatch; ++i) {
             xv[x][i] = u32x4{0, 0, 0, 0};
             ls[x][i] = -INFINITY;
             if (at[x][i] >= 0) {
@@ -852,7 +862,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
         for (int x = 0; x < 2; ++x) {
           float Mb = M[x];
 #pragma unroll
-          for (int i = 0; i < kMergeBatch; ++i) Mb = fmaxf(Mb, ls[x][i]);
+          for (int i = 0; i < kBatch; ++i) Mb = fmaxf(Mb, ls[x][i]);
           if (Mb == -INFINITY) continue;  // no kept column in this batch or before it
           const float rescale = __expf(M[x] - Mb);  // 0 on the first non-empty batch
           Ls[x] *= rescale;
@@ -860,7 +870,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           for (int c = 0; c < 8; ++c) acc[x][c] *= rescale;
           M[x] = Mb;
 #pragma unroll
-          for (int i = 0; i < kMergeBatch; ++i) {
+          for (int i = 0; i < kBatch; ++i) {
             const float w = __expf(ls[x][i] - Mb);  // exp(-inf) = 0 for columns that are off
             Ls[x] += w;
             acc[x][0] += w * bf16_lo(xv[x][i].x); acc[x][1] += w * bf16_hi(xv[x][i].x);
@@ -869,6 +879,20 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
             acc[x][6] += w * bf16_lo(xv[x][i].w); acc[x][7] += w * bf16_hi(xv[x][i].w);
           }
         }
+      };
+      int left = max((int)__builtin_popcount(vm[0]), (int)__builtin_popcount(vm[1]));  // columns of the row that has most
+      left = max(max(__builtin_amdgcn_readlane(left, 0), __builtin_amdgcn_readlane(left, 16)),
+                 max(__builtin_amdgcn_readlane(left, 32), __builtin_amdgcn_readlane(left, 48)));
+      while (left > 0) {
+        const int n = batch_of(left);
+        switch (n) {
+          case 8: gather(std::integral_constant<int, 8>{}); break;
+          case 7: gather(std::integral_constant<int, 7>{}); break;
+          case 6: gather(std::integral_constant<int, 6>{}); break;
+          case 5: gather(std::integral_constant<int, 5>{}); break;
+          default: gather(std::integral_constant<int, 4>{});
+        }
+        left -= n;
       }
       // the finished rows wait in LDS, in the place of phase 1's, until the workgroup writes all of them (see rows_wait)
 #pragma unroll

@@ -192,3 +192,12 @@ def test_rows_past_a_ragged_block_are_never_used(block, dense):
         assert torch.equal(o[good], o0[good]) and torch.equal(lse[good], lse0[good]) and bool(torch.isfinite(o[good]).all())
         for a, b in zip(grads, g0):
             assert torch.equal(a[good], b[good])
+
+
+@pytest.mark.parametrize("topk,sink", [(2, False), (6, True), (9, True), (10, True), (10, False), (17, False), (19, True), (26, True),
+                                       (27, False), (32, False)])
+def test_rounds_of_gathered_columns(topk, sink):
+    """The columns that are not dense (all but the own block and, with a sink, block 0) are gathered in rounds of like size, four to
+    eight columns each: one round (four of them in part empty), a full one, two, three and four."""
+    print("case rounds", topk, sink, flush=True)
+    _check(wl.realise(wl.Workload("rounds", [2560, 61], hq=2, hkv=1, topk=topk, sink=sink, seed=59)))
