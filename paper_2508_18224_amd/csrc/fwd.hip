@@ -553,9 +553,10 @@ inline int dense_lds_bytes(int g, int topk, bool parked_gated) {
 // 1119 us with one workgroup a unit, 689 so.
 inline bool rows_wait(int g, int topk, bool gated) { return !gated || dense_lds_bytes(g, topk, true) <= 80 * 1024; }
 // Columns of a row gathered next in phase 2 when `left` are: at most eight, as few rounds as possible, of like size.  A place in a
-// round that no row fills costs nearly as much as a column: 16384 tokens, g = 4, with 15 columns to gather 431 us in rounds of
-// seven, 425 of eight, 411 of five, 403 as eight and seven; with 14 columns 396, 419, 405 and 395; with 30 columns 779, 783, 772 and 762; with
-// 7 columns 226, 238, 249 and 226; with 2 columns 212 in one of seven and 192 in one of four.
+// round that no row fills costs nearly as much as a column: 16384 tokens, g = 4, with 15 columns to gather 427 us in rounds of
+// seven, 403 as eight and seven; with 14 columns 392 in rounds of seven, 419 as eight and six; with 30 columns 774 in rounds of seven, 759 as
+// eight, eight, seven and seven; with 2 columns 212 in a round of seven, 192 in one of four.  Rounds that all rows of a wavefront fill go
+// without a branch a column: 386, 386, 751 us with 15 (bidirectional), 14 and 30 columns, and 362 for 382 with 7 local picks of 16.
 constexpr int kMergeBatch = 8;
 __device__ __forceinline__ int batch_of(int left) {
   constexpr int b = kMergeBatch;
@@ -834,7 +835,9 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           }
         }
       }
-      auto gather = [&](auto count) __attribute__((always_inline)) {  // the next `count` columns of both rows
+      int n[2];  // columns of the round
+      // the next n[x] <= count columns of both rows; with `all`, exactly count of them
+      auto gather = [&](auto count, auto all) __attribute__((always_inline)) {
         constexpr int kBatch = decltype(count)::value;
         u32x4 xv[2][kBatch];
         float ls[2][kBatch];
@@ -843,8 +846,9 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
         for (int x = 0; x < 2; ++x)
 #pragma unroll
           for (int i = 0; i < kBatch; ++i) {
-            at[x][i] = vm[x] != 0u ? sp[x][__builtin_ctz(vm[x] | 0x80000000u)] : -1;
-            vm[x] &= vm[x] - 1u;
+            const bool on = all || i < n[x];
+            at[x][i] = on ? sp[x][__builtin_ctz(vm[x] | 0x80000000u)] : -1;
+            if (on) vm[x] &= vm[x] - 1u;
           }
 #pragma unroll
         for (int x = 0; x < 2; ++x)
@@ -852,7 +856,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           for (int i = 0; i < kBatch; ++i) {
             xv[x][i] = u32x4{0, 0, 0, 0};
             ls[x][i] = -INFINITY;
-            if (at[x][i] >= 0) {
+            if (all || at[x][i] >= 0) {
               const size_t pr = (size_t)(at[x][i] - pos0) * P.g + hh[x];
               xv[x][i] = load_streaming(opart + pr * kD + 8 * sub);
               ls[x][i] = lse_part[pr];
@@ -880,19 +884,24 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           }
         }
       };
-      int left = max((int)__builtin_popcount(vm[0]), (int)__builtin_popcount(vm[1]));  // columns of the row that has most
-      left = max(max(__builtin_amdgcn_readlane(left, 0), __builtin_amdgcn_readlane(left, 16)),
-                 max(__builtin_amdgcn_readlane(left, 32), __builtin_amdgcn_readlane(left, 48)));
-      while (left > 0) {
-        const int n = batch_of(left);
-        switch (n) {
-          case 8: gather(std::integral_constant<int, 8>{}); break;
-          case 7: gather(std::integral_constant<int, 7>{}); break;
-          case 6: gather(std::integral_constant<int, 6>{}); break;
-          case 5: gather(std::integral_constant<int, 5>{}); break;
-          default: gather(std::integral_constant<int, 4>{});
+      // every row takes what its own columns call for, so that its bits do not depend on the wavefront's other rows; where all
+      // eight have as many left, as far from the start of a sequence, that is one size and no branch a column
+      while (true) {
+        const int left0 = __builtin_popcount(vm[0]), left1 = __builtin_popcount(vm[1]);
+        const int left = __builtin_amdgcn_readfirstlane(left0);
+        const bool even = __builtin_amdgcn_ballot_w64(left0 != left || left1 != left) == 0ull;
+        if (even && left == 0) break;
+        n[0] = batch_of(left0);
+        n[1] = batch_of(left1);
+        switch (even ? batch_of(left) : 0) {
+          case 8: gather(std::integral_constant<int, 8>{}, std::true_type{}); break;
+          case 7: gather(std::integral_constant<int, 7>{}, std::true_type{}); break;
+          case 6: gather(std::integral_constant<int, 6>{}, std::true_type{}); break;
+          case 5: gather(std::integral_constant<int, 5>{}, std::true_type{}); break;
+          case 4: gather(std::integral_constant<int, 4>{}, std::true_type{}); break;
+          case 0: gather(std::integral_constant<int, 8>{}, std::false_type{}); break;
+          default: gather(std::integral_constant<int, 3>{}, std::false_type{});
         }
-        left -= n;
       }
       // the finished rows wait in LDS, in the place of phase 1's, until the workgroup writes all of them (see rows_wait)
 #pragma unroll

@@ -201,3 +201,24 @@ def test_rounds_of_gathered_columns(topk, sink):
     eight columns each: one round (four of them in part empty), a full one, two, three and four."""
     print("case rounds", topk, sink, flush=True)
     _check(wl.realise(wl.Workload("rounds", [2560, 61], hq=2, hkv=1, topk=topk, sink=sink, seed=59)))
+
+
+def test_a_row_does_not_depend_on_its_neighbours():
+    """Odd tokens keep the same blocks in both selections, even ones up to twenty more in the second, none of them dense: the partial
+    rows of a wavefront are gathered in rounds that differ in length, and the odd tokens' bits are the same."""
+    print("case neighbours", flush=True)
+    tokens, hkv, topk = 8192, 2, 32
+    w = wl.realise(wl.Workload("neighbours", [tokens], hq=4, hkv=hkv, topk=topk, sink=True, seed=61))
+    c = Case(w, bwd=False, dense=True)
+    keep = np.random.default_rng(2).integers(5, 18, size=(tokens, hkv))
+    column = np.arange(topk)[None, None, :]
+    outs = []
+    for more in (0, 1):
+        idx = w.idx.copy()
+        kept = np.where((np.arange(tokens) % 2 == 0)[:, None], keep + more * np.random.default_rng(3).integers(0, 21, size=keep.shape), keep)
+        idx[column >= kept[..., None]] = -1
+        c.idx = torch.from_numpy(idx).cuda()
+        o, lse = c.forward()
+        assert c.attn.dense_entries().any()
+        outs.append((o[6145::2].clone(), lse[6145::2].clone()))    # (earlier tiles have few blocks: what is dense there differs)
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
