@@ -526,10 +526,10 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 //            LDS, so that phase 2 starts with its addresses known and the only memory latency left in it is that of the
 //            gathers themselves.  A row's columns are taken from its bit mask, so that dense ones cost no place in a batch; the
 //            finished rows wait in LDS until the workgroup writes them all (see "the two reduction kernels" in common.h).  With
-//            the columns in place, plain loads and every row written as it was done: 1.79 instead of 1.69 ms at 65536 tokens, g = 4,
-//            1.78 instead of 1.65 with 9 of 16 columns dense at g = 7, 1.02 instead of 0.93 gated at 32768 tokens.
+//            the columns in place, plain loads and every row written as it was done: 1.79 instead of 1.62 ms at 65536 tokens, g = 4,
+//            1.78 instead of 1.54 with 9 of 16 columns dense at g = 7, 1.02 instead of 0.91 gated at 32768 tokens.
 // Tiles without a dense piece skip phase 1, so with the dense route on this kernel is the merge of every row.
-// Phase 2 is bound by memory (65536 tokens, g = 4: 9.15 GB in 1.69 ms for the whole kernel), phase 1 by the order S product,
+// Phase 2 is bound by memory (65536 tokens, g = 4: 8.9 GB in 1.62 ms for the whole kernel), phase 1 by the order S product,
 // softmax, PV product inside each of the two wavefronts of a SIMD.  Staging through registers with the piece table read inside the
 // loop took 1.87 ms there, 1.10 instead of 1.05 ms for a window of 512 at 65536 tokens and 1.88 instead of 1.81 ms with 9 of 16
 // columns dense at g = 7.  A second K tile (requests one piece earlier) gave nothing; three workgroups per CU leave 168
