@@ -19,7 +19,7 @@
 // k_fwd_main128 (B_K = 128): see the comment above it.
 // k_fwd_merge: per (token, head) combines the kept slots: LSE = ln sum_s exp(lse_s), O = sum_s exp(lse_s-LSE) O_s.
 //   This replaces the paper's separate statistics pre-pass: per-slot log-sum-exps make the merge exact.
-#include "common.h"
+#include "dense_piece.h"
 #include <type_traits>
 
 namespace nsa {
@@ -512,12 +512,11 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 // gather and no partial row in memory at all.  One workgroup takes 128 rows (row = (token of the tile, head of the
 // group)) of one (tile, kv head):
 //   phase 1  keeps the rows' Q fragments in registers and walks the tile's dense blocks, 64 keys at a time (the index
-//            lists them as pieces) through LDS, with a running (max, sum) per row and the output accumulated in
-//            registers across the pieces.  The 64-bit mask of a piece says which tokens of the tile keep its block;
-//            the others see none of its keys.  S^T = K Q^T and O^T = V^T P^T as in the kernels above (K fragments
-//            are 16-byte LDS reads, V^T fragments LDS transpose reads).  K and V go from memory straight to LDS, each
-//            requested as soon as its tile has been read: the next K flies during the PV product, the next V during the
-//            S product and the softmax.  The result, normalised, goes to LDS with its log-sum-exp.
+//            lists them as pieces) through LDS, with a running (reference, sum) per row and the output accumulated in
+//            registers across the pieces (dense_piece.h).  The 64-bit mask of a piece says which tokens of the tile keep its
+//            block; the others see none of its keys.  K and V go from memory straight to LDS, to two pairs of tiles: a
+//            piece's PV product runs beside the next piece's S product, and beside both the K after that and the next V arrive.  The
+//            result, normalised, goes to LDS with its log-sum-exp.
 //   phase 2  is the reduction step of Sec. 3.2 for the same rows: 16 lanes per row gather the partial rows the gather
 //            route left for the row's other kept columns (two rows and up to eight columns at a time per lane: the few
 //            wavefronts of this kernel need that many loads in flight) and combine them, together with the row of
@@ -529,29 +528,23 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 //            the columns in place, plain loads and every row written as it was done: 1.79 instead of 1.62 ms at 65536 tokens, g = 4,
 //            1.78 instead of 1.54 with 9 of 16 columns dense at g = 7, 1.02 instead of 0.91 gated at 32768 tokens.
 // Tiles without a dense piece skip phase 1, so with the dense route on this kernel is the merge of every row.
-// Phase 2 is bound by memory (65536 tokens, g = 4: 8.9 GB in 1.62 ms for the whole kernel), phase 1 by the order S product,
-// softmax, PV product inside each of the two wavefronts of a SIMD.  Staging through registers with the piece table read inside the
-// loop took 1.87 ms there, 1.10 instead of 1.05 ms for a window of 512 at 65536 tokens and 1.88 instead of 1.81 ms with 9 of 16
-// columns dense at g = 7.  A second K tile (requests one piece earlier) gave nothing; three workgroups per CU leave 168
-// registers, 30 of them spilled.
-// LDS: the K and the V tile of a piece, row-major and unpadded, their rows turned (see row_turn): 0.55 -> 0.51 ms for a window of
+// Phase 2 is bound by memory (65536 tokens, g = 4: 8.9 GB in 1.62 ms for the whole kernel), phase 1 by vector instructions: a wavefront's
+// piece takes 1000 clocks of them and 1024 of the matrix pipe, and two wavefronts share a SIMD.  One pair of tiles, with two barriers a
+// piece and the S product, softmax and PV product one after the other, took 1.54 instead of 1.39 ms with 9 of 16 columns dense at g
+// = 7, 65536 tokens, and 530 instead of 510 us for a window of 512 at 32768; there every access of the piece loop also waited for the loads just
+// sent on their way (see await_rows).  Three workgroups per CU leave 168 registers, 30 of them spilled.
+// LDS: unpadded, turned rows (see row_turn): 0.55 -> 0.51 ms for a window of
 // 512 at 32768 tokens, 6.3 -> 6.1 ms at 131072, g = 8, against a turn of the low three bits, which left the transposing reads at a
-// quarter of their rate.  Phase 1's result takes the same area afterwards (place c ^ (r & 15)).
+// quarter of their rate.  Phase 1's result takes the same area afterwards (place c ^ (r & 15)), and with a gate the gated rows.
 constexpr int kDnRow = kD * 2;
 constexpr int kDnK = 0;
-constexpr int kDnV = kDnK + 64 * kDnRow;
-constexpr int kDnLse = kDnV + 64 * kDnRow;
+constexpr int kDnV = kDnK + 2 * kPieceBytes;
+constexpr int kDnLse = kDnV + 2 * kPieceBytes;
 constexpr int kDnMeta = kDnLse + 4 * 32 * 4;
-static_assert(4 * 32 * kDnRow <= kDnLse, "phase 1's result must fit the K / V area");
+static_assert(2 * 4 * 32 * kDnRow <= kDnLse, "phase 1's result and the gated rows must fit the K / V area");
 // words of phase 2's index data of one wavefront: (kept, dense, positions) of every token its 32 rows can touch
 inline __host__ __device__ int dense_meta_words(int g, int topk) { return (31 / g + 2) * (topk + 2); }
-inline int dense_lds_bytes(int g, int topk, bool parked_gated) {
-  return kDnMeta + 16 * dense_meta_words(g, topk) + (parked_gated ? 4 * 32 * kDnRow : 0);
-}
-// Whether finished rows wait in LDS until the workgroup writes them.  With a gate that takes another 32 KB, and where two workgroups
-// would no longer fit a compute unit (g = 1, top-k above 28) rows are written as they are done: 16384 tokens, 16 heads, g = 1, top-k 32, gated:
-// 1119 us with one workgroup a unit, 689 so.
-inline bool rows_wait(int g, int topk, bool gated) { return !gated || dense_lds_bytes(g, topk, true) <= 80 * 1024; }
+inline int dense_lds_bytes(int g, int topk) { return kDnMeta + (g == 1 ? 8 : 16) * dense_meta_words(g, topk); }  // g = 1: two wavefronts have rows
 // Columns of a row gathered next in phase 2 when `left` are: at most eight, as few rounds as possible, of like size.  A place in a
 // round that no row fills costs nearly as much as a column: 16384 tokens, g = 4, with 15 columns to gather 427 us in rounds of
 // seven, 403 as eight and seven; with 14 columns 392 in rounds of seven, 419 as eight and six; with 30 columns 774 in rounds of seven, 759 as
@@ -564,7 +557,6 @@ __device__ __forceinline__ int batch_of(int left) {
 }
 static_assert(4 * kMergeBatch >= kMaxTopk, "at most four rounds");
 
-template <bool kWait>
 __global__ void __launch_bounds__(256, 2)
 k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
                   const int32_t* __restrict__ tile_tok0, const int32_t* __restrict__ tile_len,
@@ -633,18 +625,24 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
     const int srow = 4 * wave + (lane >> 4);
     const uint32_t row_bytes = (uint32_t)P.hkv * kDnRow;
     const uint32_t stage_off = srow * row_bytes + (((lane & 15) ^ row_turn(srow)) << 4);
+    // the rows of piece `step` of K or V, past the last piece none: they arrive as zeros
+    auto piece_of = [&](const bf16_t* X, int step) __attribute__((always_inline)) {
+      const int first = __builtin_amdgcn_readlane(my_piece.x, min(step, nd - 1)), len = __builtin_amdgcn_readlane(my_piece.y, min(step, nd - 1));
+      return buffer_of(X + ((size_t)first * P.hkv + j) * kD, step < nd ? (uint32_t)((len - 1) * P.hkv + 1) * kDnRow : 0u);
+    };
+    auto load = [&](__amdgpu_buffer_rsrc_t buf, int lds_off, int i) __attribute__((always_inline)) {
+      uint32_t from = stage_off;
+      asm volatile("" : "+v"(from));  // the offsets are not kept in registers
+      load_to_lds(buf, lds_address(smem + lds_off) + (16 * i + 4 * wave) * kDnRow, from + 16 * i * row_bytes);
+    };
     auto stage = [&](const bf16_t* X, int lds_off, int step) __attribute__((always_inline)) {
-      UnitRec B;
-      B.tok0 = __builtin_amdgcn_readlane(my_piece.x, step);
-      B.blen = __builtin_amdgcn_readlane(my_piece.y, step);
-      B.j = j;
-      const __amdgpu_buffer_rsrc_t buf = block_buffer(X, P, B);
+      const __amdgpu_buffer_rsrc_t buf = piece_of(X, step);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        load_to_lds(buf, lds_address(smem + lds_off) + (16 * i + 4 * wave) * kDnRow, stage_off + 16 * i * row_bytes);
+      for (int i = 0; i < 4; ++i) load(buf, lds_off, i);
     };
     stage(K, kDnK, 0);
     stage(V, kDnV, 0);
+    stage(K, kDnK + kPieceBytes, 1);
     // this wavefront's 32 rows of Q as B-operand fragments, kept for the whole tile
     const int r = row0 + col;                        // this lane's row
     const bool valid = r < rows_total;
@@ -664,112 +662,61 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;            // running maximum (raw scores) and sum of the row
-    const int grp = lane >> 4, sl = lane & 15;
-    // K fragment of contraction step s, keys 32 mb..: chunk 2 s + qh of row 32 mb + col
-    uint32_t kaddr[8];
-#pragma unroll
-    for (int s = 0; s < 8; ++s) kaddr[s] = lds_address(smem + kDnK) + col * kDnRow + (((2 * s + qh) ^ row_turn(col)) << 4);
-    // V^T fragments: transposing reads of rows (sl / 4) + 4 (grp / 2) + 16 sp (+ 8), channels 32 db + 16 (grp & 1) + 4 (sl & 3)
-    const int vrow = (sl >> 2) + 4 * (grp >> 1), vchunk = 2 * (grp & 1) + ((sl & 3) >> 1);
-    uint32_t vaddr[2][4];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int d = 0; d < 4; ++d)
-        vaddr[h][d] = lds_address(smem + kDnV) + (vrow + 8 * h) * kDnRow + (((4 * d + vchunk) ^ row_turn(vrow + 8 * h)) << 4) + 8 * (sl & 1);
+    float m_ref = -INFINITY, l_run = 0.f;            // reference score and sum of the row (see new_reference)
+    const float slack = kSlack / c2;
+    uint32_t kaddr[8], vaddr[2][4];
+    piece_addresses(lds_address(smem + kDnK), lds_address(smem + kDnV), lane, kaddr, vaddr);
 
+    await_rows(qf);
     wait_loads();
-    __syncthreads();  // the first piece is staged
-    for (int step = 0; step < nd; ++step) {
-      // the reads below differ from these addresses by immediate offsets only
-      asm volatile("" : "+v"(kaddr[0]), "+v"(kaddr[1]), "+v"(kaddr[2]), "+v"(kaddr[3]), "+v"(kaddr[4]), "+v"(kaddr[5]),
-                   "+v"(kaddr[6]), "+v"(kaddr[7]));
-      asm volatile("" : "+v"(vaddr[0][0]), "+v"(vaddr[0][1]), "+v"(vaddr[0][2]), "+v"(vaddr[0][3]), "+v"(vaddr[1][0]),
-                   "+v"(vaddr[1][1]), "+v"(vaddr[1][2]), "+v"(vaddr[1][3]));
+    __syncthreads();  // the first piece and the second one's K are staged
+    f32x16 even[2], odd[2];
+    piece_scores(kaddr, qf, even);
+    float m = max_scores(even);
+    __syncthreads();  // every wavefront has read the first K
+    auto piece = [&](int step, f32x16 (&cur)[2], f32x16 (&next)[2], int side) __attribute__((always_inline)) {
+      // this piece's K tile has been read in the step before: K of the piece after the next flies there, V of the next to the
+      // other tile
+      const __amdgpu_buffer_rsrc_t kbuf = piece_of(K, step + 2), vbuf = piece_of(V, step + 1);
+      keep_addresses(kaddr, vaddr);
+      uint32_t ka[8], va[2][4];
+#pragma unroll
+      for (int s = 0; s < 8; ++s) ka[s] = kaddr[s] + (side ^ 1) * kPieceBytes;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        va[0][d] = vaddr[0][d] + side * kPieceBytes;
+        va[1][d] = vaddr[1][d] + side * kPieceBytes;
+      }
       const unsigned long long members =
           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_mask, step) |
           (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_mask >> 32), step) << 32;
       // first key of the piece and its number of keys
       const int ktok0 = __builtin_amdgcn_readlane(my_piece.x, step), klen = __builtin_amdgcn_readlane(my_piece.y, step);
-      f32x16 sacc[2];
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sacc[mb][v] = 0.f;
-#pragma unroll
-      for (int s = 0; s < 8; ++s)
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-          const bf16x8 kf = lds_read_frag(kaddr[s] + 32 * mb * kDnRow);
-          sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sacc[mb], 0, 0, 0);
-        }
       // keys [lo, lim) of the piece are visible to this row: none if the token does not keep the block
       int lim = P.causal ? min(klen, t - ktok0 + 1) : klen;
       if (!valid || !((members >> e_row) & 1ull)) lim = 0;
-      const int lo = P.window > 0 ? t - P.window + 1 - ktok0 : 0;
-      float m = -INFINITY;
-      if (__builtin_amdgcn_ballot_w64(lim < 64 || lo > 0) == 0) {
+      const int lo = P.window > 0 ? max(t - P.window + 1 - ktok0, 0) : 0;
+      const bool sees = lim > lo;
+      if (__builtin_amdgcn_ballot_w64(sees && (lim < 64 || lo > 0)) != 0ull) {
+        m = mask_scores(cur, lo, lim, qh);
+      } else if (__builtin_amdgcn_ballot_w64(!sees) != 0ull) {  // rows see all of the piece or nothing of it
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) m = fmaxf(m, sacc[mb][v]);
-      } else {
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int key = 32 * mb + 8 * (v >> 2) + 4 * qh + (v & 3);
-            const float x = (key < lim && key >= lo) ? sacc[mb][v] : -INFINITY;
-            sacc[mb][v] = x;
-            m = fmaxf(m, x);
-          }
+          for (int v = 0; v < 16; ++v) cur[mb][v] = sees ? cur[mb][v] : -INFINITY;
       }
-      m = fmaxf(m, __shfl_xor(m, 32));
-      // Online softmax: new running maximum, rescale of what has been accumulated.  For every piece, also where no maximum of
-      // the wavefront has grown much: a rescale put off until some row's has would make a row's rounding depend on the
-      // rows it shares the wavefront with.
-      const float m_new = fmaxf(m_run, m);
-      const float mc = (m_new == -INFINITY) ? 0.f : m_new * c2;
-      const float alpha = __builtin_amdgcn_exp2f(fmaf(m_run, c2, -mc));  // exp2(-inf) = 0 on the first visible piece
-      m_run = m_new;
-      float l = 0.f;
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(sacc[mb][v], c2, -mc));
-          sacc[mb][v] = p;
-          l += p;
-        }
-      l += __shfl_xor(l, 32);
-      l_run = l_run * alpha + l;
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
-
-      bf16x8 pf[4];
-#pragma unroll
-      for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int e2 = 0; e2 < 8; ++e2) pf[sp][e2] = (bf16_t)sacc[sp >> 1][8 * (sp & 1) + e2];
-      // K of this piece has been read and, with every wavefront's loads done, V of it is staged: the next K flies during the
-      // PV product, the next V during the S product and the softmax after it
+      new_reference(row_max(m), sees, c2, slack, m_ref, l_run, oacc);
+      m = piece_values_and_next_scores(ka, va, qf, c2, m_ref == -INFINITY ? 0.f : m_ref * c2, cur, next, l_run, oacc,
+                                       [&](int i) __attribute__((always_inline)) {
+                                         if (i < 4) load(vbuf, kDnV + (side ^ 1) * kPieceBytes, i);
+                                         else if (i < 8) load(kbuf, kDnK + side * kPieceBytes, i - 4);
+                                       });
       wait_loads();
-      __syncthreads();
-      if (step + 1 < nd) stage(K, kDnK, step + 1);
-#pragma unroll
-      for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int db = 0; db < 4; ++db) {
-          const bf16x4 a0 = lds_read_tr_at(vaddr[0][db] + 16 * sp * kDnRow), a1 = lds_read_tr_at(vaddr[1][db] + 16 * sp * kDnRow);
-          const bf16x8 vf = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
-          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[sp], oacc[db], 0, 0, 0);
-        }
-      wait_loads();
-      __syncthreads();  // V of this piece has been read (after the last piece: the K / V area is free), the next K is staged
-      if (step + 1 < nd) stage(V, kDnV, step + 1);
+      __syncthreads();  // this piece has been read (after the last one: the K / V area is free), the next one is staged
+    };
+    for (int step = 0; step < nd; step += 2) {
+      piece(step, even, odd, 0);
+      if (step + 1 < nd) piece(step + 1, odd, even, 1);
     }
     if (wave_on) {
       // the rows' dense result, normalised, and its log-sum-exp (natural log; -inf for a row that keeps none of the
@@ -786,7 +733,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           *reinterpret_cast<uint2*>(od_lds + col * kDnRow + (((4 * db + a) ^ (col & 15)) << 4) + 8 * qh) = w;
         }
       if (qh == 0) {
-        const float mcf = (m_run == -INFINITY) ? 0.f : m_run * c2;
+        const float mcf = (m_ref == -INFINITY) ? 0.f : m_ref * c2;
         lse_lds[col] = l_run > 0.f ? (mcf + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f : -INFINITY;
       }
       wave_sync();
@@ -797,7 +744,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
   int lane_b = threadIdx.x & 63;
   asm volatile("" : "+v"(lane_b));
   const int sub = lane_b & 15, crow_b = lane_b >> 4;
-  unsigned char* gated_lds = smem + kDnMeta + 16 * dense_meta_words(P.g, P.topk) + wave * 32 * kDnRow;
+  unsigned char* gated_lds = smem + (4 + wave) * 32 * kDnRow;
   if (wave_on) {
     if (nd == 0) park_meta();
     const int pos0 = off[P.j0 * P.b_cap];  // first list position of the pass: partial rows are relative to it
@@ -903,32 +850,22 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           default: gather(std::integral_constant<int, 3>{}, std::false_type{});
         }
       }
-      // the finished rows wait in LDS, in the place of phase 1's, until the workgroup writes all of them (see rows_wait)
+      // the finished rows wait in LDS, in the place of phase 1's, until the workgroup writes all of them
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
         const int wrow = 4 * pass + crow_b + 16 * x;
-        if (!kWait && row0 + wrow >= rows_total) continue;
         const bool empty = vm_all[x] == 0u;  // nothing visible: O = 0, LSE = -inf, and the gated sum is what the other branches gave
         const float inv = empty ? 0.f : 1.f / Ls[x];
         const int place = wrow * kDnRow + ((sub ^ (wrow & 15)) << 4);
         const u32x4 o = {pack_bf16x2(acc[x][0] * inv, acc[x][1] * inv), pack_bf16x2(acc[x][2] * inv, acc[x][3] * inv),
                          pack_bf16x2(acc[x][4] * inv, acc[x][5] * inv), pack_bf16x2(acc[x][6] * inv, acc[x][7] * inv)};
         const float lse = empty ? -INFINITY : M[x] + __logf(Ls[x]);
-        auto row_of = [&]() {
-          const int e = div_g(min(row0 + wrow, rows_total - 1), P.g, P.g_magic);
-          return (int64_t)(ttok0 + e) * P.hq + hbase + hh[x];
-        };
-        if constexpr (kWait) {
-          *reinterpret_cast<u32x4*>(od_lds + place) = o;
-          if (sub == 0) lse_lds[wrow] = lse;
-        } else {
-          store_streaming(O + row_of() * kD + 8 * sub, o);
-          if (sub == 0) LSE[row_of()] = lse;
-        }
+        *reinterpret_cast<u32x4*>(od_lds + place) = o;
+        if (sub == 0) lse_lds[wrow] = lse;
         if (gate != nullptr) {
           // Eq. (2): O_out = O_acc + gate * O, from the fp32 result (Oout may be the buffer Oacc points to: every lane
           // reads its own 16 bytes before it writes them)
-          const int64_t grow = row_of();
+          const int64_t grow = (int64_t)(ttok0 + div_g(min(row0 + wrow, rows_total - 1), P.g, P.g_magic)) * P.hq + hbase + hh[x];
           const float tau = gate[grow] * inv;
           u32x4 a = {0, 0, 0, 0};
           if (Oacc != nullptr) a = *reinterpret_cast<const u32x4*>(Oacc + grow * kD + 8 * sub);
@@ -938,13 +875,11 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
             a.z = pack_bf16x2(bf16_lo(a.z) + tau * acc[x][4], bf16_hi(a.z) + tau * acc[x][5]);
             a.w = pack_bf16x2(bf16_lo(a.w) + tau * acc[x][6], bf16_hi(a.w) + tau * acc[x][7]);
           }
-          if constexpr (kWait) *reinterpret_cast<u32x4*>(gated_lds + place) = a;
-          else store_streaming(Oout + grow * kD + 8 * sub, a);
+          *reinterpret_cast<u32x4*>(gated_lds + place) = a;
         }
       }
     }
   }
-  if constexpr (!kWait) return;
   __syncthreads();
   if (!wave_on) return;
 #pragma unroll
@@ -1085,9 +1020,8 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
   auto* main64 = wide ? k_fwd_main<true> : k_fwd_main<false>;
   auto* main128 = wide ? k_fwd_main128<true> : k_fwd_main128<false>;
   if (P0.dense) {
-    static std::atomic<uint64_t> ready_dense[2];
-    hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge<true>, 80 * 1024, ready_dense[0]);
-    if (e == hipSuccess) e = allow_dynamic_lds((const void*)k_fwd_dense_merge<false>, 80 * 1024, ready_dense[1]);
+    static std::atomic<uint64_t> ready_dense;
+    const hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge, 80 * 1024, ready_dense);
     if (e != hipSuccess) return e;
   } else {
     static std::atomic<uint64_t> ready_merge[2];
@@ -1128,9 +1062,7 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
       const int chunks = (kTileTokens * P.g + 127) / 128;
       const int per = (P.nj * P.t_cap * chunks + 7) / 8;
       ProfScope ps(KID_FWD_DENSE, st);
-      const bool gated = G.gate != nullptr, wait = rows_wait(P.g, P.topk, gated);
-      auto* kern = wait ? k_fwd_dense_merge<true> : k_fwd_dense_merge<false>;
-      hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per)), dim3(256), dense_lds_bytes(P.g, P.topk, gated && wait), st, P, (const bf16_t*)Q,
+      hipLaunchKernelGGL(k_fwd_dense_merge, dim3((unsigned)(8 * per)), dim3(256), dense_lds_bytes(P.g, P.topk), st, P, (const bf16_t*)Q,
                          (const bf16_t*)K, (const bf16_t*)V, p.tile_tok0, p.tile_len, p.d_cnt, p.d_piece, p.d_mask,
                          (const bf16_t*)opart, (const float*)lse_part, p.vmask, p.dmask, p.slotpos, p.off, (bf16_t*)O,
                          LSE, G.gate, (const bf16_t*)G.o_acc, (bf16_t*)G.o_out);
