@@ -2,7 +2,6 @@
 #include "common.h"
 
 namespace nsa {
-int index_chunks(int T, int nseq);
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -56,7 +55,8 @@ static IndexLayout make_layout(const nsa_sel_shape* s) {
   // K / V piece, which costs more than the gather route saves (measured per step: +7 % .. +10 % at g = 1, even
   // at g = 2, -2 % .. -9 % at g = 4 .. 8), unless the call is the sliding-window branch, where every pair is dense
   // (and not for inputs so small that the step is a few launch latencies: below 2^18 (token, kv head, column) triples)
-  L.dense = s->dense == 1 || (s->dense == 0 && L.p_max >= (1 << 18) && (s->hq / s->hkv >= 2 || s->window > 0)) ? 1 : 0;
+  L.brief = s->dense == 0 && short_forward(L.T, L.nseq, s->hq, L.topk, L.bk, L.causal != 0, L.window) ? 1 : 0;
+  L.dense = s->dense == 1 || (s->dense == 0 && !L.brief && L.p_max >= (1 << 18) && (s->hq / s->hkv >= 2 || s->window > 0)) ? 1 : 0;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
   L.blk_base = take(4 * (size_t)(L.nseq + 1));
@@ -219,8 +219,12 @@ static int fwd_impl(const nsa_sel_shape* shape, const void* Q, const void* K, co
   if (index_bytes < L.total || hpp < 1) return NSA_SEL_EWORKSPACE;
   if (shape->total_tokens == 0) return NSA_SEL_OK;
   hipStream_t st = (hipStream_t)stream;
-  if (rebuild_index && launch_build_index(L, idx, cu_seqlens, index_ws, st) != hipSuccess) return NSA_SEL_EHIP;
   Problem P = make_problem(shape, L);
+  if (L.brief)
+    return launch_fwd_short(P, L, rebuild_index != 0, Q, K, V, idx, cu_seqlens, index_ws, O, LSE, G, st) == hipSuccess
+               ? NSA_SEL_OK
+               : NSA_SEL_EHIP;
+  if (rebuild_index && launch_build_index(L, idx, cu_seqlens, index_ws, st) != hipSuccess) return NSA_SEL_EHIP;
   const size_t rows = partial_rows(shape, hpp);
   void* opart = ws;
   float* lse_part = (float*)((char*)ws + align256(rows * kD * 2));

@@ -33,6 +33,7 @@ struct IndexLayout {
   int32_t unit;         // list entries per work unit of the attention kernels (see work_unit_entries)
   int32_t units_max;    // upper bound of the number of work units
   int32_t dense;        // 1: (query tile, KV block) pairs most of the tile's tokens keep go through the dense path
+  int32_t brief;        // 1: the forward is k_fwd_short (see short_forward)
   int32_t t_cap;        // query tiles of kTileTokens tokens: T / kTileTokens + nseq (>= real number of tiles)
   size_t blk_base, blk_tok0, blk_len, chunk_off, cnt, off, qent, vmask, slotpos;
   size_t u_nu, u_rec, group_sum;
@@ -144,6 +145,35 @@ inline int work_unit_entries(int64_t total_pairs, int topk, int g, int bk) {
 // tokens in 10000 sequences 1128 / 420 us and 938 / 438 MB of index workspace.
 inline bool index_by_token(int T, int nseq) { return nseq > 16 + T / 256; }
 
+// Chunks of the inversion: kTilesPerChunk query tiles, or as many times 64 tokens, each.
+constexpr int kTilesPerChunk = 8;
+inline int index_chunks(int T, int nseq) {
+  const int tiles = index_by_token(T, nseq) ? (T + kTileTokens - 1) / kTileTokens : T / kTileTokens + nseq;
+  return (tiles + kTilesPerChunk - 1) / kTilesPerChunk;
+}
+// Whether the scatter sums the histogram's counters by itself instead of a launch before it: while a workgroup reads no more of them
+// than a few loads a thread.  Inversion with and without that launch, us: 1000 tokens x 1 kv head 14.3 -> 12.4, 2000 x 2 23.7 -> 21.7, 4096 x 8
+// 25.9 -> 24.1 (4680 counters), 8192 x 8 29.2 -> 28.7 (17 544), 8192 x 32 55 -> 65 (70 176).
+inline bool index_folds(int T, int nseq, int hkv, int bk) {
+  const int64_t chunks = index_chunks(T, nseq), lists = T / bk + nseq;
+  return !index_by_token(T, nseq) && hkv * chunks * lists <= (1 << 14) && chunks <= 32 && lists <= 1024;
+}
+
+// Whether the library's choice of forward is the one of short inputs (k_fwd_short), which computes every (row group, 64 keys) pair that any
+// of the group's tokens keeps: by x, the blocks of the whole input for every column (twice that where nothing hides the later ones).
+// A packed batch counts as one sequence: its rows see fewer blocks than that.  Measured, whole forward with the inversion, gather or dense
+// route -> short, us; 64-token blocks, causal, x = 2 / 3 / 4 / 6: 4 heads, g = 4 44 -> 40, 55 -> 50, 59 -> 60, 78 -> 123; 8 heads, g = 4 58 -> 42,
+// 79 -> 73, 90 -> 97, 126 -> 144; 32 heads, g = 4 139 -> 81, 179 -> 131, 235 -> 198, 342 -> 361 (top-k 16, 2000, 3000, 4096 and 6000 tokens); top-k 8,
+// 2000 tokens (x = 4) 4 heads 31 -> 35, 32 heads 90 -> 71.  All keys, x = 4 / 6 / 8: 4 heads 45 -> 40, 56 -> 52, 65 -> 73; 32 heads 159 -> 99, 233
+// -> 183, 281 -> 293.  Blocks of 128 tokens, of which the other routes gather half as many: x = 1 / 2 / 3, 8 heads 38 -> 24, 45 -> 36, 51 -> 67; 4 heads,
+// g = 1, 31 -> 35 at x = 2.
+inline bool short_forward(int T, int nseq, int hq, int topk, int bk, bool causal, int window) {
+  if (T > 8192 || nseq > 64 || index_by_token(T, nseq)) return false;  // what k_fwd_short has room for
+  const int64_t rows = (int64_t)T * hq, blocks = (int64_t)(window > 0 && window < T ? window : T) * (causal ? 1 : 2);
+  const int64_t x10 = bk == kBlock ? (!causal ? 60 : rows >= 50000 ? 42 : 30) : (rows >= (1 << 14) ? 20 : 10);
+  return blocks * 10 <= x10 * topk * bk;
+}
+
 // Upper bound of the work units of nj KV heads (one per non-empty list plus one per full unit of entries); the
 // real count is only known on the device.
 inline int64_t units_bound(int nj, int b_cap, int T, int topk, int unit) {
@@ -161,7 +191,7 @@ inline int64_t bwd_units_min(int b_cap, int T, int topk, int unit) {
 // ---- optional per-kernel timing (off unless nsa_sel_profile_enable was called) ---------------------------
 enum KernelId {
   KID_INDEX_PREP = 0, KID_INDEX_HIST, KID_INDEX_DENSE, KID_INDEX_SCAN, KID_INDEX_SCATTER, KID_FWD_MAIN, KID_FWD_MERGE,
-  KID_FWD_DENSE, KID_FWD_QUERY_OUTER, KID_BWD_DELTA, KID_BWD_MAIN, KID_BWD_DQ_REDUCE, KID_BWD_DKV_REDUCE, KID_SELECT_BLOCKS,
+  KID_FWD_DENSE, KID_FWD_SHORT, KID_FWD_QUERY_OUTER, KID_BWD_DELTA, KID_BWD_MAIN, KID_BWD_DQ_REDUCE, KID_BWD_DKV_REDUCE, KID_SELECT_BLOCKS,
   KID_COUNT
 };
 // Records a HIP event on `st` at construction and destruction when profiling is on; does nothing otherwise.
@@ -200,6 +230,10 @@ hipError_t launch_build_index(const IndexLayout& L, const int32_t* idx, const in
 hipError_t launch_fwd(const Problem& P, const IndexLayout& L, int heads_per_pass, const void* Q, const void* K,
                       const void* V, const void* index_ws, void* opart, float* lse_part, void* O, float* LSE,
                       const GateArgs& G, hipStream_t st);
+// the forward of short inputs, with (build) the index; without, it reads the one that is there (see short.hip)
+hipError_t launch_fwd_short(const Problem& P, const IndexLayout& L, bool build, const void* Q, const void* K, const void* V,
+                            const int32_t* idx, const int32_t* cu, void* index_ws, void* O, float* LSE, const GateArgs& G,
+                            hipStream_t st);
 // the same forward in query-outer loop order (no workspaces, no index): see qouter.hip
 hipError_t launch_fwd_query_outer(const Problem& P, const void* Q, const void* K, const void* V, const int32_t* idx,
                                   const int32_t* cu, void* O, float* LSE, hipStream_t st);

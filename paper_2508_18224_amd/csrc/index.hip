@@ -4,7 +4,9 @@
 // (token, kv head, column), the entry's position in its list, which is where its partial result lives in the
 // compact partial buffers (the role of the paper's O_i), plus the work-unit tables of the attention kernels.
 //
-// Three launches (for packed batches k_prep before them, and k_dense where the tokens are walked without regard to sequences):
+// Three launches (for packed batches k_prep before them, and k_dense where the tokens are walked without regard to sequences; small
+// inputs without the dense route go without k_prefix, see index_folds; the forward of short inputs does the work of the launches
+// before it in its own, see short.hip):
 //   k_hist     per (kv head, chunk, block) counts, kept columns per token, dense (query tile, KV block) pairs
 //   k_prefix   per list: prefix over the chunks, length; per 64 lists: sums
 //   k_scatter  exclusive scan of the list lengths (redone by every workgroup from the 64-list sums), list entries and
@@ -21,24 +23,12 @@
 // The inversion reads a few MB and is bound by latency and launches, not by bandwidth: 137 us at 65536 tokens x 8 kv heads (52
 // histogram, 8 prefix, 76 scatter).  An earlier cut (12 launches; one wavefront walked a chunk's 512 tokens in eight dependent
 // rounds; separate scan, dense-detection and unit kernels) took 233 us there.
-#include "common.h"
+#include "inversion.h"
 
 namespace nsa {
 
-constexpr int kTilesPerChunk = 8;                    // wavefronts of a k_hist / k_scatter workgroup
-constexpr int kChunkThreads = 64 * kTilesPerChunk;
 constexpr int kPrefixWaves = 16;                     // wavefronts of a k_prefix workgroup (64 lists each)
 constexpr int kScatterWindow = 1024;                 // most blocks k_scatter handles at a time (its LDS tables)
-
-struct IndexGeom {
-  int32_t nseq, T, hkv, k, bk, causal, window, b_cap, t_cap, n_chunks, n_groups, unit, dense;
-};
-
-// The tokens of a wavefront: the first one and their number (0: none); bounds and first global block of their sequence.  In
-// a query tile the latter are the same for all lanes; by token they are those of the lane's token (of the last one past it).
-struct Tile {
-  int tok0, len, c0, c1, bb;
-};
 
 template <bool kByToken>
 __device__ __forceinline__ Tile load_tile(const IndexGeom& G, int qt, int lane, const int32_t* cu, const IndexPtrs& p) {
@@ -69,12 +59,6 @@ __device__ __forceinline__ Tile load_tile(const IndexGeom& G, int qt, int lane, 
   return t;
 }
 
-// Last block of its sequence the token can keep, -1 if none.  (A token past the last sequence's end lies past its blocks.)
-__device__ __forceinline__ int last_block(const IndexGeom& G, const Tile& t, int tok) {
-  const int last = (t.c1 - t.c0 + G.bk - 1) / G.bk - 1;
-  return G.causal ? min((tok - t.c0) / G.bk, last) : last;
-}
-
 // The window [lo, hi) of global blocks the tokens of a chunk can keep; block-wide (every wavefront passes its own tile).
 // Blocks ascend with the tokens: the first lane knows where a tile's begin, the last where they end.
 __device__ __forceinline__ void chunk_window(const IndexGeom& G, const Tile& t, int wave, int* s_win, int& lo, int& hi) {
@@ -90,46 +74,6 @@ __device__ __forceinline__ void chunk_window(const IndexGeom& G, const Tile& t, 
     hi = max(hi, s_win[2 * w + 1]);
   }
   if (lo > hi) lo = hi;
-}
-
-// One row of idx in registers; columns past k hold -1.
-template <int KMAX>
-__device__ __forceinline__ void load_row(const int32_t* __restrict__ src, int k, bool vec4, int32_t (&row)[KMAX]) {
-  if (vec4) {
-#pragma unroll
-    for (int m = 0; m < KMAX; m += 4) {
-      int4 x = make_int4(-1, -1, -1, -1);
-      if (m < k) x = *reinterpret_cast<const int4*>(src + m);
-      row[m] = x.x; row[m + 1] = x.y; row[m + 2] = x.z; row[m + 3] = x.w;
-    }
-  } else {
-#pragma unroll
-    for (int m = 0; m < KMAX; ++m) row[m] = m < k ? src[m] : -1;
-  }
-}
-
-__device__ __forceinline__ bool rows_are_vec4(const void* a, int k) {
-  return (k & 3) == 0 && (reinterpret_cast<uintptr_t>(a) & 15) == 0;
-}
-
-__device__ __forceinline__ void wave_lds_sync() {  // orders a wavefront's own LDS traffic
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// table[x] += 1 for every lane with `on`.  The forced columns (sink, own block) hold the same id in every lane, which
-// would serialise 64 atomics on one address: a column all of whose lanes agree is counted by one of them.
-__device__ __forceinline__ void count_column(int32_t* table, int x, bool on, int lane) {
-  const unsigned long long act = __builtin_amdgcn_ballot_w64(on);
-  if (act == 0ull) return;
-  const int lead = __builtin_ctzll(act);
-  const int x0 = __builtin_amdgcn_readlane(x, lead);
-  if (__builtin_amdgcn_ballot_w64(on && x == x0) == act) {
-    if (lane == lead) atomicAdd(&table[x0], __popcll(act));
-  } else if (on) {
-    atomicAdd(&table[x], 1);
-  }
 }
 
 // ------------------------------------------------------------------------------------------------ prep
@@ -357,20 +301,9 @@ __global__ void __launch_bounds__(kChunkThreads) k_hist(IndexGeom G, const int32
       p.blk_len[gb] = len;
     }
   }
-  // Bit m of vm: column m is a kept selection - in range for the sequence, not in the token's future when causal, not
-  // wholly before the token's window, and not a repeat of an earlier column.
   uint32_t vm = 0;
   if (live) {
-    const int last = last_block(G, t, tok);
-    // oldest key a window of G.window tokens shows to this token: position tok - c0 - window + 1 of its sequence
-    const int first = G.window > 0 ? max(tok - t.c0 - G.window + 1, 0) / G.bk : 0;
-#pragma unroll
-    for (int m = 0; m < KMAX; ++m) {
-      bool dup = false;
-#pragma unroll
-      for (int mp = 0; mp < m; ++mp) dup |= row[mp] == row[m];
-      if (m < G.k && row[m] >= first && row[m] <= last && !dup) vm |= 1u << m;
-    }
+    vm = kept_columns<KMAX>(G, t, tok, row);
     p.vmask[(size_t)tok * G.hkv + j] = vm;
   }
   __syncthreads();
@@ -498,7 +431,9 @@ __device__ __forceinline__ int2 block_scan(int2 v, int2* s_red, int2& total) {
 // as the wavefront's byte of the block's word; a token's position is list offset + entries of earlier chunks +
 // the bytes of the wavefronts before its own + popcount(mask below its lane).
 // Dynamic LDS: win * (8 masks + 1 word of bytes + 1 offset) = 76 win bytes.
-template <int KMAX, bool kByToken>
+// kFold: the prefix over the chunks is not a launch before this one; the counters are still k_hist's, and every workgroup
+// sums the few it needs by itself (see index_folds).
+template <int KMAX, bool kByToken, bool kFold>
 __global__ void __launch_bounds__(kChunkThreads) k_scatter(IndexGeom G, int win, const int32_t* __restrict__ idx,
                                                            const int32_t* __restrict__ cu, IndexPtrs p) {
   extern __shared__ __attribute__((aligned(16))) int32_t lds[];
@@ -506,23 +441,44 @@ __global__ void __launch_bounds__(kChunkThreads) k_scatter(IndexGeom G, int win,
   __shared__ int2 s_red[kTilesPerChunk];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = blockIdx.y;
   const int2* gsum = p.group_sum + j * G.n_groups;  // the 64-list sums of this kv head, those of the others before it
+  // (length, entries of the chunks before `upto`) of list gb of kv head jj, from the histogram's counters
+  auto list_counts = [&](int jj, int gb, int upto) {
+    const int32_t* c = p.chunk_off + (size_t)jj * G.n_chunks * G.b_cap + gb;
+    int2 r = make_int2(0, 0);
+#pragma unroll 4
+    for (int i = 0; i < G.n_chunks; ++i, c += G.b_cap) {
+      const int x = *c;
+      r.x += x;
+      r.y += i < upto ? x : 0;
+    }
+    return r;
+  };
   if (blockIdx.x == 0) {
     int2 run = make_int2(0, 0);
-    for (int i = tid - j * G.n_groups; i < 0; i += kChunkThreads) {
-      const int2 x = gsum[i];
-      run.x += x.x;
-      run.y += x.y;
+    if constexpr (kFold) {
+      for (int i = tid; i < j * G.b_cap; i += kChunkThreads) {
+        const int len = list_counts(i / G.b_cap, i % G.b_cap, 0).x;
+        run.x += len;
+        run.y += (len + G.unit - 1) / G.unit;
+      }
+    } else {
+      for (int i = tid - j * G.n_groups; i < 0; i += kChunkThreads) {
+        const int2 x = gsum[i];
+        run.x += x.x;
+        run.y += x.y;
+      }
     }
     run = block_sum(run, s_red);
     for (int b0 = 0; b0 < G.b_cap; b0 += kChunkThreads) {
       const int gb = b0 + tid, L = j * G.b_cap + gb;
-      const int len = gb < G.b_cap ? p.cnt[L] : 0, nu = (len + G.unit - 1) / G.unit;
+      const int len = gb < G.b_cap ? (kFold ? list_counts(j, gb, 0).x : p.cnt[L]) : 0, nu = (len + G.unit - 1) / G.unit;
       int2 total;
       const int2 ex = block_scan(make_int2(len, nu), s_red, total);
       const int e0 = run.x + ex.x, u0 = run.y + ex.y;
       if (gb < G.b_cap) {
         p.off[L] = e0;
         p.u_nu[L] = u0;
+        if constexpr (kFold) p.cnt[L] = len;
         const int tok0 = p.blk_tok0[gb], blen = p.blk_len[gb];
         for (int u = 0; u < nu; ++u) {
           int4* rec = reinterpret_cast<int4*>(p.u_rec + u0 + u);
@@ -563,17 +519,28 @@ __global__ void __launch_bounds__(kChunkThreads) k_scatter(IndexGeom G, int win,
 #pragma unroll
   for (int m = 0; m < KMAX; ++m) pos[m] = -1;
 
-  const int w_first = gb_lo & ~63;  // passes start at a 64-list boundary
+  const int w_first = kFold ? 0 : gb_lo & ~63;  // passes start at a 64-list boundary
   int2 part = make_int2(0, 0);
-  for (int i = tid - j * G.n_groups; i < (w_first >> 6); i += kChunkThreads) part.x += gsum[i].x;
+  if constexpr (kFold) {
+#pragma unroll 4
+    for (int i = tid; i < j * G.n_chunks * G.b_cap; i += kChunkThreads) part.x += p.chunk_off[i];
+  } else {
+    for (int i = tid - j * G.n_groups; i < (w_first >> 6); i += kChunkThreads) part.x += gsum[i].x;
+  }
   int run = block_sum(part, s_red).x;  // first position of list (j, w_first)
   const int32_t* chunk_off = p.chunk_off + ((size_t)j * G.n_chunks + chunk) * G.b_cap;
   for (int w0 = w_first; w0 < gb_hi; w0 += win) {
     // list offsets of the window's blocks: two consecutive blocks per thread
     const int i0 = 2 * tid, gb = w0 + i0;
     const bool on0 = i0 < win && gb < G.b_cap, on1 = i0 + 1 < win && gb + 1 < G.b_cap;
-    const int len0 = on0 ? p.cnt[j * G.b_cap + gb] : 0, len1 = on1 ? p.cnt[j * G.b_cap + gb + 1] : 0;
-    const int co0 = on0 ? chunk_off[gb] : 0, co1 = on1 ? chunk_off[gb + 1] : 0;
+    int len0 = 0, len1 = 0, co0 = 0, co1 = 0;
+    if constexpr (kFold) {
+      const int2 a = on0 ? list_counts(j, gb, chunk) : make_int2(0, 0), b = on1 ? list_counts(j, gb + 1, chunk) : make_int2(0, 0);
+      len0 = a.x; co0 = a.y; len1 = b.x; co1 = b.y;
+    } else {
+      if (on0) { len0 = p.cnt[j * G.b_cap + gb]; co0 = chunk_off[gb]; }
+      if (on1) { len1 = p.cnt[j * G.b_cap + gb + 1]; co1 = chunk_off[gb + 1]; }
+    }
     for (int i = tid; i < 9 * win / 2; i += kChunkThreads)  // masks and bytes, 16 bytes at a time
       reinterpret_cast<uint4*>(lds)[i] = make_uint4(0, 0, 0, 0);
     int2 total;
@@ -636,41 +603,57 @@ __global__ void __launch_bounds__(kChunkThreads) k_scatter(IndexGeom G, int win,
   }
 }
 
+template <int KMAX, bool kByToken, bool kFold>
+static hipError_t launch_scatter(const IndexGeom& G, const int32_t* idx, const int32_t* cu, const IndexPtrs& p, hipStream_t st) {
+  const int win = min((G.b_cap + 63) & ~63, kScatterWindow);
+  const int lds = 76 * win;
+  if (lds > 60 * 1024) {  // beyond the default 64 KB
+    static std::atomic<uint64_t> ready;
+    const hipError_t e = allow_dynamic_lds((const void*)(k_scatter<KMAX, kByToken, kFold>), 150 * 1024, ready);
+    if (e != hipSuccess) return e;
+  }
+  ProfScope ps(KID_INDEX_SCATTER, st);
+  hipLaunchKernelGGL((k_scatter<KMAX, kByToken, kFold>), dim3(G.n_chunks + 1, G.hkv), dim3(kChunkThreads), lds, st, G, win, idx, cu, p);
+  return hipGetLastError();
+}
+
+// From the histogram's counters to the lists.
+template <int KMAX, bool kByToken>
+static hipError_t launch_lists(const IndexGeom& G, const int32_t* idx, const int32_t* cu, const IndexPtrs& p, hipStream_t st) {
+  if constexpr (!kByToken)
+    if (!G.dense && index_folds(G.T, G.nseq, G.hkv, G.bk)) return launch_scatter<KMAX, false, true>(G, idx, cu, p, st);
+  {
+    ProfScope ps(KID_INDEX_SCAN, st);
+    hipLaunchKernelGGL(k_prefix, dim3(G.n_groups, G.hkv), dim3(64 * kPrefixWaves), 0, st, G, p.chunk_off, p.cnt,
+                       p.group_sum);
+  }
+  return launch_scatter<KMAX, kByToken, false>(G, idx, cu, p, st);
+}
+
 template <int KMAX, bool kByToken>
 static hipError_t launch_inversion(const IndexGeom& G, const int32_t* idx, const int32_t* cu, const IndexPtrs& p,
                                    hipStream_t st) {
   const int lds_dense = 4 * kTilesPerChunk * kDenseHash, lds_hist = 4 * G.b_cap + (G.dense && !kByToken ? lds_dense : 0);
-  const int win = min((G.b_cap + 63) & ~63, kScatterWindow);
-  const int lds_scat = 76 * win;
-  if (lds_hist > 60 * 1024 || lds_scat > 60 * 1024) {  // beyond the default 64 KB
-    static std::atomic<uint64_t> ready_hist, ready_scat;
-    hipError_t e = allow_dynamic_lds((const void*)(k_hist<KMAX, kByToken>), 150 * 1024, ready_hist);
-    if (e == hipSuccess) e = allow_dynamic_lds((const void*)(k_scatter<KMAX, kByToken>), 150 * 1024, ready_scat);
+  if (lds_hist > 60 * 1024) {  // beyond the default 64 KB
+    static std::atomic<uint64_t> ready;
+    const hipError_t e = allow_dynamic_lds((const void*)(k_hist<KMAX, kByToken>), 150 * 1024, ready);
     if (e != hipSuccess) return e;
   }
   {
     ProfScope ps(KID_INDEX_HIST, st);
     hipLaunchKernelGGL((k_hist<KMAX, kByToken>), dim3(G.n_chunks, G.hkv), dim3(kChunkThreads), lds_hist, st, G, idx, cu, p);
   }
-  if constexpr (kByToken)
+  if constexpr (kByToken) {
     if (G.dense) {
       ProfScope ps(KID_INDEX_DENSE, st);
       hipLaunchKernelGGL(k_dense<KMAX>, dim3((G.t_cap + kTilesPerChunk - 1) / kTilesPerChunk, G.hkv), dim3(kChunkThreads),
                          lds_dense, st, G, idx, cu, p);
     }
-  {
-    ProfScope ps(KID_INDEX_SCAN, st);
-    hipLaunchKernelGGL(k_prefix, dim3(G.n_groups, G.hkv), dim3(64 * kPrefixWaves), 0, st, G, p.chunk_off, p.cnt,
-                       p.group_sum);
   }
-  ProfScope ps(KID_INDEX_SCATTER, st);
-  hipLaunchKernelGGL((k_scatter<KMAX, kByToken>), dim3(G.n_chunks + 1, G.hkv), dim3(kChunkThreads), lds_scat, st, G, win, idx, cu, p);
-  return hipGetLastError();
+  return launch_lists<KMAX, kByToken>(G, idx, cu, p, st);
 }
 
-hipError_t launch_build_index(const IndexLayout& L, const int32_t* idx, const int32_t* cu, void* index_ws,
-                              hipStream_t st) {
-  const IndexPtrs p = index_ptrs(L, index_ws);
+IndexGeom index_geom(const IndexLayout& L) {
   IndexGeom G;
   G.nseq = L.nseq;
   G.T = L.T;
@@ -685,6 +668,13 @@ hipError_t launch_build_index(const IndexLayout& L, const int32_t* idx, const in
   G.n_groups = L.n_groups;
   G.unit = L.unit;
   G.dense = L.dense;
+  return G;
+}
+
+hipError_t launch_build_index(const IndexLayout& L, const int32_t* idx, const int32_t* cu, void* index_ws,
+                              hipStream_t st) {
+  const IndexPtrs p = index_ptrs(L, index_ws);
+  const IndexGeom G = index_geom(L);
   if (G.nseq > 1) {
     ProfScope ps(KID_INDEX_PREP, st);
     hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, G, cu, p);
@@ -700,9 +690,13 @@ hipError_t launch_build_index(const IndexLayout& L, const int32_t* idx, const in
   return launch_inversion<32, false>(G, idx, cu, p, st);
 }
 
-int index_chunks(int T, int nseq) {
-  const int tiles = index_by_token(T, nseq) ? (T + kTileTokens - 1) / kTileTokens : T / kTileTokens + nseq;
-  return (tiles + kTilesPerChunk - 1) / kTilesPerChunk;
+// The same after a kernel that did the histogram's work and the tables' (k_fwd_short).
+hipError_t launch_short_lists(const IndexLayout& L, const int32_t* idx, const int32_t* cu, void* index_ws, hipStream_t st) {
+  const IndexPtrs p = index_ptrs(L, index_ws);
+  const IndexGeom G = index_geom(L);
+  if (G.k <= 8) return launch_lists<8, false>(G, idx, cu, p, st);
+  if (G.k <= 16) return launch_lists<16, false>(G, idx, cu, p, st);
+  return launch_lists<32, false>(G, idx, cu, p, st);
 }
 
 }  // namespace nsa

@@ -14,7 +14,7 @@ int g_used = 0;
 bool g_on = false;
 unsigned g_mask = ~0u;  // kernel kinds that are recorded (bit = index in kNames)
 const char* const kNames[KID_COUNT] = {"index_prep", "index_hist", "index_dense", "index_scan", "index_scatter", "fwd_main",
-                                       "fwd_merge", "fwd_dense", "fwd_query_outer", "bwd_delta", "bwd_main",
+                                       "fwd_merge", "fwd_dense", "fwd_short", "fwd_query_outer", "bwd_delta", "bwd_main",
                                        "bwd_dq_reduce", "bwd_dkv_reduce", "select_blocks"};
 }  // namespace
 
