@@ -19,7 +19,7 @@
 //                     CU; its waves specialise (four compute P / dS of tile n, four accumulate tile n - 1) instead
 //                     of all stepping through the same phases (see the comment above the kernel).
 //   k_bwd_dq_reduce   dQ[t,h] = sum over kept slots of the partial rows
-//   k_bwd_dkv_reduce  dK_i, dV_i = sum over the list's units in unit order (fixed order: bit-reproducible); a list
+//   k_bwd_dkv_reduce  (with k_bwd_dq_reduce) dK_i, dV_i = sum over the list's units in unit order (fixed order: bit-reproducible); a list
 //                     that fitted one unit was already written by that unit, a list with no entry gets zeros
 #include "common.h"
 #include <type_traits>
@@ -899,18 +899,87 @@ k_bwd_pipe128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
     pipe_role<kWin, kWide, false>(P, U, smem, wave - 4, Q, K, V, dO, stats, qent, dqpart, dkv_part, dK, dV);
 }
 
+// dK / dV of the lists whose units left partial sums: the sum runs in unit order, four units in flight.  A piece of this work is
+// (`per` <= 64 lists, dK or dV, 8 keys), so that the units of a long list (the sink block's list has 32 of them) are walked by
+// B_K / 8 pieces side by side, 256 threads each; thread = 4 consecutive channels of one key.  Most lists fit one unit, which wrote the
+// final values itself: a piece looks at its lists at once (one per lane) and walks only those that need it, so that there are some
+// thousand of them and not one per list and key group (25 900 lists: 414 000 workgroups, 174 us).
+// (Its pointers are arguments of the kernels themselves: out of a structure the compiler does not take them to be distinct, and the table
+// reads of a list wait for the stores of the one before.)
+__device__ __forceinline__ void dkv_reduce(const Problem& P, int per, int group, int which, int part, int tid,
+                                           const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ blk_tok0,
+                                           const int32_t* __restrict__ blk_len, const float* __restrict__ dkv_part,
+                                           bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
+  const int lane = tid & 63, l0 = P.l0 + group * per;
+  const int ubase = P.l0 > 0 ? nu_scan[P.l0] : 0;
+  const int mine = min(l0 + lane, P.l1 - 1);
+  const int my_u0 = nu_scan[mine], my_nu = nu_scan[mine + 1] - my_u0;
+  unsigned long long todo = __builtin_amdgcn_ballot_w64(lane < per && l0 + lane < P.l1 && my_nu != 1);
+  bf16_t* out = which ? dV : dK;
+  const int d4 = (tid & 31) * 4;
+  const int key = 8 * part + (tid >> 5);
+  const size_t unit_stride = (size_t)2 * P.bk * kD;
+  while (todo != 0ull) {
+    const int i = __builtin_ctzll(todo);
+    todo &= todo - 1ull;
+    const int u0 = __builtin_amdgcn_readlane(my_u0, i), nu = __builtin_amdgcn_readlane(my_nu, i);
+    const int j = (l0 + i) / P.b_cap, gb = l0 + i - j * P.b_cap;
+    if (key >= blk_len[gb]) continue;
+    const float* src = dkv_part + (size_t)(u0 - ubase) * unit_stride + (size_t)which * P.bk * kD + key * kD + d4;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    int u = 0;
+    for (; u + 4 <= nu; u += 4, src += 4 * unit_stride) {
+      float4 x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[q] = *reinterpret_cast<const float4*>(src + q * unit_stride);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { acc.x += x[q].x; acc.y += x[q].y; acc.z += x[q].z; acc.w += x[q].w; }
+    }
+    for (; u < nu; ++u, src += unit_stride) {
+      const float4 x = *reinterpret_cast<const float4*>(src);
+      acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
+    }
+    uint2 w;
+    w.x = pack_bf16x2(acc.x, acc.y);
+    w.y = pack_bf16x2(acc.z, acc.w);
+    *reinterpret_cast<uint2*>(out + ((size_t)(blk_tok0[gb] + key) * P.hkv + j) * kD + d4) = w;
+  }
+}
+
+// The pieces alone: beside a dQ reduction in bursts, and where a head's KV blocks are taken in ranges, of all ranges but the last.
+__global__ void __launch_bounds__(256)
+k_bwd_dkv_reduce(Problem P, int per, const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ blk_tok0,
+                 const int32_t* __restrict__ blk_len, const float* __restrict__ dkv_part, bf16_t* __restrict__ dK,
+                 bf16_t* __restrict__ dV) {
+  dkv_reduce(P, per, blockIdx.x, blockIdx.y, blockIdx.z, threadIdx.x, nu_scan, blk_tok0, blk_len, dkv_part, dK, dV);
+}
+
 // dQ of every (token, head) row from its columns' partial rows: plain sums, in column order.  Rows and workgroups: see "the two
-// reduction kernels" in common.h.  (k_fwd_merge is the same with weights.)
+// reduction kernels" in common.h.  (k_fwd_merge is the same with weights.)  Row by row, on smaller inputs, its first `before` workgroups
+// do the dK / dV sums, which are independent of it, instead of a launch for them: 13.6 -> 7.7 us for both at 1024 tokens, 32 -> 29 on a
+// batch of short documents.  In bursts they would leave the others one workgroup a compute unit less: 214 -> 250 us at 8192 tokens, 32
+// heads, g = 1.
 template <int kRows, int kThreads>
 __global__ void __launch_bounds__(kThreads)
 k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const int32_t* __restrict__ slotpos,
-                const int32_t* __restrict__ off, bf16_t* __restrict__ dQ) {
+                const int32_t* __restrict__ off, bf16_t* __restrict__ dQ, int before, int per, int groups,
+                const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ blk_tok0, const int32_t* __restrict__ blk_len,
+                const float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
+  if constexpr (kRows == 1) {
+    static_assert(kThreads == 256, "one piece of the dK / dV sums a workgroup");
+    if ((int)blockIdx.x < before) {
+      const int side = blockIdx.x / groups;  // the lists side by side, then dK and dV, then the keys
+      if (side < P.bk / 4)
+        dkv_reduce(P, per, blockIdx.x - side * groups, side & 1, side >> 1, threadIdx.x, nu_scan, blk_tok0, blk_len, dkv_part, dK, dV);
+      return;
+    }
+  }
   constexpr int kBatch = 8;  // independent 256-byte gathers in flight per row
   const int sub = threadIdx.x & 15;
   const int pos0 = off[P.j0 * P.b_cap];
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u32x4* const out = reinterpret_cast<u32x4*>(smem) + threadIdx.x;
-  const ReduceSpan span = reduce_span<kRows, kThreads>(P);
+  const ReduceSpan span = reduce_span<kRows, kThreads>(P, blockIdx.x - before, gridDim.x - before);
   if (span.count == 0) return;  // the whole workgroup
   ReduceRow R = reduce_row<kThreads>(P, span.first);
   SlotRow slots = load_slots(slotpos, P, R);
@@ -963,52 +1032,6 @@ k_bwd_dq_reduce(Problem P, const bf16_t* __restrict__ dqpart, const int32_t* __r
     if (q >= span.count) break;
     const ReduceRow R = reduce_row<kThreads>(P, span.first + q);
     if (R.on) store_streaming(dQ + ((int64_t)R.t * P.hq + R.j * P.g + R.hh) * kD + 8 * sub, out[q * kThreads]);
-  }
-}
-
-// grid (ceil(lists / per), 2, B_K / 8): y = 0 -> dK, 1 -> dV; z = group of 8 keys, so that the units of a long list (the sink
-// block's list has 32 of them) are walked by B_K / 8 workgroups side by side.  Thread = 4 consecutive channels of one
-// key; the sum runs in unit order, four units in flight.  Most lists fit one unit, which wrote the final values itself:
-// a workgroup looks at `per` <= 64 lists at once (one per lane) and walks only those that need it, so that a launch is
-// some thousand workgroups and not one per list and key group (25 900 lists: 414 000 workgroups, 174 us).
-__global__ void __launch_bounds__(256)
-k_bwd_dkv_reduce(Problem P, int per, const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ blk_tok0,
-                 const int32_t* __restrict__ blk_len, const float* __restrict__ dkv_part, bf16_t* __restrict__ dK,
-                 bf16_t* __restrict__ dV) {
-  const int which = blockIdx.y, lane = threadIdx.x & 63;
-  const int l0 = P.l0 + blockIdx.x * per;
-  const int ubase = P.l0 > 0 ? nu_scan[P.l0] : 0;
-  const int mine = min(l0 + lane, P.l1 - 1);
-  const int my_u0 = nu_scan[mine], my_nu = nu_scan[mine + 1] - my_u0;
-  unsigned long long todo = __builtin_amdgcn_ballot_w64(lane < per && l0 + lane < P.l1 && my_nu != 1);
-  bf16_t* out = which ? dV : dK;
-  const int d4 = (threadIdx.x & 31) * 4;
-  const int key = 8 * blockIdx.z + (threadIdx.x >> 5);
-  const size_t unit_stride = (size_t)2 * P.bk * kD;
-  while (todo != 0ull) {
-    const int i = __builtin_ctzll(todo);
-    todo &= todo - 1ull;
-    const int u0 = __builtin_amdgcn_readlane(my_u0, i), nu = __builtin_amdgcn_readlane(my_nu, i);
-    const int j = (l0 + i) / P.b_cap, gb = l0 + i - j * P.b_cap;
-    if (key >= blk_len[gb]) continue;
-    const float* src = dkv_part + (size_t)(u0 - ubase) * unit_stride + (size_t)which * P.bk * kD + key * kD + d4;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    int u = 0;
-    for (; u + 4 <= nu; u += 4, src += 4 * unit_stride) {
-      float4 x[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) x[q] = *reinterpret_cast<const float4*>(src + q * unit_stride);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) { acc.x += x[q].x; acc.y += x[q].y; acc.z += x[q].z; acc.w += x[q].w; }
-    }
-    for (; u < nu; ++u, src += unit_stride) {
-      const float4 x = *reinterpret_cast<const float4*>(src);
-      acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
-    }
-    uint2 w;
-    w.x = pack_bf16x2(acc.x, acc.y);
-    w.y = pack_bf16x2(acc.z, acc.w);
-    *reinterpret_cast<uint2*>(out + ((size_t)(blk_tok0[gb] + key) * P.hkv + j) * kD + d4) = w;
   }
 }
 
@@ -1073,22 +1096,27 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
       hipLaunchKernelGGL(main_kernel, dim3(units_max), dim3(main_threads), main_lds, st, P, (const bf16_t*)Q,
                          (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, (const float2*)delta, p.u_rec, p.u_nu,
                          p.off, p.qent, (bf16_t*)dqpart, dkv_part, (bf16_t*)dK, (bf16_t*)dV); }
-      if (P.l1 == end) {
-        ProfScope ps(KID_BWD_DQ_REDUCE, st);
-        auto launch = [&](auto rows, auto threads) {
-          constexpr int kRows = decltype(rows)::value, kThreads = decltype(threads)::value;
-          hipLaunchKernelGGL((k_bwd_dq_reduce<kRows, kThreads>), dim3(reduce_groups<kRows, kThreads>(P)), dim3(kThreads),
-                             reduce_lds(kThreads, kRows, 1, false), st, P, (const bf16_t*)dqpart, p.slotpos, p.off, (bf16_t*)dQ);
-        };
-        if (dq_in_bursts(P))
-          launch(std::integral_constant<int, kBurstRows>{}, std::integral_constant<int, kBurstThreads>{});
-        else
-          launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 256>{});
-      }
-      ProfScope ps(KID_BWD_DKV_REDUCE, st);
       const int lists = P.l1 - P.l0, per = max(1, min(64, lists * (P.bk / 4) / 4096));
-      hipLaunchKernelGGL(k_bwd_dkv_reduce, dim3((lists + per - 1) / per, 2, P.bk / 8), dim3(256), 0, st, P, per, p.u_nu,
-                         p.blk_tok0, p.blk_len, (const float*)dkv_part, (bf16_t*)dK, (bf16_t*)dV);
+      const int groups = (lists + per - 1) / per;
+      const bool last = P.l1 == end, bursts = dq_in_bursts(P);
+      if (last) {
+        ProfScope ps(KID_BWD_DQ_REDUCE, st);
+        auto launch = [&](auto rows, auto threads, int before) {
+          constexpr int kRows = decltype(rows)::value, kThreads = decltype(threads)::value;
+          hipLaunchKernelGGL((k_bwd_dq_reduce<kRows, kThreads>), dim3(before + reduce_groups<kRows, kThreads>(P)), dim3(kThreads),
+                             reduce_lds(kThreads, kRows, 1, false), st, P, (const bf16_t*)dqpart, p.slotpos, p.off, (bf16_t*)dQ, before, per,
+                             groups, p.u_nu, p.blk_tok0, p.blk_len, (const float*)dkv_part, (bf16_t*)dK, (bf16_t*)dV);
+        };
+        if (bursts)
+          launch(std::integral_constant<int, kBurstRows>{}, std::integral_constant<int, kBurstThreads>{}, 0);
+        else  // (a multiple of eight, so that the XCDs of the workgroups after them stay the same)
+          launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 256>{}, (groups * (P.bk / 4) + 7) & ~7);
+      }
+      if (!last || bursts) {
+        ProfScope ps(KID_BWD_DKV_REDUCE, st);
+        hipLaunchKernelGGL(k_bwd_dkv_reduce, dim3(groups, 2, P.bk / 8), dim3(256), 0, st, P, per, p.u_nu, p.blk_tok0, p.blk_len,
+                           (const float*)dkv_part, (bf16_t*)dK, (bf16_t*)dV);
+      }
     }
   }
   return hipGetLastError();

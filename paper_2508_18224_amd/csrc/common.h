@@ -410,12 +410,12 @@ struct ReduceSpan {
   int count;       // at most kRows
 };
 template <int kRows, int kThreads>
-__device__ __forceinline__ ReduceSpan reduce_span(const Problem& P) {
+__device__ __forceinline__ ReduceSpan reduce_span(const Problem& P, uint32_t group, uint32_t groups) {
   constexpr uint32_t kStep = kThreads / 16;
   const uint32_t steps = ((uint32_t)P.T * (uint32_t)(P.nj * P.g) + kStep - 1) / kStep;  // total_tokens * hq < 2^31 is checked on the host
-  const uint32_t blk = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const uint32_t blk = (group & 7) * (groups >> 3) + (group >> 3);
   if constexpr (kRows == 1) return {blk, blk < steps ? 1 : 0};
-  const uint32_t each = steps / gridDim.x, more = steps - each * gridDim.x;
+  const uint32_t each = steps / groups, more = steps - each * groups;
   return {blk * each + min(blk, more), (int)(each + (blk < more ? 1 : 0))};
 }
 struct ReduceRow {

@@ -912,7 +912,7 @@ k_fwd_merge(Problem P, const bf16_t* __restrict__ opart, const float* __restrict
   u32x4* const out = reinterpret_cast<u32x4*>(smem) + threadIdx.x;
   u32x4* const gated = out + kRows * kThreads;
   float* const lse = reinterpret_cast<float*>(smem + kRows * kThreads * (kGate ? 32 : 16)) + (threadIdx.x >> 4);
-  const ReduceSpan span = reduce_span<kRows, kThreads>(P);
+  const ReduceSpan span = reduce_span<kRows, kThreads>(P, blockIdx.x, gridDim.x);
   if (span.count == 0) return;  // the whole workgroup
   ReduceRow R = reduce_row<kThreads>(P, span.first);
   SlotRow slots = load_slots(slotpos, P, R);
