@@ -31,7 +31,10 @@ constexpr int kCandPerLane = kMaxChunks * kMaxTopk / 64;   // chunk picks each l
 // octave, let everything within 25 % of the bound survive, and ordinary scores of a narrower range than exp(1.5 z) outgrew the list of
 // survivors: exp(0.1 z) took 1470 us at 65536 tokens x 8 heads x 1024 blocks instead of 344, uniform ones 592 instead of 343.
 constexpr int kTauLowBit = 16;
-constexpr int kMaxSurv = 128;                 // survivors the fast method ranks; rows with more take the general one
+// Survivors the fast method ranks; rows with more take the general one.  A chunk in which fewer than r lanes hold a score, r <= 35,
+// keeps all of its up to 136 without a search, after what the chunks before it left: with room for 128 all rows of 129 to 136 blocks
+// (top-k 32, all keys) took the general method, 3540 us for 65536 tokens x 8 heads.
+constexpr int kMaxSurv = 256;
 
 // All four steps stay inside a row of 16 lanes (quad swaps, then mirrors of 8 and of 16 lanes), after which every
 // lane of a row holds the row's result; the four rows are combined on the scalar unit.
@@ -226,13 +229,16 @@ __device__ __forceinline__ void chunk_survivors(const RowInfo& R, int base, int 
   if (tau <= 0x007fffffu) {  // the key of -inf
     thr = -__builtin_inff();
 #pragma unroll
-    for (int e = 0; e < E; ++e) x[e] = __builtin_bit_cast(uint32_t, __builtin_fmaxf(__builtin_bit_cast(float, x[e]), thr));
+    for (int e = 0; e < E; ++e) {  // what was not loaded reads as -inf and would survive here, so it becomes a NaN
+      asm volatile("" : "+v"(x[e]));  // keeps this in its branch: worked out for every row it was 47 instructions of 16 scores a lane
+      const bool loaded = blk_of<kVec>(base, lane, kVec ? (e & ~3) : e) < R.b_vis;
+      x[e] = loaded ? __builtin_bit_cast(uint32_t, __builtin_fmaxf(__builtin_bit_cast(float, x[e]), thr)) : 0x7fc00000u;
+    }
   }
   const uint32_t not_blk = ~(uint32_t)blk_of<kVec>(base, lane, 0);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const bool loaded = blk_of<kVec>(base, lane, kVec ? (e & ~3) : e) < R.b_vis;
-    const bool sv = loaded & (__builtin_bit_cast(float, x[e]) >= thr);
+    const bool sv = __builtin_bit_cast(float, x[e]) >= thr;
     const uint64_t m = __builtin_amdgcn_ballot_w64(sv);
     // (a list that overflows is discarded: its writes only have to stay inside the wavefront's LDS)
     const int at = min(n_surv, kMaxChunks * kMaxTopk - 64);

@@ -237,3 +237,21 @@ def test_narrow_ranges_of_scores(kind, topk):
             end.synchronize()
             fastest[k] = min(fastest[k], start.elapsed_time(end))
     assert fastest[kind] < 1.3 * fastest["heavy"], fastest
+
+
+@pytest.mark.parametrize("blocks,kind", [(129, "heavy"), (132, "wild"), (136, "ties"), (137, "heavy"), (1140, "wild"), (1160, "ties")])
+def test_partly_filled_chunks_keep_everything(blocks, kind):
+    """Up to 136 scores of a chunk survive without a search at top-k 32, alone or after the survivors of a full chunk; what was not
+    loaded (NaN beside -inf) never does."""
+    print("case partly filled", blocks, kind, flush=True)
+    rng, tokens, seqlens = np.random.default_rng(blocks), 60 if blocks < 1000 else 12, [blocks * 64 - 5]
+    x = np.zeros((seqlens[0], 1, -(-blocks // 4) * 4), dtype=np.float32)        # only the first rows are looked at
+    z = rng.standard_normal((tokens, 1, x.shape[2]))
+    x[:tokens] = np.exp(1.5 * z) if kind == "heavy" else np.round(np.exp(1.5 * z)) if kind == "ties" else z
+    if kind == "wild":
+        x[:tokens][rng.random((tokens, 1, x.shape[2])) < 0.3] = np.nan
+    x[:tokens:5, :, 3:] = -np.inf
+    x[1:tokens:5, :, 40:] = np.nan
+    got = _gpu_select(x, None, 32, causal=False)[:tokens]
+    ref = tko.select_blocks(x, _cu(seqlens), 32, causal=False, tokens=range(tokens))
+    assert np.array_equal(got, ref[:tokens])
