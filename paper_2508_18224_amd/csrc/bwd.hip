@@ -41,11 +41,99 @@ __device__ __forceinline__ void wave_sync_bwd() {  // orders a wavefront's own L
 constexpr int kDeltaTokens = 8;
 constexpr int kDeltaKv = 8;   // kv heads per workgroup: at most 64 query heads
 
+// ---- the order in which the main kernels take the work units -----------------------------------------------------
+// With a workgroup a unit the hardware deals the units out to the XCDs in turn, by number: at 65536 tokens, g = 4, the first
+// XCD had finished 6 % before the last one, a slot stood empty for 5 us or more between two workgroups, and the sink's long
+// units of the last KV head, started last, ran alone at the end (8192 tokens, g = 1: 540 us of work a slot in 660 us).  So where there are several
+// units for each of the workgroups that the chip holds, the kernels stay resident, draw their units from a counter, and the long
+// units come first.  The first workgroup of k_bwd_delta prepares counters and order in the room of the one unit's dK / dV
+// sums that the bound on the number of units always leaves free (a list of c entries has less than c / unit + 1 units).
+struct UnitQueue {
+  int32_t* next;         // tickets drawn beyond the first one of every workgroup; null: one unit a workgroup, by number
+  const int32_t* order;  // unit by ticket; null: by number
+};
+constexpr int kQueuePasses = 64;                                                // counters, one a pass over KV heads
+constexpr int kQueueUnits = 2 * kBlock * kD - kQueuePasses;                     // entries of the order: 64 KB in all
+// Main kernel with a workgroup a unit -> from the queue, in us.  64-token blocks: 8192 tokens x 32 heads, g = 1 (6177 units at most)
+// 580 -> 527, 32768 x 32, g = 4 (6153) 2087 -> 2031, its window of 512 1170 -> 1150, 4096 x 32, g = 4 (2569) 243 -> 236; but 65536 x 32,
+// g = 4 (12297) 4086 -> 4078 in one run and 4168 -> 4199 in another, 65536 x 28, g = 7 (6149) 3526 -> 3548: the tail is a small part of
+// so long a kernel, and what the idle slots gave up the others had as clock rate (the chip runs these kernels at 1.8 of its 2.4
+// GHz).  128-token blocks, one workgroup a compute unit: window of 512 at 32768 tokens 1455 -> 1123, 8192 x 32, g = 1 532 -> 487,
+// 16384 x 16, g = 2 496 -> 464, 65536 x 32, g = 4 3240 -> 3188.  Fewer units than 2048 are a few a slot: 2000 x 32, g = 4 117 -> 118.
+constexpr int kQueueMinUnits = 2048;
+constexpr int64_t kQueueMaxRows64 = (int64_t)3 << 23;  // (token, query head, column) triples
+
+// Units in order of their length class, longest first: more than 1/2, 1/4 and less of a full unit.  A thread takes a run of units,
+// so that a class stays in the order of the KV heads, whose statistics the main kernels find in L2; the lengths are read once, 16
+// at a time, and kept as classes of two bits.
+__device__ __forceinline__ void prepare_queue(const Problem& P, const UnitRec* __restrict__ u_rec, const int32_t* __restrict__ nu_scan,
+                                              int32_t* __restrict__ queue, bool ordered) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid < kQueuePasses) queue[tid] = 0;
+  if (!ordered) return;
+  const int n = min(nu_scan[P.hkv * P.b_cap], kQueueUnits);
+  const int per = (n + 255) / 256, first = tid * per, mine = max(0, min(per, n - first));
+  constexpr int kB = 16, kMost = (kQueueUnits + 255) / 256;
+  static_assert(kMost <= 4 * kB, "four words of classes a thread");
+  uint32_t cls[4] = {0, 0, 0, 0};
+  uint64_t counts = 0;  // of the three classes, 21 bits each
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    if (b * kB >= per) break;
+    int ne[kB];
+#pragma unroll
+    for (int i = 0; i < kB; ++i) ne[i] = u_rec[min(first + b * kB + i, n - 1)].ne;
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+      const uint32_t c = 2 * ne[i] > P.unit ? 0 : 4 * ne[i] > P.unit ? 1 : 2;
+      cls[b] |= c << (2 * i);
+      if (b * kB + i < mine) counts += (uint64_t)1 << (21 * c);
+    }
+  }
+  uint64_t before = counts;  // of the threads up to this one
+#pragma unroll
+  for (int d = 1; d < 64; d *= 2) {
+    const uint64_t x = __shfl_up((unsigned long long)before, d);
+    if (lane >= d) before += x;
+  }
+  __shared__ uint64_t wave_sum[4];
+  if (lane == 63) wave_sum[wave] = before;
+  __syncthreads();
+  before -= counts;
+  uint64_t all = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    if (w < wave) before += wave_sum[w];
+    all += wave_sum[w];
+  }
+  constexpr uint64_t kMask = (1 << 21) - 1;
+  const int n0 = (int)(all & kMask), n1 = (int)(all >> 21 & kMask);
+  int at0 = (int)(before & kMask), at1 = n0 + (int)(before >> 21 & kMask), at2 = n0 + n1 + (int)(before >> 42);
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    if (b * kB >= per) break;
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+      if (b * kB + i >= mine) break;
+      const uint32_t c = cls[b] >> (2 * i) & 3;
+      queue[kQueuePasses + (c == 0 ? at0 : c == 1 ? at1 : at2)] = first + b * kB + i;
+      at0 += c == 0;
+      at1 += c == 1;
+      at2 += c == 2;
+    }
+  }
+}
+
 __global__ void __launch_bounds__(256)
 k_bwd_delta(Problem P, const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO, const float* __restrict__ LSE,
-            float2* __restrict__ stats, const float* __restrict__ gate, float* __restrict__ dgate) {
+            float2* __restrict__ stats, const float* __restrict__ gate, float* __restrict__ dgate, const UnitRec* __restrict__ u_rec,
+            const int32_t* __restrict__ nu_scan, int32_t* __restrict__ queue, bool ordered) {
   __shared__ float deltas[kDeltaTokens * kDeltaKv * 8];
-  const int t0 = blockIdx.x * kDeltaTokens, j0 = blockIdx.y * kDeltaKv;
+  if (queue != nullptr && blockIdx.x == 0) {
+    if (blockIdx.y == 0) prepare_queue(P, u_rec, nu_scan, queue, ordered);
+    return;
+  }
+  const int t0 = (blockIdx.x - (queue != nullptr)) * kDeltaTokens, j0 = blockIdx.y * kDeltaKv;
   const int nt = min(kDeltaTokens, P.T - t0), nj = min(kDeltaKv, P.hkv - j0), nh = nj * P.g;
   const int sub = threadIdx.x & 15, rows = nt * nh;
   constexpr int kB = 4, kOut = kDeltaTokens * kDeltaKv * 8 / 256;
@@ -143,24 +231,72 @@ struct BwdLds {
   static constexpr int DSt = Pt + 64 * kPStride * 2;
   static constexpr int Ent = DSt + 64 * kPStride * 2;
   static constexpr int Rec = Ent + kEntSeg * 4;      // per row of the tile: LSE (log2 domain), delta * scale, visible keys
-  static constexpr int Bytes = Rec + 3 * kTile * 4;  // 72448
+  static constexpr int Next = Rec + 3 * kTile * 4;   // the unit after this one, two words in turn
+  static constexpr int Bytes = Next + 16;            // 72464
 };
 static_assert(2 * BwdLds::Bytes <= 160 * 1024, "two workgroups of the 64-key backward must fit one CU's LDS");
+
+// A workgroup's way through the units (the same in all its threads).
+struct UnitTurn {
+  const Problem& P;
+  const UnitQueue q;
+  int32_t* const next;  // two words of LDS in turn: a wavefront may read one while the first already writes the other
+  int base, count, pos0, ticket, par, unit;
+  __device__ __forceinline__ UnitTurn(const Problem& P_, const int32_t* nu_scan, const int32_t* off, const UnitQueue& q_, int32_t* next_)
+      : P(P_), q(q_), next(next_), ticket((int)blockIdx.x), par(0) {
+    base = P.l0 > 0 ? nu_scan[P.l0] : 0;
+    pos0 = P.j0 > 0 ? off[P.j0 * P.b_cap] : 0;
+    count = nu_scan[P.l1] - base;
+    unit = ticket >= count ? -1 : q.order != nullptr ? q.order[ticket] : ticket;
+  }
+  __device__ __forceinline__ UnitRec record(const UnitRec* __restrict__ u_rec) const {
+    UnitRec U;
+    const int4 a = *reinterpret_cast<const int4*>(u_rec + base + unit);
+    const int2 b = *reinterpret_cast<const int2*>(&u_rec[base + unit].j);
+    U.e0 = a.x; U.ne = a.y; U.tok0 = a.z; U.blen = a.w; U.j = b.x; U.n_units = b.y;
+    asm volatile("" : "+s"(U.e0), "+s"(U.ne), "+s"(U.tok0), "+s"(U.blen), "+s"(U.j), "+s"(U.n_units));  // requested here
+    return U;
+  }
+  // Once a unit, between its first requests and its first block-wide barrier.
+  __device__ __forceinline__ void draw() {
+    if (threadIdx.x == 0) {
+      int u = -1;
+      if (q.next != nullptr) {
+        const int t = (int)gridDim.x + atomicAdd(q.next, 1);
+        if (t < count) u = q.order != nullptr ? q.order[t] : t;
+      }
+      next[par] = u;
+    }
+  }
+  __device__ __forceinline__ void advance() {  // with a block-wide barrier: the unit's LDS is free after it
+    if (q.next == nullptr) {
+      unit = -1;
+      return;
+    }
+    __syncthreads();
+    unit = __builtin_amdgcn_readfirstlane(next[par]);
+    par ^= 1;
+  }
+};
 
 template <bool kWin, bool kWide>
 __global__ void __launch_bounds__(256, 2)
 k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
             const bf16_t* __restrict__ dO, const float2* __restrict__ stats, const UnitRec* __restrict__ u_rec,
             const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off, const int2* __restrict__ qent,
-            bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
+            bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV,
+            UnitQueue queue) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
   int32_t* ent = reinterpret_cast<int32_t*>(smem + BwdLds::Ent);
-  UnitRec U;
-  int ubase, pos0;
-  if (!load_unit(P, u_rec, nu_scan, off, U, ubase, pos0)) return;
+  UnitTurn turn(P, nu_scan, off, queue, reinterpret_cast<int32_t*>(smem + BwdLds::Next));
+  const int pos0 = turn.pos0;
+  for (; turn.unit >= 0; turn.advance()) {
+  const UnitRec U = turn.record(u_rec);
   constexpr int kRow = BwdLds::Row;
   const int j = U.j, ne = U.ne, tok0 = U.tok0, blen = U.blen;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // keeps what depends on it inside the loop over units
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, qh = lane >> 5, rb = wave >> 1, kb = wave & 1;
   const uint32_t hbase = (uint32_t)(j * P.g), row_bytes = (uint32_t)P.hkv * (kD * 2);
 
@@ -176,6 +312,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 #pragma unroll
     for (int s = 0; s < 8; ++s) vf[s] = load_frag(v_buf, (32 * kb + col) * row_bytes + 16 * qh + 32 * s);
   }
+  turn.draw();
 #pragma unroll
   for (int i = 0; i < kEntSeg / 256; ++i) ent[tid + 256 * i] = ids[i];
 #pragma unroll
@@ -416,12 +553,12 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
         }
       }
     }
-    return;
+    continue;
   }
   // unit partial: [u][0 = dK, 1 = dV][key][d] fp32, summed by k_bwd_dkv_reduce in unit order
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) {
-    float* outk = dkv_part + (size_t)blockIdx.x * 2 * 64 * kD + 64 * kb + 32 * cb + col;
+    float* outk = dkv_part + (size_t)turn.unit * 2 * 64 * kD + 64 * kb + 32 * cb + col;
     float* outv = outk + 64 * kD;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -429,6 +566,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
       outk[key * kD] = dkacc[cb][v];
       outv[key * kD] = dvacc[cb][v];
     }
+  }
   }
 }
 
@@ -463,7 +601,8 @@ struct PipeLds {
   static constexpr int St0 = Ent + kEntSeg * 4;       // per-row records of a staged tile, two buffers: three arrays
   static constexpr int SB = 3 * kTile * 4;            // of 64: LSE (log2 domain), delta * scale, visible key range
   static constexpr int Tb0 = St0 + 2 * SB;            // per row of the tile to request next: row of Q / dO, place in
-  static constexpr int Bytes = Tb0 + kTile * 12;      // the kv head's statistics, visible keys; 145664 in all
+  static constexpr int Next = Tb0 + kTile * 12;       // the kv head's statistics, visible keys
+  static constexpr int Bytes = Next + 16;             // as in BwdLds; 145680 in all
 };
 static_assert(PipeLds::Bytes <= 160 * 1024, "the pipelined 128-key backward must fit one CU's LDS");
 constexpr int kDqPitch = 36;  // bf16 per row of an A-wave's dQ staging (64 rows x 32 channels + pad = 4608 bytes)
@@ -488,18 +627,20 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // What one workgroup of k_bwd_pipe128 works on.
 struct PipeUnit : UnitRec {
-  int pos0;
+  int pos0, number;
 };
 
 // One role of the pipeline (kS: an S-wave, else an A-wave).  Both roles run this same skeleton, so they execute the same
 // sequence of block-wide barriers: every loop bound below depends only on the unit, never on the role or the lane.
 template <bool kWin, bool kWide, bool kS>
 __device__ __forceinline__ void
-pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw, const bf16_t* __restrict__ Q,
+pipe_role(const Problem& P, const PipeUnit& U, UnitTurn& turn, unsigned char* smem, const int sw, const bf16_t* __restrict__ Q,
           const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO,
           const float2* __restrict__ stats, const int2* __restrict__ qent, bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
   int32_t* ent = reinterpret_cast<int32_t*>(smem + PipeLds::Ent);
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // keeps what depends on it inside the loop over units: carried round it, it spills
+  const int lane = tid & 63;
   int col = lane & 31, qh = lane >> 5;
   const int j = U.j, tok0 = U.tok0, blen = U.blen;
   const float c2 = P.scale * 1.4426950408889634f;
@@ -537,6 +678,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
         kf[sp][e] = key < blen ? kk : (bf16_t)0.f;
       }
   }
+  turn.draw();
   f32x16 dkacc[kS ? 1 : 4], dvacc[kS ? 1 : 4];  // A-wave: keys 32 sw.., by 32-channel block
   if constexpr (!kS) {
 #pragma unroll
@@ -870,7 +1012,7 @@ pipe_role(const Problem& P, const PipeUnit& U, unsigned char* smem, const int sw
     // unit partial: [u][0 = dK, 1 = dV][key][d] fp32, summed by k_bwd_dkv_reduce in unit order
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
-      float* outk = dkv_part + (size_t)blockIdx.x * 2 * 128 * kD + 32 * cb + col;
+      float* outk = dkv_part + (size_t)U.number * 2 * 128 * kD + 32 * cb + col;
       float* outv = outk + 128 * kD;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -887,16 +1029,18 @@ __global__ void __launch_bounds__(512, 1)
 k_bwd_pipe128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
               const bf16_t* __restrict__ dO, const float2* __restrict__ stats, const UnitRec* __restrict__ u_rec,
               const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off, const int2* __restrict__ qent,
-              bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
+              bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV,
+              UnitQueue queue) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
-  PipeUnit U;
-  int ubase;
-  if (!load_unit(P, u_rec, nu_scan, off, U, ubase, U.pos0)) return;
+  UnitTurn turn(P, nu_scan, off, queue, reinterpret_cast<int32_t*>(smem + PipeLds::Next));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wave < 4)
-    pipe_role<kWin, kWide, true>(P, U, smem, wave, Q, K, V, dO, stats, qent, dqpart, dkv_part, dK, dV);
-  else
-    pipe_role<kWin, kWide, false>(P, U, smem, wave - 4, Q, K, V, dO, stats, qent, dqpart, dkv_part, dK, dV);
+  for (; turn.unit >= 0; turn.advance()) {
+    const PipeUnit U = {turn.record(u_rec), turn.pos0, turn.unit};
+    if (wave < 4)
+      pipe_role<kWin, kWide, true>(P, U, turn, smem, wave, Q, K, V, dO, stats, qent, dqpart, dkv_part, dK, dV);
+    else
+      pipe_role<kWin, kWide, false>(P, U, turn, smem, wave - 4, Q, K, V, dO, stats, qent, dqpart, dkv_part, dK, dV);
+  }
 }
 
 // dK / dV of the lists whose units left partial sums: the sum runs in unit order, four units in flight.  A piece of this work is
@@ -1072,11 +1216,18 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
                             ready_reduce);
     if (e != hipSuccess) return e;
   }
+  const int passes = (P0.hkv + heads_per_pass - 1) / heads_per_pass;
+  const int64_t pass_units = units_bound(heads_per_pass, P0.b_cap, P0.T, P0.topk, P0.unit);
+  int32_t* queue = nullptr;
+  if (lists_per_pass == 0 && passes <= kQueuePasses && pass_units >= kQueueMinUnits &&
+      (b128 || (int64_t)P0.T * P0.hq * P0.topk <= kQueueMaxRows64))
+    queue = reinterpret_cast<int32_t*>(dkv_part + (size_t)(pass_units - 1) * 2 * P0.bk * kD);
+  const bool ordered = queue != nullptr && passes == 1 && pass_units <= kQueueUnits;
   {
     ProfScope ps(KID_BWD_DELTA, st);
-    hipLaunchKernelGGL(k_bwd_delta, dim3((P0.T + kDeltaTokens - 1) / kDeltaTokens, (P0.hkv + kDeltaKv - 1) / kDeltaKv),
+    hipLaunchKernelGGL(k_bwd_delta, dim3((P0.T + kDeltaTokens - 1) / kDeltaTokens + (queue != nullptr), (P0.hkv + kDeltaKv - 1) / kDeltaKv),
                        dim3(256), 0, st, P0, (const bf16_t*)O,
-                       (const bf16_t*)dO, LSE, (float2*)delta, G.gate, G.dgate);
+                       (const bf16_t*)dO, LSE, (float2*)delta, G.gate, G.dgate, p.u_rec, p.u_nu, queue, ordered);
   }
   // KV heads are processed heads_per_pass at a time, every pass reusing the partial-dQ and unit-sum buffers; of one head,
   // where its unit sums do not fit, lists_per_pass lists at a time, every range reusing the unit sums.
@@ -1092,10 +1243,12 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
       const int64_t bound = units_bound(P.nj, P.b_cap, P.T, P.topk, P.unit);
       const unsigned units_max =
           (unsigned)(lists_per_pass > 0 ? min(bound, (int64_t)step * ((P.T + P.unit - 1) / P.unit)) : bound);
+      const UnitQueue turns = {queue != nullptr ? queue + j0 / heads_per_pass : nullptr, ordered ? queue + kQueuePasses : nullptr};
+      const unsigned slots = b128 ? 256 : 512;  // workgroups that the chip holds
       { ProfScope ps(KID_BWD_MAIN, st);
-      hipLaunchKernelGGL(main_kernel, dim3(units_max), dim3(main_threads), main_lds, st, P, (const bf16_t*)Q,
+      hipLaunchKernelGGL(main_kernel, dim3(queue != nullptr ? min(units_max, slots) : units_max), dim3(main_threads), main_lds, st, P, (const bf16_t*)Q,
                          (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, (const float2*)delta, p.u_rec, p.u_nu,
-                         p.off, p.qent, (bf16_t*)dqpart, dkv_part, (bf16_t*)dK, (bf16_t*)dV); }
+                         p.off, p.qent, (bf16_t*)dqpart, dkv_part, (bf16_t*)dK, (bf16_t*)dV, turns); }
       const int lists = P.l1 - P.l0, per = max(1, min(64, lists * (P.bk / 4) / 4096));
       const int groups = (lists + per - 1) / per;
       const bool last = P.l1 == end, bursts = dq_in_bursts(P);

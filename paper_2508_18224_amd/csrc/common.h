@@ -175,7 +175,8 @@ inline bool short_forward(int T, int nseq, int hq, int topk, int bk, bool causal
 }
 
 // Upper bound of the work units of nj KV heads (one per non-empty list plus one per full unit of entries); the
-// real count is only known on the device.
+// real count is only known on the device.  It is never reached, and the backward keeps its queue of units in the room of the last
+// one's sums (see UnitQueue).
 inline int64_t units_bound(int nj, int b_cap, int T, int topk, int unit) {
   return (int64_t)nj * b_cap + (int64_t)nj * T * topk / unit + 1;
 }

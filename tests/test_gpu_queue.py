@@ -1,0 +1,60 @@
+"""The backward's main kernels draw their work units from a counter where there are some thousands of them (see UnitQueue in
+csrc/bwd.hip).  Which workgroup computes a unit changes nothing about it: the results are those of a workgroup a unit, which
+small enough a workspace brings about (few KV heads a pass, few units), bit for bit, and the same every time."""
+import pytest
+import torch
+
+import paper_2508_18224_amd as nsa
+import workloads as wl
+from gpu_util import Case
+
+pytestmark = pytest.mark.gpu
+MIN_UNITS = 2048  # of the rule
+
+
+def _bound(w, hkv, unit):
+    blocks = w.total_tokens // w.block + len(w.seqlens)
+    return hkv * blocks + hkv * w.total_tokens * w.topk // unit + 1
+
+
+#        lengths, query heads, KV heads, top-k, block, window, units at most, KV heads a pass (0: all)
+CASES = [([4096], 8, 8, 16, 64, 0, 2569, 0),                     # all lists ordered
+         ([3000, 1, 64, 1500, 531], 16, 8, 16, 64, 0, 3221, 0),  # packed, ragged, g = 2
+         ([5000], 8, 8, 9, 64, 512, 2039, 0),                # below the rule's least: a workgroup a unit
+         ([8192], 8, 8, 9, 64, 512, 3337, 0),                    # the window's form
+         ([4096], 16, 8, 16, 128, 0, 2313, 0),                   # 128-token blocks
+         ([8192], 8, 8, 5, 128, 512, 1801, 0),                   # their window, below the least
+         ([16384], 16, 16, 5, 128, 512, 7185, 0),                # and above
+         ([4096], 20, 20, 16, 64, 0, 6421, 11),                  # two passes, a counter each, by number
+         ([16384], 16, 16, 16, 128, 0, 18449, 0)]                # more units than the order has room for: by number
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,topk,block,window,units,heads", CASES)
+def test_units_from_the_queue_are_those_of_a_workgroup_each(lengths, hq, hkv, topk, block, window, units, heads):
+    w = wl.realise(wl.Workload("queue", lengths, hq=hq, hkv=hkv, topk=topk, sink=True, seed=3, block=block))
+    assert _bound(w, hkv, 256) == units
+    case = Case(w, window=window)
+
+    def attention(cap=None):
+        return nsa.SelAttention(w.total_tokens, hq, hkv, topk, nseq=len(lengths), block=block, window=window, unit=256, ws_cap_bytes=cap)
+    idx = case.idx
+    if window:
+        idx = nsa.window_blocks(w.total_tokens, hkv, window, case.cu, block=block)
+        assert idx.shape[2] == topk
+    whole = attention()
+    if heads:  # a workspace of `heads` KV heads: more than the least number of units a pass
+        rows = lambda n: w.total_tokens * n * (hq // hkv) * topk * 256 + _bound(w, n, 256) * 2 * block * 512
+        whole = attention(rows(heads) + w.total_tokens * hq * 8 + 1024)
+        assert whole.bwd_ws.numel() < nsa.workspace_bytes(whole.shape)[1] and _bound(w, heads, 256) >= MIN_UNITS
+    single = attention(0)  # one KV head a pass
+    assert _bound(w, 1, 256) < MIN_UNITS
+    o, lse = whole.forward(case.q, case.k, case.v, idx, case.cu)
+    single.build_index(idx, case.cu)
+    single.bwd_ws.fill_(0x7F)
+    want = single.backward(case.q, case.k, case.v, o, lse, case.do, case.cu)
+    assert all(bool(torch.isfinite(x).all()) for x in want)
+    for _ in range(3):
+        whole.bwd_ws.fill_(0x7F)  # counters and order are made anew by every call
+        got = whole.backward(case.q, case.k, case.v, o, lse, case.do, case.cu)
+        for name, a, b in zip(("dQ", "dK", "dV"), got, want):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16)), name
