@@ -110,6 +110,7 @@ struct Problem {
   int32_t dense;   // 1: the dense forward path is on (the index carries dense flags and tables)
   int32_t t_cap;   // stride of the per-(tile, kv head) dense tables
   int32_t j0, nj;  // KV heads [j0, j0 + nj) handled by this launch (all of them unless the workspace is capped)
+  int32_t in_turn; // forward main kernels: the heads' units in turn (units_in_turn)
   int32_t l0, l1;  // lists [l0, l1): those of the heads, or a range of one head's (see launch_bwd)
   int32_t units_max;  // last index the table of work units has room for
   float scale;
@@ -180,6 +181,15 @@ inline bool short_forward(int T, int nseq, int hq, int topk, int bk, bool causal
 inline int64_t units_bound(int nj, int b_cap, int T, int topk, int unit) {
   return (int64_t)nj * b_cap + (int64_t)nj * T * topk / unit + 1;
 }
+
+// Whether the forward main kernels take the first units of all KV heads, then the second ones and so on, instead of head by
+// head.  A head's first lists are its longest (the sink's, then the early blocks'), and those of the last head would otherwise
+// start last: at 8192 tokens x 32 heads, g = 1, they ran alone for a seventh of the kernel.  Measured head by head / in turn, us:
+// g = 1, 8192 tokens x 32 heads 348 / 298, with 128-token blocks 251 / 231, 12288 x 32 520 / 505, but 24576 x 16 523 / 551, 16384 x 32 707 /
+// 733, 40000 x 16 849 / 960; g = 4, 4096 x 32 63 / 55, 8192 x 32 217 / 183, 16384 x 32 493 / 423, with 128-token blocks 317 / 310,
+// 32768 x 8 262 / 253, but 24576 x 32 772 / 793, 65536 x 32 2064 / 2250; g = 8, 6000 x 64 277 / 236, 131072 x 64 7800 / 9900.  On long
+// inputs the tail is a small part, and gathers from one head at a time are the faster ones.
+inline bool units_in_turn(int T, int hq, int g) { return (int64_t)T * hq <= (g == 1 ? 1 << 18 : 1 << 19); }
 
 // Work units whose dK/dV sums the smallest backward workspace holds: those of one KV head at units of at least kMinUnit.  The
 // smaller units of tiny inputs have more; where they do not fit, the backward goes through the head's lists in ranges.  One
@@ -314,19 +324,27 @@ __device__ __forceinline__ bf16x8 load_frag(__amdgpu_buffer_rsrc_t b, uint32_t o
   return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0));
 }
 
-// The unit of this workgroup, or false when the launch (sized by an upper bound) has no unit left for it.  The record is
-// requested before the unit count is known: the two loads are independent and every index up to the bound is allocated.
-// base = the launch's first unit, pos0 = the first list position of its KV heads (partial rows are relative to it).
+// The unit of this workgroup of a forward main kernel, or false when the launch (sized by an upper bound) has no unit left
+// for it.  By number, the record is requested before the unit count is known: the two loads are independent and every
+// index up to the bound is allocated.  With the heads in turn (see units_in_turn) consecutive workgroups take the same place among the
+// units of each of the pass's heads, and the launch has room for as many units as one head can have, for each.
+// pos0 = the first list position of the pass's KV heads (partial rows are relative to it).
 __device__ __forceinline__ bool load_unit(const Problem& P, const UnitRec* __restrict__ u_rec,
                                           const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off,
-                                          UnitRec& U, int& base, int& pos0) {
-  base = P.l0 > 0 ? nu_scan[P.l0] : 0;
+                                          UnitRec& U, int& pos0) {
   pos0 = P.j0 > 0 ? off[P.j0 * P.b_cap] : 0;
-  const int u = base + (int)blockIdx.x;
+  int u, end;
+  if (P.in_turn) {
+    const int i = (int)(blockIdx.x / (unsigned)P.nj), l = (P.j0 + (int)blockIdx.x - i * P.nj) * P.b_cap;
+    u = nu_scan[l] + i;
+    end = nu_scan[l + P.b_cap];
+  } else {
+    u = (P.l0 > 0 ? nu_scan[P.l0] : 0) + (int)blockIdx.x;
+    end = nu_scan[P.l1];
+  }
   const int ur = min(u, P.units_max);
   const int4 a = *reinterpret_cast<const int4*>(u_rec + ur);
   const int2 b = *reinterpret_cast<const int2*>(&u_rec[ur].j);
-  const int end = nu_scan[P.l1];
   U.e0 = a.x; U.ne = a.y; U.tok0 = a.z; U.blen = a.w; U.j = b.x; U.n_units = b.y;
   asm volatile("" : "+s"(U.e0), "+s"(U.ne), "+s"(U.tok0), "+s"(U.blen), "+s"(U.j), "+s"(U.n_units));  // requested here
   return u < end;

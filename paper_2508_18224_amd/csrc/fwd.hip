@@ -148,8 +148,8 @@ k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   uint16_t* epos = reinterpret_cast<uint16_t*>(smem + kF64Epos);  // and their index inside the unit
   int32_t* cnts = reinterpret_cast<int32_t*>(smem + kF64Cnts);
   UnitRec U;
-  int ubase, pos0;
-  if (!load_unit(P, u_rec, nu_scan, off, U, ubase, pos0)) return;
+  int pos0;
+  if (!load_unit(P, u_rec, nu_scan, off, U, pos0)) return;
   const int j = U.j, e0 = U.e0, ne_all = U.ne, tok0 = U.tok0, blen = U.blen;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, qh = lane >> 5;
   const int crow = lane >> 4, cchunk = (lane & 15) * 8;  // coalesced layout: 16 lanes per row, 4 rows per access
@@ -341,8 +341,8 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
   uint16_t* epos = reinterpret_cast<uint16_t*>(smem + kF128Epos);
   int32_t* cnts = reinterpret_cast<int32_t*>(smem + kF128Cnts);
   UnitRec U;
-  int ubase, pos0;
-  if (!load_unit(P, u_rec, nu_scan, off, U, ubase, pos0)) return;
+  int pos0;
+  if (!load_unit(P, u_rec, nu_scan, off, U, pos0)) return;
   const int j = U.j, e0 = U.e0, ne_all = U.ne, tok0 = U.tok0, blen = U.blen;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int col = lane & 31, qh = lane >> 5;                 // not const: see the top of the tile loop
@@ -1047,7 +1047,8 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
     P.l0 = j0 * P.b_cap;
     P.l1 = (j0 + P.nj) * P.b_cap;
     // upper bound of the work units of the pass (the real count is only known on the device)
-    const unsigned units_max = (unsigned)units_bound(P.nj, P.b_cap, P.T, P.topk, P.unit);
+    const unsigned units_max = (unsigned)(P.in_turn ? P.nj * units_bound(1, P.b_cap, P.T, P.topk, P.unit)
+                                                    : units_bound(P.nj, P.b_cap, P.T, P.topk, P.unit));
     if (P.bk == 128) {
       ProfScope ps(KID_FWD_MAIN, st);
       hipLaunchKernelGGL(main128, dim3(units_max), dim3(64 * kWaves128), kF128Bytes, st, P, (const bf16_t*)Q,

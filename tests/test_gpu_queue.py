@@ -1,6 +1,7 @@
-"""The backward's main kernels draw their work units from a counter where there are some thousands of them (see UnitQueue in
+"""The order in which the main kernels take the work units.  The backward's draw their work units from a counter where there are some thousands of them (see UnitQueue in
 csrc/bwd.hip).  Which workgroup computes a unit changes nothing about it: the results are those of a workgroup a unit, which
-small enough a workspace brings about (few KV heads a pass, few units), bit for bit, and the same every time."""
+small enough a workspace brings about (few KV heads a pass, few units), bit for bit, and the same every time.
+The forward's take the KV heads in turn or one after the other (units_in_turn in csrc/common.h), with the same results."""
 import pytest
 import torch
 
@@ -58,3 +59,29 @@ def test_units_from_the_queue_are_those_of_a_workgroup_each(lengths, hq, hkv, to
         got = whole.backward(case.q, case.k, case.v, o, lse, case.do, case.cu)
         for name, a, b in zip(("dQ", "dK", "dV"), got, want):
             assert torch.equal(a.view(torch.int16), b.view(torch.int16)), name
+
+
+@pytest.mark.parametrize("lengths,g,hkv,block,part", [([8200], 1, 33, 64, 4), ([16385], 4, 8, 64, 3), ([9000, 1, 7400], 2, 16, 128, 1)])
+def test_forward_of_all_heads_and_of_a_few_agree(lengths, g, hkv, block, part):
+    T, topk = sum(lengths), 8
+    most = 1 << (18 if g == 1 else 19)
+    assert part * g * T <= most < hkv * g * T  # the few in turn, all of them head by head
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q = torch.randn(T, hkv * g, 128, generator=gen, device="cuda").to(torch.bfloat16)
+    k, v = (torch.randn(T, hkv, 128, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    cu = torch.tensor([sum(lengths[:i]) for i in range(len(lengths) + 1)], dtype=torch.int32, device="cuda")
+    stride = -(-max(lengths) // block)
+    idx = nsa.select_blocks(torch.rand(T, hkv, stride + -stride % 4, generator=gen, device="cuda"), cu, topk, block=block)
+
+    def forward(j0, n):
+        attn = nsa.SelAttention(T, n * g, n, topk, nseq=len(lengths), block=block, unit=512, dense=g > 1, bwd=False)
+        kv = slice(j0, j0 + n)
+        return attn.forward(q[:, j0 * g:(j0 + n) * g].contiguous(), k[:, kv].contiguous(), v[:, kv].contiguous(),
+                            idx[:, kv].contiguous(), cu)
+    o, lse = forward(0, hkv)
+    assert bool(torch.isfinite(lse).all())
+    for j0 in range(0, hkv, part):
+        n = min(part, hkv - j0)
+        o_part, lse_part = forward(j0, n)
+        assert torch.equal(o[:, j0 * g:(j0 + n) * g].view(torch.int16), o_part.view(torch.int16)), j0
+        assert torch.equal(lse[:, j0 * g:(j0 + n) * g].view(torch.int32), lse_part.view(torch.int32)), j0
