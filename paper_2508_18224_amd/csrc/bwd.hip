@@ -57,7 +57,7 @@ constexpr int kQueueUnits = 2 * kBlock * kD - kQueuePasses;                     
 // Main kernel with a workgroup a unit -> from the queue, in us.  64-token blocks: 8192 tokens x 32 heads, g = 1 (6177 units at most)
 // 580 -> 527, 32768 x 32, g = 4 (6153) 2087 -> 2031, its window of 512 1170 -> 1150, 4096 x 32, g = 4 (2569) 243 -> 236; but 65536 x 32,
 // g = 4 (12297) 4086 -> 4078 in one run and 4168 -> 4199 in another, 65536 x 28, g = 7 (6149) 3526 -> 3548: the tail is a small part of
-// so long a kernel, and what the idle slots gave up the others had as clock rate (the chip runs these kernels at 1.8 of its 2.4
+// so long a kernel, and what the idle slots gave up the others may have had as clock rate (the chip runs these kernels at 1.8 of its 2.4
 // GHz).  128-token blocks, one workgroup a compute unit: window of 512 at 32768 tokens 1455 -> 1123, 8192 x 32, g = 1 532 -> 487,
 // 16384 x 16, g = 2 496 -> 464, 65536 x 32, g = 4 3240 -> 3188.  Fewer units than 2048 are a few a slot: 2000 x 32, g = 4 117 -> 118.
 constexpr int kQueueMinUnits = 2048;
