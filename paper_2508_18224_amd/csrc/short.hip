@@ -336,6 +336,9 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
     lo = P.window > 0 ? max(tok - P.window + 1 - k0, 0) : 0;
   };
 
+  // what a piece's exponents are taken against; a row that sees only scores of -inf so far has no reference yet
+  auto offset_of = [&](bool sees, float ref) __attribute__((always_inline)) { return !sees ? INFINITY : ref == -INFINITY ? 0.f : ref * c2; };
+
   f32x16 oacc[4];
   float m_ref = -INFINITY, l_run = 0.f;
   auto clear = [&]() __attribute__((always_inline)) {
@@ -379,7 +382,7 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
       if (__builtin_amdgcn_ballot_w64(sees && (lim < 64 || lo > 0)) != 0ull) m = row_max(mask_scores(cur, lo, lim, qh));
       new_reference(m, sees, c2, slack, m_ref, l_run, oacc);
       members = members_of(q1);
-      m = piece_values_and_next_scores(ka, va, qf, c2, sees ? m_ref * c2 : INFINITY, cur, next, l_run, oacc,
+      m = piece_values_and_next_scores(ka, va, qf, c2, offset_of(sees, m_ref), cur, next, l_run, oacc,
                                        [&](int i) __attribute__((always_inline)) {
                                          if (i < kLoads) load(vbuf, v_lds + (side ^ 1) * kPieceBytes, i);
                                          else if (i < 2 * kLoads) load(kbuf, k_lds + side * kPieceBytes, i - kLoads);
@@ -417,7 +420,7 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
         f32x16 sacc[2];
         piece_scores(kaddr, qf, sacc);
         new_reference(row_max(mask_scores(sacc, lo, lim, qh)), sees, c2, slack, m_ref, l_run, oacc);
-        const float mc = sees ? m_ref * c2 : INFINITY;
+        const float mc = offset_of(sees, m_ref);
         bf16x8 pf[4];
         float l = 0.f;
 #pragma unroll
@@ -470,11 +473,14 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
       st[s] = stats[32 * kGroups * s + rr];
       M = fmaxf(M, st[s].x);
     }
-    const bool empty = M == -INFINITY;  // nothing visible: O = 0, LSE = -inf, and the gated sum is what the other branches gave
+    // nothing visible: O = 0, LSE = -inf, and the gated sum is what the other branches gave (where the visible scores are all -inf,
+    // LSE is that too and O is not a number)
+    bool empty = M == -INFINITY;
+    for (int b = 0; empty && b < n_blocks; ++b) empty = ((masks[2 * b + (e >> 6)] >> (e & 63)) & 1ull) == 0ull;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      L += empty ? 0.f : st[s].y * __builtin_amdgcn_exp2f(fmaf(st[s].x, c2, -M * c2));
+      L += st[s].x == -INFINITY ? 0.f : st[s].y * __builtin_amdgcn_exp2f(fmaf(st[s].x, c2, -M * c2));
       const unsigned char* src = smem + (kGroups * s + (rr >> 5)) * 32 * 512 + (rr & 31) * 512;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {

@@ -120,6 +120,40 @@ def test_foreign_infinities_and_neighbours_do_not_show(tokens, hq, hkv):
     assert torch.equal(o_less[0::2], o[0::2]) and torch.equal(lse_less[0::2], lse[0::2])
 
 
+@pytest.mark.parametrize("tokens,hq,hkv,window,block", [(600, 4, 2, 0, 64), (2000, 32, 8, 0, 64), (1100, 8, 4, 300, 64), (700, 8, 2, 0, 128)])
+def test_scores_of_minus_infinity(tokens, hq, hkv, window, block):
+    """Keys masked with -inf in K: rows whose first pieces score -inf throughout, rows that meet such a piece behind a finite one, and
+    rows that see nothing else, whose LSE is -inf and whose O is not a number, as by every other route."""
+    print("case short -inf scores", tokens, hq, hkv, window, block, flush=True)
+    if window:
+        w = wl.realise(wl.Workload("masked", [tokens], hq=hq, hkv=hkv, topk=1, block=block, seed=91), tensors=True)
+        w.idx = wl.window_block_indices(w.seqlens, w.hkv, window, block)
+        w.topk = w.idx.shape[2]
+    else:
+        w = wl.realise(wl.Workload("masked", [tokens], hq=hq, hkv=hkv, topk=8, block=block, sink=True, seed=91))
+    c = Case(w, window=window)
+    c.q[..., 0] = c.q[..., 0].abs() + 0.125
+    c.k[:128, :, 0] = float("-inf")          # the first pieces of the sequence, and one within it
+    c.k[384:448, :, 0] = float("-inf")
+    gate = torch.from_numpy(wl.draw_gates(w.seed, w.total_tokens, w.hq)).cuda()
+    attn = _attn(w, window)
+    (out, o, lse), kinds = _kinds(lambda: attn.forward_gated(c.q, c.k, c.v, c.idx, gate, c.do, c.cu))
+    assert "fwd_short" in kinds
+    with np.errstate(invalid="ignore", divide="ignore"):
+        rO, rL = orc.forward(to_f64(c.q), to_f64(c.k), to_f64(c.v), w.idx, w.cu_seqlens, block=block, window=window)
+    lost = ~np.isfinite(rL)                  # everything such a row sees is masked
+    assert lost.any() and not lost.all() and np.isnan(rO[lost]).all()
+    assert_close("O", to_f64(o)[~lost], rO[~lost], TOL_O)
+    assert np.abs(to_f64(lse) - rL)[~lost].max() <= 1e-3
+    assert np.isneginf(to_f64(lse)[lost]).all() and np.isnan(to_f64(o)[lost]).all() and np.isnan(to_f64(out)[lost]).all()
+    assert np.isfinite(to_f64(out)[~lost]).all()
+    # the dense route says the same (the partial rows of the gather route, of which a window leaves none, are not numbers there)
+    o_d, lse_d = _attn(w, window, dense=True).forward(c.q, c.k, c.v, c.idx, c.cu)
+    assert torch.equal(torch.isneginf(lse_d), torch.isneginf(lse)) and bool(torch.isfinite(lse_d)[torch.isfinite(lse)].all())
+    if window:
+        assert torch.equal(torch.isnan(o_d), torch.isnan(o))
+
+
 def test_short_gated_forward():
     print("case short gated", flush=True)
     w = wl.realise(wl.Workload("gated", [800, 130], hq=6, hkv=2, topk=8, sink=True, seed=86))
