@@ -71,8 +71,10 @@ __device__ __forceinline__ float max_scores(const f32x16 (&sacc)[2]) {
 // ask once; a rescale for every piece is a fifth of a piece's vector instructions.)  `m`: the row's maximum; rows that see nothing of
 // the piece keep everything.
 constexpr float kSlack = 8.f;
+// kSlack as a difference of scores.  Finite under any scale: added to -inf it must not give a NaN, which no maximum exceeds.
+__device__ __forceinline__ float score_slack(float c2) { return fminf(kSlack / c2, 3e38f); }
 __device__ __forceinline__ void new_reference(float m, bool sees, float c2, float slack, float& m_ref, float& l_run, f32x16 (&oacc)[4]) {
-  const bool up = sees && m > m_ref + slack;  // slack = kSlack / c2; also from -inf, where nothing has been seen yet
+  const bool up = sees && m > m_ref + slack;  // slack = score_slack(c2); also from -inf, where nothing has been seen yet
   if (__builtin_amdgcn_ballot_w64(up) != 0ull) {
     const float alpha = up ? __builtin_amdgcn_exp2f((m_ref - m) * c2) : 1.f;
     m_ref = up ? m : m_ref;

@@ -663,7 +663,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
 #pragma unroll
       for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
     float m_ref = -INFINITY, l_run = 0.f;            // reference score and sum of the row (see new_reference)
-    const float slack = kSlack / c2;
+    const float slack = score_slack(c2);
     uint32_t kaddr[8], vaddr[2][4];
     piece_addresses(lds_address(smem + kDnK), lds_address(smem + kDnV), lane, kaddr, vaddr);
 

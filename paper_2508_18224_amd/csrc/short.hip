@@ -288,7 +288,7 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
     steps = max(steps, count);
   }
 
-  const float c2 = P.scale * 1.4426950408889634f, slack = kSlack / c2;
+  const float c2 = P.scale * 1.4426950408889634f, slack = score_slack(c2);
   const uint32_t k_lds = lds_address(smem) + split * 4 * kPieceBytes, v_lds = k_lds + 2 * kPieceBytes;
   uint32_t kaddr[8], vaddr[2][4];
   piece_addresses(k_lds, v_lds, lane, kaddr, vaddr);

@@ -154,6 +154,19 @@ def test_scores_of_minus_infinity(tokens, hq, hkv, window, block):
         assert torch.equal(torch.isnan(o_d), torch.isnan(o))
 
 
+@pytest.mark.parametrize("dense", [None, True])
+def test_scale_next_to_nothing(dense):
+    """A scale whose reciprocal times eight is infinite in fp32: every visible key counts the same."""
+    print("case short scale", dense, flush=True)
+    w = wl.realise(wl.Workload("flat", [500, 90], hq=4, hkv=2, topk=6, sink=True, seed=92))
+    c = Case(w, bwd=False, scale=1e-38, dense=dense)
+    o, lse = c.forward()
+    Q, K, V, _ = c.host_f64()
+    rO, rL = orc.forward(Q, K, V, w.idx, w.cu_seqlens, scale=1e-38)
+    assert_close("O", to_f64(o), rO, TOL_O)
+    assert_lse_close(to_f64(lse), rL)
+
+
 def test_short_gated_forward():
     print("case short gated", flush=True)
     w = wl.realise(wl.Workload("gated", [800, 130], hq=6, hkv=2, topk=8, sink=True, seed=86))
