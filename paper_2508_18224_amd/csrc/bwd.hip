@@ -49,7 +49,7 @@ constexpr int kDeltaKv = 8;   // kv heads per workgroup: at most 64 query heads
 // units come first.  The first workgroup of k_bwd_delta prepares counters and order in the room of the one unit's dK / dV
 // sums that the bound on the number of units always leaves free (a list of c entries has less than c / unit + 1 units).
 struct UnitQueue {
-  int32_t* next;         // tickets drawn beyond the first one of every workgroup; null: one unit a workgroup, by number
+  int32_t* next;         // tickets drawn beyond the first one of every workgroup
   const int32_t* order;  // unit by ticket; null: by number
 };
 constexpr int kQueuePasses = 64;                                                // counters, one a pass over KV heads
@@ -236,20 +236,30 @@ struct BwdLds {
 };
 static_assert(2 * BwdLds::Bytes <= 160 * 1024, "two workgroups of the 64-key backward must fit one CU's LDS");
 
-// A workgroup's way through the units (the same in all its threads).
+// A workgroup's way through the units (the same in all its threads).  kQueue: one after the other from the queue; otherwise the unit of
+// its number alone, in a kernel without the loop: what the loop carries round costs registers, and the forms that have none to spare spill
+// them (k_bwd_pipe128 with 64-bit row addresses: 12 bytes a lane).
+template <bool kQueue>
 struct UnitTurn {
   const Problem& P;
   const UnitQueue q;
   int32_t* const next;  // two words of LDS in turn: a wavefront may read one while the first already writes the other
+  UnitRec only;
   int base, count, pos0, ticket, par, unit;
-  __device__ __forceinline__ UnitTurn(const Problem& P_, const int32_t* nu_scan, const int32_t* off, const UnitQueue& q_, int32_t* next_)
+  __device__ __forceinline__ UnitTurn(const Problem& P_, const UnitRec* __restrict__ u_rec, const int32_t* nu_scan, const int32_t* off,
+                                      const UnitQueue& q_, int32_t* next_)
       : P(P_), q(q_), next(next_), ticket((int)blockIdx.x), par(0) {
-    base = P.l0 > 0 ? nu_scan[P.l0] : 0;
-    pos0 = P.j0 > 0 ? off[P.j0 * P.b_cap] : 0;
-    count = nu_scan[P.l1] - base;
-    unit = ticket >= count ? -1 : q.order != nullptr ? q.order[ticket] : ticket;
+    if constexpr (!kQueue) {
+      unit = load_unit<false>(P, u_rec, nu_scan, off, only, pos0) ? ticket : -1;
+    } else {
+      base = P.l0 > 0 ? nu_scan[P.l0] : 0;
+      pos0 = P.j0 > 0 ? off[P.j0 * P.b_cap] : 0;
+      count = nu_scan[P.l1] - base;
+      unit = ticket >= count ? -1 : q.order != nullptr ? q.order[ticket] : ticket;
+    }
   }
   __device__ __forceinline__ UnitRec record(const UnitRec* __restrict__ u_rec) const {
+    if constexpr (!kQueue) return only;
     UnitRec U;
     const int4 a = *reinterpret_cast<const int4*>(u_rec + base + unit);
     const int2 b = *reinterpret_cast<const int2*>(&u_rec[base + unit].j);
@@ -259,17 +269,14 @@ struct UnitTurn {
   }
   // Once a unit, between its first requests and its first block-wide barrier.
   __device__ __forceinline__ void draw() {
+    if constexpr (!kQueue) return;
     if (threadIdx.x == 0) {
-      int u = -1;
-      if (q.next != nullptr) {
-        const int t = (int)gridDim.x + atomicAdd(q.next, 1);
-        if (t < count) u = q.order != nullptr ? q.order[t] : t;
-      }
-      next[par] = u;
+      const int t = (int)gridDim.x + atomicAdd(q.next, 1);
+      next[par] = t >= count ? -1 : q.order != nullptr ? q.order[t] : t;
     }
   }
   __device__ __forceinline__ void advance() {  // with a block-wide barrier: the unit's LDS is free after it
-    if (q.next == nullptr) {
+    if constexpr (!kQueue) {
       unit = -1;
       return;
     }
@@ -279,7 +286,7 @@ struct UnitTurn {
   }
 };
 
-template <bool kWin, bool kWide>
+template <bool kWin, bool kWide, bool kQueue>
 __global__ void __launch_bounds__(256, 2)
 k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
             const bf16_t* __restrict__ dO, const float2* __restrict__ stats, const UnitRec* __restrict__ u_rec,
@@ -288,14 +295,14 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
             UnitQueue queue) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
   int32_t* ent = reinterpret_cast<int32_t*>(smem + BwdLds::Ent);
-  UnitTurn turn(P, nu_scan, off, queue, reinterpret_cast<int32_t*>(smem + BwdLds::Next));
+  UnitTurn<kQueue> turn(P, u_rec, nu_scan, off, queue, reinterpret_cast<int32_t*>(smem + BwdLds::Next));
   const int pos0 = turn.pos0;
-  for (; turn.unit >= 0; turn.advance()) {
+  for (; turn.unit >= 0; turn.advance()) {  // (once without the queue)
   const UnitRec U = turn.record(u_rec);
   constexpr int kRow = BwdLds::Row;
   const int j = U.j, ne = U.ne, tok0 = U.tok0, blen = U.blen;
   int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));  // keeps what depends on it inside the loop over units
+  if constexpr (kQueue) asm volatile("" : "+v"(tid));  // keeps what depends on it inside the loop over units
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, qh = lane >> 5, rb = wave >> 1, kb = wave & 1;
   const uint32_t hbase = (uint32_t)(j * P.g), row_bytes = (uint32_t)P.hkv * (kD * 2);
@@ -558,7 +565,7 @@ k_bwd_tiled(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
   // unit partial: [u][0 = dK, 1 = dV][key][d] fp32, summed by k_bwd_dkv_reduce in unit order
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) {
-    float* outk = dkv_part + (size_t)turn.unit * 2 * 64 * kD + 64 * kb + 32 * cb + col;
+    float* outk = dkv_part + (size_t)(kQueue ? turn.unit : (int)blockIdx.x) * 2 * 64 * kD + 64 * kb + 32 * cb + col;
     float* outv = outk + 64 * kD;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -632,14 +639,14 @@ struct PipeUnit : UnitRec {
 
 // One role of the pipeline (kS: an S-wave, else an A-wave).  Both roles run this same skeleton, so they execute the same
 // sequence of block-wide barriers: every loop bound below depends only on the unit, never on the role or the lane.
-template <bool kWin, bool kWide, bool kS>
+template <bool kWin, bool kWide, bool kS, bool kQueue>
 __device__ __forceinline__ void
-pipe_role(const Problem& P, const PipeUnit& U, UnitTurn& turn, unsigned char* smem, const int sw, const bf16_t* __restrict__ Q,
+pipe_role(const Problem& P, const PipeUnit& U, UnitTurn<kQueue>& turn, unsigned char* smem, const int sw, const bf16_t* __restrict__ Q,
           const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ dO,
           const float2* __restrict__ stats, const int2* __restrict__ qent, bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
   int32_t* ent = reinterpret_cast<int32_t*>(smem + PipeLds::Ent);
   int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));  // keeps what depends on it inside the loop over units: carried round it, it spills
+  if constexpr (kQueue) asm volatile("" : "+v"(tid));  // keeps what depends on it inside the loop over units: carried round it, it spills
   const int lane = tid & 63;
   int col = lane & 31, qh = lane >> 5;
   const int j = U.j, tok0 = U.tok0, blen = U.blen;
@@ -1012,7 +1019,7 @@ pipe_role(const Problem& P, const PipeUnit& U, UnitTurn& turn, unsigned char* sm
     // unit partial: [u][0 = dK, 1 = dV][key][d] fp32, summed by k_bwd_dkv_reduce in unit order
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
-      float* outk = dkv_part + (size_t)U.number * 2 * 128 * kD + 32 * cb + col;
+      float* outk = dkv_part + (size_t)(kQueue ? U.number : (int)blockIdx.x) * 2 * 128 * kD + 32 * cb + col;
       float* outv = outk + 128 * kD;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -1024,7 +1031,7 @@ pipe_role(const Problem& P, const PipeUnit& U, UnitTurn& turn, unsigned char* sm
   }
 }
 
-template <bool kWin, bool kWide>
+template <bool kWin, bool kWide, bool kQueue>
 __global__ void __launch_bounds__(512, 1)
 k_bwd_pipe128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
               const bf16_t* __restrict__ dO, const float2* __restrict__ stats, const UnitRec* __restrict__ u_rec,
@@ -1032,15 +1039,17 @@ k_bwd_pipe128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
               bf16_t* __restrict__ dqpart, float* __restrict__ dkv_part, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV,
               UnitQueue queue) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
-  UnitTurn turn(P, nu_scan, off, queue, reinterpret_cast<int32_t*>(smem + PipeLds::Next));
+  UnitTurn<kQueue> turn(P, u_rec, nu_scan, off, queue, reinterpret_cast<int32_t*>(smem + PipeLds::Next));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (; turn.unit >= 0; turn.advance()) {
+  if (turn.unit < 0) return;
+  do {
     const PipeUnit U = {turn.record(u_rec), turn.pos0, turn.unit};
     if (wave < 4)
       pipe_role<kWin, kWide, true>(P, U, turn, smem, wave, Q, K, V, dO, stats, qent, dqpart, dkv_part, dK, dV);
     else
       pipe_role<kWin, kWide, false>(P, U, turn, smem, wave - 4, Q, K, V, dO, stats, qent, dqpart, dkv_part, dK, dV);
-  }
+    if constexpr (kQueue) turn.advance();
+  } while (kQueue && turn.unit >= 0);  // (without the queue no loop, which a condition on the unit alone would leave)
 }
 
 // dK / dV of the lists whose units left partial sums: the sum runs in unit order, four units in flight.  A piece of this work is
@@ -1200,32 +1209,34 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
   const bool b128 = P0.bk == 128;
   const bool win = P0.window > 0;
   const bool wide = rows_are_wide((int64_t)P0.T * P0.hq);
-  auto pick = [&](auto* w1d1, auto* w1d0, auto* w0d1, auto* w0d0) { return win ? (wide ? w1d1 : w1d0) : (wide ? w0d1 : w0d0); };
-  auto* main_kernel = b128 ? pick(k_bwd_pipe128<true, true>, k_bwd_pipe128<true, false>, k_bwd_pipe128<false, true>,
-                                  k_bwd_pipe128<false, false>)
-                           : pick(k_bwd_tiled<true, true>, k_bwd_tiled<true, false>, k_bwd_tiled<false, true>,
-                                  k_bwd_tiled<false, false>);
   const int main_threads = b128 ? 512 : 256;
   const int main_lds = b128 ? PipeLds::Bytes : BwdLds::Bytes;
+  const int passes = (P0.hkv + heads_per_pass - 1) / heads_per_pass;
+  const int64_t pass_units = units_bound(heads_per_pass, P0.b_cap, P0.T, P0.topk, P0.unit);
+  // (Q of 4 GB and more: units by the hundred a slot)
+  const bool queued = lists_per_pass == 0 && passes <= kQueuePasses && pass_units >= kQueueMinUnits && !wide &&
+                      (b128 || (int64_t)P0.T * P0.hq * P0.topk <= kQueueMaxRows64);
+  int32_t* const queue = queued ? reinterpret_cast<int32_t*>(dkv_part + (size_t)(pass_units - 1) * 2 * P0.bk * kD) : nullptr;
+  const bool ordered = queued && passes == 1 && pass_units <= kQueueUnits;
+  auto form = [&](auto* keys64, auto* keys128) { return b128 ? keys128 : keys64; };
+  auto* main_kernel = win ? queued ? form(k_bwd_tiled<true, false, true>, k_bwd_pipe128<true, false, true>)
+                            : wide ? form(k_bwd_tiled<true, true, false>, k_bwd_pipe128<true, true, false>)
+                                   : form(k_bwd_tiled<true, false, false>, k_bwd_pipe128<true, false, false>)
+                          : queued ? form(k_bwd_tiled<false, false, true>, k_bwd_pipe128<false, false, true>)
+                            : wide ? form(k_bwd_tiled<false, true, false>, k_bwd_pipe128<false, true, false>)
+                                   : form(k_bwd_tiled<false, false, false>, k_bwd_pipe128<false, false, false>);
   {
-    static std::atomic<uint64_t> ready[8];
+    static std::atomic<uint64_t> ready[16];
     static std::atomic<uint64_t> ready_reduce;
-    hipError_t e = allow_dynamic_lds((const void*)main_kernel, main_lds, ready[win + 2 * wide + 4 * b128]);
+    hipError_t e = allow_dynamic_lds((const void*)main_kernel, main_lds, ready[win + 2 * wide + 4 * b128 + 8 * queued]);
     if (e == hipSuccess)
       e = allow_dynamic_lds((const void*)(k_bwd_dq_reduce<kBurstRows, kBurstThreads>), reduce_lds(kBurstThreads, kBurstRows, 1, false),
                             ready_reduce);
     if (e != hipSuccess) return e;
   }
-  const int passes = (P0.hkv + heads_per_pass - 1) / heads_per_pass;
-  const int64_t pass_units = units_bound(heads_per_pass, P0.b_cap, P0.T, P0.topk, P0.unit);
-  int32_t* queue = nullptr;
-  if (lists_per_pass == 0 && passes <= kQueuePasses && pass_units >= kQueueMinUnits &&
-      (b128 || (int64_t)P0.T * P0.hq * P0.topk <= kQueueMaxRows64))
-    queue = reinterpret_cast<int32_t*>(dkv_part + (size_t)(pass_units - 1) * 2 * P0.bk * kD);
-  const bool ordered = queue != nullptr && passes == 1 && pass_units <= kQueueUnits;
   {
     ProfScope ps(KID_BWD_DELTA, st);
-    hipLaunchKernelGGL(k_bwd_delta, dim3((P0.T + kDeltaTokens - 1) / kDeltaTokens + (queue != nullptr), (P0.hkv + kDeltaKv - 1) / kDeltaKv),
+    hipLaunchKernelGGL(k_bwd_delta, dim3((P0.T + kDeltaTokens - 1) / kDeltaTokens + queued, (P0.hkv + kDeltaKv - 1) / kDeltaKv),
                        dim3(256), 0, st, P0, (const bf16_t*)O,
                        (const bf16_t*)dO, LSE, (float2*)delta, G.gate, G.dgate, p.u_rec, p.u_nu, queue, ordered);
   }
@@ -1243,10 +1254,10 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
       const int64_t bound = units_bound(P.nj, P.b_cap, P.T, P.topk, P.unit);
       const unsigned units_max =
           (unsigned)(lists_per_pass > 0 ? min(bound, (int64_t)step * ((P.T + P.unit - 1) / P.unit)) : bound);
-      const UnitQueue turns = {queue != nullptr ? queue + j0 / heads_per_pass : nullptr, ordered ? queue + kQueuePasses : nullptr};
+      const UnitQueue turns = {queued ? queue + j0 / heads_per_pass : nullptr, ordered ? queue + kQueuePasses : nullptr};
       const unsigned slots = b128 ? 256 : 512;  // workgroups that the chip holds
       { ProfScope ps(KID_BWD_MAIN, st);
-      hipLaunchKernelGGL(main_kernel, dim3(queue != nullptr ? min(units_max, slots) : units_max), dim3(main_threads), main_lds, st, P, (const bf16_t*)Q,
+      hipLaunchKernelGGL(main_kernel, dim3(queued ? min(units_max, slots) : units_max), dim3(main_threads), main_lds, st, P, (const bf16_t*)Q,
                          (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, (const float2*)delta, p.u_rec, p.u_nu,
                          p.off, p.qent, (bf16_t*)dqpart, dkv_part, (bf16_t*)dK, (bf16_t*)dV, turns); }
       const int lists = P.l1 - P.l0, per = max(1, min(64, lists * (P.bk / 4) / 4096));

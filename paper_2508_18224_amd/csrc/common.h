@@ -324,17 +324,18 @@ __device__ __forceinline__ bf16x8 load_frag(__amdgpu_buffer_rsrc_t b, uint32_t o
   return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0));
 }
 
-// The unit of this workgroup of a forward main kernel, or false when the launch (sized by an upper bound) has no unit left
+// The unit of this workgroup of a main kernel, or false when the launch (sized by an upper bound) has no unit left
 // for it.  By number, the record is requested before the unit count is known: the two loads are independent and every
-// index up to the bound is allocated.  With the heads in turn (see units_in_turn) consecutive workgroups take the same place among the
+// index up to the bound is allocated.  With the heads in turn (the forward's, see units_in_turn) consecutive workgroups take the same place among the
 // units of each of the pass's heads, and the launch has room for as many units as one head can have, for each.
 // pos0 = the first list position of the pass's KV heads (partial rows are relative to it).
+template <bool kInTurn>
 __device__ __forceinline__ bool load_unit(const Problem& P, const UnitRec* __restrict__ u_rec,
                                           const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off,
                                           UnitRec& U, int& pos0) {
   pos0 = P.j0 > 0 ? off[P.j0 * P.b_cap] : 0;
   int u, end;
-  if (P.in_turn) {
+  if (kInTurn && P.in_turn) {
     const int i = (int)(blockIdx.x / (unsigned)P.nj), l = (P.j0 + (int)blockIdx.x - i * P.nj) * P.b_cap;
     u = nu_scan[l] + i;
     end = nu_scan[l + P.b_cap];

@@ -149,7 +149,7 @@ k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   int32_t* cnts = reinterpret_cast<int32_t*>(smem + kF64Cnts);
   UnitRec U;
   int pos0;
-  if (!load_unit(P, u_rec, nu_scan, off, U, pos0)) return;
+  if (!load_unit<true>(P, u_rec, nu_scan, off, U, pos0)) return;
   const int j = U.j, e0 = U.e0, ne_all = U.ne, tok0 = U.tok0, blen = U.blen;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, qh = lane >> 5;
   const int crow = lane >> 4, cchunk = (lane & 15) * 8;  // coalesced layout: 16 lanes per row, 4 rows per access
@@ -342,7 +342,7 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
   int32_t* cnts = reinterpret_cast<int32_t*>(smem + kF128Cnts);
   UnitRec U;
   int pos0;
-  if (!load_unit(P, u_rec, nu_scan, off, U, pos0)) return;
+  if (!load_unit<true>(P, u_rec, nu_scan, off, U, pos0)) return;
   const int j = U.j, e0 = U.e0, ne_all = U.ne, tok0 = U.tok0, blen = U.blen;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int col = lane & 31, qh = lane >> 5;                 // not const: see the top of the tile loop
