@@ -104,7 +104,6 @@ static Problem make_problem(const nsa_sel_shape* s, const IndexLayout& L) {
   P.l0 = 0;
   P.l1 = L.n_lists;
   P.units_max = L.units_max;
-  P.in_turn = units_in_turn(P.T, P.hq, P.g) ? 1 : 0;
   P.scale = s->scale > 0.f ? s->scale : 0.08838834764831845f;  // 1/sqrt(128)
   return P;
 }

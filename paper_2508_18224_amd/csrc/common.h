@@ -110,7 +110,6 @@ struct Problem {
   int32_t dense;   // 1: the dense forward path is on (the index carries dense flags and tables)
   int32_t t_cap;   // stride of the per-(tile, kv head) dense tables
   int32_t j0, nj;  // KV heads [j0, j0 + nj) handled by this launch (all of them unless the workspace is capped)
-  int32_t in_turn; // forward main kernels: the heads' units in turn (units_in_turn)
   int32_t l0, l1;  // lists [l0, l1): those of the heads, or a range of one head's (see launch_bwd)
   int32_t units_max;  // last index the table of work units has room for
   float scale;
@@ -182,14 +181,26 @@ inline int64_t units_bound(int nj, int b_cap, int T, int topk, int unit) {
   return (int64_t)nj * b_cap + (int64_t)nj * T * topk / unit + 1;
 }
 
-// Whether the forward main kernels take the first units of all KV heads, then the second ones and so on, instead of head by
-// head.  A head's first lists are its longest (the sink's, then the early blocks'), and those of the last head would otherwise
-// start last: at 8192 tokens x 32 heads, g = 1, they ran alone for a seventh of the kernel.  Measured head by head / in turn, us:
-// g = 1, 8192 tokens x 32 heads 348 / 298, with 128-token blocks 251 / 231, 12288 x 32 520 / 505, but 24576 x 16 523 / 551, 16384 x 32 707 /
-// 733, 40000 x 16 849 / 960; g = 4, 4096 x 32 63 / 55, 8192 x 32 217 / 183, 16384 x 32 493 / 423, with 128-token blocks 317 / 310,
-// 32768 x 8 262 / 253, but 24576 x 32 772 / 793, 65536 x 32 2064 / 2250; g = 8, 6000 x 64 277 / 236, 131072 x 64 7800 / 9900.  On long
-// inputs the tail is a small part, and gathers from one head at a time are the faster ones.
-inline bool units_in_turn(int T, int hq, int g) { return (int64_t)T * hq <= (g == 1 ? 1 << 18 : 1 << 19); }
+// Whether the forward main kernels take the first units of all `heads` KV heads of a pass, then the second ones and so on, instead of
+// head by head.  Causal, a head's first lists are its longest (the sink's, then the early blocks'), and those of the last head would
+// otherwise start last: at 8192 tokens x 32 heads, g = 1, they ran alone for a seventh of the kernel.  Against that, head by head every XCD
+// has one head's Q in its L2; in turn it has that of the heads whose workgroups it is dealt, few where their number is a multiple of eight
+// and all of them where it is odd.  Measured head by head -> in turn, us (top-k 16, tokens x KV heads):
+//   g = 1   8192 x 32 with a sink 331 -> 309, without one 339 -> 297; 16000 x 16 316 -> 322; 30000 x 8 282 -> 293
+//           all keys: 4096 x 16 95 -> 90, 8192 x 16 155 -> 156, x 24 229 -> 225, x 32 311 -> 325, 4096 x 64 304 -> 322
+//           other numbers of heads: 8192 x 20 186 -> 184, 26360 x 5 152 -> 166, 6660 x 31 226 -> 264, 5843 x 30, all keys, 198 -> 235
+//   g = 2   8192 x 32 480 -> 432, 9000 x 24 -8 %, 11000 x 16 -5 %, 16000 x 16 507 -> 537, 16384 x 8 -9 %, 28000 x 8 +2 %, 24000 x 4 -6 %
+//           all keys: 16384 x 8 -8 %, 14500 x 16 +6 %; other numbers: 8849 x 21 298 -> 338, 24815 x 6 279 -> 302
+//   g >= 4  8192 x 16 444 -> 354, g = 5, 12000 x 8 419 -> 347, g = 7, 16000 x 4 412 -> 386, 12729 x 6 274 -> 260, 34739 x 2 286 -> 262, 65536 x 2
+//           526 -> 568; all keys: 16384 x 8 574 -> 562, 7887 x 10 333 -> 379, 5688 x 12 368 -> 390; other numbers: 6523 x 19 +4 %, 6416 x 14 +4 %, 4323 x 15 194 -> 225
+//   128-token blocks, of which a head has half as many: g = 1, 8192 x 32 251 -> 230, x 28 232 -> 234; g = 2, 16384 x 8 198 -> 181, 4920 x 41
+//           212 -> 190, 28000 x 8 +1 %; g = 4, 8192 x 16 264 -> 238, 6667 x 13 88 -> 81, 10936 x 11 301 -> 282; all keys: 7708 x 19 225 -> 233
+inline bool units_in_turn(int T, int heads, int hq, int g, int bk, bool causal) {
+  const bool even = heads % (g == 1 || !causal ? 8 : 4) == 0 || (g >= 2 && heads == 4) || (causal && g >= 4 && (heads == 2 || heads == 6)) ||
+                    (causal && g >= 2 && bk == 2 * kBlock && T <= 24576);
+  const int64_t rows = (int64_t)T * hq, near = (int64_t)(g < 4 ? g : 4) << 17;
+  return even && T <= 40960 && (rows <= near || (causal && T <= 12288 && rows <= min(2 * near, (int64_t)1 << 19)));
+}
 
 // Work units whose dK/dV sums the smallest backward workspace holds: those of one KV head at units of at least kMinUnit.  The
 // smaller units of tiny inputs have more; where they do not fit, the backward goes through the head's lists in ranges.  One
@@ -335,7 +346,7 @@ __device__ __forceinline__ bool load_unit(const Problem& P, const UnitRec* __res
                                           UnitRec& U, int& pos0) {
   pos0 = P.j0 > 0 ? off[P.j0 * P.b_cap] : 0;
   int u, end;
-  if (kInTurn && P.in_turn) {
+  if constexpr (kInTurn) {
     const int i = (int)(blockIdx.x / (unsigned)P.nj), l = (P.j0 + (int)blockIdx.x - i * P.nj) * P.b_cap;
     u = nu_scan[l] + i;
     end = nu_scan[l + P.b_cap];

@@ -137,7 +137,7 @@ static_assert(2 * kF64Bytes <= 160 * 1024, "two workgroups of the 64-key forward
 // moves at 7.0 TB/s.  Rows move by branch-free buffer instructions with the row's place worked out once per tile and lane: with
 // branches around the stores and 64-bit addresses per access every wait for the next rows also drained the stores and the tile
 // cost a third more vector instructions (2.14 -> 2.04 ms; at 8192 tokens, g = 1: 367 -> 330 us).
-template <bool kWide>
+template <bool kWide, bool kInTurn>
 __global__ void __launch_bounds__(256, 2)  // two workgroups per CU: 256 registers per wavefront
 k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
            const UnitRec* __restrict__ u_rec, const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off,
@@ -149,7 +149,7 @@ k_fwd_main(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   int32_t* cnts = reinterpret_cast<int32_t*>(smem + kF64Cnts);
   UnitRec U;
   int pos0;
-  if (!load_unit<true>(P, u_rec, nu_scan, off, U, pos0)) return;
+  if (!load_unit<kInTurn>(P, u_rec, nu_scan, off, U, pos0)) return;
   const int j = U.j, e0 = U.e0, ne_all = U.ne, tok0 = U.tok0, blen = U.blen;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, qh = lane >> 5;
   const int crow = lane >> 4, cchunk = (lane & 15) * 8;  // coalesced layout: 16 lanes per row, 4 rows per access
@@ -329,7 +329,7 @@ constexpr int kF128Cnts = kF128Epos + kMaxUnit * 2;
 constexpr int kF128Bytes = kF128Cnts + (kMaxUnit / 64) * 4;
 static_assert(kF128Bytes <= 160 * 1024, "forward 128-key tile set must fit the CU's LDS");
 
-template <bool kWide>
+template <bool kWide, bool kInTurn>
 __global__ void __launch_bounds__(64 * kWaves128)
 k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
               const UnitRec* __restrict__ u_rec, const int32_t* __restrict__ nu_scan, const int32_t* __restrict__ off,
@@ -342,7 +342,7 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
   int32_t* cnts = reinterpret_cast<int32_t*>(smem + kF128Cnts);
   UnitRec U;
   int pos0;
-  if (!load_unit<true>(P, u_rec, nu_scan, off, U, pos0)) return;
+  if (!load_unit<kInTurn>(P, u_rec, nu_scan, off, U, pos0)) return;
   const int j = U.j, e0 = U.e0, ne_all = U.ne, tok0 = U.tok0, blen = U.blen;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int col = lane & 31, qh = lane >> 5;                 // not const: see the top of the tile loop
@@ -1017,8 +1017,9 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
                       const GateArgs& G, hipStream_t st) {
   IndexPtrs p = index_ptrs(L, const_cast<void*>(index_ws));
   const bool wide = rows_are_wide((int64_t)P0.T * P0.hq);
-  auto* main64 = wide ? k_fwd_main<true> : k_fwd_main<false>;
-  auto* main128 = wide ? k_fwd_main128<true> : k_fwd_main128<false>;
+  const bool in_turn = units_in_turn(P0.T, heads_per_pass, P0.hq, P0.g, P0.bk, P0.causal != 0);  // (far fewer rows than the wide forms are for)
+  auto* main64 = in_turn ? k_fwd_main<false, true> : wide ? k_fwd_main<true, false> : k_fwd_main<false, false>;
+  auto* main128 = in_turn ? k_fwd_main128<false, true> : wide ? k_fwd_main128<true, false> : k_fwd_main128<false, false>;
   if (P0.dense) {
     static std::atomic<uint64_t> ready_dense;
     const hipError_t e = allow_dynamic_lds((const void*)k_fwd_dense_merge, 80 * 1024, ready_dense);
@@ -1033,9 +1034,10 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
     if (e != hipSuccess) return e;
   }
   {
-    static std::atomic<uint64_t> ready[4];
-    hipError_t e = P0.bk == 128 ? allow_dynamic_lds((const void*)main128, kF128Bytes, ready[2 + wide])
-                                : allow_dynamic_lds((const void*)main64, kF64Bytes, ready[wide]);
+    static std::atomic<uint64_t> ready[6];
+    const int form = in_turn ? 2 : wide;
+    hipError_t e = P0.bk == 128 ? allow_dynamic_lds((const void*)main128, kF128Bytes, ready[3 + form])
+                                : allow_dynamic_lds((const void*)main64, kF64Bytes, ready[form]);
     if (e != hipSuccess) return e;
   }
   // KV heads are processed heads_per_pass at a time; every pass reuses the same partial buffers (the lists of
@@ -1047,7 +1049,7 @@ hipError_t launch_fwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
     P.l0 = j0 * P.b_cap;
     P.l1 = (j0 + P.nj) * P.b_cap;
     // upper bound of the work units of the pass (the real count is only known on the device)
-    const unsigned units_max = (unsigned)(P.in_turn ? P.nj * units_bound(1, P.b_cap, P.T, P.topk, P.unit)
+    const unsigned units_max = (unsigned)(in_turn ? P.nj * units_bound(1, P.b_cap, P.T, P.topk, P.unit)
                                                     : units_bound(P.nj, P.b_cap, P.T, P.topk, P.unit));
     if (P.bk == 128) {
       ProfScope ps(KID_FWD_MAIN, st);
