@@ -60,12 +60,17 @@ constexpr int kQueueUnits = 2 * kBlock * kD - kQueuePasses;                     
 // so long a kernel, and what the idle slots gave up the others may have had as clock rate (the chip runs these kernels at 1.8 of its 2.4
 // GHz).  128-token blocks, one workgroup a compute unit: window of 512 at 32768 tokens 1455 -> 1123, 8192 x 32, g = 1 532 -> 487,
 // 16384 x 16, g = 2 496 -> 464, 65536 x 32, g = 4 3240 -> 3188.  Fewer units than 2048 are a few a slot: 2000 x 32, g = 4 117 -> 118.
+// With all keys visible the lists are alike.  64-token blocks, lists that fit one unit (top-k x block entries below 3/4 of it): no long
+// ones to start early, 31821 x 28, g = 2 1644 -> 1684, 15075 x 66, g = 2 1820 -> 1852, so none there; with full units and remainders 16384 x 32, g = 4
+// 1049 -> 993, 12000 x 32, top-k 24 1249 -> 1113, 25530 x 12, g = 2 639 -> 605, but packed short ones 302 -> 307 and 336 -> 343.
 constexpr int kQueueMinUnits = 2048;
 constexpr int64_t kQueueMaxRows64 = (int64_t)3 << 23;  // (token, query head, column) triples
 
-// Units in order of their length class, longest first: more than 1/2, 1/4 and less of a full unit.  A thread takes a run of units,
-// so that a class stays in the order of the KV heads, whose statistics the main kernels find in L2; the lengths are read once, 16
-// at a time, and kept as classes of two bits.
+// Units in order of their length class, longest first: more than 3/8, 3/16 and less of a full unit.  A thread takes a run of units,
+// so that a class stays in the order of the KV heads, whose Q, dO and statistics the main kernels find in L2; the lengths are read once,
+// 16 at a time, and kept as classes of two bits.  Lists of like length (no causal mask) have about top-k x block entries, for units of
+// a power of two mostly a power of two of a unit too: the classes part where such lists don't, at 1/2 and 1/4 they went through the heads
+// once for each class (32768 tokens, g = 4, all keys: 1855 us with a workgroup a unit, 1980 so).
 __device__ __forceinline__ void prepare_queue(const Problem& P, const UnitRec* __restrict__ u_rec, const int32_t* __restrict__ nu_scan,
                                               int32_t* __restrict__ queue, bool ordered) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -85,7 +90,7 @@ __device__ __forceinline__ void prepare_queue(const Problem& P, const UnitRec* _
     for (int i = 0; i < kB; ++i) ne[i] = u_rec[min(first + b * kB + i, n - 1)].ne;
 #pragma unroll
     for (int i = 0; i < kB; ++i) {
-      const uint32_t c = 2 * ne[i] > P.unit ? 0 : 4 * ne[i] > P.unit ? 1 : 2;
+      const uint32_t c = 8 * ne[i] > 3 * P.unit ? 0 : 16 * ne[i] > 3 * P.unit ? 1 : 2;
       cls[b] |= c << (2 * i);
       if (b * kB + i < mine) counts += (uint64_t)1 << (21 * c);
     }
@@ -1215,7 +1220,7 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
   const int64_t pass_units = units_bound(heads_per_pass, P0.b_cap, P0.T, P0.topk, P0.unit);
   // (Q of 4 GB and more: units by the hundred a slot)
   const bool queued = lists_per_pass == 0 && passes <= kQueuePasses && pass_units >= kQueueMinUnits && !wide &&
-                      (b128 || (int64_t)P0.T * P0.hq * P0.topk <= kQueueMaxRows64);
+                      (b128 || ((int64_t)P0.T * P0.hq * P0.topk <= kQueueMaxRows64 && (P0.causal || 4 * P0.topk * P0.bk >= 3 * P0.unit)));
   int32_t* const queue = queued ? reinterpret_cast<int32_t*>(dkv_part + (size_t)(pass_units - 1) * 2 * P0.bk * kD) : nullptr;
   const bool ordered = queued && passes == 1 && pass_units <= kQueueUnits;
   auto form = [&](auto* keys64, auto* keys128) { return b128 ? keys128 : keys64; };

@@ -61,6 +61,51 @@ def test_units_from_the_queue_are_those_of_a_workgroup_each(lengths, hq, hkv, to
             assert torch.equal(a.view(torch.int16), b.view(torch.int16)), name
 
 
+def _queue(attn, w, lengths, block):
+    """(counters, order) the last backward left in the room of the last unit's sums; None where it had no queue (and 0x7F was filled in)."""
+    room = attn.bwd_ws[-2 * block * 512:].view(torch.int32).cpu().numpy()
+    return None if (room[:64] == 0x7F7F7F7F).all() else (room[:64], room[64:])
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,topk,block,causal,queued", [
+    ([4096], 8, 8, 16, 64, True, True), ([3000, 1, 64, 1500, 531], 16, 8, 16, 64, True, True), ([4096], 16, 8, 16, 128, True, True),
+    ([8192], 8, 8, 8, 64, False, True),      # lists of about two units of 256
+    ([8192], 8, 8, 2, 64, False, False),     # of half a unit: all alike and one unit each
+    ([8192], 8, 8, 2, 64, True, False)])     # (too few units)
+def test_order_of_the_units(lengths, hq, hkv, topk, block, causal, queued):
+    """Long units first, in classes that part where lists of like length don't, each class by number."""
+    w = wl.realise(wl.Workload("order", lengths, hq=hq, hkv=hkv, topk=topk, sink=causal, seed=4, block=block, causal=causal))
+    case = Case(w)
+    attn = nsa.SelAttention(w.total_tokens, hq, hkv, topk, nseq=len(lengths), block=block, unit=256, causal=causal)
+    o, lse = attn.forward(case.q, case.k, case.v, case.idx, case.cu)
+    attn.bwd_ws.fill_(0x7F)
+    attn.backward(case.q, case.k, case.v, o, lse, case.do, case.cu)
+    found = _queue(attn, w, lengths, block)
+    assert (found is not None) == queued
+    if not queued:
+        return
+    cnt = attn.index_arrays()[0].ravel()
+    units = [min(256, n - at) for n in map(int, cnt) for at in range(0, n, 256)]
+    slots = 512 if block == 64 else 256
+    assert found[0][0] == len(units) or found[0][0] >= len(units) - slots  # every workgroup drew until nothing was left
+    want = sorted(range(len(units)), key=lambda u: (units[u] * 8 <= 3 * 256) + (units[u] * 16 <= 3 * 256))
+    assert list(found[1][:len(units)]) == want
+
+
+def test_all_keys_by_number():
+    """32768 tokens, 32 heads, all keys: lists of half a unit, which the length classes once split down the middle."""
+    w = wl.Workload("like", [32768], hq=32, hkv=8, topk=16, causal=False)
+    attn = nsa.SelAttention(32768, 32, 8, 16, causal=False)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, do = (torch.randn(32768, 32, 128, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    k, v = (torch.randn(32768, 8, 128, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    idx = torch.rand(32768, 8, 512, generator=gen, device="cuda").argsort(dim=2)[..., :16].int().contiguous()
+    o, lse = attn.forward(q, k, v, idx)
+    attn.bwd_ws.fill_(0x7F)
+    attn.backward(q, k, v, o, lse, do)
+    assert _queue(attn, w, [32768], 64) is None
+
+
 def test_heads_in_turn_where_their_number_suits():
     """A number of KV heads that is no multiple of eight costs the forward's main kernel no more a head than one that is (in turn the XCDs
     would gather from the Q of all of them: 1.3 times as long)."""
