@@ -153,6 +153,20 @@ __device__ __forceinline__ float piece_values_and_next_scores(const uint32_t (&k
   return m;
 }
 
+// The same for the last piece, after which no scores are wanted.
+__device__ __forceinline__ void piece_values(const uint32_t (&vaddr)[2][4], float c2, float mc, const f32x16 (&cur)[2], float& l_run,
+                                             f32x16 (&oacc)[4]) {
+  float l = 0.f;
+#pragma unroll
+  for (int sp = 0; sp < 4; ++sp) {
+    __builtin_amdgcn_sched_barrier(0);
+    const bf16x8 pf = piece_probabilities(cur, sp, c2, mc, l);
+#pragma unroll
+    for (int db = 0; db < 4; ++db) oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(value_frag(vaddr, sp, db), pf, oacc[db], 0, 0, 0);
+  }
+  l_run += l + __shfl_xor(l, 32);
+}
+
 // Q's fragments are there.  In front of a loop whose loads go to LDS by assembly: the compiler does not count those and would
 // wait inside the loop for as many accesses as Q's loads were, which are then the ones in flight for the next piece.
 __device__ __forceinline__ void await_rows(bf16x8 (&qf)[8]) {

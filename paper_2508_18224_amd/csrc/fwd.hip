@@ -531,8 +531,9 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 // Phase 2 is bound by memory (65536 tokens, g = 4: 8.9 GB in 1.62 ms for the whole kernel), phase 1 by vector instructions: a wavefront's
 // piece takes 1000 clocks of them and 1024 of the matrix pipe, and two wavefronts share a SIMD.  One pair of tiles, with two barriers a
 // piece and the S product, softmax and PV product one after the other, took 1.54 instead of 1.39 ms with 9 of 16 columns dense at g
-// = 7, 65536 tokens, and 530 instead of 510 us for a window of 512 at 32768; there every access of the piece loop also waited for the loads just
-// sent on their way (see await_rows).  Three workgroups per CU leave 168 registers, 30 of them spilled.
+// = 7, 65536 tokens, and 520 instead of 494 us for a window of 512 at 32768; there every access of the piece loop also waited for the loads just
+// sent on their way (see await_rows).  The last piece goes without scores of a next one, which tiles of one or two pieces paid for with
+// what the order gained them: one piece, 32768 tokens, g = 4, own block 310 us with them, 290 without; a window of 100 139 and 135.  Three workgroups per CU leave 168 registers, 30 of them spilled.
 // LDS: unpadded, turned rows (see row_turn): 0.55 -> 0.51 ms for a window of
 // 512 at 32768 tokens, 6.3 -> 6.1 ms at 131072, g = 8, against a turn of the low three bits, which left the transposing reads at a
 // quarter of their rate.  Phase 1's result takes the same area afterwards (place c ^ (r & 15)), and with a gate the gated rows.
@@ -625,7 +626,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
     const int srow = 4 * wave + (lane >> 4);
     const uint32_t row_bytes = (uint32_t)P.hkv * kDnRow;
     const uint32_t stage_off = srow * row_bytes + (((lane & 15) ^ row_turn(srow)) << 4);
-    // the rows of piece `step` of K or V, past the last piece none: they arrive as zeros
+    // the rows of piece `step` of K or V; of K past the last piece none: they arrive as zeros
     auto piece_of = [&](const bf16_t* X, int step) __attribute__((always_inline)) {
       const int first = __builtin_amdgcn_readlane(my_piece.x, min(step, nd - 1)), len = __builtin_amdgcn_readlane(my_piece.y, min(step, nd - 1));
       return buffer_of(X + ((size_t)first * P.hkv + j) * kD, step < nd ? (uint32_t)((len - 1) * P.hkv + 1) * kDnRow : 0u);
@@ -642,7 +643,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
     };
     stage(K, kDnK, 0);
     stage(V, kDnV, 0);
-    stage(K, kDnK + kPieceBytes, 1);
+    if (nd > 1) stage(K, kDnK + kPieceBytes, 1);
     // this wavefront's 32 rows of Q as B-operand fragments, kept for the whole tile
     const int r = row0 + col;                        // this lane's row
     const bool valid = r < rows_total;
@@ -673,20 +674,9 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
     f32x16 even[2], odd[2];
     piece_scores(kaddr, qf, even);
     float m = max_scores(even);
-    __syncthreads();  // every wavefront has read the first K
-    auto piece = [&](int step, f32x16 (&cur)[2], f32x16 (&next)[2], int side) __attribute__((always_inline)) {
-      // this piece's K tile has been read in the step before: K of the piece after the next flies there, V of the next to the
-      // other tile
-      const __amdgpu_buffer_rsrc_t kbuf = piece_of(K, step + 2), vbuf = piece_of(V, step + 1);
-      keep_addresses(kaddr, vaddr);
-      uint32_t ka[8], va[2][4];
-#pragma unroll
-      for (int s = 0; s < 8; ++s) ka[s] = kaddr[s] + (side ^ 1) * kPieceBytes;
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        va[0][d] = vaddr[0][d] + side * kPieceBytes;
-        va[1][d] = vaddr[1][d] + side * kPieceBytes;
-      }
+    if (nd > 1) __syncthreads();  // every wavefront has read the first K
+    // visibility and reference of piece `step`, whose scores are `cur`; returns what its exponents are taken against
+    auto prepare = [&](int step, f32x16 (&cur)[2]) __attribute__((always_inline)) {
       const unsigned long long members =
           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_mask, step) |
           (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_mask >> 32), step) << 32;
@@ -706,17 +696,50 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           for (int v = 0; v < 16; ++v) cur[mb][v] = sees ? cur[mb][v] : -INFINITY;
       }
       new_reference(row_max(m), sees, c2, slack, m_ref, l_run, oacc);
-      m = piece_values_and_next_scores(ka, va, qf, c2, m_ref == -INFINITY ? 0.f : m_ref * c2, cur, next, l_run, oacc,
-                                       [&](int i) __attribute__((always_inline)) {
-                                         if (i < 4) load(vbuf, kDnV + (side ^ 1) * kPieceBytes, i);
-                                         else if (i < 8) load(kbuf, kDnK + side * kPieceBytes, i - 4);
-                                       });
-      wait_loads();
-      __syncthreads();  // this piece has been read (after the last one: the K / V area is free), the next one is staged
+      return m_ref == -INFINITY ? 0.f : m_ref * c2;
     };
-    for (int step = 0; step < nd; step += 2) {
+    // every piece but the last: with the scores of the next one
+    auto piece = [&](int step, f32x16 (&cur)[2], f32x16 (&next)[2], int side) __attribute__((always_inline)) {
+      // this piece's K tile has been read in the step before: K of the piece after the next flies there, V of the next to the
+      // other tile
+      const __amdgpu_buffer_rsrc_t kbuf = piece_of(K, step + 2), vbuf = piece_of(V, step + 1);
+      keep_addresses(kaddr, vaddr);
+      uint32_t ka[8], va[2][4];
+#pragma unroll
+      for (int s = 0; s < 8; ++s) ka[s] = kaddr[s] + (side ^ 1) * kPieceBytes;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        va[0][d] = vaddr[0][d] + side * kPieceBytes;
+        va[1][d] = vaddr[1][d] + side * kPieceBytes;
+      }
+      const float mc = prepare(step, cur);
+      m = piece_values_and_next_scores(ka, va, qf, c2, mc, cur, next, l_run, oacc, [&](int i) __attribute__((always_inline)) {
+        if (i < 4) load(vbuf, kDnV + (side ^ 1) * kPieceBytes, i);
+        else if (i < 8) load(kbuf, kDnK + side * kPieceBytes, i - 4);
+      });
+      wait_loads();
+      __syncthreads();  // this piece has been read, the next one is staged
+    };
+    for (int step = 0; step + 1 < nd; step += 2) {
       piece(step, even, odd, 0);
-      if (step + 1 < nd) piece(step + 1, odd, even, 1);
+      if (step + 2 < nd) {
+        piece(step + 1, odd, even, 1);
+      } else {
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) even[mb] = odd[mb];
+      }
+    }
+    {
+      keep_addresses(kaddr, vaddr);
+      uint32_t va[2][4];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        va[0][d] = vaddr[0][d] + ((nd - 1) & 1) * kPieceBytes;
+        va[1][d] = vaddr[1][d] + ((nd - 1) & 1) * kPieceBytes;
+      }
+      const float mc = prepare(nd - 1, even);
+      piece_values(va, c2, mc, even, l_run, oacc);
+      __syncthreads();  // the K / V area is free
     }
     if (wave_on) {
       // the rows' dense result, normalised, and its log-sum-exp (natural log; -inf for a row that keeps none of the

@@ -48,6 +48,16 @@ def test_both_routes_match_the_oracle(name):
     _check(wl.realise(wl.small(name)), bwd=name in ("g4", "g1_varlen", "b128_g4"))
 
 
+@pytest.mark.parametrize("g,block,causal", [(1, 64, True), (3, 64, True), (5, 128, True), (8, 64, False), (2, 128, False)])
+def test_tiles_of_one_piece_and_more(g, block, causal):
+    """Every block kept by every token that sees it: causal, tiles of 1, 2, 3 .. pieces, the last one ragged; without the mask of an odd and
+    of an even number."""
+    print("case dense pieces", g, block, causal, flush=True)
+    lengths = [block * 5 - 3] if causal else [block * 3 - 7, block, 4 * block - 1]
+    w = wl.realise(wl.Workload("pieces", lengths, hq=2 * g, hkv=2, topk=8, causal=causal, block=block, sink=causal, seed=37))
+    _check(w, expect_dense=(1.0, 1.0))
+
+
 def test_sink_and_own_block_are_found_dense():
     """Sink + own block forced, 14 uniform picks: 2 of 16 slots of every late token, everything near the start."""
     print("case dense share", flush=True)
