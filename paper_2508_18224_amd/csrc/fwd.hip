@@ -512,7 +512,7 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 // gather and no partial row in memory at all.  One workgroup takes 128 rows (row = (token of the tile, head of the
 // group)) of one (tile, kv head):
 //   phase 1  keeps the rows' Q fragments in registers and walks the tile's dense blocks, 64 keys at a time (the index
-//            lists them as pieces) through LDS, with a running (reference, sum) per row and the output accumulated in
+//            lists them as pieces) through LDS, with a running (max, sum) per row and the output accumulated in
 //            registers across the pieces (dense_piece.h).  The 64-bit mask of a piece says which tokens of the tile keep its
 //            block; the others see none of its keys.  K and V go from memory straight to LDS, to two pairs of tiles: a
 //            piece's PV product runs beside the next piece's S product, and beside both the K after that and the next V arrive.  The
@@ -530,10 +530,10 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 // Tiles without a dense piece skip phase 1, so with the dense route on this kernel is the merge of every row.
 // Phase 2 is bound by memory (65536 tokens, g = 4: 8.9 GB in 1.62 ms for the whole kernel), phase 1 by vector instructions: a wavefront's
 // piece takes 1000 clocks of them and 1024 of the matrix pipe, and two wavefronts share a SIMD.  One pair of tiles, with two barriers a
-// piece and the S product, softmax and PV product one after the other, took 1.54 instead of 1.39 ms with 9 of 16 columns dense at g
-// = 7, 65536 tokens, and 520 instead of 494 us for a window of 512 at 32768; there every access of the piece loop also waited for the loads just
+// piece and the S product, softmax and PV product one after the other, took 1.55 instead of 1.40 ms with 9 of 16 columns dense at g
+// = 7, 65536 tokens, and 532 instead of 514 us for a window of 512 at 32768; there every access of the piece loop also waited for the loads just
 // sent on their way (see await_rows).  The last piece goes without scores of a next one, which tiles of one or two pieces paid for with
-// what the order gained them: one piece, 32768 tokens, g = 4, own block 310 us with them, 290 without; a window of 100 139 and 135.  Three workgroups per CU leave 168 registers, 30 of them spilled.
+// what the order gained them: one piece, 32768 tokens, g = 4, own block 310 us with them, 290 without; a window of 100 142 and 139.  Three workgroups per CU leave 168 registers, 30 of them spilled.
 // LDS: unpadded, turned rows (see row_turn): 0.55 -> 0.51 ms for a window of
 // 512 at 32768 tokens, 6.3 -> 6.1 ms at 131072, g = 8, against a turn of the low three bits, which left the transposing reads at a
 // quarter of their rate.  Phase 1's result takes the same area afterwards (place c ^ (r & 15)), and with a gate the gated rows.
@@ -663,8 +663,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
-    float m_ref = -INFINITY, l_run = 0.f;            // reference score and sum of the row (see new_reference)
-    const float slack = score_slack(c2);
+    float m_run = -INFINITY, l_run = 0.f;            // running maximum (raw scores) and sum of the row
     uint32_t kaddr[8], vaddr[2][4];
     piece_addresses(lds_address(smem + kDnK), lds_address(smem + kDnV), lane, kaddr, vaddr);
 
@@ -675,8 +674,8 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
     piece_scores(kaddr, qf, even);
     float m = max_scores(even);
     if (nd > 1) __syncthreads();  // every wavefront has read the first K
-    // visibility and reference of piece `step`, whose scores are `cur`; returns what its exponents are taken against
-    auto prepare = [&](int step, f32x16 (&cur)[2]) __attribute__((always_inline)) {
+    // visibility and maximum of piece `step`, whose scores are `cur` (see new_maximum)
+    auto prepare = [&](int step, f32x16 (&cur)[2], float& alpha) __attribute__((always_inline)) {
       const unsigned long long members =
           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_mask, step) |
           (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_mask >> 32), step) << 32;
@@ -695,8 +694,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
 #pragma unroll
           for (int v = 0; v < 16; ++v) cur[mb][v] = sees ? cur[mb][v] : -INFINITY;
       }
-      new_reference(row_max(m), sees, c2, slack, m_ref, l_run, oacc);
-      return m_ref == -INFINITY ? 0.f : m_ref * c2;
+      return new_maximum(row_max(m), sees, c2, m_run, alpha);
     };
     // every piece but the last: with the scores of the next one
     auto piece = [&](int step, f32x16 (&cur)[2], f32x16 (&next)[2], int side) __attribute__((always_inline)) {
@@ -712,8 +710,9 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
         va[0][d] = vaddr[0][d] + side * kPieceBytes;
         va[1][d] = vaddr[1][d] + side * kPieceBytes;
       }
-      const float mc = prepare(step, cur);
-      m = piece_values_and_next_scores(ka, va, qf, c2, mc, cur, next, l_run, oacc, [&](int i) __attribute__((always_inline)) {
+      float alpha;
+      const float mc = prepare(step, cur, alpha);
+      m = piece_values_and_next_scores(ka, va, qf, c2, mc, alpha, cur, next, l_run, oacc, [&](int i) __attribute__((always_inline)) {
         if (i < 4) load(vbuf, kDnV + (side ^ 1) * kPieceBytes, i);
         else if (i < 8) load(kbuf, kDnK + side * kPieceBytes, i - 4);
       });
@@ -737,8 +736,9 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
         va[0][d] = vaddr[0][d] + ((nd - 1) & 1) * kPieceBytes;
         va[1][d] = vaddr[1][d] + ((nd - 1) & 1) * kPieceBytes;
       }
-      const float mc = prepare(nd - 1, even);
-      piece_values(va, c2, mc, even, l_run, oacc);
+      float alpha;
+      const float mc = prepare(nd - 1, even, alpha);
+      piece_values(va, c2, mc, alpha, even, l_run, oacc);
       __syncthreads();  // the K / V area is free
     }
     if (wave_on) {
@@ -756,7 +756,7 @@ k_fwd_dense_merge(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restr
           *reinterpret_cast<uint2*>(od_lds + col * kDnRow + (((4 * db + a) ^ (col & 15)) << 4) + 8 * qh) = w;
         }
       if (qh == 0) {
-        const float mcf = (m_ref == -INFINITY) ? 0.f : m_ref * c2;
+        const float mcf = (m_run == -INFINITY) ? 0.f : m_run * c2;
         lse_lds[col] = l_run > 0.f ? (mcf + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f : -INFINITY;
       }
       wave_sync();

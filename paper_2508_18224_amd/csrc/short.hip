@@ -141,7 +141,7 @@ __device__ void short_histogram(const IndexGeom& G, int chunk, int j, const int3
 }
 
 // Dynamic LDS: per split two pairs of K and V tiles (afterwards the wavefronts' sums), then which of the workgroup's tokens keep a block (two
-// 64-bit words), then a (reference, sum) per row and split.
+// 64-bit words), then a (max, sum) per row and split.
 constexpr int kShortBlocks = 128;  // most blocks, and 64-key pieces, of a sequence
 template <int S>
 struct ShortLds {
@@ -155,7 +155,7 @@ struct ShortLds {
 // fall out here), and walks the 64-key pieces of the blocks that some token keeps: with S = 2 two wavefronts each take every other
 // piece of the sequence, and their sums are combined at the end.  A piece goes to the split of its place in the sequence, and one
 // that a row does not keep leaves the row's sums as they are, so a row's bits do not depend on its neighbours.
-// Rows that see nothing of a piece get the reference +inf there: their probabilities come out as exp2(-inf) = 0 without a select a score.
+// Rows that see nothing of a piece get +inf for a maximum there: their probabilities come out as exp2(-inf) = 0 without a select a score.
 // Where K or V of a piece holds an infinity or a NaN, that shows in rows that never selected it.  So when anything the workgroup is
 // about to write is not finite it walks its pieces again with selects, and with the sums of rows that do not keep a piece set back.
 template <int S, int KMAX>
@@ -288,7 +288,7 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
     steps = max(steps, count);
   }
 
-  const float c2 = P.scale * 1.4426950408889634f, slack = score_slack(c2);
+  const float c2 = P.scale * 1.4426950408889634f;
   const uint32_t k_lds = lds_address(smem) + split * 4 * kPieceBytes, v_lds = k_lds + 2 * kPieceBytes;
   uint32_t kaddr[8], vaddr[2][4];
   piece_addresses(k_lds, v_lds, lane, kaddr, vaddr);
@@ -336,17 +336,23 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
     lo = P.window > 0 ? max(tok - P.window + 1 - k0, 0) : 0;
   };
 
-  // what a piece's exponents are taken against; a row that sees only scores of -inf so far has no reference yet
-  auto offset_of = [&](bool sees, float ref) __attribute__((always_inline)) { return !sees ? INFINITY : ref == -INFINITY ? 0.f : ref * c2; };
-
   f32x16 oacc[4];
-  float m_ref = -INFINITY, l_run = 0.f;
+  float mc_run = -INFINITY, l_run = 0.f;
+  // The row's running maximum takes in that of a piece.  It is kept as the exponents use it, times c2 and rounded: where it stays, the sums
+  // stay to the bit, and over a sequence's 128 pieces nothing adds up (taken anew from the raw maximum, what the rounding leaves of m * c2
+  // went into the sums with every piece: LSE off by 1.7e-5 instead of 4e-6 over 8000 tokens with wide scores).
+  auto take_in = [&](float m, bool sees, float& alpha) __attribute__((always_inline)) {
+    const float mc = sees ? fmaxf(mc_run, m * c2) : mc_run;
+    alpha = mc == mc_run ? 1.f : __builtin_amdgcn_exp2f(mc_run - mc);
+    mc_run = mc;
+    return !sees ? INFINITY : mc == -INFINITY ? 0.f : mc;  // what the piece's exponents are taken against
+  };
   auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
-    m_ref = -INFINITY;
+    mc_run = -INFINITY;
     l_run = 0.f;
   };
   clear();
@@ -380,9 +386,10 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
       visible(q0, members, lo, lim);
       const bool sees = lim > lo;
       if (__builtin_amdgcn_ballot_w64(sees && (lim < 64 || lo > 0)) != 0ull) m = row_max(mask_scores(cur, lo, lim, qh));
-      new_reference(m, sees, c2, slack, m_ref, l_run, oacc);
+      float alpha;
+      const float mc = take_in(m, sees, alpha);
       members = members_of(q1);
-      m = piece_values_and_next_scores(ka, va, qf, c2, offset_of(sees, m_ref), cur, next, l_run, oacc,
+      m = piece_values_and_next_scores(ka, va, qf, c2, mc, alpha, cur, next, l_run, oacc,
                                        [&](int i) __attribute__((always_inline)) {
                                          if (i < kLoads) load(vbuf, v_lds + (side ^ 1) * kPieceBytes, i);
                                          else if (i < 2 * kLoads) load(kbuf, k_lds + side * kPieceBytes, i - kLoads);
@@ -419,16 +426,18 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
         const bool sees = lim > lo;
         f32x16 sacc[2];
         piece_scores(kaddr, qf, sacc);
-        new_reference(row_max(mask_scores(sacc, lo, lim, qh)), sees, c2, slack, m_ref, l_run, oacc);
-        const float mc = offset_of(sees, m_ref);
+        float alpha;
+        const float mc = take_in(row_max(mask_scores(sacc, lo, lim, qh)), sees, alpha);
         bf16x8 pf[4];
         float l = 0.f;
 #pragma unroll
         for (int sp = 0; sp < 4; ++sp) pf[sp] = piece_probabilities(sacc, sp, c2, mc, l);
-        l_run += l + __shfl_xor(l, 32);
+        l_run = fmaf(l_run, alpha, l + __shfl_xor(l, 32));
 #pragma unroll
         for (int db = 0; db < 4; ++db) {
-          f32x16 sum = oacc[db];
+          f32x16 sum;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) sum[v] = oacc[db][v] * alpha;
 #pragma unroll
           for (int sp = 0; sp < 4; ++sp)
             sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(value_frag(vaddr, sp, db), pf[sp], sum, 0, 0, 0);
@@ -445,13 +454,13 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
   const int col_b = lane_b & 31, qh_b = lane_b >> 5;
   // combine the splits: row sums scaled to the row's maximum over them, 512 bytes a row, 16-byte chunk c of row r at place c ^ r
   float2* stats = reinterpret_cast<float2*>(smem + Lds::Stats);
-  if (qh_b == 0) stats[32 * wave + col_b] = make_float2(m_ref, l_run);
+  if (qh_b == 0) stats[32 * wave + col_b] = make_float2(mc_run, l_run);
   __syncthreads();
   {
     float M = -INFINITY;
 #pragma unroll
     for (int s = 0; s < S; ++s) M = fmaxf(M, stats[32 * (s * kGroups + rg) + col_b].x);
-    const float f = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(fmaf(m_ref, c2, -M * c2));
+    const float f = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mc_run - M);
     unsigned char* dst = smem + wave * 32 * 512 + col_b * 512;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
@@ -480,7 +489,7 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      L += st[s].x == -INFINITY ? 0.f : st[s].y * __builtin_amdgcn_exp2f(fmaf(st[s].x, c2, -M * c2));
+      L += st[s].x == -INFINITY ? 0.f : st[s].y * __builtin_amdgcn_exp2f(st[s].x - M);
       const unsigned char* src = smem + (kGroups * s + (rr >> 5)) * 32 * 512 + (rr & 31) * 512;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -493,7 +502,7 @@ k_fwd_short(Problem P, IndexGeom G, int n_index, int groups, const bf16_t* __res
     const u32x4 o = {pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),
                      pack_bf16x2(acc[4] * inv, acc[5] * inv), pack_bf16x2(acc[6] * inv, acc[7] * inv)};
     *reinterpret_cast<u32x4*>(O + grow * kD + 8 * sub) = o;
-    if (sub == 0) LSE[grow] = empty ? -INFINITY : (M * c2 + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
+    if (sub == 0) LSE[grow] = empty ? -INFINITY : (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
     if (gate != nullptr) {
       // Eq. (2): O_out = O_acc + gate * O, from the fp32 result (Oout may be the buffer Oacc points to: every lane
       // reads its own 16 bytes before it writes them)

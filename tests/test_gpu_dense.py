@@ -232,3 +232,23 @@ def test_a_row_does_not_depend_on_its_neighbours():
         assert c.attn.dense_entries().any()
         outs.append((o[6145::2].clone(), lse[6145::2].clone()))    # (earlier tiles have few blocks: what is dense there differs)
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+
+
+@pytest.mark.parametrize("dense", [True, None])
+def test_the_largest_probability_is_exact(dense):
+    """Wide scores, whose rows are carried by few keys: against the running maximum the largest probability is 1, which bf16 holds, and what
+    is left of O's error is little more than its own rounding to bf16 (1.04 and 1.03 times that; 1.26 and 1.22 against a maximum that was
+    let lag behind).  With every probability rounded, two independent errors of a size, it would be 1.4 times."""
+    print("case largest probability", dense, flush=True)
+    w = wl.realise(wl.Workload("wide", [1500], hq=8, hkv=2, topk=1, seed=39), tensors=True)
+    w.idx = wl.window_block_indices(w.seqlens, w.hkv, 512, 64)
+    w.topk = w.idx.shape[2]
+    c = Case(w, bwd=False, window=512, dense=dense)
+    c.q *= 4
+    o, lse = c.forward()
+    rO, rL = orc.forward(to_f64(c.q), to_f64(c.k), to_f64(c.v), w.idx, w.cu_seqlens, window=512)
+    rounding = np.linalg.norm(to_f64(torch.from_numpy(rO).bfloat16()) - rO)
+    ratio = np.linalg.norm(to_f64(o) - rO) / rounding
+    print("  error over that of rounding O", round(ratio, 3), flush=True)
+    assert ratio < 1.1
+    assert np.abs(to_f64(lse) - rL).max() < 2e-5  # 32-bit sums and a maximum of some tens
