@@ -141,8 +141,8 @@ def test_selected_and_window_branches_gated_into_one_output():
 
 @pytest.mark.parametrize("seqlens,topk", [([3000, 1, 333], 28), ([3000, 1, 333], 29), ([16384], 32)])
 def test_gated_dense_route_one_head_per_kv_head_and_many_columns(seqlens, topk):
-    """g = 1 on the dense route: up to 28 columns a workgroup's finished rows wait in LDS, from 29 on they are written as they are done,
-    since two workgroups would not fit a compute unit with them.  In place, against the plain output (the library adds before it
+    """g = 1 on the dense route: the finished and the gated rows of a workgroup wait in LDS, in the place of K and V, beside the index data of
+    its many columns, and two workgroups still fit a compute unit.  In place, against the plain output (the library adds before it
     rounds: two bf16 roundings apart) and, at the largest, against the time without a gate: 1.05 times that, and 1.8 times with one
     workgroup a unit.  Compared on the fastest of several."""
     print("case gated g1", seqlens, topk, flush=True)

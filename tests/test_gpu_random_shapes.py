@@ -106,7 +106,7 @@ def test_units_below_256_entries(seqlens, hq, hkv, topk):
     _, rk, rv = orc.backward(Q, K, V, dO, w.idx, w.cu_seqlens)
     outs = []
     for unit in (0, 256):
-        a = nsa.SelAttention(w.total_tokens, hq, hkv, topk, nseq=len(seqlens), unit=unit)
+        a = nsa.SelAttention(w.total_tokens, hq, hkv, topk, nseq=len(seqlens), unit=unit, dense=False)  # (the short forward has no units)
         o, lse = a.forward(c.q, c.k, c.v, c.idx, c.cu)
         dq, dk, dv = a.backward(c.q, c.k, c.v, o, lse, c.do, c.cu)
         assert_close("dK", to_f64(dk), rk, TOL_GRAD)

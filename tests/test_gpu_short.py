@@ -57,7 +57,8 @@ def _check(w, window=0, backward=True):
 @pytest.mark.parametrize("seqlens,g,hkv,topk,block", [
     ([1], 1, 1, 1, 64), ([63], 8, 1, 1, 64), ([64, 65], 2, 2, 2, 64), ([129, 1, 0, 127, 128], 1, 3, 4, 64), ([1000], 4, 1, 8, 64),
     ([900, 300], 7, 2, 7, 64), ([2000], 4, 8, 16, 64), ([700, 64, 1, 333, 0], 3, 2, 10, 64), ([1500, 37], 5, 1, 32, 64),
-    ([1100], 8, 2, 32, 128), ([257, 128, 1, 515], 2, 2, 9, 128), ([2500], 1, 2, 16, 64)])
+    ([1100], 8, 2, 32, 128), ([257, 128, 1, 515], 2, 2, 9, 128), ([2500], 1, 2, 16, 64),
+    ([4096], 1, 32, 16, 64)])  # the last: more counters than the scatter folds in, their prefix is a launch of its own
 def test_short_forward_matches_oracle(seqlens, g, hkv, topk, block):
     print("case short", seqlens, g, hkv, topk, block, flush=True)
     w = wl.realise(wl.Workload("short", seqlens, hq=g * hkv, hkv=hkv, topk=topk, block=block, sink=topk > 2, seed=81))

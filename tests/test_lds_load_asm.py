@@ -12,12 +12,13 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
-def test_a_wait_state_follows_every_write_of_m0(tmp_path):
+@pytest.mark.parametrize("source,least", [("fwd.hip", 8), ("short.hip", 48)])  # K and V of a piece: four row groups each, six forms
+def test_a_wait_state_follows_every_write_of_m0(tmp_path, source, least):
     from paper_2508_18224_amd.build import FLAGS
-    out = tmp_path / "fwd.s"
+    out = tmp_path / "out.s"
     flags = [f for f in FLAGS if f not in ("-shared", "-fPIC")]
     res = subprocess.run([HIPCC, *flags, "--offload-device-only", "-S", "-o", str(out),
-                          os.path.join(ROOT, "paper_2508_18224_amd", "csrc", "fwd.hip")], capture_output=True, text=True)
+                          os.path.join(ROOT, "paper_2508_18224_amd", "csrc", source)], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-3000:]
     loads, since = 0, 99                                           # wait states since the last write of m0
     for line in out.read_text().splitlines():
@@ -31,4 +32,4 @@ def test_a_wait_state_follows_every_write_of_m0(tmp_path):
             since = 0
         else:
             since += int(op.split()[1], 0) + 1 if op.startswith("s_nop") else 1
-    assert loads >= 8                                              # K and V of a piece, four row groups each
+    assert loads >= least

@@ -11,8 +11,8 @@ from gpu_util import Case
 pytestmark = pytest.mark.gpu
 
 
-def _both(w, window=0):
-    c = Case(w, bwd=False, window=window)
+def _both(w, window=0, dense=True):
+    c = Case(w, bwd=False, window=window, dense=dense)
     o_ref, lse_ref = c.forward()
     # poison the outputs so that a call that writes nothing cannot pass
     o = torch.full_like(o_ref, float("nan"))
@@ -37,6 +37,9 @@ def test_static_forward_equals_workspace_forward_on_two_calls_in_a_row():
     _both(wl.realise(wl.small("b128_g4")))
     _both(wl.realise(wl.small("g7")), window=100)
     _both(wl.realise(wl.small("g1_varlen")))
+    # the library's choice of route: the short forward, which needs nothing of the array, and the gather route
+    _both(wl.realise(wl.small("g7")), dense=None)
+    _both(wl.realise(wl.Workload("static_gather", [3300], hq=4, hkv=2, topk=8, sink=True, seed=74)), dense=None)
 
 
 def test_static_forward_rejects_shapes_beyond_its_array():
