@@ -26,9 +26,10 @@ PEAK_HBM_GBS = 8000.0
 # kernel kinds of nsa_sel_profile_collect -> kernel names in the rocprofv3 summaries under profiles/ (template arguments left out)
 KERNEL_NAMES = {
     "fwd_main": ("nsa::k_fwd_main", "nsa::k_fwd_main128"), "fwd_merge": ("nsa::k_fwd_merge",),
-    "fwd_dense": ("nsa::k_fwd_dense_merge",),
+    "fwd_dense": ("nsa::k_fwd_dense_merge",), "fwd_short": ("nsa::k_fwd_short",),  # the latter with the inversion's histogram
     "bwd_main": ("nsa::k_bwd_tiled", "nsa::k_bwd_pipe128"), "bwd_delta": ("nsa::k_bwd_delta",),
-    "bwd_dq_reduce": ("nsa::k_bwd_dq_reduce",), "bwd_dkv_reduce": ("nsa::k_bwd_dkv_reduce",),
+    "bwd_dq_reduce": ("nsa::k_bwd_dq_reduce",),  # with the dK / dV sums where the dQ rows are not written in bursts
+    "bwd_dkv_reduce": ("nsa::k_bwd_dkv_reduce",),
 }
 NOT_IN_STEP = ("nsa::k_select_blocks", "k_calib_copy", "nsa::k_mfma_probe", "nsa::k_fwd_query_outer")
 
@@ -330,7 +331,7 @@ def main():
     f, b = effective_flops(T, w.hq, w.topk, block=w.block)
     for name, avg in sorted(per_kernel.items(), key=lambda kv: -kv[1]):
         print(f"[bench] {name:16s} {avg:9.3f} ms/launch", file=sys.stderr)
-    fwd_ms = sum(per_kernel.get(n, 0.0) for n in ("fwd_main", "fwd_dense", "fwd_merge"))
+    fwd_ms = sum(per_kernel.get(n, 0.0) for n in ("fwd_main", "fwd_dense", "fwd_merge", "fwd_short"))
     bwd_ms = sum(per_kernel.get(n, 0.0) for n in ("bwd_delta", "bwd_main", "bwd_dq_reduce", "bwd_dkv_reduce"))
     idx_ms = sum(vv for n, vv in per_kernel.items() if n.startswith("index_"))
     # algorithmic work of the dominant kernel: the MFMA contractions it performs (forward main: QK^T and PV,
