@@ -72,10 +72,13 @@ typedef struct {
                              of the tile's tokens keep - found by counting, e.g. the attention-sink block (App. E) and
                              the tokens' own and neighbouring blocks - go through a query-tile-outer kernel, fused
                              with the reduction step, that needs no gather and no partial row.  -1: every pair
-                             takes the gather route.  0: the library picks (the dense route when hq / hkv >= 2 or a
-                             window is set, and total_tokens * hkv * topk >= 2^18).  Same results up to
-                             rounding; an index workspace built for one routing must not be used with the
-                             other                                                                             */
+                             takes the gather route.  0: the library picks: for inputs of at most 8192 tokens in at most
+                             64 sequences whose tokens keep a good part of the blocks they see (by total_tokens, window,
+                             topk, block, causal and hq) a kernel that computes every pair of a few rows and 64 keys that
+                             any of the rows keeps, with a mask, and uses neither route nor workspace; else the dense route
+                             when hq / hkv >= 2 or a window is set and total_tokens * hkv * topk >= 2^18, else the gather
+                             route.  Same results up to rounding; an index workspace built for one routing must not be used
+                             with the other                                                                    */
 } nsa_sel_shape;
 
 /* Bytes of the three caller-owned workspaces for `shape` (any of the outputs may be NULL).

@@ -1114,7 +1114,7 @@ k_bwd_dkv_reduce(Problem P, int per, const int32_t* __restrict__ nu_scan, const 
 
 // dQ of every (token, head) row from its columns' partial rows: plain sums, in column order.  Rows and workgroups: see "the two
 // reduction kernels" in common.h.  (k_fwd_merge is the same with weights.)  Row by row, on smaller inputs, its first `before` workgroups
-// do the dK / dV sums, which are independent of it, instead of a launch for them: 13.6 -> 7.7 us for both at 1024 tokens, 32 -> 29 on a
+// do the dK / dV sums, which are independent of it, instead of a launch for them: 12.6 -> 7.2 us for both at 1024 tokens, 31 -> 28 on a
 // batch of short documents.  In bursts they would leave the others one workgroup a compute unit less: 214 -> 250 us at 8192 tokens, 32
 // heads, g = 1.
 template <int kRows, int kThreads>

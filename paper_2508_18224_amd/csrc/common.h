@@ -55,7 +55,7 @@ struct IndexPtrs {
   int32_t* blk_base;
   int32_t* blk_tok0;
   int32_t* blk_len;
-  int32_t* chunk_off;  // [hkv][n_chunks][b_cap]: entries a list receives from the chunks before this one
+  int32_t* chunk_off;  // [hkv][n_chunks][b_cap]: entries a list receives from the chunks before this one (index_folds: from this one)
   int32_t* cnt;        // [n_lists] list lengths
   int32_t* off;        // [n_lists + 1] exclusive scan of cnt: first position of every list in qent
   int2* qent;        // list entries: (token, column of idx it came from)
@@ -64,7 +64,7 @@ struct IndexPtrs {
   // work units (shared by forward and backward): scanned units per list, and a record per unit in list order
   int32_t* u_nu;
   UnitRec* u_rec;
-  int2* group_sum;     // [hkv, n_groups] (entries, work units) of 64 lists
+  int2* group_sum;     // [hkv, n_groups] (entries, work units) of 64 lists (index_folds: not written)
   // dense forward path: query tiles (kTileTokens consecutive tokens of one sequence) and, per (tile, kv head), the
   // 64-key pieces of the KV blocks at least half of the tile's tokens keep, each with the 64-bit mask of the tokens
   // that keep its block

@@ -98,8 +98,9 @@ __device__ __forceinline__ bf16x8 value_frag(const uint32_t (&vaddr)[2][4], int 
 // keys, which is returned.  A wavefront issues in order, and left to themselves the two products and the exponentials come one after the
 // other, and every product waits for its own LDS read.  So the order is fixed by hand: 32 steps of one product, the LDS read of the
 // product four steps on, the exponentials that are due (those of contraction step sp of the PV product four products before it), the rescale of the
-// sums before the PV product and whatever `beside(step)` issues: the loads of pieces to come, which would hold the wavefront up if they were issued at once.  Measured
-// with clock stamps: 1040 clocks, of which the products need 1024.
+// sums before the PV product and whatever `beside(step)` issues: the loads of pieces to come, which would hold the wavefront up if they were issued at once.  Without
+// the rescale it measured 1040 clocks, of which the products need 1024; with it the kernels take 0.5 % (k_fwd_dense_merge, nine pieces) to 6 %
+// (k_fwd_short, 6000 tokens) longer.
 template <class Beside>
 __device__ __forceinline__ float piece_values_and_next_scores(const uint32_t (&kaddr)[8], const uint32_t (&vaddr)[2][4],
                                                               const bf16x8 (&qf)[8], float c2, float mc, float alpha, const f32x16 (&cur)[2],
