@@ -54,17 +54,31 @@ struct UnitQueue {
 };
 constexpr int kQueuePasses = 64;                                                // counters, one a pass over KV heads
 constexpr int kQueueUnits = 2 * kBlock * kD - kQueuePasses;                     // entries of the order: 64 KB in all
-// Main kernel with a workgroup a unit -> from the queue, in us.  64-token blocks: 8192 tokens x 32 heads, g = 1 (6177 units at most)
-// 580 -> 527, 32768 x 32, g = 4 (6153) 2087 -> 2031, its window of 512 1170 -> 1150, 4096 x 32, g = 4 (2569) 243 -> 236; but 65536 x 32,
-// g = 4 (12297) 4086 -> 4078 in one run and 4168 -> 4199 in another, 65536 x 28, g = 7 (6149) 3526 -> 3548: the tail is a small part of
-// so long a kernel, and what the idle slots gave up the others may have had as clock rate (the chip runs these kernels at 1.8 of its 2.4
-// GHz).  128-token blocks, one workgroup a compute unit: window of 512 at 32768 tokens 1455 -> 1123, 8192 x 32, g = 1 532 -> 487,
-// 16384 x 16, g = 2 496 -> 464, 65536 x 32, g = 4 3240 -> 3188.  Fewer units than 2048 are a few a slot: 2000 x 32, g = 4 117 -> 118.
-// With all keys visible the lists are alike.  64-token blocks, lists that fit one unit (top-k x block entries below 3/4 of it): no long
-// ones to start early, 31821 x 28, g = 2 1644 -> 1684, 15075 x 66, g = 2 1820 -> 1852, so none there; with full units and remainders 16384 x 32, g = 4
-// 1049 -> 993, 12000 x 32, top-k 24 1249 -> 1113, 25530 x 12, g = 2 639 -> 605, but packed short ones 302 -> 307 and 336 -> 343.
+// Where there is a queue.  Main kernel with a workgroup a unit -> from the queue, in us (tokens x query heads, top-k 16):
+//   64-token blocks, causal: 8192 x 32, g = 1 529 -> 503, 32768 x 32, g = 4 2077 -> 1984, 19897 x 26, g = 1 1075 -> 1047, 4096 x 32, g = 4 243 -> 236; but
+//     65536 x 32, g = 4 4086 -> 4078 in one run and 4168 -> 4199 in another, 65536 x 28, g = 7 3526 -> 3548: the tail is a small part of so long a kernel,
+//     and what the idle slots gave up the others may have had as clock rate (the chip runs these kernels at 1.8 of its 2.4 GHz).  On shorter
+//     inputs a KV head with more than half a unit's entries for each slot leaves little of a tail, and the classes go through the heads'
+//     Q and dO three times: 27033 x 20, g = 4, top-k 8 527 -> 538, 18046 x 7, g = 1 289 -> 296, 33223 x 20, g = 4, top-k 8 633 -> 656, 34873 x 3 241 -> 250; not so
+//     with three units and more for each slot (54612 x 8, g = 4, packed 823 -> 792, 52116 x 4, g = 4 231 -> 224), with lists of four units and more (14455 x 8, g = 2
+//     247 -> 237, 14094 x 8, g = 4 228 -> 221) and from g = 5 on (16760 x 10 340 -> 330, 49467 x 5, top-k 32 930 -> 916, at worst 5493 x 50 484 -> 492)
+//   all keys, where the lists are alike: with full units and remainders 16384 x 32, g = 4 1049 -> 993, 38968 x 10, g = 2 785 -> 732; lists of one unit
+//     (top-k x block entries below 3/4 of it) leave nothing to start early, 31821 x 28, g = 2 1644 -> 1684; packed short documents, lists of several
+//     units: 6831 x 26, g = 2 352 -> 362, 16743 x 24, g = 8 733 -> 753, of one 20741 x 18, g = 2 707 -> 686, few heads 40760 x 4, g = 4, top-k 32 600 -> 565
+//   windows: 512 over 32768 x 32, g = 4 1155 -> 1117, over 47450 x 32, g = 2 1708 -> 1640, 256 over 30277 x 16, g = 4 419 -> 335; 100 over 25385 x 40, g = 8 349 -> 357
+//   128-token blocks, one workgroup a compute unit: window of 512 at 32768 tokens 1455 -> 1123, 8192 x 32, g = 1 532 -> 487, 65536 x 32, g = 4 3240 -> 3188,
+//     15810 x 56, g = 4, all keys 1474 -> 1363; at worst +0.6 %
+// Fewer units than 2048 are a few a slot: 2000 x 32, g = 4 117 -> 118.
 constexpr int kQueueMinUnits = 2048;
-constexpr int64_t kQueueMaxRows64 = (int64_t)3 << 23;  // (token, query head, column) triples
+inline bool queue_pays(const Problem& P) {
+  if (P.bk == 2 * kBlock) return true;
+  const int64_t rows = (int64_t)P.T * P.hq * P.topk;  // (token, query head, column) triples
+  const int list = P.topk * P.bk;                     // entries of an average list
+  const int64_t head = (int64_t)P.T * P.topk, round = 512 * (int64_t)P.unit;  // entries of a KV head, and a unit for each slot
+  if (rows > (int64_t)3 << 23) return false;
+  if (!P.causal) return 4 * list >= 3 * P.unit && (P.nseq == 1 || rows >= (1 << 23) || list <= P.unit || head >= 4 * round);
+  return P.window > 0 || rows >= (1 << 23) || P.g >= 5 || list >= 4 * P.unit || 2 * head <= round || head >= 3 * round;
+}
 
 // Units in order of their length class, longest first: more than 3/8, 3/16 and less of a full unit.  A thread takes a run of units,
 // so that a class stays in the order of the KV heads, whose Q, dO and statistics the main kernels find in L2; the lengths are read once,
@@ -1220,7 +1234,7 @@ hipError_t launch_bwd(const Problem& P0, const IndexLayout& L, int heads_per_pas
   const int64_t pass_units = units_bound(heads_per_pass, P0.b_cap, P0.T, P0.topk, P0.unit);
   // (Q of 4 GB and more: units by the hundred a slot)
   const bool queued = lists_per_pass == 0 && passes <= kQueuePasses && pass_units >= kQueueMinUnits && !wide &&
-                      (b128 || ((int64_t)P0.T * P0.hq * P0.topk <= kQueueMaxRows64 && (P0.causal || 4 * P0.topk * P0.bk >= 3 * P0.unit)));
+                      queue_pays(P0);
   int32_t* const queue = queued ? reinterpret_cast<int32_t*>(dkv_part + (size_t)(pass_units - 1) * 2 * P0.bk * kD) : nullptr;
   const bool ordered = queued && passes == 1 && pass_units <= kQueueUnits;
   auto form = [&](auto* keys64, auto* keys128) { return b128 ? keys128 : keys64; };

@@ -20,7 +20,8 @@ def _bound(w, hkv, unit):
 
 #        lengths, query heads, KV heads, top-k, block, window, units at most, KV heads a pass (0: all)
 CASES = [([4096], 8, 8, 16, 64, 0, 2569, 0),                     # all lists ordered
-         ([3000, 1, 64, 1500, 531], 16, 8, 16, 64, 0, 3221, 0),  # packed, ragged, g = 2
+         ([2000, 1, 64, 1500, 531], 16, 8, 16, 64, 0, 2601, 0),  # packed, ragged, g = 2
+         ([12000], 40, 8, 8, 64, 0, 4505, 0),                    # more than half a unit for each slot, g = 5
          ([5000], 8, 8, 9, 64, 512, 2039, 0),                # below the rule's least: a workgroup a unit
          ([8192], 8, 8, 9, 64, 512, 3337, 0),                    # the window's form
          ([4096], 16, 8, 16, 128, 0, 2313, 0),                   # 128-token blocks
@@ -68,7 +69,8 @@ def _queue(attn, w, lengths, block):
 
 
 @pytest.mark.parametrize("lengths,hq,hkv,topk,block,causal,queued", [
-    ([4096], 8, 8, 16, 64, True, True), ([3000, 1, 64, 1500, 531], 16, 8, 16, 64, True, True), ([4096], 16, 8, 16, 128, True, True),
+    ([4096], 8, 8, 16, 64, True, True), ([2000, 1, 64, 1500, 531], 16, 8, 16, 64, True, True), ([4096], 16, 8, 16, 128, True, True),
+    ([12000], 40, 8, 8, 64, True, True), ([12000], 32, 8, 8, 64, True, False),  # more than half a unit for each slot, g = 5 and 4
     ([8192], 8, 8, 8, 64, False, True),      # lists of about two units of 256
     ([8192], 8, 8, 2, 64, False, False),     # of half a unit: all alike and one unit each
     ([8192], 8, 8, 2, 64, True, False)])     # (too few units)
