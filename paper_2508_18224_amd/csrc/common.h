@@ -166,7 +166,8 @@ inline bool index_folds(int T, int nseq, int hkv, int bk) {
 // 79 -> 73, 90 -> 97, 126 -> 144; 32 heads, g = 4 139 -> 81, 179 -> 131, 235 -> 198, 342 -> 361 (top-k 16, 2000, 3000, 4096 and 6000 tokens); top-k 8,
 // 2000 tokens (x = 4) 4 heads 31 -> 35, 32 heads 90 -> 71.  All keys, x = 4 / 6 / 8: 4 heads 45 -> 40, 56 -> 52, 65 -> 73; 32 heads 159 -> 99, 233
 // -> 183, 281 -> 293.  Blocks of 128 tokens, of which the other routes gather half as many: x = 1 / 2 / 3, 8 heads 38 -> 24, 45 -> 36, 51 -> 67; 4 heads,
-// g = 1, 31 -> 35 at x = 2.
+// g = 1, 31 -> 35 at x = 2.  (k_fwd_short takes 2 to 6 % longer since it rescales for every piece; 184 inputs drawn inside the rule took 16 % less and more
+// than by the other routes with either.)
 inline bool short_forward(int T, int nseq, int hq, int topk, int bk, bool causal, int window) {
   if (T > 8192 || nseq > 64 || index_by_token(T, nseq)) return false;  // what k_fwd_short has room for
   const int64_t rows = (int64_t)T * hq, blocks = (int64_t)(window > 0 && window < T ? window : T) * (causal ? 1 : 2);

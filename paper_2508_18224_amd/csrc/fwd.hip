@@ -528,8 +528,10 @@ k_fwd_main128(Problem P, const bf16_t* __restrict__ Q, const bf16_t* __restrict_
 //            the columns in place, plain loads and every row written as it was done: 1.79 instead of 1.62 ms at 65536 tokens, g = 4,
 //            1.78 instead of 1.54 with 9 of 16 columns dense at g = 7, 1.02 instead of 0.91 gated at 32768 tokens.
 // Tiles without a dense piece skip phase 1, so with the dense route on this kernel is the merge of every row.
-// Phase 2 is bound by memory (65536 tokens, g = 4: 8.9 GB in 1.62 ms for the whole kernel), phase 1 by vector instructions: a wavefront's
-// piece takes 1000 clocks of them and 1024 of the matrix pipe, and two wavefronts share a SIMD.  One pair of tiles, with two barriers a
+// Phase 2 is bound by memory (65536 tokens, g = 4: 8.9 GB in 1.62 ms for the whole kernel), phase 1 by what two
+// wavefronts a SIMD issue: for a window of 512 over 32768 tokens, where nothing is left to gather, 15 vector instructions go with a product, the
+// matrix pipe is 32 % busy, and the wavefronts wait 29 % of their time; the piece loop itself keeps the pipe busy (see
+// piece_values_and_next_scores), the rest is tables, Q, the first piece's scores, the reduction and the write.  One pair of tiles, with two barriers a
 // piece and the S product, softmax and PV product one after the other, took 1.55 instead of 1.40 ms with 9 of 16 columns dense at g
 // = 7, 65536 tokens, and 532 instead of 514 us for a window of 512 at 32768; there every access of the piece loop also waited for the loads just
 // sent on their way (see await_rows).  The last piece goes without scores of a next one, which tiles of one or two pieces paid for with
